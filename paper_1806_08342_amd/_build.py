@@ -1,16 +1,19 @@
-"""Builds libqnn.so (the C-ABI library) from the HIP sources with hipcc for gfx950.
+"""Builds libqnn.so (the C-ABI library) from the HIP sources with hipcc for gfx950, and _native.so, the
+compiled Python binding on top of it.
 
-The library is built in-tree, next to this file; nothing is compiled at import time.
+Both are built in-tree, next to this file; nothing is compiled at import time.
 """
 from __future__ import annotations
 
 import concurrent.futures as cf
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqnn.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["host_helpers.hip", "elementwise.hip", "igemm.hip", "igemm_tiles.hip", "igemm_shortk.hip", "igemm_bres.hip",
            "igemm_stem.hip", "igemm_rowsum.hip", "dwconv.hip", "calibrate.hip"]
 FLAGS = [
@@ -36,13 +39,31 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_binding() -> str:
+    """The Python binding is host code only: a plain C++ compilation against torch's headers."""
+    from torch.utils import cpp_extension
+
+    obj = os.path.join(CSRC, "binding.o")
+    incs = [f"-I{d}" for d in cpp_extension.include_paths("cuda") + [sysconfig.get_paths()["include"]] if os.path.isdir(d)]
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                           *incs, "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj])
+    return obj
+
+
 def build_library(verbose: bool = True) -> str:
-    """Compile every HIP source for gfx950 and link libqnn.so.  Always recompiles."""
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
+    """Compile every HIP source for gfx950, link libqnn.so and the Python binding.  Always recompiles."""
+    from torch.utils import cpp_extension
+
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as pool:
+        binding = pool.submit(_compile_binding)
         objs = list(pool.map(_compile, SOURCES))
+        binding_obj = binding.result()
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    torch_lib = cpp_extension.library_paths("cuda")[0]
+    subprocess.check_call(["g++", "-shared", "-o", NATIVE, binding_obj, f"-L{HERE}", "-lqnn", f"-L{torch_lib}", "-lc10", "-ltorch_cpu", "-ltorch_python",
+                           "-lc10_hip", "-ltorch_hip", "-Wl,-rpath,$ORIGIN"])
     if verbose:
-        print(f"built {LIB}")
+        print(f"built {LIB} and {NATIVE}")
     return LIB
 
 

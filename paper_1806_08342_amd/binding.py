@@ -1,8 +1,10 @@
-"""ctypes binding of libqnn.so: argument marshalling only.
+"""Python binding of libqnn.so: argument marshalling only.
 
-Device tensors are torch tensors on a HIP device; the functions pass their ``data_ptr()`` and
-the current torch stream to the C ABI (``include/qnn.h``) and allocate the output tensor.
-No arithmetic of the method happens in Python.
+Device tensors are torch tensors on a HIP device.  The device functions below name and document the
+arguments; the compiled module ``_native`` (``csrc/binding.cpp``) checks the tensors, allocates the output and
+calls the C ABI (``include/qnn.h``) on the current torch stream -- a Python-level ctypes call took longer than
+a small layer runs.  Host helpers and the calibration calls go through ctypes.  No arithmetic of the method
+happens in Python.
 """
 from __future__ import annotations
 
@@ -114,6 +116,25 @@ def _torch():
     return torch
 
 
+_nat = None  # the compiled module, once loaded
+
+
+def _native():
+    """Load the compiled binding (and with it libqnn.so).  There is no fallback: a missing module is an error."""
+    global _nat
+    if _nat is None:
+        load_library()
+        _torch()  # its shared libraries are what the module links against
+        try:
+            from . import _native as mod
+        except ImportError as e:
+            raise RuntimeError(f"the compiled binding is missing or unusable ({e}): build it first (python -m "
+                               "paper_1806_08342_amd._build, or __graft_entry__.build()); there is no Python fallback") from e
+        mod.set_check(_check)
+        _nat = mod
+    return _nat
+
+
 def _stream():
     return C.c_void_p(_torch().cuda.current_stream().cuda_stream)
 
@@ -136,17 +157,6 @@ def _dev_rows(t, dtype, name):
             (t.shape[1] == 1 or t.stride(1) == 1) and (t.shape[0] == 1 or t.stride(0) >= t.shape[1])):
         raise TypeError(f"{name}: expected a 2-D device tensor of {dtype} with contiguous rows")
     return C.c_void_p(t.data_ptr()), (t.stride(0) if t.shape[0] > 1 else t.shape[1])
-
-
-def _out(out, shape, device, name="out"):
-    """The output tensor: a new uint8 tensor of `shape`, or the caller's `out` after a shape check (the
-    kernels write shape-many elements through its pointer)."""
-    torch = _torch()
-    if out is None:
-        return torch.empty(shape, dtype=torch.uint8, device=device)
-    if tuple(out.shape) != tuple(shape):
-        raise ValueError(f"{name} has shape {tuple(out.shape)}, expected {tuple(shape)}")
-    return out
 
 
 def _workspace(nbytes, device, workspace):
@@ -266,95 +276,37 @@ def qgemm_plan(M, N, K):
 # ---------------------------------------------------------------- device kernels
 
 def quantize(x, scale, zero_point, qmin=0, qmax=255, out=None):
-    torch = _torch()
-    q = _out(out, x.shape, x.device)
-    _check("qnn_quantize", load_library().qnn_quantize(_dev(x, torch.float32, "x"), _dev(q, torch.uint8, "q"),
-                                                      x.numel(), scale, zero_point, qmin, qmax, _stream()))
-    return q
+    return (_nat or _native()).quantize(x, scale, zero_point, qmin, qmax, out)
 
 
 def dequantize(q, scale, zero_point, out=None):
-    torch = _torch()
-    x = torch.empty(q.shape, dtype=torch.float32, device=q.device) if out is None else out
-    _check("qnn_dequantize", load_library().qnn_dequantize(_dev(q, torch.uint8, "q"), _dev(x, torch.float32, "x"),
-                                                          q.numel(), scale, zero_point, _stream()))
-    return x
+    return (_nat or _native()).dequantize(q, scale, zero_point, out)
 
 
 def quantize_u16(x, scale, zero_point, qmin=0, qmax=65535, out=None):
     """Codes of up to 16 bits as a uint16 tensor."""
-    torch = _torch()
-    q = torch.empty(x.shape, dtype=torch.uint16, device=x.device) if out is None else out
-    if tuple(q.shape) != tuple(x.shape):
-        raise ValueError(f"out: shape {tuple(q.shape)}, expected {tuple(x.shape)}")
-    _check("qnn_quantize_u16", load_library().qnn_quantize_u16(_dev(x, torch.float32, "x"), _dev(q, torch.uint16, "q"),
-                                                              x.numel(), scale, zero_point, qmin, qmax, _stream()))
-    return q
+    return (_nat or _native()).quantize_u16(x, scale, zero_point, qmin, qmax, out)
 
 
 def dequantize_u16(q, scale, zero_point, out=None):
-    torch = _torch()
-    x = torch.empty(q.shape, dtype=torch.float32, device=q.device) if out is None else out
-    if tuple(x.shape) != tuple(q.shape):
-        raise ValueError(f"out: shape {tuple(x.shape)}, expected {tuple(q.shape)}")
-    _check("qnn_dequantize_u16", load_library().qnn_dequantize_u16(_dev(q, torch.uint16, "q"), _dev(x, torch.float32, "x"),
-                                                                  q.numel(), scale, zero_point, _stream()))
-    return x
+    return (_nat or _native()).dequantize_u16(q, scale, zero_point, out)
 
 
 def requantize(acc, mult, shift, per_channel, z_out, act_min, act_max, out=None):
-    torch = _torch()
-    rows, ch = acc.shape
-    y = _out(out, (rows, ch), acc.device)
-    _check("qnn_requantize", load_library().qnn_requantize(
-        _dev(acc, torch.int32, "acc"), _dev(y, torch.uint8, "y"), rows, ch, _dev(mult, torch.int32, "mult"),
-        _dev(shift, torch.int32, "shift"), int(bool(per_channel)), z_out, act_min, act_max, _stream()))
-    return y
+    return (_nat or _native()).requantize(acc, mult, shift, per_channel, z_out, act_min, act_max, out)
 
 
 def qgemm(A, z_a, B, mult, shift, z_out, act_min, act_max, bias=None, weight_bits=8,
           b_layout=B_COLUMNS_CONTIGUOUS, out=None, workspace=None):
     """A: uint8 [M,K] (rows may be spaced apart: a column slice of a wider matrix; same for `out`).  B: int8 [N,K] (columns contiguous), int8 [K,N] (rows contiguous), or uint8
     [N,K/2] nibble-packed when weight_bits == 4.  Returns uint8 [M,N]."""
-    torch = _torch()
-    M, K = A.shape
-    if weight_bits == 4:
-        N, ldb = B.shape[0], B.shape[1] * 2
-        bp = _dev(B, torch.uint8, "B")
-    elif b_layout == B_COLUMNS_CONTIGUOUS:
-        N, ldb = B.shape
-        bp = _dev(B, torch.int8, "B")
-    else:
-        ldb = N = B.shape[1]
-        bp = _dev(B, torch.int8, "B")
-    Cm = _out(out, (M, N), A.device)
-    ap, lda = _dev_rows(A, torch.uint8, "A")
-    cp, ldc = _dev_rows(Cm, torch.uint8, "C")
-    wp, wbytes, _ws = _workspace(qgemm_workspace_bytes(M, N, K, weight_bits), A.device, workspace)
-    _check("qnn_qgemm", load_library().qnn_qgemm(
-        ap, lda, z_a, bp, ldb, b_layout, weight_bits, M, N, K, _dev(bias, torch.int32, "bias"),
-        _dev(mult, torch.int32, "mult"), _dev(shift, torch.int32, "shift"), z_out, act_min, act_max,
-        cp, ldc, wp, wbytes, _stream()))
-    return Cm
+    return (_nat or _native()).qgemm(A, z_a, B, mult, shift, z_out, act_min, act_max, bias, weight_bits, b_layout, out, workspace)
 
 
 def qgemm_noalloc(A, z_a, B, mult, shift, z_out, act_min, act_max, out, bias=None, weight_bits=8):
     """qnn_qgemm_noalloc: `qgemm` with columns-contiguous B into the caller's `out`, with the library's static
     scratch array; neither this wrapper nor the library allocates."""
-    torch = _torch()
-    M, K = A.shape
-    if weight_bits == 4:
-        N, ldb, bp = B.shape[0], B.shape[1] * 2, _dev(B, torch.uint8, "B")
-    else:
-        (N, ldb), bp = B.shape, _dev(B, torch.int8, "B")
-    if tuple(out.shape) != (M, N):
-        raise ValueError(f"out has shape {tuple(out.shape)}, expected {(M, N)}")
-    ap, lda = _dev_rows(A, torch.uint8, "A")
-    cp, ldc = _dev_rows(out, torch.uint8, "C")
-    _check("qnn_qgemm_noalloc", load_library().qnn_qgemm_noalloc(
-        ap, lda, z_a, bp, ldb, B_COLUMNS_CONTIGUOUS, weight_bits, M, N, K, _dev(bias, torch.int32, "bias"),
-        _dev(mult, torch.int32, "mult"), _dev(shift, torch.int32, "shift"), z_out, act_min, act_max, cp, ldc, _stream()))
-    return out
+    return (_nat or _native()).qgemm_noalloc(A, z_a, B, mult, shift, z_out, act_min, act_max, out, bias, weight_bits)
 
 
 def prepare_qgemm(A, z_a, B, mult, shift, z_out, act_min, act_max, out, bias=None, weight_bits=8,
@@ -391,34 +343,13 @@ def prepare_qgemm(A, z_a, B, mult, shift, z_out, act_min, act_max, out, bias=Non
 
 def pack_b(B_rows):
     """int8 [K,N] with contiguous rows -> int8 [N,K] (the layout qgemm runs fastest on)."""
-    torch = _torch()
-    K, N = B_rows.shape
-    out = torch.empty((N, K), dtype=torch.int8, device=B_rows.device)
-    _check("qnn_pack_b", load_library().qnn_pack_b(_dev(B_rows, torch.int8, "B"), N, K, N,
-                                                  _dev(out, torch.int8, "out"), K, _stream()))
-    return out
-
-
-def _out_hw(H, W, kh, kw, stride, pad):
-    return (H + 2 * pad[0] - kh) // stride[0] + 1, (W + 2 * pad[1] - kw) // stride[1] + 1
+    return (_nat or _native()).pack_b(B_rows)
 
 
 def qconv2d(x, z_x, w, stride, pad, mult, shift, z_out, act_min, act_max, bias=None, weight_bits=8, out=None,
             workspace=None):
     """x: uint8 NHWC.  w: int8 [Cout,kh,kw,Cin], or uint8 [Cout,kh,kw,Cin/2] packed 4-bit."""
-    torch = _torch()
-    N, H, W, Cin = x.shape
-    Cout, kh, kw = w.shape[:3]
-    wp = _dev(w, torch.uint8 if weight_bits == 4 else torch.int8, "w")
-    Ho, Wo = _out_hw(H, W, kh, kw, stride, pad)
-    y = _out(out, (N, Ho, Wo, Cout), x.device)
-    sp, sbytes, _ws = _workspace(qconv2d_workspace_bytes(N, H, W, Cin, Cout, kh, kw, stride, pad, weight_bits), x.device,
-                                 workspace)
-    _check("qnn_qconv2d", load_library().qnn_qconv2d(
-        _dev(x, torch.uint8, "x"), N, H, W, Cin, z_x, wp, Cout, kh, kw, weight_bits, stride[0], stride[1], pad[0],
-        pad[1], _dev(bias, torch.int32, "bias"), _dev(mult, torch.int32, "mult"), _dev(shift, torch.int32, "shift"),
-        z_out, act_min, act_max, _dev(y, torch.uint8, "y"), sp, sbytes, _stream()))
-    return y
+    return (_nat or _native()).qconv2d(x, z_x, w, stride, pad, mult, shift, z_out, act_min, act_max, bias, weight_bits, out, workspace)
 
 
 class _AddParams(C.Structure):
@@ -426,94 +357,33 @@ class _AddParams(C.Structure):
                                          "shift_o", "z_out", "act_min", "act_max")]
 
 
-def _add_struct(z_r, params, z_out, act_min, act_max):
-    """`params` is what qadd_params(s_mid, s_residual, s_out) returns (operand a = the layer's own result)."""
-    p = params
-    return _AddParams(p["mult_a"], p["shift_a"], z_r, p["mult_b"], p["shift_b"], p["left_shift"], p["mult_o"],
-                      p["shift_o"], z_out, act_min, act_max)
-
-
 def qgemm_add(A, z_a, B, mult, shift, z_mid, mid_min, mid_max, residual, z_r, params, z_out, act_min, act_max,
               bias=None, weight_bits=8, out=None, workspace=None):
     """qgemm (columns-contiguous B) whose uint8 result, quantized with (z_mid, mid_min, mid_max), is added to
-    `residual` (uint8 [M,N], rows may be spaced apart) with the rescaling add of `params`; returns uint8 [M,N]."""
-    torch = _torch()
-    M, K = A.shape
-    if weight_bits == 4:
-        N, ldb, bp = B.shape[0], B.shape[1] * 2, _dev(B, torch.uint8, "B")
-    else:
-        (N, ldb), bp = B.shape, _dev(B, torch.int8, "B")
-    Cm = _out(out, (M, N), A.device)
-    ap, lda = _dev_rows(A, torch.uint8, "A")
-    cp, ldc = _dev_rows(Cm, torch.uint8, "C")
-    rp, ldr = _dev_rows(residual, torch.uint8, "residual")
-    add = _add_struct(z_r, params, z_out, act_min, act_max)
-    wp, wbytes, _ws = _workspace(qgemm_workspace_bytes(M, N, K, weight_bits), A.device, workspace)
-    _check("qnn_qgemm_add", load_library().qnn_qgemm_add(
-        ap, lda, z_a, bp, ldb, B_COLUMNS_CONTIGUOUS, weight_bits, M, N, K, _dev(bias, torch.int32, "bias"),
-        _dev(mult, torch.int32, "mult"), _dev(shift, torch.int32, "shift"), z_mid, mid_min, mid_max, rp, ldr,
-        C.addressof(add), cp, ldc, wp, wbytes, _stream()))
-    return Cm
+    `residual` (uint8 [M,N], rows may be spaced apart) with the rescaling add of `params` (what
+    qadd_params(s_mid, s_residual, s_out) returns); returns uint8 [M,N]."""
+    return (_nat or _native()).qgemm_add(A, z_a, B, mult, shift, z_mid, mid_min, mid_max, residual, z_r, params, z_out, act_min,
+                                         act_max, bias, weight_bits, out, workspace)
 
 
 def qconv2d_add(x, z_x, w, stride, pad, mult, shift, z_mid, mid_min, mid_max, residual, z_r, params, z_out, act_min,
                 act_max, bias=None, weight_bits=8, out=None, workspace=None):
     """qconv2d followed by the rescaling add with `residual` (uint8 NHWC, the shape of the output), fused."""
-    torch = _torch()
-    N, H, W, Cin = x.shape
-    Cout, kh, kw = w.shape[:3]
-    wp = _dev(w, torch.uint8 if weight_bits == 4 else torch.int8, "w")
-    Ho, Wo = _out_hw(H, W, kh, kw, stride, pad)
-    y = _out(out, (N, Ho, Wo, Cout), x.device)
-    if tuple(residual.shape) != (N, Ho, Wo, Cout):
-        raise ValueError(f"residual has shape {tuple(residual.shape)}, the output {(N, Ho, Wo, Cout)}")
-    add = _add_struct(z_r, params, z_out, act_min, act_max)
-    sp, sbytes, _ws = _workspace(qconv2d_workspace_bytes(N, H, W, Cin, Cout, kh, kw, stride, pad, weight_bits), x.device,
-                                 workspace)
-    _check("qnn_qconv2d_add", load_library().qnn_qconv2d_add(
-        _dev(x, torch.uint8, "x"), N, H, W, Cin, z_x, wp, Cout, kh, kw, weight_bits, stride[0], stride[1], pad[0],
-        pad[1], _dev(bias, torch.int32, "bias"), _dev(mult, torch.int32, "mult"), _dev(shift, torch.int32, "shift"),
-        z_mid, mid_min, mid_max, _dev(residual, torch.uint8, "residual"), C.addressof(add),
-        _dev(y, torch.uint8, "y"), sp, sbytes, _stream()))
-    return y
+    return (_nat or _native()).qconv2d_add(x, z_x, w, stride, pad, mult, shift, z_mid, mid_min, mid_max, residual, z_r, params, z_out,
+                                           act_min, act_max, bias, weight_bits, out, workspace)
 
 
 def qgemm_asym(A, z_a, B, z_w, mult, shift, z_out, act_min, act_max, bias=None, weight_bits=8, out=None, workspace=None):
     """qgemm with a zero-point per weight column: z_w int32 [N] on the device.  B: int8 [N,K] (columns
     contiguous) or uint8 [N,K/2] nibble-packed."""
-    torch = _torch()
-    M, K = A.shape
-    if weight_bits == 4:
-        N, ldb, bp = B.shape[0], B.shape[1] * 2, _dev(B, torch.uint8, "B")
-    else:
-        (N, ldb), bp = B.shape, _dev(B, torch.int8, "B")
-    Cm = _out(out, (M, N), A.device)
-    ap, lda = _dev_rows(A, torch.uint8, "A")
-    cp, ldc = _dev_rows(Cm, torch.uint8, "C")
-    wp, wbytes, _ws = _workspace(qgemm_workspace_bytes(M, N, K, weight_bits, True), A.device, workspace)
-    _check("qnn_qgemm_asym", load_library().qnn_qgemm_asym(
-        ap, lda, z_a, bp, ldb, B_COLUMNS_CONTIGUOUS, weight_bits, _dev(z_w, torch.int32, "z_w"), M, N, K,
-        _dev(bias, torch.int32, "bias"), _dev(mult, torch.int32, "mult"), _dev(shift, torch.int32, "shift"), z_out,
-        act_min, act_max, cp, ldc, wp, wbytes, _stream()))
-    return Cm
+    return (_nat or _native()).qgemm_asym(A, z_a, B, z_w, mult, shift, z_out, act_min, act_max, bias, weight_bits, out, workspace)
 
 
 def qconv2d_asym(x, z_x, w, z_w, stride, pad, mult, shift, z_out, act_min, act_max, bias=None, weight_bits=8, out=None,
                  workspace=None):
     """qconv2d with a zero-point per output channel: z_w int32 [Cout] on the device."""
-    torch = _torch()
-    N, H, W, Cin = x.shape
-    Cout, kh, kw = w.shape[:3]
-    wp = _dev(w, torch.uint8 if weight_bits == 4 else torch.int8, "w")
-    Ho, Wo = _out_hw(H, W, kh, kw, stride, pad)
-    y = _out(out, (N, Ho, Wo, Cout), x.device)
-    sp, sbytes, _ws = _workspace(qconv2d_workspace_bytes(N, H, W, Cin, Cout, kh, kw, stride, pad, weight_bits, True), x.device,
-                                 workspace)
-    _check("qnn_qconv2d_asym", load_library().qnn_qconv2d_asym(
-        _dev(x, torch.uint8, "x"), N, H, W, Cin, z_x, wp, Cout, kh, kw, weight_bits, _dev(z_w, torch.int32, "z_w"),
-        stride[0], stride[1], pad[0], pad[1], _dev(bias, torch.int32, "bias"), _dev(mult, torch.int32, "mult"),
-        _dev(shift, torch.int32, "shift"), z_out, act_min, act_max, _dev(y, torch.uint8, "y"), sp, sbytes, _stream()))
-    return y
+    return (_nat or _native()).qconv2d_asym(x, z_x, w, z_w, stride, pad, mult, shift, z_out, act_min, act_max, bias, weight_bits, out,
+                                            workspace)
 
 
 def new_range_state(xmin=0.0, xmax=0.0):
@@ -533,93 +403,41 @@ def read_range_state(state):
 
 def minmax(x, state, momentum=0.0, bits=8):
     """Range of the finite elements of x (or its moving average) and the quantizer parameters, into `state`."""
-    torch = _torch()
-    _check("qnn_minmax", load_library().qnn_minmax(_dev(x, torch.float32, "x"), x.numel(), float(momentum), int(bits),
-                                                   _dev(state, torch.int32, "state"), _stream()))
-    return state
+    return (_nat or _native()).minmax(x, state, momentum, bits)
 
 
 def quantize_with(x, state, out=None):
-    torch = _torch()
-    q = _out(out, x.shape, x.device)
-    _check("qnn_quantize_with", load_library().qnn_quantize_with(_dev(x, torch.float32, "x"), _dev(q, torch.uint8, "q"),
-                                                                 x.numel(), _dev(state, torch.int32, "state"), _stream()))
-    return q
+    return (_nat or _native()).quantize_with(x, state, out)
 
 
 def quantize_dynamic(x, state, out=None):
     """uint8 codes of x with the quantizer of its own range; the parameters are left in `state`."""
-    torch = _torch()
-    q = _out(out, x.shape, x.device)
-    _check("qnn_quantize_dynamic", load_library().qnn_quantize_dynamic(
-        _dev(x, torch.float32, "x"), _dev(q, torch.uint8, "q"), x.numel(), _dev(state, torch.int32, "state"), _stream()))
-    return q
+    return (_nat or _native()).quantize_dynamic(x, state, out)
 
 
 def simquant(x, scale, zero_point, qmin=0, qmax=255, out=None):
-    torch = _torch()
-    y = torch.empty(x.shape, dtype=torch.float32, device=x.device) if out is None else out
-    _check("qnn_simquant", load_library().qnn_simquant(_dev(x, torch.float32, "x"), _dev(y, torch.float32, "y"), x.numel(),
-                                                       float(scale), int(zero_point), int(qmin), int(qmax), _stream()))
-    return y
+    return (_nat or _native()).simquant(x, scale, zero_point, qmin, qmax, out)
 
 
 def simquant_backward(x, grad_y, scale, zero_point, qmin=0, qmax=255, out=None):
-    torch = _torch()
-    gx = torch.empty(x.shape, dtype=torch.float32, device=x.device) if out is None else out
-    _check("qnn_simquant_backward", load_library().qnn_simquant_backward(
-        _dev(x, torch.float32, "x"), _dev(grad_y, torch.float32, "grad_y"), _dev(gx, torch.float32, "grad_x"), x.numel(),
-        float(scale), int(zero_point), int(qmin), int(qmax), _stream()))
-    return gx
+    return (_nat or _native()).simquant_backward(x, grad_y, scale, zero_point, qmin, qmax, out)
 
 
 def rescale_u8(x, z_in, mult, shift, z_out, act_min=0, act_max=255, out=None):
     """uint8 [rows, cols] (rows may be spaced apart) re-quantized to another quantizer; `out` may be a
     column slice of a wider tensor (the destination of a concatenation)."""
-    torch = _torch()
-    rows, cols = x.shape
-    y = _out(out, (rows, cols), x.device)
-    xp, ldx = _dev_rows(x, torch.uint8, "x")
-    yp, ldy = _dev_rows(y, torch.uint8, "y")
-    _check("qnn_rescale_u8", load_library().qnn_rescale_u8(xp, ldx, int(z_in), int(mult), int(shift), int(z_out), int(act_min),
-                                                           int(act_max), yp, ldy, rows, cols, _stream()))
-    return y
+    return (_nat or _native()).rescale_u8(x, z_in, mult, shift, z_out, act_min, act_max, out)
 
 
 def qdwconv2d_asym(x, z_x, w, z_w, stride, pad, mult, shift, z_out, act_min, act_max, bias=None, out=None):
     """Depthwise layer with a weight zero-point per channel: z_w int32 [C] on the device."""
-    torch = _torch()
-    N, H, W, Cc = x.shape
-    kh, kw = w.shape[:2]
-    Ho, Wo = _out_hw(H, W, kh, kw, stride, pad)
-    y = _out(out, (N, Ho, Wo, Cc), x.device)
-    _check("qnn_qdwconv2d_asym", load_library().qnn_qdwconv2d_asym(
-        _dev(x, torch.uint8, "x"), N, H, W, Cc, z_x, _dev(w, torch.int8, "w"), kh, kw, _dev(z_w, torch.int32, "z_w"), stride[0],
-        stride[1], pad[0], pad[1], _dev(bias, torch.int32, "bias"), _dev(mult, torch.int32, "mult"),
-        _dev(shift, torch.int32, "shift"), z_out, act_min, act_max, _dev(y, torch.uint8, "y"), _stream()))
-    return y
+    return (_nat or _native()).qdwconv2d_asym(x, z_x, w, z_w, stride, pad, mult, shift, z_out, act_min, act_max, bias, out)
 
 
 def qdwconv2d(x, z_x, w, stride, pad, mult, shift, z_out, act_min, act_max, bias=None, out=None):
     """x: uint8 NHWC.  w: int8 [kh,kw,C]."""
-    torch = _torch()
-    N, H, W, Cc = x.shape
-    kh, kw = w.shape[:2]
-    Ho, Wo = _out_hw(H, W, kh, kw, stride, pad)
-    y = _out(out, (N, Ho, Wo, Cc), x.device)
-    _check("qnn_qdwconv2d", load_library().qnn_qdwconv2d(
-        _dev(x, torch.uint8, "x"), N, H, W, Cc, z_x, _dev(w, torch.int8, "w"), kh, kw, stride[0], stride[1], pad[0],
-        pad[1], _dev(bias, torch.int32, "bias"), _dev(mult, torch.int32, "mult"), _dev(shift, torch.int32, "shift"),
-        z_out, act_min, act_max, _dev(y, torch.uint8, "y"), _stream()))
-    return y
+    return (_nat or _native()).qdwconv2d(x, z_x, w, stride, pad, mult, shift, z_out, act_min, act_max, bias, out)
 
 
 def qadd(a, z_a, b, z_b, params, z_out, act_min, act_max, out=None):
-    torch = _torch()
-    y = _out(out, a.shape, a.device)
-    p = params
-    _check("qnn_qadd", load_library().qnn_qadd(
-        _dev(a, torch.uint8, "a"), z_a, p["mult_a"], p["shift_a"], _dev(b, torch.uint8, "b"), z_b, p["mult_b"],
-        p["shift_b"], p["left_shift"], p["mult_o"], p["shift_o"], z_out, act_min, act_max, _dev(y, torch.uint8, "y"),
-        a.numel(), _stream()))
-    return y
+    return (_nat or _native()).qadd(a, z_a, b, z_b, params, z_out, act_min, act_max, out)
