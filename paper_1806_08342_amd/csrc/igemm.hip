@@ -243,7 +243,7 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
         qnn_status st;
         IgemmArgs plain = g;
         plain.R = nullptr;
-        if (try_skinny(plain, a_mode, b_mode, vec, s, &st)) return add_pass(st);
+        if (try_skinny(plain, a_mode, b_mode, s, &st)) return add_pass(st);
         if (try_bres(plain, a_mode, b_mode, s, &st)) return add_pass(st);
     }
     const bool mat = a_mode == A_MATRIX;
@@ -480,7 +480,7 @@ const char *qnn_qgemm_plan(int64_t M, int64_t N, int64_t K)
     if (M <= 0 || N <= 0 || K <= 0) return "";
     const Tuning &tu = tuning();
     if (M > 64 && K <= 256 && (K % 8) == 0 && !tu.forced() && !tu.no_shortk) return "shortk";
-    if (M <= 64 && (K % 64) == 0) return "skinny16";
+    if (M <= 64) return "skinny16";
     if (M >= 32768 && K > 256 && K <= 1024 && (K % 32) == 0 && N <= 256 && !tu.forced() && tu.bres != 0) return "bres";
     // reported for the aligned int8 case (what the benchmark shapes are), with all the scratch memory it asks for
     const Plan plan = choose_plan(M, N, K, (K % 64) == 0, false, (size_t)kMaxSplitBytes);

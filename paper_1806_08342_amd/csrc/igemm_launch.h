@@ -38,7 +38,7 @@ bool shortk_eligible(const IgemmArgs &g, int b_mode, bool strided);
 qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s);
 
 // Few rows (M <= 64): weight-streaming kernel of skinny.h.  Returns false if the shape does not fit.
-bool try_skinny(const IgemmArgs &g, int a_mode, int b_mode, int vec, hipStream_t s, qnn_status *status);
+bool try_skinny(const IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *status);
 
 // Medium reduction, few output channels: weight-resident kernel of bres.h.  Returns false when the
 // shape or the alignment does not fit (the caller then takes the tiled route).
