@@ -2,18 +2,19 @@
 //
 // The product is bound by streaming the weights once (K*N bytes, half of that for 4-bit weights), so the
 // kernel is organised around memory-level parallelism, not MFMA rate: one workgroup owns 16 output
-// columns, its 8 or 16 waves split K between them, and every lane fetches its own MFMA fragments
-// straight from global memory with 16-byte loads, a whole batch of K-steps in flight, no LDS staging.
+// columns, its 8 or 16 waves split K between them, and every wave keeps a whole batch of K-steps in flight.
 // The roles of the operands are swapped with respect to the big kernel: the weights are the A operand of
 // v_mfma_i32_16x16x64_i8 (16 columns n x 64 k) and the activations the B operand (16 rows m), so a lane
 // ends up with 4 consecutive output columns of one row m: one dword store, no transposition.
 //
-// A K-step is 128 deep, two matrix instructions.  8-bit weights: instruction h takes k = 64 h + 16 q +
-// (0..15) in quarter q of the lanes, so that a wave reads the two halves of every 128-byte line back to
-// back.  4-bit weights: one 16-byte load holds 32 consecutive weights, instruction h takes k = 32 q +
-// 16 h + (0..15) -- on both operands alike; a sum does not care about the order of its terms -- so that
-// as many weight bytes are in flight as with 8-bit weights; they are unpacked in registers (kept times
-// 16 in int8, accumulators shifted back exactly).
+// A fragment has its 16 rows in 16 consecutive lanes.  Loaded like that, every lane sits on a cache line
+// of its own and the vector cache delivers 15 bytes per clock and CU whatever the hit rate (measured
+// 9.3 TB/s over the chip from L2, against 31 TB/s when 8 consecutive lanes read one 128-byte line).  So a
+// load takes 8 rows x 128 bytes, and the rows change places in 4 KB of LDS that belong to the wave alone
+// (no barrier; chunk c of row r sits at c ^ (r / 2), conflict-free for the 8-bit fragment reads).
+//
+// A K-step is 128 bytes of every weight row: 128 weights, or 256 packed 4-bit weights, which are widened in
+// registers (kept times 16 in int8, accumulators shifted back exactly).
 //
 // Any K, any pitch, any alignment: gfx950 loads 16 bytes from any byte address, and the piece that
 // sticks out of a row's end is read from K - 16 instead and shifted (load_tail16).  Only the last,
@@ -70,33 +71,48 @@ __device__ __forceinline__ i32x4 widen_int4(uint32_t r0, uint32_t r1)
     return w;
 }
 
-template <int MT, bool INT4, int NW>
+// AI: load instructions per 128 bytes of the activation rows, 8 rows each
+template <int AI, bool INT4, int NW>
 __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
 {
-    constexpr int BN = 16, STEP = 128, NB = INT4 ? 1 : 2; // weight loads per step and lane
-    constexpr int UNROLL = MT == 1 ? 4 : 2;               // steps in flight per wave
-    constexpr int PW = NW < 8 ? NW : 8;                   // waves whose partial sums fit LDS at a time
-    __shared__ i32x4 part[PW][MT][64];
+    constexpr int MT = (AI + 1) / 2, BN = 16, STEP = INT4 ? 256 : 128, HALVES = STEP / 128;
+    constexpr int STEP_REGS = 4 * (2 + AI * HALVES);
+    constexpr int UNROLL = STEP_REGS <= 16 ? 4 : (STEP_REGS <= (NW > 8 ? 24 : 40) ? 2 : 1); // steps in flight per wave (what the registers hold)
+    constexpr int PW = NW < 8 ? NW : 8; // waves whose partial sums fit LDS at a time
+    static_assert(NW * 4096 >= PW * MT * 1024, "the partial sums take the place of the row exchange");
+    __shared__ __attribute__((aligned(16))) uint8_t smem[NW * 4096];
     __shared__ int32_t csum[NW][BN];
+    i32x4(*const part)[MT][64] = reinterpret_cast<i32x4(*)[MT][64]>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform
     const int n0 = blockIdx.x * BN;
-    const int frow = lane & 15, quarter = lane >> 4;
+    const int frow = lane & 15, quarter = lane >> 4; // fragment layout
+    const int lrow = lane >> 3, lchunk = lane & 7;   // load layout
 
-    // weight row (output column) and activation rows of this lane's fragments, clamped
-    int nw = n0 + frow;
-    nw = nw < g.N ? nw : g.N - 1;
-    const uint8_t *const brow = INT4 ? g.B + (((int64_t)nw * g.ldb) >> 1) : g.B + (int64_t)nw * g.ldb;
-    const uint8_t *arow[MT];
+    // weight and activation rows this lane loads from, clamped
+    const uint8_t *brow[2], *arow[AI];
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        int64_t m = t * 16 + frow;
-        m = m < g.M ? m : g.M - 1;
-        arow[t] = g.A + m * g.lda;
+    for (int i = 0; i < 2; ++i) {
+        int n = n0 + 8 * i + lrow;
+        n = n < g.N ? n : g.N - 1;
+        brow[i] = INT4 ? g.B + (((int64_t)n * g.ldb) >> 1) : g.B + (int64_t)n * g.ldb;
     }
-    // byte offsets inside a step: weights, and the activations of the two matrix instructions
-    const int boff = 16 * quarter;
-    const int aoff[2] = {INT4 ? 32 * quarter : 16 * quarter, INT4 ? 32 * quarter + 16 : 64 + 16 * quarter};
+#pragma unroll
+    for (int i = 0; i < AI; ++i) {
+        int64_t m = 8 * i + lrow;
+        m = m < g.M ? m : g.M - 1;
+        arow[i] = g.A + m * g.lda;
+    }
+    // row exchange: 16 weight rows, behind them 16 activation rows, of 128 bytes each
+    uint8_t *const xb = smem + wave * 4096, *const xa = xb + 2048;
+    auto slot = [](int row, int chunk) { return row * 128 + ((chunk ^ (row >> 1)) & 7) * 16; };
+    const int put[2] = {slot(lrow, lchunk), slot(8 + lrow, lchunk)};
+    int get_b[2], get_a[2]; // chunk read for matrix instruction h (4-bit weights: for pair h of instructions, see multiply)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        get_b[h] = slot(frow, 4 * h + quarter);
+        get_a[h] = slot(frow, INT4 ? 2 * quarter + h : 4 * h + quarter);
+    }
 
     // per-column parameters of the output this thread writes: row m = 16 t + (lane & 15), 4 columns from nb
     const int nb = n0 + 4 * quarter;
@@ -122,22 +138,40 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
     for (int t = 0; t < MT; ++t) acc[t] = i32x4{0, 0, 0, 0};
     int32_t colsum = 0;
     const bool need_colsum = g.z_a != 128;
-    // one step: wv the weight loads, av the activation loads of both matrix instructions
-    auto multiply = [&](const u32x4 (&wv)[NB], const u32x4 (&av)[2][MT]) __attribute__((always_inline)) {
+    // one step: wv the weight rows, av the activation rows, by halves of 128 bytes
+    auto multiply = [&](const u32x4 (&wv)[2], const u32x4 (&av)[HALVES][AI]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            i32x4 fb;
-            if constexpr (INT4) fb = widen_int4(wv[0][2 * h], wv[0][2 * h + 1]);
-            else fb = i32x4{(int32_t)wv[h].x, (int32_t)wv[h].y, (int32_t)wv[h].z, (int32_t)wv[h].w};
+        for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4 *>(xb + put[i]) = wv[i];
+        u32x4 w[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) w[h] = *reinterpret_cast<const u32x4 *>(xb + get_b[h]);
+#pragma unroll
+        for (int p = 0; p < HALVES; ++p) {
+            // the weights of the two matrix instructions on activation half p.  8-bit: chunk 4 h + q, k = 64 h + 16 q + (0..15).
+            // 4-bit: chunk 4 p + q holds k = 128 p + 32 q + (0..31), instruction h takes 16 h + (0..15) of them, on both
+            // operands alike -- a sum does not care about the order of its terms.
+            i32x4 fb[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if constexpr (INT4) fb[h] = widen_int4(w[p][2 * h], w[p][2 * h + 1]);
+                else fb[h] = i32x4{(int32_t)w[h].x, (int32_t)w[h].y, (int32_t)w[h].z, (int32_t)w[h].w};
+            }
             if (need_colsum) {
 #pragma unroll
-                for (int d = 0; d < 4; ++d) colsum = __builtin_amdgcn_sdot4(fb[d], 0x01010101, colsum, false);
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) colsum = __builtin_amdgcn_sdot4(fb[h][d], 0x01010101, colsum, false);
             }
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
-                const u32x4 x = av[h][t] ^ 0x80808080u; // uint8 code -> signed (code - 128)
-                const i32x4 xs = {(int32_t)x.x, (int32_t)x.y, (int32_t)x.z, (int32_t)x.w};
-                acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb, xs, acc[t], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (2 * t + i < AI) *reinterpret_cast<u32x4 *>(xa + put[i]) = av[p][2 * t + i] ^ 0x80808080u; // code -> signed (code - 128)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const i32x4 xs = *reinterpret_cast<const i32x4 *>(xa + get_a[h]); // (AI odd: rows 8..15 of the tile are nobody's)
+                    acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[h], xs, acc[t], 0, 0, 0);
+                }
             }
         }
     };
@@ -146,16 +180,16 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
     // `count` steps of this wave, all their loads ahead of the first wait
     auto batch = [&](int s0, auto count) __attribute__((always_inline)) {
         constexpr int U = decltype(count)::value;
-        u32x4 wv[U][NB], av[U][2][MT];
+        u32x4 wv[U][2], av[U][HALVES][AI];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = (s0 + u * NW) * STEP;
+            const int st = s0 + u * NW;
 #pragma unroll
-            for (int i = 0; i < NB; ++i) wv[u][i] = load16_any(brow + (INT4 ? k >> 1 : k) + boff + 64 * i);
+            for (int i = 0; i < 2; ++i) wv[u][i] = load16_any(brow[i] + st * 128 + 16 * lchunk);
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int p = 0; p < HALVES; ++p)
 #pragma unroll
-                for (int t = 0; t < MT; ++t) av[u][h][t] = load16_any(arow[t] + k + aoff[h]);
+                for (int i = 0; i < AI; ++i) av[u][p][i] = load16_any(arow[i] + st * STEP + p * 128 + 16 * lchunk);
         }
         asm volatile("" ::: "memory"); // the loads stay where they are
 #pragma unroll
@@ -163,18 +197,17 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
     };
     int s0 = wave;
     for (; s0 + (UNROLL - 1) * NW < steps; s0 += UNROLL * NW) batch(s0, std::integral_constant<int, UNROLL>{});
-    if (UNROLL > 3 && s0 + 2 * NW < steps) batch(s0, std::integral_constant<int, 3>{});
-    else if (UNROLL > 2 && s0 + NW < steps) batch(s0, std::integral_constant<int, 2>{});
+    if (UNROLL > 3 && s0 + 2 * NW < steps) batch(s0, std::integral_constant<int, UNROLL < 3 ? UNROLL : 3>{});
+    else if (UNROLL > 2 && s0 + NW < steps) batch(s0, std::integral_constant<int, UNROLL < 2 ? UNROLL : 2>{});
     else if (s0 < steps) batch(s0, std::integral_constant<int, 1>{});
     if (steps * STEP < g.K && wave == steps % NW) { // the partial step: weights beyond K read as zero
-        const int k = steps * STEP;
-        u32x4 wv[NB], av[2][MT];
+        u32x4 wv[2], av[HALVES][AI];
 #pragma unroll
-        for (int i = 0; i < NB; ++i) wv[i] = INT4 ? load_tail16(brow, (k >> 1) + boff, g.K >> 1) : load_tail16(brow, k + boff + 64 * i, g.K);
+        for (int i = 0; i < 2; ++i) wv[i] = load_tail16(brow[i], steps * 128 + 16 * lchunk, INT4 ? g.K >> 1 : g.K);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int p = 0; p < HALVES; ++p)
 #pragma unroll
-            for (int t = 0; t < MT; ++t) av[h][t] = load_tail16(arow[t], k + aoff[h], g.K);
+            for (int i = 0; i < AI; ++i) av[p][i] = load_tail16(arow[i], steps * STEP + p * 128 + 16 * lchunk, g.K);
         multiply(wv, av);
     }
 
@@ -182,6 +215,7 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
     colsum += __shfl_xor(colsum, 16);
     colsum += __shfl_xor(colsum, 32);
     if (lane < BN) csum[wave][lane] = colsum;
+    __syncthreads(); // every wave is done with its row exchange
     if constexpr (NW > PW) {
         if (wave >= PW) {
 #pragma unroll
