@@ -37,8 +37,9 @@ inline bool aligned_to(const void *p, size_t a) { return (reinterpret_cast<uintp
 bool shortk_eligible(const IgemmArgs &g, int b_mode, bool strided);
 qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s);
 
-// Few rows (M <= 64): weight-streaming kernel of skinny.h.  Returns false if the shape does not fit.
-bool try_skinny(const IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *status);
+// Few rows, and launches that are small altogether: kernel of smallk.h.  Returns false if the shape does not fit.
+bool small_shape(int64_t M, int64_t N, int64_t K, bool conv, bool int4); // sizes only
+bool try_small(const IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *status);
 
 // Medium reduction, few output channels: weight-resident kernel of bres.h.  Returns false when the
 // shape or the alignment does not fit (the caller then takes the tiled route).
@@ -46,10 +47,21 @@ bool try_bres(IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *s
 
 // Network stems (very few input channels): kernels of stemwave.h / stemconv.h.  `g` carries the
 // convolution geometry; returns false if the layer is not a stem these kernels cover.
+bool stem_shape(int64_t W, int Cin, int Cout, int kh, int kw, int stride_w, int weight_bits);
 bool try_stem(IgemmArgs &g, int batch, int kh, int stride_h, int stride_w, int weight_bits, hipStream_t s, qnn_status *status);
 
 // Row sums of the activations for per-channel weight zero-points: out[m], M int32 (igemm_rowsum.hip)
 qnn_status launch_rowsum(const IgemmArgs &g, int a_mode, int kh, int32_t *out, hipStream_t s);
+
+struct SplitK;
+// Pipelined tiles bm x bn for K % 64 != 0 (igemm_tail.hip)
+hipError_t launch_tail_tile(const IgemmArgs &g, int bm, int bn, bool mat, bool i4, const SplitK &sk, hipStream_t s);
+
+// Zero-padded copies of operands that are no whole, aligned 16-byte chunks (igemm_repack.hip).  `length`: K of a
+// matrix, Cin of a convolution.  launch_repack points g at the copies in `workspace` (repack_bytes of it).
+int repack_length(int length, int weight_bits);
+size_t repack_bytes(int64_t rows_a, int64_t rows_b, int length, int weight_bits);
+qnn_status launch_repack(IgemmArgs &g, int a_mode, int weight_bits, int kh, void *workspace, hipStream_t s);
 
 // Register-staged tiles of igemm.h (any alignment, any weight layout): 64x64 or 128x128.
 void launch_plain_tile(bool big, const IgemmArgs &g, int a_mode, int b_mode, int vec, hipStream_t s);

@@ -6,13 +6,16 @@
 
 namespace qnn {
 
+// a handful of input channels, one kernel row = one short contiguous byte run
+bool stem_shape(int64_t W, int Cin, int Cout, int kh, int kw, int stride_w, int weight_bits)
+{
+    return weight_bits == 8 && Cin < 16 && kw * Cin <= 32 && stride_w * Cin <= 7 && (kh == 3 || kh == 7) && Cout <= 64 && W * Cin >= 4;
+}
+
 bool try_stem(IgemmArgs &g, int batch, int kh, int stride_h, int stride_w, int weight_bits, hipStream_t s, qnn_status *status)
 {
     const int Cin = g.Cin, kw = g.kw, Cout = g.N, Ho = g.Ho, Wo = g.Wo;
-    // a handful of input channels, one kernel row = one short contiguous byte run
-    if (!(weight_bits == 8 && Cin < 16 && kw * Cin <= 32 && stride_w * Cin <= 7 && (kh == 3 || kh == 7) && Cout <= 64 &&
-          ((int64_t)g.W * Cin) % 4 == 0 && aligned_to(g.A, 4)))
-        return false;
+    if (!stem_shape(g.W, Cin, Cout, kh, kw, stride_w, weight_bits)) return false;
     g.small_acc = 2;
     g.c_vec16 = aligned_to(g.C, 16) && (g.ldc % 16 == 0);
     // default: the barrier-free kernel (one wave per 32-pixel strip), built for row strides 1 and 2
@@ -42,6 +45,7 @@ bool try_stem(IgemmArgs &g, int batch, int kh, int stride_h, int stride_w, int w
             return true;
         }
     }
+    if (((int64_t)g.W * Cin) % 4 != 0 || !aligned_to(g.A, 4)) return false; // this one loads aligned dwords only
     StemArgs st = {};
     st.g = g, st.kh = kh, st.run = kw * Cin;
     st.strips = (Wo + 127) / 128;

@@ -6,7 +6,7 @@
 // sub-steps, the weights (zero-padded to 32 per kernel row) stay in registers as MFMA B
 // fragments.  The image rows the strip needs (at most 256 bytes each: one dword per lane) live in
 // a wave-private LDS ring of 8 rows; going from one output row to the next only stride_h new
-// image rows are fetched (aligned dword loads, out-of-image dwords replaced by the code z_x; the
+// image rows are fetched (dword loads, out-of-image bytes replaced by the code z_x; the
 // loads for the next output row are in flight while the current one is computed; the row stride
 // is a template parameter so that these fetches are straight-line code).  Each lane
 // cuts its 32-byte window out of the ring with dword reads + v_alignbyte (the codes are stored
@@ -123,17 +123,21 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
     }
     const bool fused = __all(fused_ok);
 
-    // ---- the strip's patch of an image row: 64 aligned dwords starting at the aligned-down byte
-    // column of the first tap; lane l owns dword l.  Image rows are a multiple of 4 bytes long and
-    // the tensor is 4-byte aligned (dispatcher-checked), so a dword lies fully inside or outside.
+    // ---- the strip's patch of an image row: 64 dwords starting at the byte column of the first tap, rounded
+    // down to a multiple of 4; lane l owns dword l.  Rows may have any length and alignment (gfx950 loads a
+    // dword from any byte address): the dword that sticks out of the row's end is read from the row's last 4 bytes
+    // and shifted, its outside bytes are the code z_x like those of the dwords fully outside.
     const int row_bytes = g.W * g.Cin;
     const int patch_first = (wo0 * g.sw - g.pw) * g.Cin; // may be negative
     const int phase = patch_first & 3;
     const int my_col = patch_first - phase + lane * 4;
-    const bool col_inside = my_col >= 0 && my_col < row_bytes;
-    const uint32_t fill = (uint32_t)g.z_a * 0x01010101u;
+    const int inside = my_col < 0 ? 0 : (row_bytes - my_col >= 4 ? 4 : (row_bytes > my_col ? row_bytes - my_col : 0)); // bytes in the row
+    const uint32_t keep_shift = inside > 0 ? 8u * (uint32_t)(4 - inside) : 0u;
+    const uint32_t keep = inside == 0 ? 0u : (0xffffffffu >> keep_shift);
+    const uint32_t outside = ~keep & ((uint32_t)g.z_a * 0x01010101u);
+    auto in_ring = [&](uint32_t v) { return (((v >> keep_shift) & keep) | outside) ^ 0x80808080u; }; // as the ring holds it: signed codes
     const uint8_t *const img = g.A + (int64_t)n * g.H * row_bytes;
-    const uint32_t my_off = (uint32_t)(col_inside ? my_col : 0);
+    const uint32_t my_off = (uint32_t)(inside == 4 ? my_col : (inside > 0 ? row_bytes - 4 : 0));
     const uint8_t *const fill_chunk = &g_fill_table.v[g.z_a][0];
     // hi is wave-uniform: a row outside the image is read from the fill table (scalar base, no branch);
     // columns outside are replaced when the dword goes into the ring, not behind the load
@@ -204,7 +208,7 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
             for (int a = 0; a < KH; ++a) first[a] = fetch_row(hi0 + a);
 #pragma unroll
             for (int a = 0; a < KH - NEW; ++a)
-                *reinterpret_cast<uint32_t *>(ring_slot(hi0 + a) + lane * 4) = (col_inside ? first[a] : fill) ^ 0x80808080u;
+                *reinterpret_cast<uint32_t *>(ring_slot(hi0 + a) + lane * 4) = in_ring(first[a]);
 #pragma unroll
             for (int a = 0; a < NEW; ++a) fresh[a] = first[KH - NEW + a];
         }
@@ -215,7 +219,7 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
             const int fresh_first = ho * SH - g.ph + KH - NEW;
 #pragma unroll
             for (int a = 0; a < NEW; ++a)
-                *reinterpret_cast<uint32_t *>(ring_slot(fresh_first + a) + lane * 4) = (col_inside ? fresh[a] : fill) ^ 0x80808080u;
+                *reinterpret_cast<uint32_t *>(ring_slot(fresh_first + a) + lane * 4) = in_ring(fresh[a]);
             wave_sync();
             // ---- previous output row's stores, then the loads for the next output row (see shortk.h);
             // behind the last row of the segment the loads repeat a row already seen (in bounds, unused)
