@@ -19,7 +19,8 @@
  *     qnn_qgemm_workspace_bytes / qnn_qconv2d_workspace_bytes say how much a
  *     shape can use (0 for most): the int32 partial sums of products whose K
  *     is divided over several workgroups because they have too few output
- *     tiles for the chip, and the activation row sums of the asymmetric-weight
+ *     tiles for the chip, zero-padded copies of operands whose rows are no whole
+ *     16-byte pieces, and the activation row sums of the asymmetric-weight
  *     entry points.  With a smaller or NULL workspace the symmetric entry
  *     points take a route that needs none (same result, possibly slower); the
  *     asymmetric ones return QNN_EINVAL.  The workspace is written and read by
@@ -148,17 +149,18 @@ size_t qnn_qconv2d_workspace_bytes(int N, int H, int W, int Cin, int Cout, int k
                                    int stride_w, int pad_h, int pad_w, int asym);
 
 /* Tuning switch `name` ("QNN_FORCE_TILE", "QNN_FORCE_SPLIT", "QNN_NO_SHORTK", "QNN_BRES", "QNN_STEM_BLOCK",
- * "QNN_XCD_ROWS", "QNN_DW_RH", "QNN_DW_MAD", "QNN_GEMM_PRIO", "QNN_PERSIST", "QNN_DW_VARIANT") set to the
+ * "QNN_XCD_ROWS", "QNN_DW_RH", "QNN_DW_MAD", "QNN_GEMM_PRIO", "QNN_PERSIST", "QNN_DW_VARIANT", "QNN_SMALL", ...) set to the
  * HOST string `value`, or back to its default with value == NULL.  The switches start from the
  * environment variables of the same names, read once when the library is first used; they select among
  * kernels that give identical results (the parity tests use them to reach every variant on small shapes).
  * Not synchronised: change them only while no other thread is inside a library call. */
 qnn_status qnn_tuning_set(const char *name, const char *value);
 
-/* Name of the kernel configuration (a tile "<BM>x<BN>", with "/k<n>" when K is divided over n
+/* Name of the kernel configuration for launches that fill the chip (a tile "<BM>x<BN>", with "/k<n>" when K is divided over n
  * workgroups per tile, or "shortk" / "skinny16") that qnn_qgemm and the convolution entry points
  * select for an aligned int8 M x N x K product (M = output pixels, N = output channels, K = kh*kw*Cin);
- * for logging and profiling.  HOST string owned by the library; "" for non-positive sizes. */
+ * for logging and profiling.  Small launches (at most 800 pieces of 32 rows x 16 columns, K < 4096) run on the
+ * few-row kernel whatever the name.  HOST string owned by the library; "" for non-positive sizes. */
 const char *qnn_qgemm_plan(int64_t M, int64_t N, int64_t K);
 
 /* Transpose a K x N int8 matrix with contiguous rows (src[k*ld_src + n]) into the

@@ -345,8 +345,9 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
             if (m >= g.M || n >= g.N) continue;
             uint8_t *dst = g.C + m * g.ldc + n;
             const uint8_t *src = so + row * OUT_PITCH + cc * 16;
-            if (g.c_vec16 && n + 16 <= g.N) {
-                *reinterpret_cast<u32x4 *>(dst) = *reinterpret_cast<const u32x4 *>(src);
+            if (n + 16 <= g.N) { // any alignment: gfx950 stores 16 bytes to any byte address
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(src);
+                __builtin_memcpy(dst, &v, 16);
             } else {
                 for (int e = 0; e < 16 && n + e < g.N; ++e) dst[e] = src[e];
             }

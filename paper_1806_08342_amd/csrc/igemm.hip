@@ -6,7 +6,7 @@
 #include <cstring>
 #include <mutex>
 
-#include "igemm_dma.h"
+#include "igemm_dma_launch.h"
 #include "igemm_launch.h"
 #include "tuning.h"
 
@@ -39,7 +39,7 @@ struct Plan {
     int splits; // > 1: split-K (128x128 and 64x64 pipelined tiles only)
 };
 
-// Tile choice.  `dma_ok`: weights with contiguous columns, 16-byte aligned chunks, K % 64 == 0.
+// Tile choice.  `dma_ok`: weights with contiguous columns, operands made of whole, aligned 16-byte chunks.
 //  - large products: 256x256 tiles (8 waves, 4 LDS stages, one workgroup per CU), or the
 //    256x128 / 128x128 / 256x64 tile that wastes the least work in partly filled rounds;
 //  - short K (<= 256): 3 LDS stages instead of 4, so that more workgroups fit a CU and one
@@ -56,22 +56,24 @@ static Plan choose_plan(int64_t M, int64_t N, int64_t K, bool dma_ok, bool int4,
                 if (int4 && t >= TILE_DMA_128x128 && t != TILE_DMA_128x128 && t != TILE_DMA_256x256 && t != TILE_DMA_64x64) break;
                 int splits = 1;
                 if (!int4 && (t == TILE_DMA_128x128 || t == TILE_DMA_64x64)) splits = tu.force_split > 0 ? tu.force_split : 1;
-                const int ksteps = (int)(K / 64);
+                const int ksteps = (int)((K + 63) / 64);
                 splits = splits < 1 ? 1 : (splits > ksteps ? ksteps : splits);
                 if (!fits(splits)) splits = 1;
                 return Plan{(TileConfig)t, splits};
             }
     }
-    if (dma_ok && M >= 128 && int4) { // the pipelined kernel expands nibbles for three tile shapes
+    if (dma_ok && int4) { // the pipelined kernel expands nibbles for three tile shapes
         const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
-        if (K > 256 && N >= 128 && t256 >= 160) return Plan{TILE_DMA_256x256, 1};
-        if (N >= 128 && t128 >= 192) return Plan{TILE_DMA_128x128, 1};
+        if (K > 256 && M >= 128 && N >= 128 && t256 >= 160) return Plan{TILE_DMA_256x256, 1};
+        if (M >= 128 && N >= 128 && t128 >= 192) return Plan{TILE_DMA_128x128, 1};
         return Plan{TILE_DMA_64x64, 1};
     }
-    if (dma_ok && M >= 128) {
-        if (K <= 256) { // epilogue-bound: small tiles, several workgroups per CU
-            if (N <= 64) return Plan{TILE_DMA_256x64_S3, 1};
-            if (N >= 128) return Plan{TILE_DMA_128x128_S3, 1};
+    if (dma_ok) {
+        if (K <= 256 && M >= 128 && (N <= 64 ? (M + 255) / 256 : ((M + 127) / 128) * ((N + 127) / 128)) >= 128) {
+            // epilogue-bound and enough tiles for half the chip: small tiles, several workgroups per CU
+            return Plan{N <= 64 ? TILE_DMA_256x64_S3 : TILE_DMA_128x128_S3, 1};
+        } else if (K <= 256) {
+            return Plan{TILE_DMA_64x64, 1};
         } else {
             // short reductions over several rounds of tiles: the 4-wave 128x256 tile with two workgroups per CU, whose
             // epilogues run under the other workgroup's loop (measured 11-25 % ahead of the 8-wave tiles for
@@ -105,7 +107,7 @@ static Plan choose_plan(int64_t M, int64_t N, int64_t K, bool dma_ok, bool int4,
             // of the MFMA pipe, so many small tiles win.  With very few tiles and a long K, the K-steps
             // of each tile are divided over several workgroups as well (measured break-even points:
             // the second pass and the partial sums cost about as much as 16 K-steps).
-            const int ksteps = (int)(K / 64);
+            const int ksteps = (int)((K + 63) / 64);
             const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128), tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
             Plan plan{TILE_DMA_64x64, 1};
             if (tiles128 <= 128 && tiles128 > 16 && ksteps >= 128) plan = Plan{TILE_DMA_128x128, tiles128 <= 64 ? 4 : 2};
@@ -121,73 +123,34 @@ static Plan choose_plan(int64_t M, int64_t N, int64_t K, bool dma_ok, bool int4,
 }
 
 // Scratch memory comes from the caller (`workspace` of the entry points): the int32 activation row
-// sums of the asymmetric-weight entry points (M values, first) and the partial sums of split-K
-// (splits x M x N values, behind them at the next multiple of 256 bytes).
+// sums of the asymmetric-weight entry points (M values), or zero-padded copies of operands that are no whole
+// 16-byte chunks, and behind them the partial sums of split-K (splits x M x N values).
 constexpr uint64_t kMaxSplitBytes = (uint64_t)1 << 40;
 static size_t rowsum_bytes(int64_t M) { return (size_t)((M * 4 + 255) / 256 * 256); }
 
-static size_t workspace_bytes_for(int64_t M, int64_t N, int64_t K, int weight_bits, bool asym)
+static size_t split_bytes_for(int64_t M, int64_t N, int64_t K, int weight_bits)
 {
-    if (M <= 0 || N <= 0 || K <= 0) return 0;
-    if (asym) return rowsum_bytes(M);
-    if ((K % 64) != 0) return 0;                                  // unaligned: the staged kernel, never split
+    if (M <= 0 || N <= 0 || K <= 0 || (K % 16) != 0) return 0;
     if (!tuning().forced() && (M <= 64 || K <= 256)) return 0; // few-row and short-K kernels
     const Plan plan = choose_plan(M, N, K, true, weight_bits == 4, (size_t)kMaxSplitBytes);
     if (plan.splits <= 1) return 0;
-    const int ksteps = (int)((K / 64 + plan.splits - 1) / plan.splits);
-    const int splits = (int)((K / 64 + ksteps - 1) / ksteps);
+    const int all = (int)((K + 63) / 64), ksteps = (all + plan.splits - 1) / plan.splits;
+    const int splits = (all + ksteps - 1) / ksteps;
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * 4 : 0;
 }
 
-// One rectangle of the tile grid per XCD: pick the cut (8x1, 4x2, 2x4, 1x8) with the least operand
-// traffic from beyond the L2s (8/r copies of A's share + r copies of B's), among those that leave
-// the XCDs within 10 % of an even load; else (xcd_rows stays 0) bands of the linear tile sequence.
-static void choose_xcd_cut(const IgemmArgs &g, int tiles_m, int tiles_n, int64_t work, int &per_xcd, int &xcd_rows)
-{
-    const int forced = tuning().xcd_rows;
-    double best = 0.0;
-    for (int r : {8, 4, 2, 1}) {
-        const int c = 8 / r;
-        if (forced >= 0 ? r != forced : false) continue;
-        if (tiles_m < r || tiles_n < c) continue;
-        const int64_t biggest = (int64_t)((tiles_m + r - 1) / r) * ((tiles_n + c - 1) / c);
-        if (forced < 0 && biggest * 8 * 10 > work * 11) continue;
-        const double traffic = (double)c * (double)g.M + (double)r * (double)g.N; // per unit of K
-        if (xcd_rows == 0 || traffic < best) best = traffic, xcd_rows = r, per_xcd = (int)biggest;
-    }
-}
+// Padded copies pay from about 2^22 multiply-accumulates on (they cost a launch of their own, about 2 us).
+static bool repack_pays(int64_t M, int64_t N, int64_t K) { return !tuning().forced() && (double)M * (double)N * (double)K >= (double)(1 << 22); }
 
-// `per_cu` > 0: persistent launch with that many workgroups per CU (each walks its XCD's tile
-// sequence); 0: one workgroup per tile.  `prio`: issue-priority scheme of the main loop (see the kernel).
-template <int BM, int BN, int WM, int WN, int A_MODE, int NSTAGE, bool SPLIT = false, bool ZW = false, bool B4 = false,
-          int MINW = 1>
-static hipError_t launch_dma(const IgemmArgs &g, hipStream_t s, SplitK sk = SplitK{1, 0, nullptr}, int per_cu = 0, int prio = 0)
+static size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int weight_bits, bool asym)
 {
-    constexpr int kStages = NSTAGE * (BM + BN) * 64;
-    constexpr int kOut = BM * (BN + 16) + 4 * WM * WN * (BN / WN / 32) * 64 + 2048 + 4 * BM; // + add tables + row sums
-    constexpr int kLds = kStages > kOut ? kStages : kOut; // operand ring, reused for the output tile + column sums + add tables
-    auto kernel = igemm_dma_kernel<BM, BN, WM, WN, A_MODE, NSTAGE, SPLIT, ZW, B4, MINW>;
-    static LdsOptIn opt_in; // per instantiation
-    if (hipError_t e = opt_in.ensure(reinterpret_cast<const void *>(kernel), kLds); e != hipSuccess) return e;
-    const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (g.N + BN - 1) / BN;
-    const int64_t work = (int64_t)tiles_m * tiles_n * sk.splits;
-    int per_xcd = (int)((work + 7) / 8), xcd_rows = 0;
-    if (!SPLIT) choose_xcd_cut(g, tiles_m, tiles_n, work, per_xcd, xcd_rows);
-    const Tuning &tu = tuning();
-    if (tu.persist == 0) per_cu = 0;
-    else if (tu.persist > 0) per_cu = tu.persist;
-    if (tu.gemm_prio >= 0) prio = tu.gemm_prio;
-    int slots = per_xcd; // workgroups per XCD
-    if (per_cu > 0 && slots > 32 * per_cu) slots = 32 * per_cu;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(slots * 8)), dim3(WM * WN * 64), kLds, s, g, tiles_m, tiles_n, per_xcd, xcd_rows,
-                       sk, prio);
-    hipError_t e = hipGetLastError();
-    if (SPLIT && e == hipSuccess) {
-        const int64_t threads = g.M * (((int64_t)g.N + 3) / 4);
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, g, sk);
-        e = hipGetLastError();
-    }
-    return e;
+    if (M <= 0 || N <= 0 || K <= 0) return 0;
+    if (asym) return rowsum_bytes(M);
+    const int64_t padded = repack_length((int)K, weight_bits);
+    if (padded == K) return split_bytes_for(M, N, K, weight_bits);
+    if (small_shape(M, N, K, false, weight_bits == 4) || !repack_pays(M, N, K) || (K <= 256 && (K % 8) == 0)) return 0; // these take it as it is
+    const size_t copies = repack_bytes(M, N, (int)K, weight_bits);
+    return copies ? copies + split_bytes_for(M, N, padded, weight_bits) : 0;
 }
 
 // Per-column weight zero-points (eq. 5-6 with z_w != 0): the activation row sums go to the caller's
@@ -233,7 +196,6 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
     g.c_vec16 = aligned_to(g.C, 16) && (g.ldc % 16 == 0);
     g.r_vec16 = g.R != nullptr && aligned_to(g.R, 16) && (g.ldr % 16 == 0);
     if (g.zw) return run_igemm_zw(g, a_mode, b_mode, vec, kh, workspace, workspace_bytes, s);
-    if (a_mode == A_MATRIX && shortk_eligible(g, b_mode, false)) return launch_shortk(g, b_mode, false, s);
     // kernels that do not apply a residual add themselves run without it; the add follows as a second pass
     auto add_pass = [&](qnn_status st) {
         if (st != QNN_OK || !g.R) return st;
@@ -243,15 +205,28 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
         qnn_status st;
         IgemmArgs plain = g;
         plain.R = nullptr;
-        if (try_skinny(plain, a_mode, b_mode, s, &st)) return add_pass(st);
+        if (try_small(plain, a_mode, b_mode, s, &st)) return add_pass(st);
+        if (a_mode == A_MATRIX && shortk_eligible(g, b_mode, false)) return launch_shortk(g, b_mode, false, s);
         if (try_bres(plain, a_mode, b_mode, s, &st)) return add_pass(st);
     }
     const bool mat = a_mode == A_MATRIX;
     const bool i4 = b_mode == B_INT4;
-    // the pipelined kernel: 16-byte aligned chunks of A and B (4-bit: 32 elements per chunk), whole K-steps
-    const bool dma_ok = (b_mode == B_INT8 || i4) && vec == 16 && (g.K % 64) == 0 && g.lda < (1 << 23) && g.ldb < (1 << 23) &&
-                        (!i4 || (aligned_to(g.B, 16) && (g.ldb % 32) == 0));
+    // the pipelined kernel: 16-byte aligned chunks of A and B (4-bit: 32 elements per chunk)
+    const bool dma_ok = (b_mode == B_INT8 || i4) && vec == 16 && g.lda < (1 << 23) && g.ldb < (1 << 23) &&
+                        (!i4 || (aligned_to(g.B, 16) && (g.ldb % 32) == 0 && (g.K % 32) == 0));
+    const bool tail = (g.K % 64) != 0;
     if (!aligned_to(workspace, 16)) workspace = nullptr;
+    if (!dma_ok && b_mode != B_INT8_ROWS && workspace && repack_pays(g.M, g.N, g.K)) {
+        // operands that are no whole chunks: zero-padded copies in the workspace, if it holds them, then from the start
+        const int bits = i4 ? 4 : 8;
+        const int64_t rows_a = mat ? g.M : g.M / ((int64_t)g.Ho * g.Wo) * g.H * g.W, rows_b = mat ? g.N : (int64_t)g.N * kh * g.kw;
+        const size_t copies = repack_bytes(rows_a, rows_b, mat ? g.K : g.Cin, bits);
+        if (copies && copies <= workspace_bytes) {
+            IgemmArgs padded = g;
+            if (qnn_status st = launch_repack(padded, a_mode, bits, kh, workspace, s); st != QNN_OK) return st;
+            return run_igemm(padded, a_mode, b_mode, 16, static_cast<uint8_t *>(workspace) + copies, workspace_bytes - copies, s, kh);
+        }
+    }
     const Plan plan = choose_plan(g.M, g.N, g.K, dma_ok, i4, workspace ? workspace_bytes : 0);
     const TileConfig cfg = plan.tile;
     const int64_t bm = kTileM[cfg], bn = kTileN[cfg];
@@ -265,22 +240,26 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
     }
     if (plan.splits > 1) {
         SplitK sk;
-        sk.ksteps = (g.K / 64 + plan.splits - 1) / plan.splits;
-        sk.splits = (g.K / 64 + sk.ksteps - 1) / sk.ksteps; // no empty K range
+        const int all = (g.K + 63) / 64;
+        sk.ksteps = (all + plan.splits - 1) / plan.splits;
+        sk.splits = (all + sk.ksteps - 1) / sk.ksteps; // no empty K range
         sk.partial = static_cast<int32_t *>(workspace);
         if (sk.partial && sk.splits > 1) {
             hipError_t e;
             IgemmArgs plain = g; // the reduction kernel writes the product's code; the add follows
             plain.R = nullptr;
-            if (cfg == TILE_DMA_128x128)
-                e = mat ? launch_dma<128, 128, 2, 2, A_MATRIX, 4, true>(plain, s, sk) : launch_dma<128, 128, 2, 2, A_CONV, 4, true>(plain, s, sk);
-            else
+            if (tail)
+                e = launch_tail_tile(plain, (int)bm, (int)bn, mat, false, sk, s);
+            else if (cfg == TILE_DMA_64x64)
                 e = mat ? launch_dma<64, 64, 2, 2, A_MATRIX, 4, true>(plain, s, sk) : launch_dma<64, 64, 2, 2, A_CONV, 4, true>(plain, s, sk);
+            else
+                e = mat ? launch_dma<128, 128, 2, 2, A_MATRIX, 4, true>(plain, s, sk) : launch_dma<128, 128, 2, 2, A_CONV, 4, true>(plain, s, sk);
             return add_pass(launch_status(e));
         }
     }
     if (((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) > max_tiles) return QNN_EINVAL;
     const SplitK one{1, 0, nullptr};
+    if (tail && cfg >= TILE_DMA_128x128) return launch_status(launch_tail_tile(g, (int)bm, (int)bn, mat, i4, one, s));
     switch (cfg) {
     case TILE_64x64:
         launch_plain_tile(false, g, a_mode, b_mode, vec, s);
@@ -492,7 +471,8 @@ const char *qnn_qgemm_plan(int64_t M, int64_t N, int64_t K)
 
 size_t qnn_qgemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int weight_bits, int asym)
 {
-    return workspace_bytes_for(M, N, K, weight_bits, asym != 0);
+    if (K > 65536) return 0; // rejected by the entry points
+    return gemm_workspace_bytes(M, N, K, weight_bits, asym != 0);
 }
 
 size_t qnn_qconv2d_workspace_bytes(int N, int H, int W, int Cin, int Cout, int kh, int kw, int weight_bits, int stride_h,
@@ -502,7 +482,17 @@ size_t qnn_qconv2d_workspace_bytes(int N, int H, int W, int Cin, int Cout, int k
         pad_h < 0 || pad_w < 0 || H + 2 * (int64_t)pad_h < kh || W + 2 * (int64_t)pad_w < kw)
         return 0;
     const int64_t Ho = (H + 2 * (int64_t)pad_h - kh) / stride_h + 1, Wo = (W + 2 * (int64_t)pad_w - kw) / stride_w + 1;
-    return workspace_bytes_for((int64_t)N * Ho * Wo, Cout, (int64_t)kh * kw * Cin, weight_bits, asym != 0);
+    const int64_t M = (int64_t)N * Ho * Wo, K = (int64_t)kh * kw * Cin;
+    if (K > 65536) return 0; // rejected by the entry points
+    const bool pointwise = kh == 1 && kw == 1 && stride_h == 1 && stride_w == 1 && pad_h == 0 && pad_w == 0;
+    if (asym || pointwise) return gemm_workspace_bytes(M, Cout, K, weight_bits, asym != 0);
+    if (stem_shape(W, Cin, Cout, kh, kw, stride_w, weight_bits)) return 0;
+    const int padded = repack_length(Cin, weight_bits);
+    if ((Cin % 16) == 0 && (weight_bits == 8 || (K % 32) == 0)) return split_bytes_for(M, Cout, K, weight_bits);
+    if (!repack_pays(M, Cout, K)) return 0;
+    if (kh == 1 && kw == 1 && pad_h == 0 && pad_w == 0 && K <= 256 && (K % 8) == 0) return 0; // strided 1x1: short-K kernel
+    const size_t copies = repack_bytes((int64_t)N * H * W, (int64_t)Cout * kh * kw, Cin, weight_bits);
+    return copies ? copies + split_bytes_for(M, Cout, (int64_t)kh * kw * padded, weight_bits) : 0;
 }
 
 qnn_status qnn_qgemm(const uint8_t *A, int64_t lda, int32_t z_a, const void *B, int64_t ldb, int b_layout,
@@ -519,7 +509,8 @@ qnn_status qnn_qgemm_noalloc(const uint8_t *A, int64_t lda, int32_t z_a, const v
                              const int32_t *shift, int32_t z_out, int32_t act_min, int32_t act_max, uint8_t *C, int64_t ldc,
                              void *stream)
 {
-    const size_t need = workspace_bytes_for(M, N, K, weight_bits, false);
+    // (padded copies are a matter of speed: without room for them the product takes another route)
+    const size_t need = split_bytes_for(M, N, K, weight_bits);
     if (need > kStaticScratchBytes) {
         char text[160];
         std::snprintf(text, sizeof text, "qnn_qgemm_noalloc: this product asks for %zu bytes of scratch, the static array holds %zu",

@@ -12,7 +12,8 @@
 // swizzle of the tile is applied on the global-address side.
 //
 // Requirements (checked by the dispatcher): every 16-byte chunk is 16-byte aligned (pitches
-// and base pointers multiples of 16; for convolutions Cin % 16 == 0), K % 64 == 0, and the
+// and base pointers multiples of 16; for convolutions Cin % 16 == 0), K % 64 == 0 (KTAIL: whole
+// 16-byte chunks of B, i.e. K % 16 == 0, 4-bit weights K % 32 == 0), and the
 // byte offsets inside one tile fit 32 bits.  Rows beyond M / columns beyond N are clamped to
 // the last valid one (their results are never stored); out-of-image taps of a convolution
 // read a constant chunk holding the code z_x.
@@ -123,8 +124,10 @@ __device__ __forceinline__ i32x4 expand_int4(u32x2 raw)
     return w;
 }
 
+// KTAIL: K need not be a multiple of 64.  Chunks of B beyond K are fetched from a chunk of zeros, chunks
+// of A from the row's last chunk (any bytes do: they meet zero weights).
 template <int BM, int BN, int WM, int WN, int A_MODE, int NSTAGE, bool SPLIT = false, bool ZW = false, bool B4 = false,
-          int MINW = 1>
+          int MINW = 1, bool KTAIL = false>
 __global__ void __launch_bounds__(WM *WN * 64, MINW)
     igemm_dma_kernel(const IgemmArgs g, const int tiles_m, const int tiles_n, const int per_xcd, const int xcd_rows,
                      const SplitK sk, const int tune)
@@ -161,6 +164,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
         const uint8_t *a_src[A_LOADS], *a_pix[A_LOADS];
         int a_koff[A_LOADS], a_hi0[A_LOADS], a_wi0[A_LOADS];
         uint32_t a_lane_off[A_LOADS], b_lane_off[B_LOADS];
+        int b_k[B_LOADS]; // KTAIL: k of the chunk within its K-step
         const uint8_t *const a_tile = g.A + m0 * g.lda;                 // A_MATRIX only
         const uint8_t *const b_tile = g.B + (B4 ? ((int64_t)n0 * g.ldb) >> 1 : (int64_t)n0 * g.ldb);
 #pragma unroll
@@ -193,21 +197,25 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
                 const int b_koff = ((lane & 1) ^ ((row >> 3) & 1)) * 16; // bytes: 32 packed elements per chunk
                 int n = n0 + row;
                 n = n < g.N ? n : g.N - 1;
+                b_k[j] = 2 * b_koff;
                 b_lane_off[j] = (uint32_t)(((int64_t)(n - n0) * g.ldb) >> 1) + (uint32_t)b_koff;
             } else {
                 const int row = (wave * B_LOADS + j) * 16 + (lane >> 2);
                 const int b_koff = (((lane & 3) ^ lds_swizzle(row)) & 3) * 16;
                 int n = n0 + row;
                 n = n < g.N ? n : g.N - 1;
+                b_k[j] = b_koff;
                 b_lane_off[j] = (uint32_t)((int64_t)(n - n0) * g.ldb) + (uint32_t)b_koff;
             }
         }
         const uint8_t *fill_a = &g_fill_table.v[g.z_a][0];
         ChannelParams<TN> cparams = {};
         if constexpr (!SPLIT) cparams = load_channel_params<BN, WN, TN>(g, n0);
-        // K-steps [kt_first, kt_first + ktiles) of the product; the dispatcher guarantees K % 64 == 0
+        // K-steps [kt_first, kt_first + ktiles) of the product
+        const int ksteps_all = KTAIL ? (g.K + BK - 1) / BK : g.K / BK;
         const int kt_first = SPLIT ? split * sk.ksteps : 0;
-        const int ktiles = SPLIT ? ((g.K / BK - kt_first) < sk.ksteps ? (g.K / BK - kt_first) : sk.ksteps) : g.K / BK;
+        const int ktiles = SPLIT ? ((ksteps_all - kt_first) < sk.ksteps ? (ksteps_all - kt_first) : sk.ksteps) : ksteps_all;
+        const uint8_t *zero_b = &g_fill_table.v[0][0];
         const bool tap_uniform = A_MODE == A_CONV && (g.Cin % BK) == 0;
 
         // load number `idx` (0 .. LOADS-1) of K-step kt: A segments first, then B segments.
@@ -221,7 +229,10 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
             if (idx < A_LOADS) {
                 const int j = idx;
                 const uint8_t *src = fill_a;
-                if constexpr (A_MODE == A_MATRIX) {
+                if constexpr (A_MODE == A_MATRIX && KTAIL) {
+                    const int over = k0 + a_koff[j] - (g.K - 16); // beyond the row's last chunk: take that one
+                    if (live) src = (a_tile + k0) + (a_lane_off[j] - (uint32_t)(over > 0 ? over : 0));
+                } else if constexpr (A_MODE == A_MATRIX) {
                     if (live) src = (a_tile + k0) + a_lane_off[j]; // K % 64 == 0: no tail
                 } else {
                     const int k = k0 + a_koff[j];
@@ -251,10 +262,14 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
                     const int seg = wave * B_LOADS + j; // wave-uniform
                     const bool mine = seg < B_SEGS;
                     const uint8_t *src = (live && mine) ? (b_tile + (k0 >> 1)) + b_lane_off[j] : fill_a;
+                    if constexpr (KTAIL)
+                        if (k0 + b_k[j] >= g.K) src = zero_b;
                     // segments beyond the tile: into the unused second half of the B area
                     dma16(src, stage + BM * BK + (mine ? seg * 1024 : BN * 32));
                 } else {
                     const uint8_t *src = live ? (b_tile + k0) + b_lane_off[j] : fill_a;
+                    if constexpr (KTAIL)
+                        if (k0 + b_k[j] >= g.K) src = zero_b;
                     dma16(src, stage + BM * BK + (wave * B_LOADS + j) * 1024);
                 }
             }
@@ -422,7 +437,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
 
 // Second pass of split-K: out[m][n] = clamp(z_out + RESCALE(sum_s partial[s][m][n] + bias[n])).
 // One thread per 4 consecutive columns of one row.
-__global__ void __launch_bounds__(256) splitk_reduce_kernel(const IgemmArgs g, const SplitK sk)
+static __global__ void __launch_bounds__(256) splitk_reduce_kernel(const IgemmArgs g, const SplitK sk)
 {
     const int64_t groups = ((int64_t)g.N + 3) / 4;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;

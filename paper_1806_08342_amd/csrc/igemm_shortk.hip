@@ -1,8 +1,7 @@
-// Launch routines of the weight-stationary short-K kernel and of the few-row kernel.
+// Launch routine of the weight-stationary short-K kernel.
 #include "igemm_launch.h"
 #include "tuning.h"
 #include "shortk.h"
-#include "skinny.h"
 
 namespace qnn {
 
@@ -118,29 +117,6 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
     const qnn_status st = launch_status(hipGetLastError());
     if (st != QNN_OK || !add_pass) return st;
     return launch_add_inplace(g.C, g.ldc, g.R, g.ldr, g.M, g.N, g.add, s);
-}
-
-template <int AI, bool INT4> static void launch_skinny(const IgemmArgs &g, hipStream_t s)
-{
-    const unsigned blocks = (unsigned)((g.N + 15) / 16);
-    // 16 waves per workgroup where one workgroup per CU leaves CUs idle and K is long enough to divide further
-    // (with 64 rows in flight 16 waves do not fit the register file)
-    constexpr int kWide = AI < 8 ? 16 : 8;
-    if (blocks <= 256 && g.K >= 2048) hipLaunchKernelGGL((skinny_gemm_kernel<AI, INT4, kWide>), dim3(blocks), dim3(kWide * 64), 0, s, g);
-    else hipLaunchKernelGGL((skinny_gemm_kernel<AI, INT4, 8>), dim3(blocks), dim3(512), 0, s, g);
-}
-
-bool try_skinny(const IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *status)
-{
-    // few rows: weight-streaming kernel (one workgroup per 16 output columns, K split over its waves)
-    if (a_mode != A_MATRIX || g.M > 64 || b_mode == B_INT8_ROWS || tuning().forced()) return false;
-    const bool i4 = b_mode == B_INT4;
-    if (g.M <= 8) i4 ? launch_skinny<1, true>(g, s) : launch_skinny<1, false>(g, s);
-    else if (g.M <= 16) i4 ? launch_skinny<2, true>(g, s) : launch_skinny<2, false>(g, s);
-    else if (g.M <= 32) i4 ? launch_skinny<4, true>(g, s) : launch_skinny<4, false>(g, s);
-    else i4 ? launch_skinny<8, true>(g, s) : launch_skinny<8, false>(g, s);
-    *status = launch_status(hipGetLastError());
-    return true;
 }
 
 } // namespace qnn

@@ -1,0 +1,79 @@
+// Launch routine of the kernel for few rows and small launches.
+#include "igemm_launch.h"
+#include "smallk.h"
+#include "tuning.h"
+
+namespace qnn {
+
+// Few rows (weights streamed once), or at most 800 workgroups of 32 rows x 16 columns: about three per CU,
+// beyond which the tiles' higher rate wins (784 workgroups: 3136 x 128 x 128 in 4.1 us against 6.7, 4 x 28x28x128 3x3
+// in 7.4 against 10.6; 1568: 1568 x 512 x 512 in 6.8 against 6.0).  Matrices with K >= 4096 and 8-bit weights are
+// left to split-K over workgroups.
+bool small_shape(int64_t M, int64_t N, int64_t K, bool conv, bool int4)
+{
+    if (M <= 64 && !conv) return true;
+    if (!tuning().small || tuning().bres == 1) return false; // tuning aids: reach the other kernels on small shapes
+    if (!conv && !int4 && K >= 4096) return false;
+    return ((N + 15) / 16) * ((M + 31) / 32) <= 800;
+}
+
+// x / d = umulhi(x, magic) >> shift for x < 2^31, d >= 2
+static void division(uint32_t d, uint32_t &magic, uint32_t &shift)
+{
+    uint32_t l = 0;
+    while ((1u << l) < d) ++l;
+    shift = l > 0 ? l - 1 : 0;
+    magic = d > 1 ? (uint32_t)((((uint64_t)1 << (31 + l)) + d - 1) / d) : 0u;
+}
+
+template <int AI, bool INT4, int A_MODE> static void launch_rows(const SmallArgs &a, int waves, hipStream_t s)
+{
+    const dim3 grid((unsigned)((a.g.N + 15) / 16), (unsigned)((a.g.M + 8 * AI - 1) / (8 * AI)));
+    // (64 rows in 16 waves do not fit the register file)
+    if (waves == 4) hipLaunchKernelGGL((smallk_kernel<AI, INT4, 4, A_MODE>), grid, dim3(256), 0, s, a);
+    else if (waves == 8 || AI == 8) hipLaunchKernelGGL((smallk_kernel<AI, INT4, 8, A_MODE>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((smallk_kernel<AI, INT4, AI == 8 ? 8 : 16, A_MODE>), grid, dim3(1024), 0, s, a);
+}
+
+template <bool INT4> static void launch_small(const SmallArgs &a, bool conv, hipStream_t s)
+{
+    const IgemmArgs &g = a.g;
+    const int64_t cols = (g.N + 15) / 16, wgs32 = cols * ((g.M + 31) / 32);
+    const int steps = (g.K + (INT4 ? 255 : 127)) / (INT4 ? 256 : 128);
+    // rows per workgroup: 64 where that still gives every CU a workgroup and halves the weight traffic, else 32 or fewer
+    const int ai = g.M <= 8 ? 1 : (g.M <= 16 ? 2 : (g.M > 32 && g.M <= 64 && wgs32 > 256 ? 8 : 4));
+    const int64_t wgs = ai == 4 ? wgs32 : cols;
+    // waves: K is divided as far as one workgroup per CU goes; several workgroups per CU overlap each other instead
+    // (784 workgroups on 8 x 14x14x256, 3x3: 8.9 us with 4 waves, 10.4 with 8; 64 x 8192 x 8192 28.5 against 31.7)
+    const bool several = wgs > (ai == 8 ? 256 : 512) && ai >= 4;
+    const int waves = several || steps <= 4 ? 4 : (ai < 8 && wgs <= 256 && steps > 8 ? 16 : 8);
+    if (conv) {
+        launch_rows<4, INT4, A_CONV>(a, waves, s);
+    } else if (ai == 1) {
+        launch_rows<1, INT4, A_MATRIX>(a, waves, s);
+    } else if (ai == 2) {
+        launch_rows<2, INT4, A_MATRIX>(a, waves, s);
+    } else if (ai == 4) {
+        launch_rows<4, INT4, A_MATRIX>(a, waves, s);
+    } else {
+        launch_rows<8, INT4, A_MATRIX>(a, waves, s);
+    }
+}
+
+bool try_small(const IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *status)
+{
+    const bool conv = a_mode == A_CONV;
+    if (b_mode == B_INT8_ROWS || tuning().forced() || !small_shape(g.M, g.N, g.K, conv, b_mode == B_INT4)) return false;
+    if (conv && (g.Cin % 16) != 0) return false;
+    SmallArgs a = {};
+    a.g = g;
+    if (conv) {
+        division((uint32_t)(g.Ho * g.Wo), a.magic_hw, a.shift_hw);
+        division((uint32_t)g.Wo, a.magic_wo, a.shift_wo);
+    }
+    b_mode == B_INT4 ? launch_small<true>(a, conv, s) : launch_small<false>(a, conv, s);
+    *status = launch_status(hipGetLastError());
+    return true;
+}
+
+} // namespace qnn

@@ -1,8 +1,11 @@
-// Quantized GEMM with very few rows (M <= 64: a fully connected layer at small batch).
+// Quantized product for launches that are small altogether: few rows (M <= 64, a fully connected layer at
+// small batch), or any matrix / convolution whose work does not fill the chip (networks at batch 1).
 //
-// The product is bound by streaming the weights once (K*N bytes, half of that for 4-bit weights), so the
-// kernel is organised around memory-level parallelism, not MFMA rate: one workgroup owns 16 output
-// columns, its 8 or 16 waves split K between them, and every wave keeps a whole batch of K-steps in flight.
+// Such a launch is bound by latencies and, with few rows, by streaming the weights once, so the kernel is
+// organised around memory-level parallelism, not MFMA rate: one workgroup owns 16 output columns of up to
+// 64 rows, its 4, 8 or 16 waves split K between them, and every wave keeps a whole batch of K-steps in flight.
+// On 64x64 tiles the same K loop is a serial chain of barriers, 0.2 us per 64 k behind 4 us of set-up (7x7x512
+// -> 512, 3x3: 31 us; 196 x 512 x 512: 5.8 us; here 4 and 3.4).
 // The roles of the operands are swapped with respect to the big kernel: the weights are the A operand of
 // v_mfma_i32_16x16x64_i8 (16 columns n x 64 k) and the activations the B operand (16 rows m), so a lane
 // ends up with 4 consecutive output columns of one row m: one dword store, no transposition.
@@ -22,9 +25,21 @@
 // the reduction their latency was a fifth of the kernel (M = 1, 4096 x 4096).
 #pragma once
 
+#include "fill_table.h"
 #include "igemm.h"
 
 namespace qnn {
+
+struct SmallArgs {
+    IgemmArgs g;
+    // convolutions: pixel m -> (image, ho, wo) by multiply-high: m / (Ho * Wo) and rest / Wo, m < 2^31
+    uint32_t magic_hw, shift_hw, magic_wo, shift_wo;
+};
+
+__device__ __forceinline__ uint32_t div_magic(uint32_t x, uint32_t d, uint32_t magic, uint32_t shift)
+{
+    return d == 1 ? x : __umulhi(x, magic) >> shift;
+}
 
 // 16 bytes from any byte address
 __device__ __forceinline__ u32x4 load16_any(const uint8_t *p)
@@ -71,10 +86,12 @@ __device__ __forceinline__ i32x4 widen_int4(uint32_t r0, uint32_t r1)
     return w;
 }
 
-// AI: load instructions per 128 bytes of the activation rows, 8 rows each
-template <int AI, bool INT4, int NW>
-__global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
+// AI: load instructions per 128 bytes of the activation rows, 8 rows each (a workgroup owns 8 * AI rows).
+// A_CONV: the 16-byte chunks of a row are gathered from the image; Cin % 16 == 0, so a chunk lies inside one tap.
+template <int AI, bool INT4, int NW, int A_MODE>
+__global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
 {
+    const IgemmArgs &g = args.g;
     constexpr int MT = (AI + 1) / 2, BN = 16, STEP = INT4 ? 256 : 128, HALVES = STEP / 128;
     constexpr int STEP_REGS = 4 * (2 + AI * HALVES);
     constexpr int UNROLL = STEP_REGS <= 16 ? 4 : (STEP_REGS <= (NW > 8 ? 24 : 40) ? 2 : 1); // steps in flight per wave (what the registers hold)
@@ -86,6 +103,7 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform
     const int n0 = blockIdx.x * BN;
+    const int64_t m0 = (int64_t)blockIdx.y * (8 * AI);
     const int frow = lane & 15, quarter = lane >> 4; // fragment layout
     const int lrow = lane >> 3, lchunk = lane & 7;   // load layout
 
@@ -97,12 +115,40 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
         n = n < g.N ? n : g.N - 1;
         brow[i] = INT4 ? g.B + (((int64_t)n * g.ldb) >> 1) : g.B + (int64_t)n * g.ldb;
     }
+    int hi0[AI], wi0[AI]; // A_CONV: window origin; arow then points at its (possibly outside) pixel
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
-        int64_t m = 8 * i + lrow;
+        int64_t m = m0 + 8 * i + lrow;
         m = m < g.M ? m : g.M - 1;
-        arow[i] = g.A + m * g.lda;
+        if constexpr (A_MODE == A_MATRIX) {
+            arow[i] = g.A + m * g.lda;
+        } else {
+            const uint32_t img = div_magic((uint32_t)m, (uint32_t)(g.Ho * g.Wo), args.magic_hw, args.shift_hw);
+            const uint32_t rest = (uint32_t)m - img * (uint32_t)(g.Ho * g.Wo);
+            const uint32_t ho = div_magic(rest, (uint32_t)g.Wo, args.magic_wo, args.shift_wo), wo = rest - ho * (uint32_t)g.Wo;
+            hi0[i] = (int)ho * g.sh - g.ph;
+            wi0[i] = (int)wo * g.sw - g.pw;
+            arow[i] = g.A + (((int64_t)img * g.H + hi0[i]) * g.W + wi0[i]) * g.Cin;
+        }
     }
+    // chunk of 16 activations at k (the lane's) of every row; TAIL: k may reach beyond K
+    auto load_a = [&](int k, auto tail, u32x4 (&v)[AI]) __attribute__((always_inline)) {
+        if constexpr (A_MODE == A_MATRIX) {
+#pragma unroll
+            for (int i = 0; i < AI; ++i) v[i] = decltype(tail)::value ? load_tail16(arow[i], k, g.K) : load16_any(arow[i] + k);
+        } else { // taps outside the image, and taps beyond the kernel that fall outside, read as the code z_a
+            const uint32_t tap = fast_div((uint32_t)k, (uint32_t)g.Cin, g.magic_cin);
+            const uint32_t ta = fast_div(tap, (uint32_t)g.kw, g.magic_kw);
+            const int a = (int)ta, b = (int)(tap - ta * (uint32_t)g.kw);
+            const int64_t delta = ((int64_t)a * g.W + b) * g.Cin + (k - (int)tap * g.Cin);
+            const uint8_t *const fill = &g_fill_table.v[g.z_a][0];
+#pragma unroll
+            for (int i = 0; i < AI; ++i) {
+                const bool inside = (unsigned)(hi0[i] + a) < (unsigned)g.H && (unsigned)(wi0[i] + b) < (unsigned)g.W;
+                v[i] = load16_any(inside ? arow[i] + delta : fill);
+            }
+        }
+    };
     // row exchange: 16 weight rows, behind them 16 activation rows, of 128 bytes each
     uint8_t *const xb = smem + wave * 4096, *const xa = xb + 2048;
     auto slot = [](int row, int chunk) { return row * 128 + ((chunk ^ (row >> 1)) & 7) * 16; };
@@ -187,9 +233,7 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
 #pragma unroll
             for (int i = 0; i < 2; ++i) wv[u][i] = load16_any(brow[i] + st * 128 + 16 * lchunk);
 #pragma unroll
-            for (int p = 0; p < HALVES; ++p)
-#pragma unroll
-                for (int i = 0; i < AI; ++i) av[u][p][i] = load16_any(arow[i] + st * STEP + p * 128 + 16 * lchunk);
+            for (int p = 0; p < HALVES; ++p) load_a(st * STEP + p * 128 + 16 * lchunk, std::false_type{}, av[u][p]);
         }
         asm volatile("" ::: "memory"); // the loads stay where they are
 #pragma unroll
@@ -205,9 +249,7 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
 #pragma unroll
         for (int i = 0; i < 2; ++i) wv[i] = load_tail16(brow[i], steps * 128 + 16 * lchunk, INT4 ? g.K >> 1 : g.K);
 #pragma unroll
-        for (int p = 0; p < HALVES; ++p)
-#pragma unroll
-            for (int i = 0; i < AI; ++i) av[p][i] = load_tail16(arow[i], steps * STEP + p * 128 + 16 * lchunk, g.K);
+        for (int p = 0; p < HALVES; ++p) load_a(steps * STEP + p * 128 + 16 * lchunk, std::true_type{}, av[p]);
         multiply(wv, av);
     }
 
@@ -235,7 +277,7 @@ __global__ void __launch_bounds__(NW * 64) skinny_gemm_kernel(const IgemmArgs g)
 
     // ---- epilogue: wave t finishes m tile t
     if (wave >= MT) return;
-    const int64_t m = wave * 16 + frow;
+    const int64_t m = m0 + wave * 16 + frow;
     if (m >= g.M || nb >= g.N) return;
     i32x4 sum = {0, 0, 0, 0};
 #pragma unroll

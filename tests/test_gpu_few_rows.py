@@ -36,3 +36,17 @@ def test_few_rows_misaligned_row_pitch():
     qnn.qgemm(wide[:, 3:3 + K], c["z_a"], dev(c["Bt"]), dev(c["mult"]), dev(c["shift"]), c["z_out"], 0, 255, out=out[:, 1:1 + N])
     assert_same(host(out[:, 1:1 + N].contiguous()), oracle.qgemm(c["A"], c["z_a"], c["Bt"], c["mult"], c["shift"], c["z_out"], 0, 255), "slices")
     assert bool((out[:, 0] == 9).all()) and bool((out[:, 1 + N:] == 9).all())
+
+
+@pytest.mark.parametrize("small", ["1", "0"])
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K", [(65, 16, 64), (300, 130, 256), (1000, 40, 72), (97, 100, 514), (800, 256, 1152), (129, 90, 2306)])
+def test_small_launches_and_the_kernels_they_replace(tuning, small, M, N, K, bits):
+    tuning.setenv("QNN_SMALL", small)
+    c = synth.gemm_case(M, N, K, 11 * M + K, oracle, weight_bits=bits)
+    bias = np.random.default_rng(N).integers(-5000, 5000, N).astype(np.int32)
+    for z_a in (128, 250):
+        want = oracle.qgemm(c["A"], z_a, c["Bt"], c["mult"], c["shift"], c["z_out"], 0, 255, bias=bias)
+        got = qnn.qgemm(dev(c["A"]), z_a, dev(c.get("Bt_packed", c["Bt"])), dev(c["mult"]), dev(c["shift"]), c["z_out"], 0, 255,
+                        bias=dev(bias), weight_bits=bits)
+        assert_same(host(got), want, f"small={small} {M}x{N}x{K} bits={bits} z_a={z_a}")
