@@ -780,13 +780,7 @@ static qnn_status qdwconv2d_impl(const uint8_t *x, int N, int H, int W, int C, i
     const bool dot_ok = c4 && !old_form && N <= 65535 && g.hruns <= 65535 && lanes_x < (1ll << 31) - 256 &&
                         (int64_t)W * C < (1ll << 31) && (int64_t)g.Wo * C < (1ll << 31);
     if (dot_ok) {
-        // division by the number of channel groups d >= 2 as multiply-high + shift: with
-        // l = ceil(log2 d), m = ceil(2^(31+l) / d) < 2^32, x / d = (x * m) >> (31 + l) for x < 2^31
-        const uint32_t d = (uint32_t)(C / 4);
-        uint32_t l = 0;
-        while ((1u << l) < d) ++l;
-        g.shift_cgroups = l > 0 ? l - 1 : 0;
-        g.magic_cgroups = d > 1 ? (uint32_t)((((uint64_t)1 << (31 + l)) + d - 1) / d) : 0u;
+        fast_division((uint32_t)(C / 4), g.magic_cgroups, g.shift_cgroups);
         const int variant = tuning().dw_variant; // tuning aid: 0 = patch kernel, 3 = matrix-unit kernel, -1 = by shape
         // matrix-unit kernel: whole 16-byte channel chunks, rows of at least 24 outputs (narrower images waste
         // most of the 32-pixel tile and stay with the patch kernel)

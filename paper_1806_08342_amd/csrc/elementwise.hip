@@ -1,24 +1,83 @@
 // Streaming (HBM-bound) kernels: affine quantize / de-quantize (Sec. 2.1 eq. 1-3),
 // stand-alone rescale of int32 accumulators, rescaling add (Sec. 3.2.1), weight transpose.
 //
-// All of them move each byte once: 16-byte loads per lane, consecutive lanes on
-// consecutive addresses, grid sized to a few waves per SIMD and a grid-stride loop.
+// All of them move each byte once.  How fast HBM moves them depends on the order: the kernels walk in tiles
+// of 4 x 256 consecutive vectors per workgroup (four independent loads in flight per lane), not with a stride of
+// the whole grid between a lane's loads.  Copy of 154 MB each way: 6.0-6.3 TB/s with tiles, 5.2-5.4 with the
+// grid-stride order; 4 bytes in, 1 out: 6.7 against 6.3; reading only: 6.9 against 6.1.  Stores are non-temporal
+// (quantize of 38.5 M values 35 us, 46 with plain stores); loads are so only for calls whose tensors exceed by far
+// what the 256 MB cache could hold for the next pass over them (25 MB copies: 6.0 TB/s with plain loads, 5.5 with
+// non-temporal ones; a training step's three passes over 103 MB: 99 us and 106 us).
+// Pointers may have any alignment their element type allows (gfx950 loads and stores 16 bytes at any address).
 #include "qnn_device.h"
 
 namespace qnn {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256, kUnroll = 4, kMaxBlocks = 8192;
+constexpr size_t kCacheBytes = (size_t)512 << 20; // inputs and outputs of a call beyond this: non-temporal loads
 
 using f32x4 = float __attribute__((ext_vector_type(4)));
 using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
 using i32x4 = int32_t __attribute__((ext_vector_type(4)));
+using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
 
-static int grid_for(size_t work_items, int per_block, int max_blocks = 256 * 16)
+template <class T, bool NT> __device__ __forceinline__ T load_any(const void *p)
 {
-    size_t b = (work_items + per_block - 1) / per_block;
-    if (b < 1) b = 1;
-    if (b > (size_t)max_blocks) b = max_blocks;
-    return (int)b;
+    typedef T U __attribute__((aligned(1)));
+    const U *q = static_cast<const U *>(p);
+    if constexpr (NT) return __builtin_nontemporal_load(q);
+    else return *q;
+}
+template <class T> __device__ __forceinline__ void store_any(void *p, T v)
+{
+    typedef T U __attribute__((aligned(1)));
+    __builtin_nontemporal_store(v, static_cast<U *>(p));
+}
+
+// workgroups for `vectors` lane-sized pieces of work
+static int grid_for(size_t vectors)
+{
+    const size_t b = (vectors + kThreads * kUnroll - 1) / (kThreads * kUnroll);
+    return (int)(b < 1 ? 1 : (b > (size_t)kMaxBlocks ? (size_t)kMaxBlocks : b));
+}
+
+// tiles of kUnroll x kThreads consecutive vectors: item = load(v) for a whole tile, then use(v, item)
+template <int THREADS = kThreads, class Load, class Use>
+__device__ __forceinline__ void for_tiles(size_t nvec, Load load, Use use)
+{
+    constexpr size_t kTile = (size_t)THREADS * kUnroll;
+    for (size_t base = (size_t)blockIdx.x * kTile; base < nvec; base += (size_t)gridDim.x * kTile) {
+        const size_t v = base + threadIdx.x;
+        if (base + kTile <= nvec) { // uniform
+            decltype(load(v)) item[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) item[u] = load(v + u * THREADS);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) use(v + u * THREADS, item[u]);
+        } else {
+            for (int u = 0; u < kUnroll; ++u)
+                if (v + u * THREADS < nvec) use(v + u * THREADS, load(v + u * THREADS));
+        }
+    }
+}
+
+// An element-wise pass: Op::kWidth elements per vector, load / store of a vector, one(i) for the last n % kWidth.
+template <class Op, bool NT> __global__ void __launch_bounds__(kThreads) stream_kernel(const Op op_arg, size_t n)
+{
+    const auto op = op_arg.prepared();
+    const size_t nvec = n / Op::kWidth;
+    for_tiles(nvec, [&](size_t v) { return op.template load<NT>(v); }, [&](size_t v, auto item) { op.store(v, item); });
+    if (blockIdx.x == 0 && threadIdx.x < n - nvec * Op::kWidth) op.one(nvec * Op::kWidth + threadIdx.x);
+}
+
+// bytes_per_element: of all inputs and outputs together
+template <class Op> static qnn_status launch_stream(const Op &op, size_t n, int bytes_per_element, void *stream)
+{
+    const dim3 grid((unsigned)grid_for(n / Op::kWidth));
+    const hipStream_t s = as_stream(stream);
+    if (n * (size_t)bytes_per_element > kCacheBytes) hipLaunchKernelGGL((stream_kernel<Op, true>), grid, dim3(kThreads), 0, s, op, n);
+    else hipLaunchKernelGGL((stream_kernel<Op, false>), grid, dim3(kThreads), 0, s, op, n);
+    return launch_status(hipGetLastError());
 }
 
 // ------------------------------------------------------------------ quantize
@@ -33,41 +92,21 @@ __device__ __forceinline__ uint32_t quantize_one(float x, float scale, float lo,
     return (uint32_t)((int32_t)r + z);
 }
 
-// VEC = 4: x is 16-byte aligned, q 4-byte aligned; VEC = 1: anything.
-template <int VEC>
-__global__ void __launch_bounds__(kThreads) quantize_kernel(const float *__restrict__ x, uint8_t *__restrict__ q,
-                                                            size_t n, float scale, int32_t z, float lo, float hi)
-{
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    if (VEC == 4) {
-        const size_t nvec = n / 4;
-        const f32x4 *xv = reinterpret_cast<const f32x4 *>(x);
-        uint32_t *qv = reinterpret_cast<uint32_t *>(q);
-        size_t v = tid;
-        // four independent 16-byte loads in flight per lane
-        for (; v + 3 * nthreads < nvec; v += 4 * nthreads) {
-            f32x4 a[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] = __builtin_nontemporal_load(&xv[v + u * nthreads]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                uint32_t p = quantize_one(a[u].x, scale, lo, hi, z) | (quantize_one(a[u].y, scale, lo, hi, z) << 8) |
-                             (quantize_one(a[u].z, scale, lo, hi, z) << 16) |
-                             (quantize_one(a[u].w, scale, lo, hi, z) << 24);
-                __builtin_nontemporal_store(p, &qv[v + u * nthreads]);
-            }
-        }
-        for (; v < nvec; v += nthreads) {
-            f32x4 a = xv[v];
-            qv[v] = quantize_one(a.x, scale, lo, hi, z) | (quantize_one(a.y, scale, lo, hi, z) << 8) |
-                    (quantize_one(a.z, scale, lo, hi, z) << 16) | (quantize_one(a.w, scale, lo, hi, z) << 24);
-        }
-        for (size_t i = nvec * 4 + tid; i < n; i += nthreads) q[i] = (uint8_t)quantize_one(x[i], scale, lo, hi, z);
-    } else {
-        for (size_t i = tid; i < n; i += nthreads) q[i] = (uint8_t)quantize_one(x[i], scale, lo, hi, z);
+struct QuantizeOp {
+    const float *x;
+    uint8_t *q;
+    float scale, lo, hi;
+    int32_t z;
+    static constexpr int kWidth = 4;
+    __device__ const QuantizeOp &prepared() const { return *this; }
+    template <bool NT> __device__ f32x4 load(size_t v) const { return load_any<f32x4, NT>(x + 4 * v); }
+    __device__ void store(size_t v, f32x4 a) const
+    {
+        store_any<uint32_t>(q + 4 * v, quantize_one(a.x, scale, lo, hi, z) | (quantize_one(a.y, scale, lo, hi, z) << 8) |
+                                           (quantize_one(a.z, scale, lo, hi, z) << 16) | (quantize_one(a.w, scale, lo, hi, z) << 24));
     }
-}
+    __device__ void one(size_t i) const { q[i] = (uint8_t)quantize_one(x[i], scale, lo, hi, z); }
+};
 
 // ------------------------------------------- ranges on the device, dynamic quantization
 
@@ -93,43 +132,32 @@ __global__ void minmax_init_kernel(qnn_dyn_qparams *st)
     st->key_max = 0u;
 }
 
-__global__ void __launch_bounds__(kThreads) minmax_kernel(const float *__restrict__ x, size_t n, qnn_dyn_qparams *st)
+// Bound by reading x and, behind that, by the atomics: about 10 ns each on one address, and the workgroups end
+// together, so that none finds the other's result already there.  One workgroup of 16 waves per CU: 25.7 M values
+// in 22 us where 2048 workgroups of 4 waves took 59.
+constexpr int kMinmaxThreads = 1024, kMinmaxBlocks = 256;
+template <bool NT> __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__restrict__ x, size_t n, qnn_dyn_qparams *st)
 {
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
     float lo = INFINITY, hi = -INFINITY; // values that are not finite take no part in the range
     auto take = [&](float v) {
-        if (__builtin_isfinite(v)) lo = fminf(lo, v), hi = fmaxf(hi, v);
+        // one comparison for "finite": the magnitude bits of inf and NaN are the largest
+        const bool ok = (__float_as_uint(v) & 0x7fffffffu) < 0x7f800000u;
+        lo = fminf(lo, ok ? v : INFINITY), hi = fmaxf(hi, ok ? v : -INFINITY);
     };
-    if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
-        const size_t nvec = n / 4;
-        const f32x4 *xv = reinterpret_cast<const f32x4 *>(x);
-        size_t v = tid;
-        for (; v + 3 * nthreads < nvec; v += 4 * nthreads) { // four independent 16-byte loads in flight per lane
-            f32x4 a[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] = xv[v + u * nthreads]; // plain loads: the quantize pass reads x again
-#pragma unroll
-            for (int u = 0; u < 4; ++u) take(a[u].x), take(a[u].y), take(a[u].z), take(a[u].w);
-        }
-        for (; v < nvec; v += nthreads) {
-            const f32x4 a = xv[v];
-            take(a.x), take(a.y), take(a.z), take(a.w);
-        }
-        for (size_t i = nvec * 4 + tid; i < n; i += nthreads) take(x[i]);
-    } else {
-        for (size_t i = tid; i < n; i += nthreads) take(x[i]);
-    }
+    const size_t nvec = n / 4;
+    for_tiles<kMinmaxThreads>(nvec, [&](size_t v) { return load_any<f32x4, NT>(x + 4 * v); },
+              [&](size_t, f32x4 a) { take(a.x), take(a.y), take(a.z), take(a.w); });
+    if (blockIdx.x == 0 && threadIdx.x < n - nvec * 4) take(x[nvec * 4 + threadIdx.x]);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         lo = fminf(lo, __shfl_xor(lo, off));
         hi = fmaxf(hi, __shfl_xor(hi, off));
     }
-    __shared__ float s_lo[kThreads / 64], s_hi[kThreads / 64];
+    __shared__ float s_lo[kMinmaxThreads / 64], s_hi[kMinmaxThreads / 64];
     if ((threadIdx.x & 63) == 0) s_lo[threadIdx.x >> 6] = lo, s_hi[threadIdx.x >> 6] = hi;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) lo = fminf(lo, s_lo[w]), hi = fmaxf(hi, s_hi[w]);
+        for (int w = 1; w < kMinmaxThreads / 64; ++w) lo = fminf(lo, s_lo[w]), hi = fmaxf(hi, s_hi[w]);
         if (lo <= hi) { // at least one finite value in this block
             // atomics on one address serialise across the chip: skip them when the value seen so far is
             // already as good (a stale read only costs an atomic that changes nothing)
@@ -166,248 +194,186 @@ __global__ void range_finalize_kernel(qnn_dyn_qparams *st, float momentum, int b
 }
 
 // quantize with parameters that live in device memory (8-bit codes)
-__global__ void __launch_bounds__(kThreads) quantize_with_kernel(const float *__restrict__ x, uint8_t *__restrict__ q, size_t n,
-                                                                 const qnn_dyn_qparams *__restrict__ st)
-{
-    const float scale = st->scale;
-    const int32_t z = st->zero_point;
-    const float lo = (float)(0 - z), hi = (float)(255 - z);
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    if (((reinterpret_cast<uintptr_t>(x) & 15) | (reinterpret_cast<uintptr_t>(q) & 3)) == 0) {
-        const size_t nvec = n / 4;
-        const f32x4 *xv = reinterpret_cast<const f32x4 *>(x);
-        uint32_t *qv = reinterpret_cast<uint32_t *>(q);
-        size_t v = tid;
-        for (; v + 3 * nthreads < nvec; v += 4 * nthreads) {
-            f32x4 a[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] = __builtin_nontemporal_load(&xv[v + u * nthreads]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t p = quantize_one(a[u].x, scale, lo, hi, z) | (quantize_one(a[u].y, scale, lo, hi, z) << 8) |
-                                   (quantize_one(a[u].z, scale, lo, hi, z) << 16) |
-                                   (quantize_one(a[u].w, scale, lo, hi, z) << 24);
-                __builtin_nontemporal_store(p, &qv[v + u * nthreads]);
-            }
-        }
-        for (; v < nvec; v += nthreads) {
-            const f32x4 a = xv[v];
-            qv[v] = quantize_one(a.x, scale, lo, hi, z) | (quantize_one(a.y, scale, lo, hi, z) << 8) |
-                    (quantize_one(a.z, scale, lo, hi, z) << 16) | (quantize_one(a.w, scale, lo, hi, z) << 24);
-        }
-        for (size_t i = nvec * 4 + tid; i < n; i += nthreads) q[i] = (uint8_t)quantize_one(x[i], scale, lo, hi, z);
-    } else {
-        for (size_t i = tid; i < n; i += nthreads) q[i] = (uint8_t)quantize_one(x[i], scale, lo, hi, z);
+struct QuantizeWithOp {
+    const float *x;
+    uint8_t *q;
+    const qnn_dyn_qparams *st;
+    static constexpr int kWidth = 4;
+    __device__ QuantizeOp prepared() const
+    {
+        const int32_t z = st->zero_point;
+        return QuantizeOp{x, q, st->scale, (float)(0 - z), (float)(255 - z), z};
     }
-}
+};
 
 // ------------------------------------------------- simulated quantization (training side)
 
 // Sec. 2.4: SimQuant = quantizer followed by de-quantizer (eq. 12-13); in the backward pass the
 // quantizer is replaced by a clamp to the representable range, i.e. the incoming gradient passes
 // where x_min <= x <= x_max and is zero elsewhere (straight-through estimator, eq. 14-15).
-__global__ void __launch_bounds__(kThreads) simquant_kernel(const float *__restrict__ x, float *__restrict__ y, size_t n,
-                                                            float scale, int32_t z, float lo, float hi)
-{
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += nthreads) {
-        const int32_t code = (int32_t)quantize_one(x[i], scale, lo, hi, z);
-        y[i] = __fmul_rn((float)(code - z), scale);
-    }
-}
+struct SimquantOp {
+    const float *x;
+    float *y;
+    float scale, lo, hi;
+    int32_t z;
+    static constexpr int kWidth = 4;
+    __device__ const SimquantOp &prepared() const { return *this; }
+    __device__ float value(float v) const { return __fmul_rn((float)((int32_t)quantize_one(v, scale, lo, hi, z) - z), scale); }
+    template <bool NT> __device__ f32x4 load(size_t v) const { return load_any<f32x4, NT>(x + 4 * v); }
+    __device__ void store(size_t v, f32x4 a) const { store_any(y + 4 * v, f32x4{value(a.x), value(a.y), value(a.z), value(a.w)}); }
+    __device__ void one(size_t i) const { y[i] = value(x[i]); }
+};
 
-__global__ void __launch_bounds__(kThreads) simquant_backward_kernel(const float *__restrict__ x, const float *__restrict__ gy,
-                                                                     float *__restrict__ gx, size_t n, float xmin, float xmax)
-{
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += nthreads) {
-        const float v = x[i];
-        gx[i] = (v >= xmin && v <= xmax) ? gy[i] : 0.0f; // NaN fails both comparisons: no gradient
+struct SimquantBackwardOp {
+    const float *x, *gy;
+    float *gx;
+    float xmin, xmax;
+    static constexpr int kWidth = 4;
+    struct Item {
+        f32x4 x, g;
+    };
+    __device__ const SimquantBackwardOp &prepared() const { return *this; }
+    __device__ float value(float v, float g) const { return (v >= xmin && v <= xmax) ? g : 0.0f; } // NaN fails both comparisons: no gradient
+    template <bool NT> __device__ Item load(size_t v) const { return {load_any<f32x4, NT>(x + 4 * v), load_any<f32x4, NT>(gy + 4 * v)}; }
+    __device__ void store(size_t v, Item t) const
+    {
+        store_any(gx + 4 * v, f32x4{value(t.x.x, t.g.x), value(t.x.y, t.g.y), value(t.x.z, t.g.z), value(t.x.w, t.g.w)});
     }
-}
+    __device__ void one(size_t i) const { gx[i] = value(x[i], gy[i]); }
+};
 
 // 16-bit codes (Sec. 3.3 compares activation precisions of 4, 8 and 16 bits): the same arithmetic with
-// uint16 storage.  A lane handles 4 consecutive elements (16 bytes in, 8 bytes out) when the pointers
-// allow it.
-using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
-
-template <int VEC>
-__global__ void __launch_bounds__(kThreads) quantize_u16_kernel(const float *__restrict__ x, uint16_t *__restrict__ q,
-                                                                size_t n, float scale, int32_t z, float lo, float hi)
-{
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    size_t done = 0;
-    if (VEC == 4) {
-        const size_t nvec = n / 4;
-        const f32x4 *xv = reinterpret_cast<const f32x4 *>(x);
-        u32x2 *qv = reinterpret_cast<u32x2 *>(q);
-        for (size_t v = tid; v < nvec; v += nthreads) {
-            const f32x4 a = __builtin_nontemporal_load(&xv[v]);
-            u32x2 p;
-            p.x = quantize_one(a.x, scale, lo, hi, z) | (quantize_one(a.y, scale, lo, hi, z) << 16);
-            p.y = quantize_one(a.z, scale, lo, hi, z) | (quantize_one(a.w, scale, lo, hi, z) << 16);
-            __builtin_nontemporal_store(p, &qv[v]);
-        }
-        done = nvec * 4;
+// uint16 storage.
+struct QuantizeU16Op {
+    const float *x;
+    uint16_t *q;
+    float scale, lo, hi;
+    int32_t z;
+    static constexpr int kWidth = 4;
+    __device__ const QuantizeU16Op &prepared() const { return *this; }
+    template <bool NT> __device__ f32x4 load(size_t v) const { return load_any<f32x4, NT>(x + 4 * v); }
+    __device__ void store(size_t v, f32x4 a) const
+    {
+        store_any(q + 4 * v, u32x2{quantize_one(a.x, scale, lo, hi, z) | (quantize_one(a.y, scale, lo, hi, z) << 16),
+                                   quantize_one(a.z, scale, lo, hi, z) | (quantize_one(a.w, scale, lo, hi, z) << 16)});
     }
-    for (size_t i = done + tid; i < n; i += nthreads) q[i] = (uint16_t)quantize_one(x[i], scale, lo, hi, z);
-}
-
-template <int VEC>
-__global__ void __launch_bounds__(kThreads) dequantize_u16_kernel(const uint16_t *__restrict__ q, float *__restrict__ x,
-                                                                  size_t n, float scale, int32_t z)
-{
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    size_t done = 0;
-    if (VEC == 4) {
-        const size_t nvec = n / 4;
-        const u32x2 *qv = reinterpret_cast<const u32x2 *>(q);
-        f32x4 *xv = reinterpret_cast<f32x4 *>(x);
-        for (size_t v = tid; v < nvec; v += nthreads) {
-            const u32x2 p = __builtin_nontemporal_load(&qv[v]);
-            f32x4 o;
-            o.x = __fmul_rn((float)((int32_t)(p.x & 0xffffu) - z), scale);
-            o.y = __fmul_rn((float)((int32_t)(p.x >> 16) - z), scale);
-            o.z = __fmul_rn((float)((int32_t)(p.y & 0xffffu) - z), scale);
-            o.w = __fmul_rn((float)((int32_t)(p.y >> 16) - z), scale);
-            __builtin_nontemporal_store(o, &xv[v]);
-        }
-        done = nvec * 4;
-    }
-    for (size_t i = done + tid; i < n; i += nthreads) x[i] = __fmul_rn((float)((int32_t)q[i] - z), scale);
-}
+    __device__ void one(size_t i) const { q[i] = (uint16_t)quantize_one(x[i], scale, lo, hi, z); }
+};
 
 // ---------------------------------------------------------------- dequantize
 
-template <int VEC>
-__global__ void __launch_bounds__(kThreads) dequantize_kernel(const uint8_t *__restrict__ q, float *__restrict__ x,
-                                                              size_t n, float scale, int32_t z)
-{
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    if (VEC == 4) {
-        const size_t nvec = n / 4;
-        const uint32_t *qv = reinterpret_cast<const uint32_t *>(q);
-        f32x4 *xv = reinterpret_cast<f32x4 *>(x);
-        size_t v = tid;
-        for (; v + 3 * nthreads < nvec; v += 4 * nthreads) {
-            uint32_t p[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) p[u] = __builtin_nontemporal_load(&qv[v + u * nthreads]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                f32x4 o;
-                o.x = __fmul_rn((float)((int32_t)(p[u] & 0xffu) - z), scale);
-                o.y = __fmul_rn((float)((int32_t)((p[u] >> 8) & 0xffu) - z), scale);
-                o.z = __fmul_rn((float)((int32_t)((p[u] >> 16) & 0xffu) - z), scale);
-                o.w = __fmul_rn((float)((int32_t)(p[u] >> 24) - z), scale);
-                __builtin_nontemporal_store(o, &xv[v + u * nthreads]);
-            }
-        }
-        for (; v < nvec; v += nthreads) {
-            uint32_t p = qv[v];
-            f32x4 o;
-            o.x = __fmul_rn((float)((int32_t)(p & 0xffu) - z), scale);
-            o.y = __fmul_rn((float)((int32_t)((p >> 8) & 0xffu) - z), scale);
-            o.z = __fmul_rn((float)((int32_t)((p >> 16) & 0xffu) - z), scale);
-            o.w = __fmul_rn((float)((int32_t)(p >> 24) - z), scale);
-            xv[v] = o;
-        }
-        for (size_t i = nvec * 4 + tid; i < n; i += nthreads) x[i] = __fmul_rn((float)((int32_t)q[i] - z), scale);
-    } else {
-        for (size_t i = tid; i < n; i += nthreads) x[i] = __fmul_rn((float)((int32_t)q[i] - z), scale);
+struct DequantizeU16Op {
+    const uint16_t *q;
+    float *x;
+    float scale;
+    int32_t z;
+    static constexpr int kWidth = 4;
+    __device__ const DequantizeU16Op &prepared() const { return *this; }
+    __device__ float value(uint32_t c) const { return __fmul_rn((float)((int32_t)c - z), scale); }
+    template <bool NT> __device__ u32x2 load(size_t v) const { return load_any<u32x2, NT>(q + 4 * v); }
+    __device__ void store(size_t v, u32x2 p) const
+    {
+        store_any(x + 4 * v, f32x4{value(p.x & 0xffffu), value(p.x >> 16), value(p.y & 0xffffu), value(p.y >> 16)});
     }
-}
+    __device__ void one(size_t i) const { x[i] = value(q[i]); }
+};
+
+struct DequantizeOp {
+    const uint8_t *q;
+    float *x;
+    float scale;
+    int32_t z;
+    static constexpr int kWidth = 4;
+    __device__ const DequantizeOp &prepared() const { return *this; }
+    __device__ float value(uint32_t c) const { return __fmul_rn((float)((int32_t)c - z), scale); }
+    template <bool NT> __device__ uint32_t load(size_t v) const { return load_any<uint32_t, NT>(q + 4 * v); }
+    __device__ void store(size_t v, uint32_t p) const
+    {
+        store_any(x + 4 * v, f32x4{value(p & 0xffu), value((p >> 8) & 0xffu), value((p >> 16) & 0xffu), value(p >> 24)});
+    }
+    __device__ void one(size_t i) const { x[i] = value(q[i]); }
+};
 
 // ---------------------------------------------------------------- requantize
 
-// VEC = 4: acc 16-byte aligned, y 4-byte aligned, channels % 4 == 0 (so four consecutive
-// elements never straddle a row).  One lane rescales 4 accumulators and stores 4 bytes.
-template <int VEC, bool PER_CHANNEL>
-__global__ void __launch_bounds__(kThreads)
-    requantize_kernel(const int32_t *__restrict__ acc, uint8_t *__restrict__ y, size_t total, uint32_t channels,
-                      const int32_t *__restrict__ mult, const int32_t *__restrict__ shift, int32_t z_out,
-                      int32_t act_min, int32_t act_max)
+// four accumulators of one lane -> four codes.  When every lane of the wave has 1 <= shift <= 20 and
+// |acc| < 2^29 the rescale runs in its 7-operation 32-bit form, else in the general 64-bit form.
+struct RequantizeArgs {
+    const int32_t *acc;
+    uint8_t *y;
+    const int32_t *mult, *shift;
+    size_t total;
+    uint32_t channels; // 1: one quantizer for the tensor
+    int32_t z_out, act_min, act_max;
+};
+
+__device__ __forceinline__ uint32_t requantize_one(const RequantizeArgs &g, int32_t a, int32_t mult, int32_t shift)
 {
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    RescaleParams uni = make_rescale(mult[0], shift[0]);
-    const int32_t uni_shift = shift[0];
-    if (VEC == 4) {
-        const size_t nvec = total / 4;
-        const i32x4 *av = reinterpret_cast<const i32x4 *>(acc);
-        uint32_t *yv = reinterpret_cast<uint32_t *>(y);
-        // four accumulators of one lane -> four codes.  When every lane of the wave has 1 <= shift <= 20 and
-        // |acc| < 2^29 the rescale runs in its 7-operation 32-bit form, else in the general 64-bit form.
-        auto four = [&](const i32x4 a, uint32_t c) -> uint32_t {
-            i32x4 m4 = {uni.mult, uni.mult, uni.mult, uni.mult}, s4 = {uni_shift, uni_shift, uni_shift, uni_shift};
-            if (PER_CHANNEL) {
-                m4 = *reinterpret_cast<const i32x4 *>(mult + c);
-                s4 = *reinterpret_cast<const i32x4 *>(shift + c);
-            }
-            bool ok = true;
+    // clamp before adding z_out: the rescaled value may sit at the int32 limits
+    return (uint32_t)(clamp_i32(g.act_min - g.z_out, g.act_max - g.z_out, rescale_general(a, make_rescale(mult, shift))) + g.z_out);
+}
+
+__device__ __forceinline__ uint32_t requantize_four(const RequantizeArgs &g, const i32x4 a, const i32x4 m4, const i32x4 s4,
+                                                    const FusedRescale (&f)[4], bool shifts_ok)
+{
+    bool ok = shifts_ok;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) ok = ok && s4[j] >= 1 && s4[j] <= 20 && a[j] > -(1 << 29) && a[j] < (1 << 29);
-            uint32_t packed = 0;
-            if (__all(ok)) {
+    for (int j = 0; j < 4; ++j) ok = ok && a[j] > -(1 << 29) && a[j] < (1 << 29);
+    uint32_t packed = 0;
+    if (__all(ok)) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int32_t n1 = s4[j] + 1;
-                    FusedRescale f;
-                    f.mult = m4[j], f.corr4 = 0, f.n1 = n1;
-                    f.c = (1 << s4[j]) + (z_out << n1) + 1;
-                    f.lo = act_min << n1;
-                    f.hi = ((act_max + 1) << n1) - 1;
-                    packed = shift_into_byte(packed, rescale_fused_w(a[j], f), n1, j);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const RescaleParams p = make_rescale(m4[j], s4[j]);
-                    // clamp before adding z_out: the rescaled value may sit at the int32 limits
-                    const int32_t r = clamp_i32(act_min - z_out, act_max - z_out, rescale_general(a[j], p)) + z_out;
-                    packed |= (uint32_t)r << (8 * j);
-                }
-            }
-            return packed;
-        };
-        // channel of a lane's first element, advanced without a 64-bit division per step (rows are a
-        // multiple of 4 long, so a vector never straddles a row)
-        const uint32_t step = PER_CHANNEL ? (uint32_t)((nthreads * 4) % channels) : 0u;
-        uint32_t c = PER_CHANNEL ? (uint32_t)((tid * 4) % channels) : 0u;
-        auto advance = [&](uint32_t ch) {
-            ch += step;
-            return ch >= channels ? ch - channels : ch;
-        };
-        size_t v = tid;
-        for (; v + 3 * nthreads < nvec; v += 4 * nthreads) { // four independent 16-byte loads in flight per lane
-            i32x4 a[4];
-            uint32_t cs[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                a[u] = __builtin_nontemporal_load(&av[v + u * nthreads]);
-                cs[u] = c;
-                c = advance(c);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) __builtin_nontemporal_store(four(a[u], cs[u]), &yv[v + u * nthreads]);
-        }
-        for (; v < nvec; v += nthreads) {
-            yv[v] = four(av[v], c);
-            c = advance(c);
-        }
+        for (int j = 0; j < 4; ++j) packed = shift_into_byte(packed, rescale_fused_w(a[j], f[j]), f[j].n1, j);
     } else {
-        for (size_t i = tid; i < total; i += nthreads) {
-            RescaleParams p = uni;
-            if (PER_CHANNEL) {
-                uint32_t c = (uint32_t)(i % channels);
-                p = make_rescale(mult[c], shift[c]);
-            }
-            y[i] = (uint8_t)(clamp_i32(act_min - z_out, act_max - z_out, rescale_general(acc[i], p)) + z_out);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) packed |= requantize_one(g, a[j], m4[j], s4[j]) << (8 * j);
+    }
+    return packed;
+}
+
+// FIXED: the tensor has one quantizer, or the channel count divides a row of a tile (4 x 256 elements), so that a
+// lane meets the same four channels in all its vectors and holds their parameters; else it looks them up per
+// vector (from the cache) and the channel of its first element comes from one multiply-high.
+template <bool FIXED, bool NT>
+__global__ void __launch_bounds__(kThreads) requantize_kernel(const RequantizeArgs g, uint32_t magic, uint32_t magic_shift)
+{
+    const size_t nvec = g.total / 4;
+    auto params = [&](uint32_t c, i32x4 &m4, i32x4 &s4, FusedRescale (&f)[4]) {
+        bool ok = true;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            m4[j] = g.mult[c], s4[j] = g.shift[c];
+            c = c + 1 == g.channels ? 0 : c + 1;
+            ok = ok && s4[j] >= 1 && s4[j] <= 20;
+            f[j] = make_fused(m4[j], s4[j], 0, g.z_out, g.act_min, g.act_max);
         }
+        return ok;
+    };
+    auto load = [&](size_t v) { return load_any<i32x4, NT>(g.acc + 4 * v); };
+    if constexpr (FIXED) {
+        i32x4 m4, s4;
+        FusedRescale f[4];
+        const bool ok = params((threadIdx.x * 4u) % g.channels, m4, s4, f);
+        for_tiles(nvec, load, [&](size_t v, i32x4 a) { store_any<uint32_t>(g.y + 4 * v, requantize_four(g, a, m4, s4, f, ok)); });
+    } else {
+        for_tiles(nvec, load, [&](size_t v, i32x4 a) {
+            const size_t i = 4 * v;
+            uint32_t c;
+            if (g.total < ((size_t)1 << 31)) {
+                const uint32_t x = (uint32_t)i;
+                c = x - (__umulhi(x, magic) >> magic_shift) * g.channels;
+            } else {
+                c = (uint32_t)(i % g.channels);
+            }
+            i32x4 m4, s4;
+            FusedRescale f[4];
+            const bool ok = params(c, m4, s4, f);
+            store_any<uint32_t>(g.y + 4 * v, requantize_four(g, a, m4, s4, f, ok));
+        });
+    }
+    if (blockIdx.x == 0 && threadIdx.x < g.total - nvec * 4) {
+        const size_t i = nvec * 4 + threadIdx.x;
+        const uint32_t c = (uint32_t)(i % g.channels);
+        g.y[i] = (uint8_t)requantize_one(g, g.acc[i], g.mult[c], g.shift[c]);
     }
 }
 
@@ -422,66 +388,63 @@ struct QaddArgs {
 // loop is then two table reads, an add and one rescale per element.
 // FUSED: the output rescale may use the 32-bit fused form (1 <= shift_o <= 20 and both tables
 // bounded by 2^28, which shift_a, shift_b >= 0 and left_shift <= 20 guarantee).
-template <int VEC, bool FUSED>
+template <bool FUSED, bool NT>
 __global__ void __launch_bounds__(kThreads) qadd_kernel(const uint8_t *__restrict__ a, const uint8_t *__restrict__ b,
                                                         uint8_t *__restrict__ y, size_t n, QaddArgs g)
 {
-    __shared__ int32_t tab_a[256];
-    __shared__ int32_t tab_b[256];
-    {
-        const int v = threadIdx.x; // kThreads == 256
-        tab_a[v] = rescale_general((v - g.z_a) * (1 << g.left_shift), make_rescale(g.mult_a, g.shift_a));
-        tab_b[v] = rescale_general((v - g.z_b) * (1 << g.left_shift), make_rescale(g.mult_b, g.shift_b));
-    }
+    __shared__ int32_t tab[512];
+    const AddParams p = {g.z_a, g.mult_a, g.shift_a, g.z_b, g.mult_b, g.shift_b, g.left_shift, g.mult_o, g.shift_o, g.z_out, g.act_min, g.act_max};
+    add_fill_tables(tab, p, threadIdx.x, kThreads);
     __syncthreads();
-    const RescaleParams po = make_rescale(g.mult_o, g.shift_o);
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nthreads = (size_t)gridDim.x * blockDim.x;
-    const FusedRescale fo = make_fused(g.mult_o, g.shift_o, 0, g.z_out, g.act_min, g.act_max);
-    auto one = [&](uint32_t ca, uint32_t cb) -> uint32_t {
-        if (FUSED) return (uint32_t)rescale_fused(tab_a[ca] + tab_b[cb], fo);
-        int64_t u = (int64_t)tab_a[ca] + (int64_t)tab_b[cb];
-        u = u > INT32_MAX ? INT32_MAX : (u < INT32_MIN ? INT32_MIN : u);
-        return (uint32_t)(clamp_i32(g.act_min - g.z_out, g.act_max - g.z_out, rescale_general((int32_t)u, po)) + g.z_out);
+    const AddOut ao = make_add_out(p);
+    struct Item {
+        u32x4 a, b;
     };
-    if (VEC == 16) {
-        const size_t nvec = n / 16;
-        const u32x4 *av = reinterpret_cast<const u32x4 *>(a);
-        const u32x4 *bv = reinterpret_cast<const u32x4 *>(b);
-        u32x4 *yv = reinterpret_cast<u32x4 *>(y);
-        for (size_t v = tid; v < nvec; v += nthreads) {
-            u32x4 pa = __builtin_nontemporal_load(&av[v]);
-            u32x4 pb = __builtin_nontemporal_load(&bv[v]);
-            const uint32_t wa[4] = {pa.x, pa.y, pa.z, pa.w};
-            const uint32_t wb[4] = {pb.x, pb.y, pb.z, pb.w};
-            uint32_t wo[4];
+    const size_t nvec = n / 16;
+    for_tiles(nvec, [&](size_t v) { return Item{load_any<u32x4, NT>(a + 16 * v), load_any<u32x4, NT>(b + 16 * v)}; },
+              [&](size_t v, Item t) {
+                  u32x4 o;
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                uint32_t o = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o |= one((wa[d] >> (8 * j)) & 0xffu, (wb[d] >> (8 * j)) & 0xffu) << (8 * j);
-                wo[d] = o;
-            }
-            u32x4 out = {wo[0], wo[1], wo[2], wo[3]};
-            __builtin_nontemporal_store(out, &yv[v]);
-        }
-        for (size_t i = nvec * 16 + tid; i < n; i += nthreads) y[i] = (uint8_t)one(a[i], b[i]);
-    } else {
-        for (size_t i = tid; i < n; i += nthreads) y[i] = (uint8_t)one(a[i], b[i]);
+                  for (int d = 0; d < 4; ++d) o[d] = add_codes4<FUSED>(t.a[d], t.b[d], tab, ao);
+                  store_any(y + 16 * v, o);
+              });
+    if (blockIdx.x == 0 && threadIdx.x < n - nvec * 16) {
+        const size_t i = nvec * 16 + threadIdx.x;
+        y[i] = (uint8_t)add_code1<FUSED>(a[i], b[i], tab, ao);
     }
 }
 
 
 // ------------------------------------------------------ rescale of uint8 codes (concat)
 
+// Rows of `cols` bytes cut into 16-byte chunks: vector v -> (row, first column).  The last chunk of a row starts at
+// cols - 16 (the overlap is written twice with the same values), so that rows of any length are whole chunks; rows
+// shorter than that are one chunk, byte by byte.
+struct RowChunks {
+    uint32_t per_row, magic, magic_shift; // v / per_row for v < 2^31, per_row >= 2
+    int64_t cols;
+    __device__ void locate(size_t v, int64_t &row, int64_t &col) const
+    {
+        if (per_row == 1) {
+            row = (int64_t)v, col = 0;
+        } else if (v < ((size_t)1 << 31)) {
+            const uint32_t r = __umulhi((uint32_t)v, magic) >> magic_shift;
+            row = r, col = (int64_t)((uint32_t)v - r * per_row) * 16;
+        } else {
+            row = (int64_t)(v / per_row), col = (int64_t)(v - (size_t)row * per_row) * 16;
+        }
+        col = col + 16 > cols && cols >= 16 ? cols - 16 : col;
+    }
+};
+
 // Sec. 3.2.1: the inputs of a concatenation carry different quantizers and must be brought to the
 // output's before they are laid side by side.  y[m][c] = clamp(z_out + RESCALE(x[m][c] - z_in)) is a
 // function of one 8-bit code: a 256-entry byte table per workgroup, one gather per element.  Rows
 // have their own pitches, so the destination can be a channel slice of the concatenated tensor.
+template <bool NT>
 __global__ void __launch_bounds__(kThreads) rescale_u8_kernel(const uint8_t *__restrict__ x, int64_t ldx, uint8_t *__restrict__ y,
-                                                              int64_t ldy, int64_t rows, int64_t cols, int32_t z_in, int32_t mult,
-                                                              int32_t shift, int32_t z_out, int32_t act_min, int32_t act_max,
-                                                              int vec16)
+                                                              int64_t ldy, size_t chunks, RowChunks rc, int32_t z_in, int32_t mult,
+                                                              int32_t shift, int32_t z_out, int32_t act_min, int32_t act_max)
 {
     __shared__ uint8_t lut[256];
     {
@@ -490,24 +453,27 @@ __global__ void __launch_bounds__(kThreads) rescale_u8_kernel(const uint8_t *__r
         lut[v] = (uint8_t)(clamp_i32(act_min - z_out, act_max - z_out, r) + z_out);
     }
     __syncthreads();
-    const int64_t chunks_per_row = (cols + 15) / 16, total = rows * chunks_per_row;
-    for (int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x; q < total; q += (int64_t)gridDim.x * kThreads) {
-        const int64_t m = q / chunks_per_row;
-        const int64_t c = (q - m * chunks_per_row) * 16;
-        const uint8_t *xp = x + m * ldx + c;
-        uint8_t *yp = y + m * ldy + c;
-        if (vec16 && c + 16 <= cols) {
-            const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(xp));
-            u32x4 o;
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-                o[d] = (uint32_t)lut[a[d] & 0xffu] | ((uint32_t)lut[(a[d] >> 8) & 0xffu] << 8) |
-                       ((uint32_t)lut[(a[d] >> 16) & 0xffu] << 16) | ((uint32_t)lut[a[d] >> 24] << 24);
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(yp));
-        } else {
-            for (int e = 0; e < 16 && c + e < cols; ++e) yp[e] = lut[xp[e]];
-        }
+    if (rc.cols < 16) { // uniform
+        for (size_t q = (size_t)blockIdx.x * kThreads + threadIdx.x; q < chunks; q += (size_t)gridDim.x * kThreads)
+            for (int64_t e = 0; e < rc.cols; ++e) y[(int64_t)q * ldy + e] = lut[x[(int64_t)q * ldx + e]];
+        return;
     }
+    for_tiles(chunks,
+              [&](size_t v) {
+                  int64_t m, c;
+                  rc.locate(v, m, c);
+                  return load_any<u32x4, NT>(x + m * ldx + c);
+              },
+              [&](size_t v, u32x4 a) {
+                  int64_t m, c;
+                  rc.locate(v, m, c);
+                  u32x4 o;
+#pragma unroll
+                  for (int d = 0; d < 4; ++d)
+                      o[d] = (uint32_t)lut[a[d] & 0xffu] | ((uint32_t)lut[(a[d] >> 8) & 0xffu] << 8) |
+                             ((uint32_t)lut[(a[d] >> 16) & 0xffu] << 16) | ((uint32_t)lut[a[d] >> 24] << 24);
+                  store_any(y + m * ldy + c, o);
+              });
 }
 
 // ------------------------------------------------ add behind a product, second-pass form
@@ -568,7 +534,8 @@ qnn_status launch_add_inplace(uint8_t *y, int64_t ldy, const uint8_t *r, int64_t
     if (ldy == N && ldr == N) rows = 1, cols = M * (int64_t)N, ldy = ldr = cols; // dense: one long row, whole chunks throughout
     const int vec16 = aligned(y, 16) && aligned(r, 16) && (rows == 1 || ((ldy % 16) == 0 && (ldr % 16) == 0));
     const size_t chunks = (size_t)rows * (size_t)((cols + 15) / 16);
-    const int grid = grid_for(chunks, kThreads * 2);
+    size_t blocks = (chunks + kThreads * 2 - 1) / (kThreads * 2);
+    const int grid = (int)(blocks > 256 * 16 ? 256 * 16 : blocks);
     const bool fused = p.shift_o >= 1 && p.shift_o <= 20 && p.shift_m >= 0 && p.shift_r >= 0 && p.left_shift <= 20;
     if (fused) hipLaunchKernelGGL((add_inplace_kernel<true>), dim3(grid), dim3(kThreads), 0, s, y, ldy, r, ldr, rows, cols, p, vec16);
     else hipLaunchKernelGGL((add_inplace_kernel<false>), dim3(grid), dim3(kThreads), 0, s, y, ldy, r, ldr, rows, cols, p, vec16);
@@ -588,16 +555,7 @@ qnn_status qnn_quantize(const float *x, uint8_t *q, size_t n, float scale, int32
     if (qmin < 0 || qmax > 255 || qmin > qmax || zero_point < qmin || zero_point > qmax) return QNN_EINVAL;
     if (n == 0) return QNN_OK;
     if (!x || !q) return QNN_EINVAL;
-    const float lo = (float)(qmin - zero_point), hi = (float)(qmax - zero_point);
-    if (aligned(x, 16) && aligned(q, 4)) {
-        const int grid = grid_for(n / 4 + 1, kThreads * 4);
-        hipLaunchKernelGGL(quantize_kernel<4>, dim3(grid), dim3(kThreads), 0, as_stream(stream), x, q, n, scale,
-                           zero_point, lo, hi);
-    } else {
-        hipLaunchKernelGGL(quantize_kernel<1>, dim3(grid_for(n, kThreads * 4)), dim3(kThreads), 0, as_stream(stream),
-                           x, q, n, scale, zero_point, lo, hi);
-    }
-    return launch_status(hipGetLastError());
+    return launch_stream(QuantizeOp{x, q, scale, (float)(qmin - zero_point), (float)(qmax - zero_point), zero_point}, n, 5, stream);
 }
 
 qnn_status qnn_dequantize(const uint8_t *q, float *x, size_t n, float scale, int32_t zero_point, void *stream)
@@ -605,14 +563,7 @@ qnn_status qnn_dequantize(const uint8_t *q, float *x, size_t n, float scale, int
     if (!(scale > 0.0f) || __builtin_isinf(scale) || zero_point < 0 || zero_point > 255) return QNN_EINVAL;
     if (n == 0) return QNN_OK;
     if (!x || !q) return QNN_EINVAL;
-    if (aligned(x, 16) && aligned(q, 4)) {
-        hipLaunchKernelGGL(dequantize_kernel<4>, dim3(grid_for(n / 4 + 1, kThreads * 4)), dim3(kThreads), 0,
-                           as_stream(stream), q, x, n, scale, zero_point);
-    } else {
-        hipLaunchKernelGGL(dequantize_kernel<1>, dim3(grid_for(n, kThreads * 4)), dim3(kThreads), 0,
-                           as_stream(stream), q, x, n, scale, zero_point);
-    }
-    return launch_status(hipGetLastError());
+    return launch_stream(DequantizeOp{q, x, scale, zero_point}, n, 5, stream);
 }
 
 qnn_status qnn_quantize_u16(const float *x, uint16_t *q, size_t n, float scale, int32_t zero_point, int32_t qmin,
@@ -622,14 +573,7 @@ qnn_status qnn_quantize_u16(const float *x, uint16_t *q, size_t n, float scale, 
     if (qmin < 0 || qmax > 65535 || qmin > qmax || zero_point < qmin || zero_point > qmax) return QNN_EINVAL;
     if (n == 0) return QNN_OK;
     if (!x || !q) return QNN_EINVAL;
-    const float lo = (float)(qmin - zero_point), hi = (float)(qmax - zero_point);
-    if (aligned(x, 16) && aligned(q, 8))
-        hipLaunchKernelGGL(quantize_u16_kernel<4>, dim3(grid_for(n / 4 + 1, kThreads * 4)), dim3(kThreads), 0,
-                           as_stream(stream), x, q, n, scale, zero_point, lo, hi);
-    else
-        hipLaunchKernelGGL(quantize_u16_kernel<1>, dim3(grid_for(n, kThreads * 4)), dim3(kThreads), 0, as_stream(stream),
-                           x, q, n, scale, zero_point, lo, hi);
-    return launch_status(hipGetLastError());
+    return launch_stream(QuantizeU16Op{x, q, scale, (float)(qmin - zero_point), (float)(qmax - zero_point), zero_point}, n, 6, stream);
 }
 
 qnn_status qnn_dequantize_u16(const uint16_t *q, float *x, size_t n, float scale, int32_t zero_point, void *stream)
@@ -637,13 +581,7 @@ qnn_status qnn_dequantize_u16(const uint16_t *q, float *x, size_t n, float scale
     if (!(scale > 0.0f) || __builtin_isinf(scale) || zero_point < 0 || zero_point > 65535) return QNN_EINVAL;
     if (n == 0) return QNN_OK;
     if (!x || !q) return QNN_EINVAL;
-    if (aligned(x, 16) && aligned(q, 8))
-        hipLaunchKernelGGL(dequantize_u16_kernel<4>, dim3(grid_for(n / 4 + 1, kThreads * 4)), dim3(kThreads), 0,
-                           as_stream(stream), q, x, n, scale, zero_point);
-    else
-        hipLaunchKernelGGL(dequantize_u16_kernel<1>, dim3(grid_for(n, kThreads * 4)), dim3(kThreads), 0,
-                           as_stream(stream), q, x, n, scale, zero_point);
-    return launch_status(hipGetLastError());
+    return launch_stream(DequantizeU16Op{q, x, scale, zero_point}, n, 6, stream);
 }
 
 qnn_status qnn_requantize(const int32_t *acc, uint8_t *y, size_t rows, size_t channels, const int32_t *mult,
@@ -653,26 +591,16 @@ qnn_status qnn_requantize(const int32_t *acc, uint8_t *y, size_t rows, size_t ch
     if (!acc || !y || !mult || !shift || rows == 0 || channels == 0 || channels > 0x7fffffffu) return QNN_EINVAL;
     if (bad_out_range(z_out, act_min, act_max)) return QNN_EINVAL;
     const size_t total = rows * channels;
-    const bool vec = aligned(acc, 16) && aligned(y, 4) && (channels % 4 == 0) && aligned(mult, 16) && aligned(shift, 16);
+    const RequantizeArgs g = {acc, y, mult, shift, total, per_channel ? (uint32_t)channels : 1u, z_out, act_min, act_max};
+    uint32_t magic, magic_shift;
+    fast_division(g.channels, magic, magic_shift);
+    const bool fixed = (4 * kThreads) % g.channels == 0, nt = total * 5 > kCacheBytes;
+    const dim3 grid((unsigned)grid_for(total / 4));
     const hipStream_t s = as_stream(stream);
-    const uint32_t ch = (uint32_t)channels;
-    if (vec) {
-        const int grid = grid_for(total / 4, kThreads * 2);
-        if (per_channel)
-            hipLaunchKernelGGL((requantize_kernel<4, true>), dim3(grid), dim3(kThreads), 0, s, acc, y, total, ch, mult,
-                               shift, z_out, act_min, act_max);
-        else
-            hipLaunchKernelGGL((requantize_kernel<4, false>), dim3(grid), dim3(kThreads), 0, s, acc, y, total, ch,
-                               mult, shift, z_out, act_min, act_max);
-    } else {
-        const int grid = grid_for(total, kThreads * 4);
-        if (per_channel)
-            hipLaunchKernelGGL((requantize_kernel<1, true>), dim3(grid), dim3(kThreads), 0, s, acc, y, total, ch, mult,
-                               shift, z_out, act_min, act_max);
-        else
-            hipLaunchKernelGGL((requantize_kernel<1, false>), dim3(grid), dim3(kThreads), 0, s, acc, y, total, ch,
-                               mult, shift, z_out, act_min, act_max);
-    }
+    if (fixed && nt) hipLaunchKernelGGL((requantize_kernel<true, true>), grid, dim3(kThreads), 0, s, g, magic, magic_shift);
+    else if (fixed) hipLaunchKernelGGL((requantize_kernel<true, false>), grid, dim3(kThreads), 0, s, g, magic, magic_shift);
+    else if (nt) hipLaunchKernelGGL((requantize_kernel<false, true>), grid, dim3(kThreads), 0, s, g, magic, magic_shift);
+    else hipLaunchKernelGGL((requantize_kernel<false, false>), grid, dim3(kThreads), 0, s, g, magic, magic_shift);
     return launch_status(hipGetLastError());
 }
 
@@ -681,7 +609,12 @@ qnn_status qnn_minmax(const float *x, size_t n, float momentum, int bits, qnn_dy
     if (!state || (n && !x) || bits < 2 || bits > 16 || !(momentum >= 0.0f) || !(momentum < 1.0f)) return QNN_EINVAL;
     const hipStream_t s = as_stream(stream);
     hipLaunchKernelGGL(minmax_init_kernel, dim3(1), dim3(1), 0, s, state);
-    if (n) hipLaunchKernelGGL(minmax_kernel, dim3(grid_for(n / 4 + 1, kThreads * 4, 256 * 8)), dim3(kThreads), 0, s, x, n, state);
+    if (n) {
+        const size_t tiles = (n / 4 + kMinmaxThreads * kUnroll - 1) / (kMinmaxThreads * kUnroll);
+        const dim3 grid((unsigned)(tiles < 1 ? 1 : (tiles < kMinmaxBlocks ? tiles : kMinmaxBlocks)));
+        if (n * 4 > kCacheBytes) hipLaunchKernelGGL(minmax_kernel<true>, grid, dim3(kMinmaxThreads), 0, s, x, n, state);
+        else hipLaunchKernelGGL(minmax_kernel<false>, grid, dim3(kMinmaxThreads), 0, s, x, n, state);
+    }
     hipLaunchKernelGGL(range_finalize_kernel, dim3(1), dim3(1), 0, s, state, momentum, bits);
     return launch_status(hipGetLastError());
 }
@@ -691,9 +624,7 @@ qnn_status qnn_quantize_with(const float *x, uint8_t *q, size_t n, const qnn_dyn
     if (!state) return QNN_EINVAL;
     if (n == 0) return QNN_OK;
     if (!x || !q) return QNN_EINVAL;
-    hipLaunchKernelGGL(quantize_with_kernel, dim3(grid_for(n / 4 + 1, kThreads * 4)), dim3(kThreads), 0, as_stream(stream), x, q,
-                       n, state);
-    return launch_status(hipGetLastError());
+    return launch_stream(QuantizeWithOp{x, q, state}, n, 5, stream);
 }
 
 qnn_status qnn_quantize_dynamic(const float *x, uint8_t *q, size_t n, qnn_dyn_qparams *state, void *stream)
@@ -710,9 +641,7 @@ qnn_status qnn_simquant(const float *x, float *y, size_t n, float scale, int32_t
     if (zero_point < qmin || zero_point > qmax) return QNN_EINVAL;
     if (n == 0) return QNN_OK;
     if (!x || !y) return QNN_EINVAL;
-    hipLaunchKernelGGL(simquant_kernel, dim3(grid_for(n, kThreads * 4)), dim3(kThreads), 0, as_stream(stream), x, y, n, scale,
-                       zero_point, (float)(qmin - zero_point), (float)(qmax - zero_point));
-    return launch_status(hipGetLastError());
+    return launch_stream(SimquantOp{x, y, scale, (float)(qmin - zero_point), (float)(qmax - zero_point), zero_point}, n, 8, stream);
 }
 
 qnn_status qnn_simquant_backward(const float *x, const float *grad_y, float *grad_x, size_t n, float scale,
@@ -724,9 +653,7 @@ qnn_status qnn_simquant_backward(const float *x, const float *grad_y, float *gra
     if (!x || !grad_y || !grad_x) return QNN_EINVAL;
     // the ends of the representable range are the de-quantized extreme codes (one binary32 product each)
     const float xmin = (float)(qmin - zero_point) * scale, xmax = (float)(qmax - zero_point) * scale;
-    hipLaunchKernelGGL(simquant_backward_kernel, dim3(grid_for(n, kThreads * 4)), dim3(kThreads), 0, as_stream(stream), x, grad_y,
-                       grad_x, n, xmin, xmax);
-    return launch_status(hipGetLastError());
+    return launch_stream(SimquantBackwardOp{x, grad_y, grad_x, xmin, xmax}, n, 12, stream);
 }
 
 qnn_status qnn_rescale_u8(const uint8_t *x, int64_t ldx, int32_t z_in, int32_t mult, int32_t shift, int32_t z_out,
@@ -738,10 +665,17 @@ qnn_status qnn_rescale_u8(const uint8_t *x, int64_t ldx, int32_t z_in, int32_t m
     if (!x || !y || ldx < cols || ldy < cols) return QNN_EINVAL;
     int64_t r = rows, c = cols;
     if (ldx == cols && ldy == cols) r = 1, c = rows * cols, ldx = ldy = c; // dense: one long row, whole chunks throughout
-    const int vec16 = aligned(x, 16) && aligned(y, 16) && (r == 1 || ((ldx % 16) == 0 && (ldy % 16) == 0));
-    const size_t chunks = (size_t)r * (size_t)((c + 15) / 16);
-    hipLaunchKernelGGL(rescale_u8_kernel, dim3(grid_for(chunks, kThreads * 2)), dim3(kThreads), 0, as_stream(stream), x, ldx, y, ldy,
-                       r, c, z_in, mult, shift, z_out, act_min, act_max, vec16);
+    RowChunks rc = {};
+    rc.per_row = (uint32_t)((c + 15) / 16), rc.cols = c;
+    fast_division(rc.per_row, rc.magic, rc.magic_shift);
+    if ((c + 15) / 16 > 0x7fffffff) return QNN_EINVAL;
+    const size_t chunks = (size_t)r * rc.per_row;
+    const dim3 grid((unsigned)grid_for(chunks));
+    const hipStream_t s = as_stream(stream);
+    if ((size_t)rows * (size_t)cols * 2 > kCacheBytes)
+        hipLaunchKernelGGL(rescale_u8_kernel<true>, grid, dim3(kThreads), 0, s, x, ldx, y, ldy, chunks, rc, z_in, mult, shift, z_out, act_min, act_max);
+    else
+        hipLaunchKernelGGL(rescale_u8_kernel<false>, grid, dim3(kThreads), 0, s, x, ldx, y, ldy, chunks, rc, z_in, mult, shift, z_out, act_min, act_max);
     return launch_status(hipGetLastError());
 }
 
@@ -758,15 +692,12 @@ qnn_status qnn_qadd(const uint8_t *a, int32_t z_a, int32_t mult_a, int32_t shift
     QaddArgs g = {z_a, mult_a, shift_a, z_b, mult_b, shift_b, left_shift, mult_o, shift_o, z_out, act_min, act_max};
     const bool fused = shift_o >= 1 && shift_o <= 20 && shift_a >= 0 && shift_b >= 0 && left_shift <= 20;
     const hipStream_t s = as_stream(stream);
-    if (aligned(a, 16) && aligned(b, 16) && aligned(y, 16)) {
-        const int grid = grid_for(n / 16 + 1, kThreads * 2);
-        if (fused) hipLaunchKernelGGL((qadd_kernel<16, true>), dim3(grid), dim3(kThreads), 0, s, a, b, y, n, g);
-        else hipLaunchKernelGGL((qadd_kernel<16, false>), dim3(grid), dim3(kThreads), 0, s, a, b, y, n, g);
-    } else {
-        const int grid = grid_for(n, kThreads * 4);
-        if (fused) hipLaunchKernelGGL((qadd_kernel<1, true>), dim3(grid), dim3(kThreads), 0, s, a, b, y, n, g);
-        else hipLaunchKernelGGL((qadd_kernel<1, false>), dim3(grid), dim3(kThreads), 0, s, a, b, y, n, g);
-    }
+    const dim3 grid((unsigned)grid_for(n / 16));
+    const bool nt = n * 3 > kCacheBytes;
+    if (fused && nt) hipLaunchKernelGGL((qadd_kernel<true, true>), grid, dim3(kThreads), 0, s, a, b, y, n, g);
+    else if (fused) hipLaunchKernelGGL((qadd_kernel<true, false>), grid, dim3(kThreads), 0, s, a, b, y, n, g);
+    else if (nt) hipLaunchKernelGGL((qadd_kernel<false, true>), grid, dim3(kThreads), 0, s, a, b, y, n, g);
+    else hipLaunchKernelGGL((qadd_kernel<false, false>), grid, dim3(kThreads), 0, s, a, b, y, n, g);
     return launch_status(hipGetLastError());
 }
 

@@ -37,11 +37,8 @@ static RepackPart make_part(const uint8_t *src, int64_t pitch, int64_t rows, int
     RepackPart p = {};
     p.src = src, p.dst = dst, p.pitch = pitch, p.len = len;
     const uint32_t d = (uint32_t)(padded / 16);
-    uint32_t l = 0;
-    while ((1u << l) < d) ++l;
     p.cpr = d;
-    p.shift = l > 0 ? l - 1 : 0;
-    p.magic = d > 1 ? (uint32_t)((((uint64_t)1 << (31 + l)) + d - 1) / d) : 0u;
+    fast_division(d, p.magic, p.shift);
     p.chunks = (uint32_t)(rows * d);
     return p;
 }

@@ -17,15 +17,6 @@ bool small_shape(int64_t M, int64_t N, int64_t K, bool conv, bool int4)
     return ((N + 15) / 16) * ((M + 31) / 32) <= 800;
 }
 
-// x / d = umulhi(x, magic) >> shift for x < 2^31, d >= 2
-static void division(uint32_t d, uint32_t &magic, uint32_t &shift)
-{
-    uint32_t l = 0;
-    while ((1u << l) < d) ++l;
-    shift = l > 0 ? l - 1 : 0;
-    magic = d > 1 ? (uint32_t)((((uint64_t)1 << (31 + l)) + d - 1) / d) : 0u;
-}
-
 template <int AI, bool INT4, int A_MODE> static void launch_rows(const SmallArgs &a, int waves, hipStream_t s)
 {
     const dim3 grid((unsigned)((a.g.N + 15) / 16), (unsigned)((a.g.M + 8 * AI - 1) / (8 * AI)));
@@ -68,8 +59,8 @@ bool try_small(const IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_st
     SmallArgs a = {};
     a.g = g;
     if (conv) {
-        division((uint32_t)(g.Ho * g.Wo), a.magic_hw, a.shift_hw);
-        division((uint32_t)g.Wo, a.magic_wo, a.shift_wo);
+        fast_division((uint32_t)(g.Ho * g.Wo), a.magic_hw, a.shift_hw);
+        fast_division((uint32_t)g.Wo, a.magic_wo, a.shift_wo);
     }
     b_mode == B_INT4 ? launch_small<true>(a, conv, s) : launch_small<false>(a, conv, s);
     *status = launch_status(hipGetLastError());

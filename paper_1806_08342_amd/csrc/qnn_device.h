@@ -16,6 +16,15 @@ void set_last_error(const char *text);
 
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
+// x / d = umulhi(x, magic) >> shift for x < 2^31 and d >= 2 (with l = ceil(log2 d), magic = ceil(2^(31 + l) / d))
+inline void fast_division(uint32_t d, uint32_t &magic, uint32_t &shift)
+{
+    uint32_t l = 0;
+    while (((uint64_t)1 << l) < d) ++l;
+    shift = l > 0 ? l - 1 : 0;
+    magic = d > 1 ? (uint32_t)((((uint64_t)1 << (31 + l)) + d - 1) / d) : 0u;
+}
+
 inline bool bad_out_range(int32_t z_out, int32_t act_min, int32_t act_max)
 {
     return act_min < 0 || act_max > 255 || act_min > act_max || z_out < 0 || z_out > 255;
