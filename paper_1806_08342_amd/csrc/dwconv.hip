@@ -344,7 +344,8 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
                         packed |= (uint32_t)y << (8 * j);
                     }
                 }
-                if (wo0 + p < g.Wo) *reinterpret_cast<uint32_t *>(out + (out_off + (uint32_t)(p * g.C))) = packed;
+                // (non-temporal: what is left in the L2s is written back when the kernel ends, 10-15 % of a 12 us launch)
+                if (wo0 + p < g.Wo) __builtin_nontemporal_store(packed, reinterpret_cast<uint32_t *>(out + (out_off + (uint32_t)(p * g.C))));
             }
         }
     };
@@ -547,7 +548,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
             uint32_t v = __builtin_amdgcn_perm(o, x[q], sel1);
             o = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);
             v = __builtin_amdgcn_perm(o, v, sel2);
-            if (o_ok[q]) *reinterpret_cast<uint32_t *>(out + o_off[q]) = v;
+            if (o_ok[q]) __builtin_nontemporal_store(v, reinterpret_cast<uint32_t *>(out + o_off[q]));
         }
         out_row += out_row_bytes;
     };
