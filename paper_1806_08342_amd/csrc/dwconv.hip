@@ -23,7 +23,7 @@ struct DwArgs {
     const int8_t *w;
     uint8_t *y;
     const int32_t *bias, *mult, *shift;
-    const int32_t *zw; // per-channel weight zero-points, or nullptr (generic kernel only)
+    const int32_t *zw; // per-channel weight zero-points in [-128, 127], or nullptr
     int N, H, W, C, Ho, Wo, kh, kw, sh, sw, ph, pw;
     int32_t z_x, z_out, lo_rel, hi_rel;
     int64_t total_work; // lanes of work
@@ -77,9 +77,13 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const DwArgs g)
     const int c0 = cg * 4;
     const int ho0 = ph * RH, wo0 = pw * RW;
 
-    // weights as sign-extended ints, and their per-channel sums
+    // weights as sign-extended ints (less their zero-point), and their per-channel sums
     int32_t wt[3][3][4];
-    int32_t wsum[4] = {0, 0, 0, 0};
+    int32_t wsum[4] = {0, 0, 0, 0}, zw[4] = {0, 0, 0, 0};
+    if (g.zw) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) zw[j] = g.zw[c0 + j];
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -87,7 +91,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const DwArgs g)
             const uint32_t wv = *reinterpret_cast<const uint32_t *>(g.w + ((int64_t)a * 3 + b) * g.C + c0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                wt[a][b][j] = sbyte(wv, j);
+                wt[a][b][j] = sbyte(wv, j) - zw[j];
                 wsum[j] += wt[a][b][j];
             }
         }
@@ -147,7 +151,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const DwArgs g)
         fused_ok = fused_ok && sf >= 1 && sf <= 20;
         fr[j] = make_fused(mu, sf, 0, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out);
     }
-    // |acc| <= |bias| + 2 * 9 * 255 * 128: the fused form needs |acc| < 2^29, i.e. a sane bias
+    // |acc| <= |bias| + 2 * 9 * 255 * 255: the fused form needs |acc| < 2^29, i.e. a sane bias
     if (g.bias) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -176,6 +180,22 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const DwArgs g)
     }
 }
 
+// Weight zero-points on 8-bit multipliers.  The effective weight w' = w - z_w needs 9 bits; it is fed as two signed
+// bytes, w' = w + (-z_w), of which the second is the same for all taps.  -z_w does not fit for z_w = -128; such a
+// channel accumulates -w' = ~w + (-127) instead and its sum changes sign in the rescale's add (|sum| <= 9 * 255 * 255
+// fits the 24-bit multiply-add that does both).  So weight zero-points cost one more dot product (or matrix
+// instruction) per tap vector and nothing else.
+struct DwZeroPoint {
+    int32_t common; // the byte shared by all taps
+    int32_t flip;   // all ones: taps enter complemented
+    int32_t sign;   // of the accumulated sum
+};
+__device__ __forceinline__ DwZeroPoint dw_zero_point(int32_t zw)
+{
+    const bool low = zw == -128;
+    return {low ? -127 : -zw, low ? -1 : 0, low ? -1 : 1};
+}
+
 // Same layer, multiply-accumulates on the 4-way int8 dot product instruction.
 //
 // In NHWC a dword holds 4 channels of one pixel, but the sum of a depthwise kernel runs over
@@ -193,7 +213,9 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const DwArgs g)
 // addresses and row bounds live in scalar registers, and a lane only keeps the byte offset and
 // the in-image flag of its COLS window columns.  Every load is unconditional (from a clamped
 // address) followed by a select of the padding code: no branches around memory operations.
-template <int S, int RH>
+// ZW: weight zero-points, see DwZeroPoint.  (One lane per output, as such layers ran before: 17.6 us on
+// 16 x 14 x 14 x 512, 7.2 us here; 57 against 14.3 us on 16 x 112 x 112 x 32 with the matrix-unit kernel below.)
+template <int S, int RH, bool ZW>
 __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
 {
     constexpr int RW = 4;
@@ -212,6 +234,20 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
     // ---- weights: wa[a][j] = [w(a,0), w(a,1), w(a,2), 0] of channel c0 + j
     uint32_t wa[3][4];
     int32_t wsum[4] = {0, 0, 0, 0};
+    uint32_t wc[4];      // ZW: [c, c, c, 0], the byte that the taps share
+    int32_t sign[4];     // ZW
+    uint32_t flip = 0u;  // ZW: byte j all ones where channel c0 + j enters complemented
+    if constexpr (ZW) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int32_t zw = g.zw[c0 + j];
+            const DwZeroPoint z = dw_zero_point(zw);
+            wc[j] = ((uint32_t)z.common & 0xffu) * 0x00010101u;
+            sign[j] = z.sign;
+            flip |= (uint32_t)z.flip & (0xffu << (8 * j));
+            wsum[j] = -9 * zw;
+        }
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         uint32_t wv[3];
@@ -222,16 +258,17 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
             const uint32_t t01 = __builtin_amdgcn_perm(wv[1], wv[0], 0x0c0c0000u | ((4u + j) << 8) | (uint32_t)j);
             wa[a][j] = __builtin_amdgcn_perm(wv[2], t01, 0x0c000100u | ((4u + j) << 16));
             wsum[j] = __builtin_amdgcn_sdot4((int)wa[a][j], 0x01010101, wsum[j], false);
+            if constexpr (ZW) wa[a][j] ^= __builtin_amdgcn_perm(0u, flip, 0x0c000000u | (uint32_t)(0x00010101 * j));
         }
     }
-    int32_t acc[RH][RW][4];
+    int32_t acc[RH][RW][4], init[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int32_t init = (g.bias ? g.bias[c0 + j] : 0) + (128 - g.z_x) * wsum[j];
+        init[j] = (g.bias ? g.bias[c0 + j] : 0) + (128 - g.z_x) * wsum[j];
 #pragma unroll
         for (int r = 0; r < RH; ++r)
 #pragma unroll
-            for (int p = 0; p < RW; ++p) acc[r][p][j] = init;
+            for (int p = 0; p < RW; ++p) acc[r][p][j] = ZW ? 0 : init[j];
     }
 
     const int hi0 = ho0 * S - g.ph, wi0 = wo0 * S - g.pw;
@@ -285,7 +322,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
             for (int r = 0; r < RH; ++r) {
                 const int a = row - r * S; // kernel row of this input row for output row r
                 if (a < 0 || a > 2) continue;
-                const uint32_t w = wa[a][j];
+                auto taps = [&](uint32_t w) __attribute__((always_inline)) {
                 if constexpr (S == 1) {
                     acc[r][0][j] = __builtin_amdgcn_sdot4((int)x0[j], (int)w, acc[r][0][j], false);
                     acc[r][1][j] = __builtin_amdgcn_sdot4((int)x0[j], (int)(w << 8), acc[r][1][j], false);
@@ -299,6 +336,9 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
                     acc[r][3][j] = __builtin_amdgcn_sdot4((int)x1[j], (int)(w << 16), acc[r][3][j], false);
                     acc[r][3][j] = __builtin_amdgcn_sdot4((int)x2[j], (int)(w >> 16), acc[r][3][j], false);
                 }
+                };
+                taps(wa[a][j]);
+                if constexpr (ZW) taps(wc[j]);
             }
         }
     }
@@ -318,6 +358,14 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
         cc[j] = 2 * ((1 << (nn - 1)) + (g.z_out << nn)) + 1;
         lo[j] = (g.lo_rel + g.z_out) << (nn + 1);
         hi_[j] = ((g.hi_rel + g.z_out + 1) << (nn + 1)) - 1;
+    }
+    if constexpr (ZW) {
+#pragma unroll
+        for (int r = 0; r < RH; ++r)
+#pragma unroll
+            for (int p = 0; p < RW; ++p)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[r][p][j] = __mul24(acc[r][p][j], sign[j]) + init[j];
     }
     const bool fused = __all(fused_ok);
     uint8_t *const out_img = g.y + (int64_t)n * g.Ho * g.Wo * g.C; // scalar
@@ -388,7 +436,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
 using dw_i32x4 = int32_t __attribute__((ext_vector_type(4)));
 using dw_i32x16 = int32_t __attribute__((ext_vector_type(16)));
 
-template <int S, int MODE>
+template <int S, int MODE, bool ZW> // ZW: weight zero-points, see DwZeroPoint
 __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, const int seg_rows, const int tiles_w,
                                                                 const int cblocks)
 {
@@ -448,18 +496,28 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     const int ch = cblk * 32 + li;                  // the channel this lane accumulates and rescales
     const bool ch_ok = ch < g.C;
     const bool diag_here = ch_ok && (li >> 4) == half;
-    dw_i32x4 wq[3][3];
+    auto diagonal = [&](int32_t w) { // the byte w of this lane's channel in its place
+        const uint32_t placed = diag_here ? ((uint32_t)(w & 0xff) << (8 * (li & 3))) : 0u;
+        const int d = (li >> 2) & 3;
+        return dw_i32x4{d == 0 ? (int32_t)placed : 0, d == 1 ? (int32_t)placed : 0, d == 2 ? (int32_t)placed : 0,
+                        d == 3 ? (int32_t)placed : 0};
+    };
+    dw_i32x4 wq[3][3], wc = {0, 0, 0, 0};
     int32_t wsum = 0;
+    DwZeroPoint zp = {0, 0, 1};
+    if constexpr (ZW) {
+        const int32_t zw = ch_ok ? g.zw[ch] : 0;
+        zp = dw_zero_point(zw);
+        wsum = -9 * zw;
+        wc = diagonal(zp.common);
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             const int32_t w = ch_ok ? (int32_t)g.w[(a * 3 + b) * g.C + ch] : 0;
             wsum += w;
-            const uint32_t placed = diag_here ? ((uint32_t)(w & 0xff) << (8 * (li & 3))) : 0u;
-            const int d = (li >> 2) & 3;
-            wq[a][b] = dw_i32x4{d == 0 ? (int32_t)placed : 0, d == 1 ? (int32_t)placed : 0, d == 2 ? (int32_t)placed : 0,
-                                d == 3 ? (int32_t)placed : 0};
+            wq[a][b] = diagonal(w ^ zp.flip);
         }
     const int32_t bias = (ch_ok && g.bias) ? g.bias[ch] : 0;
     const int32_t init = bias + (128 - g.z_x) * wsum;
@@ -515,6 +573,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     };
     auto finish = [&](int slot) __attribute__((always_inline)) {
         // wave-uniform row base (scalar registers) + 32-bit lane offsets
+        auto with_init = [&](int32_t a) { return ZW ? __mul24(a, zp.sign) + init : (int32_t)((uint32_t)a + (uint32_t)init); };
         const int64_t row_off = ((int64_t)__builtin_amdgcn_readfirstlane((int)(out_row >> 32)) << 32) |
                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)out_row);
         uint8_t *out = g.y + row_off;
@@ -525,7 +584,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
                 x[q] = 0;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int32_t tt = __mulhi((int32_t)(((uint32_t)acc[slot][4 * q + e] + (uint32_t)init) << 2), mu);
+                    const int32_t tt = __mulhi((int32_t)((uint32_t)with_init(acc[slot][4 * q + e]) << 2), mu);
                     x[q] = shift_into_byte(x[q], med3_i32(fused_w_from_t<MODE == 1>(tt, cc), lo, hi_), n1, e);
                 }
             }
@@ -536,7 +595,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
                 x[q] = 0;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general(acc[slot][4 * q + e] + init, rp)) + g.z_out;
+                    const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general(with_init(acc[slot][4 * q + e]), rp)) + g.z_out;
                     x[q] |= (uint32_t)y << (8 * e);
                 }
             }
@@ -590,6 +649,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     // consecutive matrix instructions do not depend on each other)
     auto mac1 = [&](int a, int b, int slot) __attribute__((always_inline)) {
         acc[slot] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[b], wq[a][b], acc[slot], 0, 0, 0);
+        if constexpr (ZW) acc[slot] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[b], wc, acc[slot], 0, 0, 0);
     };
 
     // Steady state of the row pipeline, free of run-time conditions: every output row involved exists and every
@@ -613,6 +673,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     };
     auto mac0 = [&](int b, int slot) __attribute__((always_inline)) { // kernel row 0: window column 0 opens the accumulator set
         acc[slot] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[b], wq[0][b], b == 0 ? zero16 : acc[slot], 0, 0, 0);
+        if constexpr (ZW) acc[slot] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[b], wc, acc[slot], 0, 0, 0);
     };
 
     if constexpr (S == 1) {
@@ -763,8 +824,7 @@ static qnn_status qdwconv2d_impl(const uint8_t *x, int N, int H, int W, int C, i
     g.z_x = z_x, g.z_out = z_out, g.lo_rel = act_min - z_out, g.hi_rel = act_max - z_out;
     const hipStream_t s = as_stream(stream);
     auto al4 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 3) == 0; };
-    // (weight zero-points: the one-lane-per-output kernel, which evaluates the defining sum directly)
-    const bool c4 = !z_w && (C % 4 == 0) && al4(x) && al4(w) && al4(y) && kh == 3 && kw == 3 && stride_h == stride_w &&
+    const bool c4 = (C % 4 == 0) && al4(x) && al4(w) && al4(y) && kh == 3 && kw == 3 && stride_h == stride_w &&
                     (stride_h == 1 || stride_h == 2);
     constexpr int RH = 2, RW = 4;
     if (c4) {
@@ -810,11 +870,15 @@ static qnn_status qdwconv2d_impl(const uint8_t *x, int N, int H, int W, int C, i
             const int segs = (g.Ho + seg_rows - 1) / seg_rows;
             const dim3 grid((unsigned)((waves_x + 3) / 4), (unsigned)segs, (unsigned)N);
             g.xcd_remap = tuning().dw_xcd != 0 && (int64_t)grid.x * grid.y * grid.z < (1ll << 31);
-            const int mode = g.lo_rel >= 0 ? 2 : 1;
-            if (stride_h == 1 && mode == 2) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 2>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-            else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 1>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-            else if (mode == 2) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 2>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-            else hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 1>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+            auto launch = [&](auto zw) {
+                constexpr bool ZW = decltype(zw)::value;
+                const bool absorbs = g.lo_rel >= 0; // the clamp absorbs the tie term
+                if (stride_h == 1 && absorbs) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 2, ZW>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 1, ZW>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                else if (absorbs) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 2, ZW>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                else hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 1, ZW>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+            };
+            z_w ? launch(std::true_type{}) : launch(std::false_type{});
             return launch_status(hipGetLastError());
         }
         // taller patches (4 output rows per lane) reuse more of the window, but need enough lanes to
@@ -825,10 +889,14 @@ static qnn_status qdwconv2d_impl(const uint8_t *x, int N, int H, int W, int C, i
         if (tall) g.hruns = (g.Ho + 3) / 4;
         const dim3 grid((unsigned)((lanes_x + 255) / 256), (unsigned)g.hruns, (unsigned)N);
         g.xcd_remap = tuning().dw_xcd != 0 && (int64_t)grid.x * grid.y * grid.z < (1ll << 31);
-        if (tall && stride_h == 1) hipLaunchKernelGGL((dwconv3x3_dot_kernel<1, 4>), grid, dim3(256), 0, s, g);
-        else if (tall) hipLaunchKernelGGL((dwconv3x3_dot_kernel<2, 4>), grid, dim3(256), 0, s, g);
-        else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_dot_kernel<1, RH>), grid, dim3(256), 0, s, g);
-        else hipLaunchKernelGGL((dwconv3x3_dot_kernel<2, RH>), grid, dim3(256), 0, s, g);
+        auto launch = [&](auto zw) {
+            constexpr bool ZW = decltype(zw)::value;
+            if (tall && stride_h == 1) hipLaunchKernelGGL((dwconv3x3_dot_kernel<1, 4, ZW>), grid, dim3(256), 0, s, g);
+            else if (tall) hipLaunchKernelGGL((dwconv3x3_dot_kernel<2, 4, ZW>), grid, dim3(256), 0, s, g);
+            else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_dot_kernel<1, RH, ZW>), grid, dim3(256), 0, s, g);
+            else hipLaunchKernelGGL((dwconv3x3_dot_kernel<2, RH, ZW>), grid, dim3(256), 0, s, g);
+        };
+        z_w ? launch(std::true_type{}) : launch(std::false_type{});
     } else if (c4 && stride_h == 1)
         hipLaunchKernelGGL((dwconv3x3_kernel<1, RH, RW>), dim3((unsigned)blocks), dim3(256), 0, s, g);
     else if (c4)

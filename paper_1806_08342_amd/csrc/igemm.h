@@ -49,9 +49,7 @@ struct IgemmArgs {
     int64_t ldc;
     int32_t c_vec16;  // C and ldc are 16-byte aligned
     int32_t small_acc; // 2: |acc| and the zero-point correction are each below 2^27; 1: below 2^28; 0: unknown
-    // optional per-column weight zero-points (eq. 5-6 with z_w != 0): zw[n] and the row sums
-    // rowsum[m] = sum_k (A[m][k] - z_a) over the taps inside the image (both int32, device); nullptr: z_w = 0
-    const int32_t *zw, *rowsum;
+    const int32_t *zw; // optional per-column weight zero-points (eq. 5-6 with z_w != 0), device; nullptr: z_w = 0
     // optional rescaling add behind the product: C = ADD(code of the product, R); R == nullptr: none
     const uint8_t *R;
     int64_t ldr;
@@ -221,11 +219,17 @@ __device__ __forceinline__ ChannelParams<TN> load_channel_params(const IgemmArgs
     return p;
 }
 
-// ZW: per-column weight zero-points; the term - z_w[n] * rowsum[m] joins every accumulator (the
-// tile's row sums are staged in LDS behind the add tables)
+// ZW: per-column weight zero-points.  sum_k (x - z_a)(w - z_w) = [sum (x - z_a) w] - z_w sum_k (x - z_a): the bracket is
+// what the symmetric case forms; the activation sum is shared by all columns of a row and comes from the A fragments
+// while they pass through the registers (rowsum: this wave's part, sum over its K sub-steps of code - 128 of row
+// frag_row of tile i; the wave columns split the sub-steps).  The parts meet in LDS behind the add tables, and
+// - z_w[n] * rowsum[m] joins every accumulator.  k_counted: k (padding included) that the sums run over.
+// (A pass of its own over A for these sums took 17 us on 16 x 224 x 224 x 3 and 2.6-6.6 us per 1x1 layer of 14-112
+// pixels; inside, the layers take what the symmetric ones take, within 1 us.)
 template <int BM, int BN, int WM, int WN, bool WEIGHTS_X16, bool ZW, int TM, int TN>
 __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (&acc)[TM][TN], int32_t (&colsum)[TN],
-                                                    const ChannelParams<TN> &cp, uint8_t *so, int64_t m0, int n0)
+                                                    const ChannelParams<TN> &cp, uint8_t *so, int64_t m0, int n0,
+                                                    const int32_t (&rowsum)[TM], int k_counted)
 {
     constexpr int NT = WM * WN * 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -247,6 +251,7 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
         if (WEIGHTS_X16) cs >>= 4;
         const int32_t b = cp.bias[j], mu = cp.mult[j], sf = cp.shift[j];
         corr[j] = b + (128 - g.z_a) * cs;
+        if constexpr (ZW) corr[j] = (int32_t)((uint32_t)corr[j] - (uint32_t)cp.zw[j] * (uint32_t)(k_counted * (128 - g.z_a))); // rowsum counts code - 128
         rp[j] = make_rescale(mu, sf);
         // |acc + corr| < 2^30 for the 64-bit fast form, < 2^29 for the fused 32-bit form
         fast_ok = fast_ok && sf >= 0 && b > -(1 << 28) && b < (1 << 28);
@@ -274,7 +279,11 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
     };
     int32_t *const rs_lds = reinterpret_cast<int32_t *>(so + ROWSUM_OFFSET);
     if constexpr (ZW) { // the caller has synchronised: the operand ring is free
-        for (int r = tid; r < BM; r += NT) rs_lds[r] = m0 + r < g.M ? g.rowsum[m0 + r] : 0;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int32_t whole = rowsum[i] + __shfl_xor(rowsum[i], 32);
+            if (frag_half == 0) rs_lds[wave_n * BM + wave_m * WTM + i * 32 + frag_row] = whole;
+        }
         __syncthreads();
     }
     auto run = [&](auto pack4) {
@@ -286,8 +295,11 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
                 for (int q = 0; q < 4; ++q) {
                     int32_t a[4];
                     i32x4 rs4 = {0, 0, 0, 0};
-                    if constexpr (ZW) // rows 8q + 4*half + {0,1,2,3} of this 32-row tile
-                        rs4 = *reinterpret_cast<const i32x4 *>(rs_lds + wave_m * WTM + i * 32 + 8 * q + 4 * frag_half);
+                    if constexpr (ZW) { // rows 8q + 4*half + {0,1,2,3} of this 32-row tile
+#pragma unroll
+                        for (int c = 0; c < WN; ++c)
+                            rs4 += *reinterpret_cast<const i32x4 *>(rs_lds + c * BM + wave_m * WTM + i * 32 + 8 * q + 4 * frag_half);
+                    }
 #pragma clang loop unroll(full)
                     for (int e = 0; e < 4; ++e) {
                         a[e] = acc[i][j][4 * q + e];
@@ -381,11 +393,19 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
     else add_tile(std::false_type{});
 }
 
-template <int BM, int BN, int WM, int WN, bool WEIGHTS_X16, bool ZW = false, int TM, int TN>
+template <int BM, int BN, int WM, int WN, bool WEIGHTS_X16, int TM, int TN>
 __device__ __forceinline__ void igemm_epilogue(const IgemmArgs &g, i32x16 (&acc)[TM][TN], int32_t (&colsum)[TN],
                                                const ChannelParams<TN> &cp, uint8_t *so, int64_t m0, int n0)
 {
-    igemm_epilogue_impl<BM, BN, WM, WN, WEIGHTS_X16, ZW, TM, TN>(g, acc, colsum, cp, so, m0, n0);
+    const int32_t no_rowsum[TM] = {};
+    igemm_epilogue_impl<BM, BN, WM, WN, WEIGHTS_X16, false, TM, TN>(g, acc, colsum, cp, so, m0, n0, no_rowsum, 0);
+}
+
+// adds code - 128 of the 16 k of an A fragment to its row's sum
+__device__ __forceinline__ void add_rowsum(int32_t &sum, const i32x4 &xs)
+{
+#pragma unroll
+    for (int d = 0; d < 4; ++d) sum = __builtin_amdgcn_sdot4(xs[d], 0x01010101, sum, false);
 }
 
 template <int BM, int BN, int WM, int WN, int A_MODE, int B_MODE, int VEC, bool ZW = false>
@@ -400,7 +420,7 @@ __global__ void __launch_bounds__(WM *WN * 64) igemm_kernel(const IgemmArgs g)
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is made of 32x32 MFMA tiles");
     constexpr int OUT_PITCH = BN + 16;
     constexpr int STAGE_BYTES = (BM + BN) * BK;
-    constexpr int OUT_BYTES = BM * OUT_PITCH + 4 * WM * WN * TN * 64 + 2048 + 4 * BM; // tile, column-sum partials, add tables, row sums
+    constexpr int OUT_BYTES = BM * OUT_PITCH + 4 * WM * WN * TN * 64 + 2048 + (ZW ? 4 * BM * WN : 0); // tile, column-sum partials, add tables, row sums
     constexpr int SMEM_BYTES = (2 * STAGE_BYTES > OUT_BYTES) ? 2 * STAGE_BYTES : OUT_BYTES;
     __shared__ __attribute__((aligned(16))) uint8_t smem[SMEM_BYTES];
 
@@ -472,6 +492,10 @@ __global__ void __launch_bounds__(WM *WN * 64) igemm_kernel(const IgemmArgs g)
 #pragma unroll
     for (int j = 0; j < TN; ++j) colsum[j] = 0;
 
+    int32_t rowsum[TM]; // ZW
+#pragma unroll
+    for (int i = 0; i < TM; ++i) rowsum[i] = 0;
+
     const int ktiles = (g.K + BK - 1) / BK;
     fetch(0);
     commit(0);
@@ -487,9 +511,12 @@ __global__ void __launch_bounds__(WM *WN * 64) igemm_kernel(const IgemmArgs g)
         for (int ks = 0; ks < 2; ++ks) {
             i32x4 fa[TM], fb[TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i) {
                 fa[i] = *reinterpret_cast<const i32x4 *>(
                     sa + lds_chunk_offset(wave_m * WTM + i * 32 + frag_row, ks * 2 + frag_half));
+                if constexpr (ZW)
+                    if (ks % WN == wave_n) add_rowsum(rowsum[i], fa[i]);
+            }
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 fb[j] = *reinterpret_cast<const i32x4 *>(
@@ -508,7 +535,7 @@ __global__ void __launch_bounds__(WM *WN * 64) igemm_kernel(const IgemmArgs g)
     }
 
     // the last __syncthreads above guarantees nobody still reads the operand tiles
-    igemm_epilogue<BM, BN, WM, WN, B_MODE == B_INT4, ZW>(g, acc, colsum, cparams, smem, m0, n0);
+    igemm_epilogue_impl<BM, BN, WM, WN, B_MODE == B_INT4, ZW>(g, acc, colsum, cparams, smem, m0, n0, rowsum, ktiles * BK);
 }
 
 } // namespace qnn

@@ -123,7 +123,7 @@ static Plan choose_plan(int64_t M, int64_t N, int64_t K, bool dma_ok, bool int4,
 }
 
 // Scratch memory comes from the caller (`workspace` of the entry points): the int32 activation row
-// sums of the asymmetric-weight entry points (M values), or zero-padded copies of operands that are no whole
+// sums of the asymmetric-weight entry points (M values; asked for, no longer used), or zero-padded copies of operands that are no whole
 // 16-byte chunks, and behind them the partial sums of split-K (splits x M x N values).
 constexpr uint64_t kMaxSplitBytes = (uint64_t)1 << 40;
 static size_t rowsum_bytes(int64_t M) { return (size_t)((M * 4 + 255) / 256 * 256); }
@@ -153,16 +153,14 @@ static size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int weight_b
     return copies ? copies + split_bytes_for(M, N, padded, weight_bits) : 0;
 }
 
-// Per-column weight zero-points (eq. 5-6 with z_w != 0): the activation row sums go to the caller's
-// scratch memory first (one pass over A), then one tile configuration whose epilogue subtracts
-// z_w[n] * rowsum[m]: a pipelined tile when the operands are aligned, else the staged 64x64 tile.
-static qnn_status run_igemm_zw(IgemmArgs &g, int a_mode, int b_mode, int vec, int kh, void *workspace, size_t workspace_bytes,
-                               hipStream_t s)
+// Per-column weight zero-points (eq. 5-6 with z_w != 0).  The kernels form the activation row sums themselves; the
+// workspace that the entry points ask for is checked but not used.
+static qnn_status run_igemm_zw(IgemmArgs &g, int a_mode, int b_mode, int vec, void *workspace, size_t workspace_bytes, hipStream_t s)
 {
     if (!workspace || workspace_bytes < rowsum_bytes(g.M) || !aligned_to(workspace, 16)) return QNN_EINVAL;
-    int32_t *rowsum = static_cast<int32_t *>(workspace);
-    if (qnn_status st = launch_rowsum(g, a_mode, kh, rowsum, s); st != QNN_OK) return st;
-    g.rowsum = rowsum;
+    qnn_status st;
+    if (try_small(g, a_mode, b_mode, s, &st)) return st;
+    if (a_mode == A_MATRIX && shortk_eligible(g, b_mode, false)) return launch_shortk(g, b_mode, false, s);
     const bool i4 = b_mode == B_INT4;
     const bool aligned_for_dma = vec == 16 && (g.K % 64) == 0 && g.lda < (1 << 23) && g.ldb < (1 << 23) &&
                                  (!i4 || (aligned_to(g.B, 16) && (g.ldb % 32) == 0));
@@ -195,7 +193,7 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
     g.small_acc = g.K <= 8192 ? 2 : (g.K <= 16384 ? 1 : 0); // |acc| <= K * 2^14
     g.c_vec16 = aligned_to(g.C, 16) && (g.ldc % 16 == 0);
     g.r_vec16 = g.R != nullptr && aligned_to(g.R, 16) && (g.ldr % 16 == 0);
-    if (g.zw) return run_igemm_zw(g, a_mode, b_mode, vec, kh, workspace, workspace_bytes, s);
+    if (g.zw) return run_igemm_zw(g, a_mode, b_mode, vec, workspace, workspace_bytes, s);
     // kernels that do not apply a residual add themselves run without it; the add follows as a second pass
     auto add_pass = [&](qnn_status st) {
         if (st != QNN_OK || !g.R) return st;
@@ -427,7 +425,7 @@ static qnn_status qconv2d_impl(const uint8_t *x, int N, int H, int W, int Cin, i
     g.zw = z_w;
     if (z_w && K > 32768) return QNN_EINVAL;
     const int b_mode = weight_bits == 4 ? B_INT4 : B_INT8;
-    if (!z_w) {
+    if (!z_w || (workspace && workspace_bytes >= rowsum_bytes(g.M) && aligned_to(workspace, 16))) {
         qnn_status st;
         IgemmArgs plain = g; // the stem kernels do not apply a residual add
         plain.R = nullptr;

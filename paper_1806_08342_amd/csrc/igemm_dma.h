@@ -318,15 +318,22 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
 #pragma unroll
                 for (int d = 0; d < 4; ++d) colsum[j] = __builtin_amdgcn_sdot4(fb[j][d], 0x01010101, colsum[j], false);
         };
+        int32_t rowsum[TM]; // ZW: wave column wave_n covers the K sub-steps ks with ks % WN == wave_n
+#pragma unroll
+        for (int i = 0; i < TM; ++i) rowsum[i] = 0;
         constexpr int PIECES = TM + TN, MMAS = TM * TN;
         // MFMAs of one K sub-step with the LDS reads of the next fragment set (and optionally the
         // DMA loads of a later stage) spread evenly between them, so that neither the LDS nor
         // the texture-address queue sees a burst that would stall MFMA issue
         auto mma_interleaved = [&](i32x4 (&fa)[TM], i32x4 (&fb)[TN], const uint8_t *next_stage, int next_ks,
-                                   i32x4 (&na)[TM], i32x4 (&nb)[TN], bool do_read, int dma_kt) {
+                                   i32x4 (&na)[TM], i32x4 (&nb)[TN], bool do_read, int dma_kt, bool sum_rows) {
             i32x4 xs[TM];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) xs[i] = fa[i] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
+            for (int i = 0; i < TM; ++i) {
+                xs[i] = fa[i] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
+                if constexpr (ZW)
+                    if (sum_rows) add_rowsum(rowsum[i], xs[i]);
+            }
             int piece = 0, load = 0;
 #pragma unroll
             for (int i = 0; i < TM; ++i)
@@ -369,7 +376,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
             const uint8_t *stage = smem + (kt % NSTAGE) * STAGE_BYTES;
             // sub-step 0: MFMAs on (fa0, fb0) while (fa1, fb1) are read from the same stage
             if (need_colsum && (0 % WM) == wave_m) add_colsum(fb0);
-            mma_interleaved(fa0, fb0, stage, 1, fa1, fb1, true, -1);
+            mma_interleaved(fa0, fb0, stage, 1, fa1, fb1, true, -1, (0 % WN) == wave_n);
 #pragma unroll
             for (int q = 0; q < PIECES; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, MMAS / PIECES, 0); // MFMA
@@ -383,7 +390,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
             // sub-step 1: MFMAs on (fa1, fb1) while the first fragments of stage kt+1 are read and the
             // loads of stage kt+NSTAGE-1 are issued (past the last stage: stale data, never used)
             if (need_colsum && (1 % WM) == wave_m) add_colsum(fb1);
-            mma_interleaved(fa1, fb1, smem + ((kt + 1) % NSTAGE) * STAGE_BYTES, 0, fa0, fb0, true, kt + NSTAGE - 1);
+            mma_interleaved(fa1, fb1, smem + ((kt + 1) % NSTAGE) * STAGE_BYTES, 0, fa0, fb0, true, kt + NSTAGE - 1, (1 % WN) == wave_n);
             if constexpr (LOADS == PIECES) {
 #pragma unroll
                 for (int q = 0; q < PIECES; ++q) {
@@ -428,7 +435,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
                     }
             }
         } else {
-            igemm_epilogue<BM, BN, WM, WN, B4, ZW>(g, acc, colsum, cparams, smem, m0, n0);
+            igemm_epilogue_impl<BM, BN, WM, WN, B4, ZW>(g, acc, colsum, cparams, smem, m0, n0, rowsum, g.K);
         }
         // every wave has left the output tile before the next tile's loads overwrite it
         block_barrier();

@@ -33,7 +33,7 @@ template <int BM, int BN, int WM, int WN, int A_MODE, int NSTAGE, bool SPLIT = f
 hipError_t launch_dma(const IgemmArgs &g, hipStream_t s, SplitK sk = SplitK{1, 0, nullptr}, int per_cu = 0, int prio = 0)
 {
     constexpr int kStages = NSTAGE * (BM + BN) * 64;
-    constexpr int kOut = BM * (BN + 16) + 4 * WM * WN * (BN / WN / 32) * 64 + 2048 + 4 * BM; // + add tables + row sums
+    constexpr int kOut = BM * (BN + 16) + 4 * WM * WN * (BN / WN / 32) * 64 + 2048 + (ZW ? 4 * BM * WN : 0); // + add tables + row sums
     constexpr int kLds = kStages > kOut ? kStages : kOut; // operand ring, reused for the output tile + column sums + add tables
     auto kernel = igemm_dma_kernel<BM, BN, WM, WN, A_MODE, NSTAGE, SPLIT, ZW, B4, MINW, KTAIL>;
     static LdsOptIn opt_in; // per instantiation

@@ -50,9 +50,6 @@ bool try_bres(IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *s
 bool stem_shape(int64_t W, int Cin, int Cout, int kh, int kw, int stride_w, int weight_bits);
 bool try_stem(IgemmArgs &g, int batch, int kh, int stride_h, int stride_w, int weight_bits, hipStream_t s, qnn_status *status);
 
-// Row sums of the activations for per-channel weight zero-points: out[m], M int32 (igemm_rowsum.hip)
-qnn_status launch_rowsum(const IgemmArgs &g, int a_mode, int kh, int32_t *out, hipStream_t s);
-
 struct SplitK;
 // Pipelined tiles bm x bn for K % 64 != 0 (igemm_tail.hip)
 hipError_t launch_tail_tile(const IgemmArgs &g, int bm, int bn, bool mat, bool i4, const SplitK &sk, hipStream_t s);
@@ -65,7 +62,7 @@ qnn_status launch_repack(IgemmArgs &g, int a_mode, int weight_bits, int kh, void
 
 // Register-staged tiles of igemm.h (any alignment, any weight layout): 64x64 or 128x128.
 void launch_plain_tile(bool big, const IgemmArgs &g, int a_mode, int b_mode, int vec, hipStream_t s);
-// the 64x64 tile with per-column weight zero-points (g.zw, g.rowsum set)
+// the 64x64 tile with per-column weight zero-points (g.zw set)
 void launch_plain_tile_zw(const IgemmArgs &g, int a_mode, int b_mode, int vec, hipStream_t s);
 
 } // namespace qnn

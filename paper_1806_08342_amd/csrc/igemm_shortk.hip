@@ -41,6 +41,11 @@ template <int KS, bool INT4, int VEC> static void launch_shortk_one(const ShortK
         }
     }
     const unsigned blocks = (unsigned)((waves + 3) / 4);
+    if (a.g.zw) {
+        if (b16) hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 16, 0, false, true>), dim3(blocks), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 4, 0, false, true>), dim3(blocks), dim3(256), 0, s, a);
+        return;
+    }
     if (b16) hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 16>), dim3(blocks), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 4>), dim3(blocks), dim3(256), 0, s, a);
 }
@@ -74,12 +79,12 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
     a.strided = strided ? 1 : 0;
     a.col_groups = (g.N + 32 * nb - 1) / (32 * nb);
     const int64_t row_blocks = (g.M + 31) / 32;
-    // as many waves as stay resident together (3 per SIMD for K <= 32, else 2, on 256 CUs), spread
+    // as many waves as stay resident together (3 per SIMD for K <= 32 without weight zero-points, else 2, on 256 CUs), spread
     // over the column groups, then trimmed so that every wave walks the same number of row blocks
     const int64_t row_pitch0 = strided ? g.Cin : g.lda;
     const bool add_fused = g.R != nullptr && aligned_to(g.A, 16) && (row_pitch0 % 16) == 0 && (g.K % 16) == 0 && g.c_vec16 &&
                            g.r_vec16 && (g.N % 16) == 0; // the variant with the add built in: 8-wave workgroups, one per CU
-    const int64_t resident = 256 * 4 * ((ks <= 1 && !add_fused) ? 3 : 2);
+    const int64_t resident = 256 * 4 * ((ks <= 1 && !add_fused && !g.zw) ? 3 : 2);
     int64_t walkers = resident / a.col_groups;
     walkers = walkers < 1 ? 1 : (walkers > row_blocks ? row_blocks : walkers);
     const int64_t per_walker = (row_blocks + walkers - 1) / walkers;
@@ -96,7 +101,7 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
     // Not with the add built in: its 8-wave workgroups (one per CU, sharing the table of code pairs) lose more at
     // the barrier of every row block than the shared rows save (measured 65 against 58 us on 50176 x 1024 x 256).
     const int wg_waves = 4;
-    const bool alds = tuning().shortk_alds != 0 && !strided && v16 && !a.g.R && (g.K == 128 || g.K == 256) && a.col_groups >= wg_waves;
+    const bool alds = tuning().shortk_alds != 0 && !strided && v16 && !a.g.R && !g.zw && (g.K == 128 || g.K == 256) && a.col_groups >= wg_waves;
     if (alds) {
         const int64_t groups = (a.col_groups + wg_waves - 1) / wg_waves;
         const int64_t resident_wgs = 256 * 2;

@@ -37,7 +37,10 @@ bool try_stem(IgemmArgs &g, int batch, int kh, int stride_h, int stride_w, int w
             const dim3 grid((unsigned)wblocks);
             const int nb = Cout <= 32 ? 1 : 2;
 #define QNN_STEMWAVE(KH_, NB_, SH_) \
-    if (kh == KH_ && nb == NB_ && stride_h == SH_) hipLaunchKernelGGL((stemwave_kernel<KH_, NB_, SH_>), grid, dim3(256), 0, s, sw)
+    if (kh == KH_ && nb == NB_ && stride_h == SH_) { \
+        if (g.zw) hipLaunchKernelGGL((stemwave_kernel<KH_, NB_, SH_, true>), grid, dim3(256), 0, s, sw); \
+        else hipLaunchKernelGGL((stemwave_kernel<KH_, NB_, SH_, false>), grid, dim3(256), 0, s, sw); \
+    }
             QNN_STEMWAVE(3, 1, 1); QNN_STEMWAVE(3, 1, 2); QNN_STEMWAVE(3, 2, 1); QNN_STEMWAVE(3, 2, 2);
             QNN_STEMWAVE(7, 1, 1); QNN_STEMWAVE(7, 1, 2); QNN_STEMWAVE(7, 2, 1); QNN_STEMWAVE(7, 2, 2);
 #undef QNN_STEMWAVE
@@ -45,7 +48,7 @@ bool try_stem(IgemmArgs &g, int batch, int kh, int stride_h, int stride_w, int w
             return true;
         }
     }
-    if (((int64_t)g.W * Cin) % 4 != 0 || !aligned_to(g.A, 4)) return false; // this one loads aligned dwords only
+    if (g.zw || ((int64_t)g.W * Cin) % 4 != 0 || !aligned_to(g.A, 4)) return false; // this one loads aligned dwords only
     StemArgs st = {};
     st.g = g, st.kh = kh, st.run = kw * Cin;
     st.strips = (Wo + 127) / 128;

@@ -57,7 +57,7 @@ template <int VEC> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t 
 // (ties up) and the rounding shift (ties away from zero) collapse into one floor division, and
 // clamping before the final shift lets that shift write its byte straight into the packed dword.
 struct ShortKColumn {
-    int32_t mult, corr, c, n1, lo, hi, shift;
+    int32_t mult, corr, c, n1, lo, hi, shift, zw;
 };
 
 // ADD: the rescaling add with a residual tensor (g.R) is applied to the output tile on its way
@@ -72,8 +72,11 @@ struct ShortKColumn {
 // of its own): counters showed the address unit busy for 58 % and the vector cache for 70-80 % of that kernel's
 // time, on a par with the vector ALU.  LDS positions are XOR-swizzled on the global-address side, so that the
 // 16 lanes that share a cycle of a 16-byte LDS read hit 16 different bank groups.
-template <int NB, int KS, bool INT4, int VEC, int BVEC, int ADD = 0, bool ALDS = false> // ADD: 0 none, 1 two 256-entry tables, 2 pair table
-__global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 ? 3 : 2)) shortk_kernel(const ShortKArgs s)
+// ZW: per-column weight zero-points (see igemm_epilogue_impl): the activation sum of a row is one more accumulator,
+// fed by one matrix instruction per K sub-step whose B fragment is all ones, which leaves the sums in the registers
+// and lanes where the rescale of the same rows needs them.
+template <int NB, int KS, bool INT4, int VEC, int BVEC, int ADD = 0, bool ALDS = false, bool ZW = false> // ADD: 0 none, 1 two 256-entry tables, 2 pair table
+__global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 && !ZW ? 3 : 2)) shortk_kernel(const ShortKArgs s)
 {
     constexpr int PITCH = 32 * NB + 32; // bytes per staged output row: the 8 rows a store instruction touches fall in distinct banks
     constexpr int WAVES = ADD == 2 ? 8 : 4; // the pair table is shared by 8 waves (one workgroup per CU)
@@ -167,6 +170,12 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         const int nn = (sf >= 1 && sf <= 20) ? sf : 1;
         col[j].mult = mu;
         col[j].corr = b + (128 - g.z_a) * colsum;
+        col[j].zw = 0;
+        if constexpr (ZW) {
+            col[j].zw = g.zw[n];
+            // the sums count code - 128, and -128 for every k from K to KS * 32 (loaded as zeros)
+            col[j].corr -= col[j].zw * (g.K * (128 - g.z_a) + 128 * (KS * 32 - g.K));
+        }
         col[j].n1 = nn + 1;
         col[j].c = 2 * ((1 << (nn - 1)) + (g.z_out << nn)) + 1;
         col[j].lo = (g.lo_rel + g.z_out) << (nn + 1);
@@ -174,6 +183,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         col[j].shift = sf; // the general path
     }
     const bool fused = __all(fused_ok);
+    const i32x4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101}; // ZW
 
     // ---- rows (the dispatcher guarantees M < 2^31)
     const int M = (int)g.M;
@@ -355,9 +365,11 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[j][r] = 0;
+        i32x16 sums = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}; // ZW: sum_k (code - 128) of the rows
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const i32x4 xs = fa[ks] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
+            if constexpr (ZW) sums = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, ones, sums, 0, 0, 0);
 #pragma unroll
             for (int j = 0; j < NB; ++j)
                 acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, fb[ks][j], acc[j], 0, 0, 0); // columns past N: clamped loads, never stored
@@ -404,6 +416,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
                     for (int e = 0; e < 4; ++e) {
                         int32_t a = acc[j][4 * q + e];
                         if (INT4) a >>= 4;
+                        if constexpr (ZW) a -= __mul24(col[j].zw, sums[4 * q + e]);
                         const int32_t t = __mulhi((int32_t)((uint32_t)(a + col[j].corr) << 2), col[j].mult);
                         x = shift_into_byte(x, med3_i32(fused_w_from_t<TIES>(t, col[j].c), col[j].lo, col[j].hi), col[j].n1, e);
                     }
@@ -422,6 +435,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
                     for (int e = 0; e < 4; ++e) {
                         int32_t a = acc[j][4 * q + e];
                         if (INT4) a >>= 4;
+                        if constexpr (ZW) a -= __mul24(col[j].zw, sums[4 * q + e]);
                         const int32_t y = clamp_i32(lo_rel, hi_rel, rescale_general(a + col[j].corr, rp)) + z_out;
                         x |= (uint32_t)y << (8 * e);
                     }

@@ -88,7 +88,8 @@ __device__ __forceinline__ i32x4 widen_int4(uint32_t r0, uint32_t r1)
 
 // AI: load instructions per 128 bytes of the activation rows, 8 rows each (a workgroup owns 8 * AI rows).
 // A_CONV: the 16-byte chunks of a row are gathered from the image; Cin % 16 == 0, so a chunk lies inside one tap.
-template <int AI, bool INT4, int NW, int A_MODE>
+// ZW: per-column weight zero-points (see igemm_epilogue_impl).
+template <int AI, bool INT4, int NW, int A_MODE, bool ZW>
 __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
 {
     const IgemmArgs &g = args.g;
@@ -99,6 +100,7 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
     static_assert(NW * 4096 >= PW * MT * 1024, "the partial sums take the place of the row exchange");
     __shared__ __attribute__((aligned(16))) uint8_t smem[NW * 4096];
     __shared__ int32_t csum[NW][BN];
+    __shared__ int32_t rsum[ZW ? NW : 1][MT][16];
     i32x4(*const part)[MT][64] = reinterpret_cast<i32x4(*)[MT][64]>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform
@@ -146,6 +148,8 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
             for (int i = 0; i < AI; ++i) {
                 const bool inside = (unsigned)(hi0[i] + a) < (unsigned)g.H && (unsigned)(wi0[i] + b) < (unsigned)g.W;
                 v[i] = load16_any(inside ? arow[i] + delta : fill);
+                if constexpr (ZW && decltype(tail)::value) // beyond K: zero like a matrix row's tail (the row sum is corrected for it)
+                    if (k >= g.K) v[i] = u32x4{0, 0, 0, 0};
             }
         }
     };
@@ -182,7 +186,9 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
     i32x4 acc[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[t] = i32x4{0, 0, 0, 0};
-    int32_t colsum = 0;
+    int32_t colsum = 0, rowsum[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) rowsum[t] = 0;
     const bool need_colsum = g.z_a != 128;
     // one step: wv the weight rows, av the activation rows, by halves of 128 bytes
     auto multiply = [&](const u32x4 (&wv)[2], const u32x4 (&av)[HALVES][AI]) __attribute__((always_inline)) {
@@ -217,6 +223,7 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
                 for (int h = 0; h < 2; ++h) {
                     const i32x4 xs = *reinterpret_cast<const i32x4 *>(xa + get_a[h]); // (AI odd: rows 8..15 of the tile are nobody's)
                     acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[h], xs, acc[t], 0, 0, 0);
+                    if constexpr (ZW) add_rowsum(rowsum[t], xs);
                 }
             }
         }
@@ -257,6 +264,15 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
     colsum += __shfl_xor(colsum, 16);
     colsum += __shfl_xor(colsum, 32);
     if (lane < BN) csum[wave][lane] = colsum;
+    if constexpr (ZW) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            int32_t r = rowsum[t];
+            r += __shfl_xor(r, 16);
+            r += __shfl_xor(r, 32);
+            if (lane < 16) rsum[wave][t][lane] = r;
+        }
+    }
     __syncthreads(); // every wave is done with its row exchange
     if constexpr (NW > PW) {
         if (wave >= PW) {
@@ -282,6 +298,12 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
     i32x4 sum = {0, 0, 0, 0};
 #pragma unroll
     for (int w = 0; w < PW; ++w) sum += part[w][wave][lane];
+    int32_t rs = 0; // sum_k (code - z_a) of this row: the parts count code - 128, and -128 for every k of the last step beyond K
+    if constexpr (ZW) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) rs += rsum[w][wave][frow];
+        rs += 128 * ((g.K + STEP - 1) / STEP * STEP - g.K) + g.K * (128 - g.z_a);
+    }
     uint32_t packed = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -295,6 +317,7 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
             cs >>= 4;
         }
         a += (g.bias ? p_bias[e] : 0) + (128 - g.z_a) * cs;
+        if constexpr (ZW) a = (int32_t)((uint32_t)a - (uint32_t)g.zw[nb + e < g.N ? nb + e : g.N - 1] * (uint32_t)rs);
         const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general(a, make_rescale(p_mult[e], p_shift[e]))) + g.z_out;
         packed |= (uint32_t)y << (8 * e);
     }

@@ -30,7 +30,7 @@ struct StemWaveArgs {
     int64_t waves;     // N * strips * segments
 };
 
-template <int KH, int NB, int SH> // kernel rows, blocks of 32 output channels, row stride (compile-time: the row fetches are unrolled)
+template <int KH, int NB, int SH, bool ZW> // kernel rows, blocks of 32 output channels, row stride (compile-time: the row fetches are unrolled)
 __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
 {
     constexpr int NEW = SH < KH ? SH : KH; // image rows that enter the window per output row
@@ -115,6 +115,7 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
         const int nn = (sf >= 1 && sf <= 20) ? sf : 1;
         c_mult[j] = mu;
         c_corr[j] = b + (128 - g.z_a) * colsum;
+        if constexpr (ZW) c_corr[j] -= g.zw[co] * KH * s.run * (128 - g.z_a);
         c_n1[j] = nn + 1;
         c_c[j] = 2 * ((1 << (nn - 1)) + (g.z_out << nn)) + 1;
         c_lo[j] = (g.lo_rel + g.z_out) << (nn + 1);
@@ -122,6 +123,13 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
         c_shift[j] = sf;
     }
     const bool fused = __all(fused_ok);
+    // ZW (per-column weight zero-points): the activation sums as one more accumulator, see shortk.h
+    i32x4 ones;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int valid = s.run - fhalf * 16 - d * 4; // bytes of this dword that belong to the kernel row
+        ones[d] = valid >= 4 ? 0x01010101 : (valid <= 0 ? 0 : (int32_t)(0x01010101u >> (8 * (4 - valid))));
+    }
 
     // ---- the strip's patch of an image row: 64 dwords starting at the byte column of the first tap, rounded
     // down to a multiple of 4; lane l owns dword l.  Rows may have any length and alignment (gfx950 loads a
@@ -235,6 +243,7 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
             for (int j = 0; j < NB; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[j][r] = 0;
+            i32x16 sums = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             const int hi0 = ho * SH - g.ph;
 #pragma unroll
             for (int a = 0; a < KH; ++a) {
@@ -246,6 +255,7 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     fa[e] = (int32_t)__builtin_amdgcn_alignbyte(d[e + 1], d[e], (uint32_t)win_shift);
+                if constexpr (ZW) sums = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, ones, sums, 0, 0, 0);
 #pragma unroll
                 for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb[a][j], acc[j], 0, 0, 0);
             }
@@ -260,12 +270,15 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 const RescaleParams rp = make_rescale(c_mult[j], c_shift[j]);
+                int32_t zw = 0;
+                if constexpr (ZW) zw = g.zw[j * 32 + frow < g.N ? j * 32 + frow : g.N - 1];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     uint32_t x = 0;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const int32_t a = acc[j][4 * q + e];
+                        int32_t a = acc[j][4 * q + e];
+                        if constexpr (ZW) a -= __mul24(zw, sums[4 * q + e]);
                         if constexpr (FUSED) {
                             const int32_t t = __mulhi((int32_t)((uint32_t)(a + c_corr[j]) << 2), c_mult[j]);
                             const int32_t wv = fused_w_from_t<TIES>(t, c_c[j]);
