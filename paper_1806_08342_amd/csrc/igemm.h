@@ -357,7 +357,10 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
             if (m >= g.M || n >= g.N) continue;
             uint8_t *dst = g.C + m * g.ldc + n;
             const uint8_t *src = so + row * OUT_PITCH + cc * 16;
-            if (n + 16 <= g.N) { // any alignment: gfx950 stores 16 bytes to any byte address
+            if (g.c_vec16 && n + 16 <= g.N) { // (of its own: as one store of unknown alignment the 256x256 tile took 49 us
+                                              // on 256 x 14x14x256, 3x3, instead of 45)
+                *reinterpret_cast<u32x4 *>(dst) = *reinterpret_cast<const u32x4 *>(src);
+            } else if (n + 16 <= g.N) { // any alignment: gfx950 stores 16 bytes to any byte address
                 const u32x4 v = *reinterpret_cast<const u32x4 *>(src);
                 __builtin_memcpy(dst, &v, 16);
             } else {

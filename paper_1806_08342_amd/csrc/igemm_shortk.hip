@@ -77,6 +77,7 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
     ShortKArgs a = {};
     a.g = g;
     a.strided = strided ? 1 : 0;
+    a.stream_out = g.M * (int64_t)g.N <= ((int64_t)32 << 20); // between 26 MB (gains) and 51 MB (the next layer loses more)
     a.col_groups = (g.N + 32 * nb - 1) / (32 * nb);
     const int64_t row_blocks = (g.M + 31) / 32;
     // as many waves as stay resident together (3 per SIMD for K <= 32 without weight zero-points, else 2, on 256 CUs), spread

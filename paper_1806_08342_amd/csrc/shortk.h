@@ -24,6 +24,7 @@ struct ShortKArgs {
     int col_groups;    // ceil(N / (32 * NB))
     int walkers;       // waves that share one column group (they interleave over the row blocks)
     int strided;       // rows of A are pixels (n, ho*sh, wo*sw) of an NHWC image (1x1 convolution, stride > 1)
+    int stream_out;    // non-temporal output stores
 };
 
 // 16 consecutive k of one row / column as 4 dwords, zero beyond K.  VEC = bytes per load.
@@ -295,8 +296,10 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         return y;
     };
 
-    // (Non-temporal stores: 4-9 % on 6-26 MB outputs -- what is left in the L2s is written back when the kernel ends --
-    // and within 2 % either way on 50-200 MB ones.  With the add built in plain stores are the faster ones, by 2-8 %.)
+    // (Non-temporal stores, s.stream_out: 4-9 % on 6-26 MB outputs -- what is left in the L2s is written back when the
+    // kernel ends.  Larger outputs and the add built in are faster with plain ones: ResNet-50 at batch 256, 103 MB,
+    // K = 256: 84 us and 93 with non-temporal ones, 70 and 76; 51 MB, K = 256: 57 and 54, but the 3x3 layer that reads
+    // them then takes 67 instead of 64.)
     // the output tile of row block rbx, from the wave's LDS area to global memory.  Called one
     // round late, right after the next block's MFMAs are issued and before the loads of the block
     // after it: the stores then never sit between a load and the wait for that load.
@@ -313,16 +316,21 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
                         add16(*reinterpret_cast<const u32x4 *>(stage + st_lds[i]), rres[i]);
                 __builtin_amdgcn_sched_barrier(0); // one chunk at a time: the table reads of all chunks at once would spill
             }
-        } else if (chunks_whole && rbx * 32 + 32 <= M) { // the common case: only the lane-invariant column test
+        } else if (chunks_whole && rbx * 32 + 32 <= M && s.stream_out) { // the common case: only the lane-invariant column test
 #pragma unroll
             for (int i = 0; i < NB; ++i)
                 if (st_col_ok[i])
                     __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(stage + st_lds[i]), reinterpret_cast<u32x4 *>(c_block + st_off[i]));
+        } else if (chunks_whole && rbx * 32 + 32 <= M) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                if (st_col_ok[i])
+                    *reinterpret_cast<u32x4 *>(c_block + st_off[i]) = *reinterpret_cast<const u32x4 *>(stage + st_lds[i]);
         } else if (chunks_whole) {
 #pragma unroll
             for (int i = 0; i < NB; ++i)
                 if (st_col_ok[i] && rbx * 32 + st_row[i] < M)
-                    __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(stage + st_lds[i]), reinterpret_cast<u32x4 *>(c_block + st_off[i]));
+                    *reinterpret_cast<u32x4 *>(c_block + st_off[i]) = *reinterpret_cast<const u32x4 *>(stage + st_lds[i]);
         } else {
 #pragma nounroll
             for (int i = 0; i < NB; ++i) {
