@@ -20,8 +20,8 @@
  *     shape can use (0 for most): the int32 partial sums of products whose K
  *     is divided over several workgroups because they have too few output
  *     tiles for the chip, zero-padded copies of operands whose rows are no whole
- *     16-byte pieces, and the activation row sums of the asymmetric-weight
- *     entry points.  With a smaller or NULL workspace the symmetric entry
+ *     16-byte pieces, and the 4 bytes per output row that the asymmetric-weight
+ *     entry points insist on.  With a smaller or NULL workspace the symmetric entry
  *     points take a route that needs none (same result, possibly slower); the
  *     asymmetric ones return QNN_EINVAL.  The workspace is written and read by
  *     the kernels of that one call only; its contents need no initialisation
@@ -316,8 +316,8 @@ qnn_status qnn_quantize_u16(const float *x, uint16_t *q, size_t n, float scale, 
                             int32_t qmax, void *stream);
 qnn_status qnn_dequantize_u16(const uint16_t *q, float *x, size_t n, float scale, int32_t zero_point, void *stream);
 
-/* Depthwise convolution with a zero-point per channel of the weights (as qnn_qconv2d_asym; one lane per
- * output evaluates sum (x - z_x)(w - z_w[c]) over the taps inside the image directly).  z_w: DEVICE int32[C]. */
+/* Depthwise convolution with a zero-point per channel of the weights (as qnn_qconv2d_asym):
+ * sum (x - z_x)(w - z_w[c]) over the taps inside the image.  z_w: DEVICE int32[C], each in [-128, 127]. */
 qnn_status qnn_qdwconv2d_asym(const uint8_t *x, int N, int H, int W, int C, int32_t z_x, const int8_t *w, int kh, int kw,
                               const int32_t *z_w, int stride_h, int stride_w, int pad_h, int pad_w, const int32_t *bias,
                               const int32_t *mult, const int32_t *shift, int32_t z_out, int32_t act_min, int32_t act_max,
