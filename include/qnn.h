@@ -317,7 +317,8 @@ qnn_status qnn_quantize_u16(const float *x, uint16_t *q, size_t n, float scale, 
 qnn_status qnn_dequantize_u16(const uint16_t *q, float *x, size_t n, float scale, int32_t zero_point, void *stream);
 
 /* Depthwise convolution with a zero-point per channel of the weights (as qnn_qconv2d_asym):
- * sum (x - z_x)(w - z_w[c]) over the taps inside the image.  z_w: DEVICE int32[C], each in [-128, 127]. */
+ * sum (x - z_x)(w - z_w[c]) over the taps inside the image, any z_w: DEVICE int32[C] (|sum + bias| < 2^31).
+ * Channels whose z_w is no signed byte run slower. */
 qnn_status qnn_qdwconv2d_asym(const uint8_t *x, int N, int H, int W, int C, int32_t z_x, const int8_t *w, int kh, int kw,
                               const int32_t *z_w, int stride_h, int stride_w, int pad_h, int pad_w, const int32_t *bias,
                               const int32_t *mult, const int32_t *shift, int32_t z_out, int32_t act_min, int32_t act_max,

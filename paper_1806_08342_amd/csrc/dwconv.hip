@@ -23,7 +23,7 @@ struct DwArgs {
     const int8_t *w;
     uint8_t *y;
     const int32_t *bias, *mult, *shift;
-    const int32_t *zw; // per-channel weight zero-points in [-128, 127], or nullptr
+    const int32_t *zw; // per-channel weight zero-points, or nullptr
     int N, H, W, C, Ho, Wo, kh, kw, sh, sw, ph, pw;
     int32_t z_x, z_out, lo_rel, hi_rel;
     int64_t total_work; // lanes of work
@@ -56,6 +56,40 @@ __device__ __forceinline__ void xcd_neighbours(bool on, uint32_t &bx, uint32_t &
 __device__ __forceinline__ int32_t sbyte(uint32_t v, int j) { return (int32_t)(int8_t)(v >> (8 * j)); }
 __device__ __forceinline__ int32_t ubyte(uint32_t v, int j) { return (int32_t)((v >> (8 * j)) & 0xffu); }
 
+// One output as the definition has it, for any kernel size, stride, channel and weight zero-point (sums modulo 2^32).
+__device__ __forceinline__ uint8_t dw_direct(const DwArgs &g, int n, int ho, int wo, int c)
+{
+    uint32_t acc = g.bias ? (uint32_t)g.bias[c] : 0u;
+    const uint32_t zw = g.zw ? (uint32_t)g.zw[c] : 0u;
+    for (int a = 0; a < g.kh; ++a) {
+        const int hi = ho * g.sh - g.ph + a;
+        if (hi < 0 || hi >= g.H) continue;
+        for (int b = 0; b < g.kw; ++b) {
+            const int wi = wo * g.sw - g.pw + b;
+            if (wi < 0 || wi >= g.W) continue;
+            const uint32_t xv = (uint32_t)((int32_t)g.x[(((int64_t)n * g.H + hi) * g.W + wi) * g.C + c] - g.z_x);
+            acc += xv * ((uint32_t)(int32_t)g.w[((int64_t)a * g.kw + b) * g.C + c] - zw); // eq. 4 taken literally
+        }
+    }
+    const RescaleParams rp = make_rescale(g.mult[c], g.shift[c]);
+    return (uint8_t)(clamp_i32(g.lo_rel, g.hi_rel, rescale_general((int32_t)acc, rp)) + g.z_out);
+}
+
+// The 3x3 kernels take weight zero-points of a signed byte (what int8 weights have).  The values live on the device,
+// so the kernels look themselves: outputs of channels with any other value are formed one by one, as defined.
+__device__ __forceinline__ bool dw_zero_point_is_byte(int32_t zw) { return zw >= -128 && zw <= 127; }
+
+// outputs ho0 .. ho1 - 1 x wo0 .. wo1 - 1 (step `step`) x c0 .. c1 - 1, cut at the output's edges
+__device__ __forceinline__ void dw_direct_block(const DwArgs &g, int n, int ho0, int ho1, int wo0, int wo1, int step, int c0, int c1)
+{
+#pragma nounroll
+    for (int ho = ho0; ho < ho1 && ho < g.Ho; ++ho)
+#pragma nounroll
+        for (int wo = wo0; wo < wo1 && wo < g.Wo; wo += step)
+#pragma nounroll
+            for (int c = c0; c < c1; ++c) g.y[(((int64_t)n * g.Ho + ho) * g.Wo + wo) * g.C + c] = dw_direct(g, n, ho, wo, c);
+}
+
 // 3x3 kernel, stride S (same in h and w).  One lane owns 4 consecutive channels and an
 // RH x RW patch of output pixels; the ((RH-1)S+3) x ((RW-1)S+3) input window is loaded once
 // (one dword = 4 channels per pixel), each byte is unpacked once and multiplied into every
@@ -81,8 +115,10 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const DwArgs g)
     int32_t wt[3][3][4];
     int32_t wsum[4] = {0, 0, 0, 0}, zw[4] = {0, 0, 0, 0};
     if (g.zw) {
+        bool byte = true;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) zw[j] = g.zw[c0 + j];
+        for (int j = 0; j < 4; ++j) zw[j] = g.zw[c0 + j], byte = byte && dw_zero_point_is_byte(zw[j]);
+        if (!byte) return dw_direct_block(g, n, ho0, ho0 + RH, wo0, wo0 + RW, 1, c0, c0 + 4);
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a)
@@ -184,7 +220,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const DwArgs g)
 // bytes, w' = w + (-z_w), of which the second is the same for all taps.  -z_w does not fit for z_w = -128; such a
 // channel accumulates -w' = ~w + (-127) instead and its sum changes sign in the rescale's add (|sum| <= 9 * 255 * 255
 // fits the 24-bit multiply-add that does both).  So weight zero-points cost one more dot product (or matrix
-// instruction) per tap vector and nothing else.
+// instruction) per tap vector and nothing else.  (Only for z_w of a signed byte, see dw_zero_point_is_byte.)
 struct DwZeroPoint {
     int32_t common; // the byte shared by all taps
     int32_t flip;   // all ones: taps enter complemented
@@ -237,10 +273,12 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
     uint32_t wc[4];      // ZW: [c, c, c, 0], the byte that the taps share
     int32_t sign[4];     // ZW
     uint32_t flip = 0u;  // ZW: byte j all ones where channel c0 + j enters complemented
+    bool zw_bytes = true; // looked at behind the loop: a branch here would wait for the zero-points (2 % of the launch)
     if constexpr (ZW) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int32_t zw = g.zw[c0 + j];
+            zw_bytes = zw_bytes && dw_zero_point_is_byte(zw);
             const DwZeroPoint z = dw_zero_point(zw);
             wc[j] = ((uint32_t)z.common & 0xffu) * 0x00010101u;
             sign[j] = z.sign;
@@ -360,6 +398,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
         hi_[j] = ((g.hi_rel + g.z_out + 1) << (nn + 1)) - 1;
     }
     if constexpr (ZW) {
+        if (!zw_bytes) return dw_direct_block(g, n, ho0, ho0 + RH, wo0, wo0 + RW, 1, c0, c0 + 4);
 #pragma unroll
         for (int r = 0; r < RH; ++r)
 #pragma unroll
@@ -505,8 +544,10 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     dw_i32x4 wq[3][3], wc = {0, 0, 0, 0};
     int32_t wsum = 0;
     DwZeroPoint zp = {0, 0, 1};
+    bool zw_bytes = true;
     if constexpr (ZW) {
         const int32_t zw = ch_ok ? g.zw[ch] : 0;
+        zw_bytes = dw_zero_point_is_byte(zw);
         zp = dw_zero_point(zw);
         wsum = -9 * zw;
         wc = diagonal(zp.common);
@@ -531,6 +572,11 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     const int32_t lo = (g.lo_rel + g.z_out) << (nn + 1);
     const int32_t hi_ = ((g.hi_rel + g.z_out + 1) << (nn + 1)) - 1;
     const bool fused = MODE != 0 && __all(fused_ok); // wave-uniform
+    if (ZW && !__all(zw_bytes)) { // the whole wave: its lanes share the matrix instructions
+        dw_direct_block(g, n, hb, hb + rows, w0 + half, w0 + TP, 2, ch, ch_ok ? ch + 1 : ch);
+        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8)); // vmcnt(0): no copy may land in LDS after the wave is gone
+        return;
+    }
 
     // read-back of window column b: pixel li * S + b of the LDS row, 16 channel bytes of this lane's half
     uint32_t l_off[3];
@@ -784,20 +830,7 @@ __global__ void __launch_bounds__(256) dwconv_generic_kernel(const DwArgs g)
     t /= g.Wo;
     const int ho = (int)(t % g.Ho);
     const int n = (int)(t / g.Ho);
-    int32_t acc = g.bias ? g.bias[c] : 0;
-    const int32_t zw = g.zw ? g.zw[c] : 0;
-    for (int a = 0; a < g.kh; ++a) {
-        const int hi = ho * g.sh - g.ph + a;
-        if (hi < 0 || hi >= g.H) continue;
-        for (int b = 0; b < g.kw; ++b) {
-            const int wi = wo * g.sw - g.pw + b;
-            if (wi < 0 || wi >= g.W) continue;
-            const int32_t xv = (int32_t)g.x[(((int64_t)n * g.H + hi) * g.W + wi) * g.C + c] - g.z_x;
-            acc += xv * ((int32_t)g.w[((int64_t)a * g.kw + b) * g.C + c] - zw); // eq. 4 taken literally
-        }
-    }
-    const RescaleParams rp = make_rescale(g.mult[c], g.shift[c]);
-    g.y[gid] = (uint8_t)(clamp_i32(g.lo_rel, g.hi_rel, rescale_general(acc, rp)) + g.z_out);
+    g.y[gid] = dw_direct(g, n, ho, wo, c);
 }
 
 } // namespace qnn

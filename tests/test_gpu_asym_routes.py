@@ -49,6 +49,28 @@ def test_depthwise_routes(N, H, W, C, stride, pad):
     assert len(np.unique(want)) > 16
 
 
+@pytest.mark.parametrize("N,H,W,C,stride,pad", [
+    (2, 9, 7, 12, 1, 1), (1, 17, 22, 68, 2, 0),            # patch kernel
+    (2, 113, 115, 112, 1, 0), (4, 113, 112, 176, 2, 1),    # matrix-unit kernel, C no multiple of 32
+    (65537, 3, 3, 4, 1, 1),                                # multiply-add form
+])
+def test_depthwise_zero_points_beyond_a_byte(N, H, W, C, stride, pad):
+    rng = np.random.default_rng(N + H * W + C)
+    x = rng.integers(0, 256, (N, H, W, C)).astype(np.uint8)
+    w = rng.integers(-128, 128, (3, 3, C)).astype(np.int8)
+    mult, shift = _rescale(rng, C, 9, 128)
+    bias = rng.integers(-2000, 2000, C).astype(np.int32)
+    z_w = _zero_points(rng, C, 128)
+    z_w[C // 2] = 128               # one channel only: its neighbours stay on the byte form
+    z_w[-1] = -129
+    for z in (z_w, rng.integers(0, 256, C).astype(np.int32), rng.integers(-70000, 70000, C).astype(np.int32)):
+        want = oracle.qdwconv2d(x, 131, w, (stride, stride), (pad, pad), mult, shift, 120, 0, 255, bias=bias, z_w=z)
+        got = host(qnn.qdwconv2d_asym(dev(x), 131, dev(w), dev(z), (stride, stride), (pad, pad), dev(mult), dev(shift), 120, 0, 255,
+                                      bias=dev(bias)))
+        assert_same(got, want, f"z_w in [{z.min()}, {z.max()}]")
+    assert len(np.unique(want)) > 1
+
+
 @pytest.mark.parametrize("M,N,K,bits", [
     (1, 16, 16, 8), (64, 70, 129, 8), (33, 40, 258, 4), (700, 48, 384, 8),      # few rows, with tails in K
     (5000, 30, 8, 8), (5001, 33, 24, 4), (4100, 96, 40, 8), (3000, 200, 72, 4), (2999, 130, 120, 8), (7001, 260, 256, 8),
