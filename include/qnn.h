@@ -211,7 +211,8 @@ qnn_status qnn_qadd(const uint8_t *a, int32_t z_a, int32_t mult_a, int32_t shift
  *   y[m][c] = clamp(act_min, act_max, z_out + RESCALE(x[m][c] - z_in; mult, shift)),
  * mult, shift from qnn_quantize_multiplier(s_in / s_out).  rows x cols elements with row pitches
  * ldx, ldy >= cols, so y can be a channel slice of the concatenated NHWC tensor (ldy = its channel count).
- * x: DEVICE uint8 (read); y: DEVICE uint8 (written); the two must not overlap. */
+ * x: DEVICE uint8 (read); y: DEVICE uint8 (written).  y may be x with the same pitch (in place), any other
+ * overlap is not allowed. */
 qnn_status qnn_rescale_u8(const uint8_t *x, int64_t ldx, int32_t z_in, int32_t mult, int32_t shift, int32_t z_out,
                           int32_t act_min, int32_t act_max, uint8_t *y, int64_t ldy, int64_t rows, int64_t cols,
                           void *stream);

@@ -418,22 +418,25 @@ __global__ void __launch_bounds__(kThreads) qadd_kernel(const uint8_t *__restric
 // ------------------------------------------------------ rescale of uint8 codes (concat)
 
 // Rows of `cols` bytes cut into 16-byte chunks: vector v -> (row, first column).  The last chunk of a row starts at
-// cols - 16 (the overlap is written twice with the same values), so that rows of any length are whole chunks; rows
+// cols - 16 (its first `before` bytes are the previous chunk's too), so that rows of any length are whole chunks; rows
 // shorter than that are one chunk, byte by byte.
 struct RowChunks {
-    uint32_t per_row, magic, magic_shift; // v / per_row for v < 2^31, per_row >= 2
+    uint64_t per_row;
+    uint32_t magic, magic_shift; // v / per_row for v < 2^31, 2 <= per_row < 2^31; else magic = 0
     int64_t cols;
-    __device__ void locate(size_t v, int64_t &row, int64_t &col) const
+    bool in_place; // source and destination overlap: every byte is written by the chunk that it belongs to, and once
+    __device__ void locate(size_t v, int64_t &row, int64_t &col, int &before) const
     {
         if (per_row == 1) {
             row = (int64_t)v, col = 0;
-        } else if (v < ((size_t)1 << 31)) {
+        } else if (magic && v < ((size_t)1 << 31)) {
             const uint32_t r = __umulhi((uint32_t)v, magic) >> magic_shift;
-            row = r, col = (int64_t)((uint32_t)v - r * per_row) * 16;
+            row = r, col = (int64_t)((uint32_t)v - r * (uint32_t)per_row) * 16;
         } else {
             row = (int64_t)(v / per_row), col = (int64_t)(v - (size_t)row * per_row) * 16;
         }
-        col = col + 16 > cols && cols >= 16 ? cols - 16 : col;
+        before = 0;
+        if (col + 16 > cols && cols >= 16) before = (int)(col - (cols - 16)), col = cols - 16;
     }
 };
 
@@ -461,18 +464,23 @@ __global__ void __launch_bounds__(kThreads) rescale_u8_kernel(const uint8_t *__r
     for_tiles(chunks,
               [&](size_t v) {
                   int64_t m, c;
-                  rc.locate(v, m, c);
+                  int before;
+                  rc.locate(v, m, c, before);
                   return load_any<u32x4, NT>(x + m * ldx + c);
               },
               [&](size_t v, u32x4 a) {
                   int64_t m, c;
-                  rc.locate(v, m, c);
+                  int before;
+                  rc.locate(v, m, c, before);
                   u32x4 o;
 #pragma unroll
                   for (int d = 0; d < 4; ++d)
                       o[d] = (uint32_t)lut[a[d] & 0xffu] | ((uint32_t)lut[(a[d] >> 8) & 0xffu] << 8) |
                              ((uint32_t)lut[(a[d] >> 16) & 0xffu] << 16) | ((uint32_t)lut[a[d] >> 24] << 24);
-                  store_any(y + m * ldy + c, o);
+                  uint8_t *const dst = y + m * ldy + c;
+                  if (rc.in_place && before > 0) // (the bytes before may have been rescaled already)
+                      for (int e = before; e < 16; ++e) dst[e] = (uint8_t)(o[e >> 2] >> (8 * (e & 3)));
+                  else store_any(dst, o);
               });
 }
 
@@ -666,9 +674,9 @@ qnn_status qnn_rescale_u8(const uint8_t *x, int64_t ldx, int32_t z_in, int32_t m
     int64_t r = rows, c = cols;
     if (ldx == cols && ldy == cols) r = 1, c = rows * cols, ldx = ldy = c; // dense: one long row, whole chunks throughout
     RowChunks rc = {};
-    rc.per_row = (uint32_t)((c + 15) / 16), rc.cols = c;
-    fast_division(rc.per_row, rc.magic, rc.magic_shift);
-    if ((c + 15) / 16 > 0x7fffffff) return QNN_EINVAL;
+    rc.per_row = (uint64_t)(c + 15) / 16, rc.cols = c;
+    if (rc.per_row <= 0x7fffffff) fast_division((uint32_t)rc.per_row, rc.magic, rc.magic_shift);
+    rc.in_place = x < y + (r - 1) * ldy + c && y < x + (r - 1) * ldx + c;
     const size_t chunks = (size_t)r * rc.per_row;
     const dim3 grid((unsigned)grid_for(chunks));
     const hipStream_t s = as_stream(stream);

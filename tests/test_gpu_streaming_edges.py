@@ -77,3 +77,17 @@ def test_add_and_concat_rescale(rows, cols):
     qnn.rescale_u8(dev(a), 9, mult, shift, 128, 1, 254, out=cat[:, 1:1 + cols])
     assert_same(host(cat[:, 1:1 + cols].contiguous()), ref, "concat slice")
     assert bool((cat[:, 0] == 77).all()) and bool((cat[:, 1 + cols:] == 77).all())
+
+
+@pytest.mark.parametrize("rows,cols,spaced", [(7, 15, 0), (300, 17, 0), (300, 17, 3), (2000, 31, 16), (64, 1000, 8), (3, 70_001, 1), (50, 48, 0)])
+def test_concat_rescale_in_place(rows, cols, spaced):
+    # each code is rescaled once, whatever pieces the rows are cut into
+    rng = np.random.default_rng(rows + cols)
+    a = rng.integers(0, 256, (rows, cols + spaced)).astype(np.uint8)
+    mult, shift = oracle.quantize_multiplier(0.7)
+    one = np.array([mult], np.int32), np.array([shift], np.int32)
+    want = a.copy()
+    want[:, :cols] = oracle.requantize(np.ascontiguousarray(a[:, :cols]).astype(np.int32) - 9, *one, False, 128, 1, 254)
+    t = dev(a)
+    qnn.rescale_u8(t[:, :cols], 9, mult, shift, 128, 1, 254, out=t[:, :cols])
+    assert_same(host(t), want, "in place")

@@ -7,6 +7,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_1806_08342_amd as qnn
@@ -234,3 +235,13 @@ def test_workload_tables_match_the_networks():
     full, skinny = workloads.gemm_sweep()
     assert len(full) == 64 and len(skinny) == 7
     assert len(shapes.unique_shapes(rn)) < len(rn)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="addresses that are not device memory: only where nothing can run")
+@pytest.mark.parametrize("rows,cols", [(1, 2 ** 35 + 5), (2 ** 20, 2 ** 16), (3, 2 ** 35 + 1)])
+def test_rescale_u8_takes_tensors_of_any_size(rows, cols):
+    # no limit of its own on the number of 16-byte pieces: the arguments are valid, only the launch fails without a GPU
+    far = 1 << 45
+    for ld in (cols, cols + 3):
+        rc = qnn.load_library().qnn_rescale_u8(far, ld, 9, 1 << 30, 1, 128, 0, 255, far + (1 << 43), ld, rows, cols, None)
+        assert qnn.binding.STATUS[rc] == "QNN_ELAUNCH"
