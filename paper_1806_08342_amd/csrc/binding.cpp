@@ -182,13 +182,23 @@ template <class Query> Workspace workspace(PyObject *o, const at::Tensor &like, 
 
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-// calls the library without the interpreter lock and raises for a status other than QNN_OK
+// the interpreter lock is given up for the lifetime of this object, however the scope is left
+struct Unlocked {
+    PyThreadState *const state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked &) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// calls the library without the interpreter lock and raises for a status other than QNN_OK; the stream is looked up
+// with the lock held, since that may throw
 template <class F> void call(const char *name, F f)
 {
-    qnn_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
+    void *const s = stream();
+    const qnn_status st = [&] {
+        const Unlocked unlocked;
+        return f(s);
+    }();
     if (st == QNN_OK) return;
     PyObject *r = PyObject_CallFunction(g_check, "si", name, (int)st);
     if (r) {
@@ -230,8 +240,8 @@ template <bool WIDE> PyObject *f_quantize(Args a) // x, scale, zero_point, qmin,
     const size_t n = (size_t)x.numel();
     const float scale = real(a[1]);
     const int32_t z = i32(a[2]), lo = i32(a[3]), hi = i32(a[4]);
-    if (WIDE) call("qnn_quantize_u16", [&] { return qnn_quantize_u16(px, static_cast<uint16_t *>(pq), n, scale, z, lo, hi, stream()); });
-    else call("qnn_quantize", [&] { return qnn_quantize(px, static_cast<uint8_t *>(pq), n, scale, z, lo, hi, stream()); });
+    if (WIDE) call("qnn_quantize_u16", [&](void *s) { return qnn_quantize_u16(px, static_cast<uint16_t *>(pq), n, scale, z, lo, hi, s); });
+    else call("qnn_quantize", [&](void *s) { return qnn_quantize(px, static_cast<uint8_t *>(pq), n, scale, z, lo, hi, s); });
     return q.release();
 }
 
@@ -244,8 +254,8 @@ template <bool WIDE> PyObject *f_dequantize(Args a) // q, scale, zero_point, out
     const size_t n = (size_t)q.numel();
     const float scale = real(a[1]);
     const int32_t z = i32(a[2]);
-    if (WIDE) call("qnn_dequantize_u16", [&] { return qnn_dequantize_u16(static_cast<const uint16_t *>(pq), px, n, scale, z, stream()); });
-    else call("qnn_dequantize", [&] { return qnn_dequantize(static_cast<const uint8_t *>(pq), px, n, scale, z, stream()); });
+    if (WIDE) call("qnn_dequantize_u16", [&](void *s) { return qnn_dequantize_u16(static_cast<const uint16_t *>(pq), px, n, scale, z, s); });
+    else call("qnn_dequantize", [&](void *s) { return qnn_dequantize(static_cast<const uint8_t *>(pq), px, n, scale, z, s); });
     return x.release();
 }
 
@@ -261,8 +271,8 @@ PyObject *f_requantize(Args a) // acc, mult, shift, per_channel, z_out, act_min,
     const int per_channel = PyObject_IsTrue(a[3]);
     if (per_channel < 0) throw PythonErrorSet{};
     const int32_t z = i32(a[4]), lo = i32(a[5]), hi = i32(a[6]);
-    call("qnn_requantize", [&] {
-        return qnn_requantize(pa, py, (size_t)acc.size(0), (size_t)acc.size(1), mult, shift, per_channel, z, lo, hi, stream());
+    call("qnn_requantize", [&](void *s) {
+        return qnn_requantize(pa, py, (size_t)acc.size(0), (size_t)acc.size(1), mult, shift, per_channel, z, lo, hi, s);
     });
     return y.release();
 }
@@ -303,9 +313,9 @@ PyObject *f_qadd(Args a) // a, z_a, b, z_b, params, z_out, act_min, act_max, out
     const auto *pb = static_cast<const uint8_t *>(dense(a[2], at::kByte, "b"));
     auto *py = static_cast<uint8_t *>(dense(y.t, at::kByte, "y"));
     const int32_t za = i32(a[1]), zb = i32(a[3]), z = i32(a[5]), lo = i32(a[6]), hi = i32(a[7]);
-    call("qnn_qadd", [&] {
+    call("qnn_qadd", [&](void *s) {
         return qnn_qadd(pa, za, d.v[P_MULT_A], d.v[P_SHIFT_A], pb, zb, d.v[P_MULT_B], d.v[P_SHIFT_B], d.v[P_LEFT], d.v[P_MULT_O],
-                        d.v[P_SHIFT_O], z, lo, hi, py, (size_t)x.numel(), stream());
+                        d.v[P_SHIFT_O], z, lo, hi, py, (size_t)x.numel(), s);
     });
     return y.release();
 }
@@ -318,8 +328,8 @@ PyObject *f_rescale_u8(Args a) // x, z_in, mult, shift, z_out, act_min, act_max,
     Out y = output(a[7], x.sizes(), at::kByte, x);
     const Rows ry = rows(y.t, "y");
     const int32_t zi = i32(a[1]), mult = i32(a[2]), shift = i32(a[3]), z = i32(a[4]), lo = i32(a[5]), hi = i32(a[6]);
-    call("qnn_rescale_u8", [&] {
-        return qnn_rescale_u8(rx.p, rx.pitch, zi, mult, shift, z, lo, hi, ry.p, ry.pitch, x.size(0), x.size(1), stream());
+    call("qnn_rescale_u8", [&](void *s) {
+        return qnn_rescale_u8(rx.p, rx.pitch, zi, mult, shift, z, lo, hi, ry.p, ry.pitch, x.size(0), x.size(1), s);
     });
     return y.release();
 }
@@ -333,7 +343,7 @@ PyObject *f_minmax(Args a) // x, state, momentum, bits
     qnn_dyn_qparams *st = range_state(a[1]);
     const float momentum = real(a[2]);
     const int bits = i32(a[3]);
-    call("qnn_minmax", [&] { return qnn_minmax(px, (size_t)x.numel(), momentum, bits, st, stream()); });
+    call("qnn_minmax", [&](void *s) { return qnn_minmax(px, (size_t)x.numel(), momentum, bits, st, s); });
     Py_INCREF(a[1]);
     return a[1];
 }
@@ -345,8 +355,8 @@ template <bool DYNAMIC> PyObject *f_quantize_state(Args a) // x, state, out
     Out q = output(a[2], x.sizes(), at::kByte, x);
     auto *pq = static_cast<uint8_t *>(dense(q.t, at::kByte, "q"));
     qnn_dyn_qparams *st = range_state(a[1]);
-    if (DYNAMIC) call("qnn_quantize_dynamic", [&] { return qnn_quantize_dynamic(px, pq, (size_t)x.numel(), st, stream()); });
-    else call("qnn_quantize_with", [&] { return qnn_quantize_with(px, pq, (size_t)x.numel(), st, stream()); });
+    if (DYNAMIC) call("qnn_quantize_dynamic", [&](void *s) { return qnn_quantize_dynamic(px, pq, (size_t)x.numel(), st, s); });
+    else call("qnn_quantize_with", [&](void *s) { return qnn_quantize_with(px, pq, (size_t)x.numel(), st, s); });
     return q.release();
 }
 
@@ -358,7 +368,7 @@ PyObject *f_simquant(Args a) // x, scale, zero_point, qmin, qmax, out
     auto *py = static_cast<float *>(dense(y.t, at::kFloat, "y"));
     const float scale = real(a[1]);
     const int32_t z = i32(a[2]), lo = i32(a[3]), hi = i32(a[4]);
-    call("qnn_simquant", [&] { return qnn_simquant(px, py, (size_t)x.numel(), scale, z, lo, hi, stream()); });
+    call("qnn_simquant", [&](void *s) { return qnn_simquant(px, py, (size_t)x.numel(), scale, z, lo, hi, s); });
     return y.release();
 }
 
@@ -371,7 +381,7 @@ PyObject *f_simquant_backward(Args a) // x, grad_y, scale, zero_point, qmin, qma
     auto *po = static_cast<float *>(dense(g.t, at::kFloat, "grad_x"));
     const float scale = real(a[2]);
     const int32_t z = i32(a[3]), lo = i32(a[4]), hi = i32(a[5]);
-    call("qnn_simquant_backward", [&] { return qnn_simquant_backward(px, pg, po, (size_t)x.numel(), scale, z, lo, hi, stream()); });
+    call("qnn_simquant_backward", [&](void *s) { return qnn_simquant_backward(px, pg, po, (size_t)x.numel(), scale, z, lo, hi, s); });
     return g.release();
 }
 
@@ -420,9 +430,9 @@ PyObject *f_qgemm(Args a) // A, z_a, B, mult, shift, z_out, act_min, act_max, bi
     const Channels ch = channels(a[8], a[3], a[4]);
     const Workspace ws = gemm_workspace(a[12], p, false);
     const int32_t za = i32(a[1]), z = i32(a[5]), lo = i32(a[6]), hi = i32(a[7]);
-    call("qnn_qgemm", [&] {
+    call("qnn_qgemm", [&](void *s) {
         return qnn_qgemm(p.a.p, p.a.pitch, za, p.b, p.ldb, layout, bits, p.M, p.N, p.K, ch.bias, ch.mult, ch.shift, z, lo, hi, rc.p, rc.pitch,
-                         ws.p, ws.bytes, stream());
+                         ws.p, ws.bytes, s);
     });
     return c.release();
 }
@@ -437,9 +447,9 @@ PyObject *f_qgemm_noalloc(Args a) // A, z_a, B, mult, shift, z_out, act_min, act
     const Rows rc = rows(out, "C");
     const Channels ch = channels(a[9], a[3], a[4]);
     const int32_t za = i32(a[1]), z = i32(a[5]), lo = i32(a[6]), hi = i32(a[7]);
-    call("qnn_qgemm_noalloc", [&] {
+    call("qnn_qgemm_noalloc", [&](void *s) {
         return qnn_qgemm_noalloc(p.a.p, p.a.pitch, za, p.b, p.ldb, QNN_B_COLUMNS_CONTIGUOUS, bits, p.M, p.N, p.K, ch.bias, ch.mult, ch.shift,
-                                 z, lo, hi, rc.p, rc.pitch, stream());
+                                 z, lo, hi, rc.p, rc.pitch, s);
     });
     Py_INCREF(a[8]);
     return a[8];
@@ -464,9 +474,9 @@ PyObject *f_qgemm_add(Args a)
     const Channels ch = channels(a[14], a[3], a[4]);
     const Workspace ws = gemm_workspace(a[17], p, false);
     const int32_t za = i32(a[1]), z = i32(a[5]), lo = i32(a[6]), hi = i32(a[7]);
-    call("qnn_qgemm_add", [&] {
+    call("qnn_qgemm_add", [&](void *s) {
         return qnn_qgemm_add(p.a.p, p.a.pitch, za, p.b, p.ldb, QNN_B_COLUMNS_CONTIGUOUS, bits, p.M, p.N, p.K, ch.bias, ch.mult, ch.shift, z, lo,
-                             hi, rr.p, rr.pitch, &add, rc.p, rc.pitch, ws.p, ws.bytes, stream());
+                             hi, rr.p, rr.pitch, &add, rc.p, rc.pitch, ws.p, ws.bytes, s);
     });
     return c.release();
 }
@@ -481,9 +491,9 @@ PyObject *f_qgemm_asym(Args a) // A, z_a, B, z_w, mult, shift, z_out, act_min, a
     const Channels ch = channels(a[9], a[4], a[5]);
     const Workspace ws = gemm_workspace(a[12], p, true);
     const int32_t za = i32(a[1]), z = i32(a[6]), lo = i32(a[7]), hi = i32(a[8]);
-    call("qnn_qgemm_asym", [&] {
+    call("qnn_qgemm_asym", [&](void *s) {
         return qnn_qgemm_asym(p.a.p, p.a.pitch, za, p.b, p.ldb, QNN_B_COLUMNS_CONTIGUOUS, bits, zw, p.M, p.N, p.K, ch.bias, ch.mult, ch.shift, z,
-                              lo, hi, rc.p, rc.pitch, ws.p, ws.bytes, stream());
+                              lo, hi, rc.p, rc.pitch, ws.p, ws.bytes, s);
     });
     return c.release();
 }
@@ -496,7 +506,7 @@ PyObject *f_pack_b(Args a) // B_rows
     at::Tensor out = fresh({N, K}, at::kChar, b);
     const auto *src = static_cast<const int8_t *>(dense(b, at::kChar, "B"));
     auto *dst = static_cast<int8_t *>(out.data_ptr());
-    call("qnn_pack_b", [&] { return qnn_pack_b(src, N, K, N, dst, K, stream()); });
+    call("qnn_pack_b", [&](void *s) { return qnn_pack_b(src, N, K, N, dst, K, s); });
     return THPVariable_Wrap(std::move(out));
 }
 
@@ -555,9 +565,9 @@ PyObject *f_qconv2d(Args a) // x, z_x, w, stride, pad, mult, shift, z_out, act_m
     const Channels ch = channels(a[10], a[5], a[6]);
     const Workspace ws = conv_workspace(a[13], c, false);
     const int32_t zx = i32(a[1]), z = i32(a[7]), lo = i32(a[8]), hi = i32(a[9]);
-    call("qnn_qconv2d", [&] {
+    call("qnn_qconv2d", [&](void *s) {
         return qnn_qconv2d(c.px, c.N, c.H, c.W, c.Cin, zx, c.pw, c.Cout, c.kh, c.kw, c.bits, c.s.h, c.s.w, c.p.h, c.p.w, ch.bias, ch.mult,
-                           ch.shift, z, lo, hi, py, ws.p, ws.bytes, stream());
+                           ch.shift, z, lo, hi, py, ws.p, ws.bytes, s);
     });
     return y.release();
 }
@@ -576,9 +586,9 @@ PyObject *f_qconv2d_add(Args a)
     const Channels ch = channels(a[16], a[5], a[6]);
     const Workspace ws = conv_workspace(a[19], c, false);
     const int32_t zx = i32(a[1]), z = i32(a[7]), lo = i32(a[8]), hi = i32(a[9]);
-    call("qnn_qconv2d_add", [&] {
+    call("qnn_qconv2d_add", [&](void *s) {
         return qnn_qconv2d_add(c.px, c.N, c.H, c.W, c.Cin, zx, c.pw, c.Cout, c.kh, c.kw, c.bits, c.s.h, c.s.w, c.p.h, c.p.w, ch.bias, ch.mult,
-                               ch.shift, z, lo, hi, pr, &add, py, ws.p, ws.bytes, stream());
+                               ch.shift, z, lo, hi, pr, &add, py, ws.p, ws.bytes, s);
     });
     return y.release();
 }
@@ -592,9 +602,9 @@ PyObject *f_qconv2d_asym(Args a) // x, z_x, w, z_w, stride, pad, mult, shift, z_
     const Channels ch = channels(a[11], a[6], a[7]);
     const Workspace ws = conv_workspace(a[14], c, true);
     const int32_t zx = i32(a[1]), z = i32(a[8]), lo = i32(a[9]), hi = i32(a[10]);
-    call("qnn_qconv2d_asym", [&] {
+    call("qnn_qconv2d_asym", [&](void *s) {
         return qnn_qconv2d_asym(c.px, c.N, c.H, c.W, c.Cin, zx, c.pw, c.Cout, c.kh, c.kw, c.bits, zw, c.s.h, c.s.w, c.p.h, c.p.w, ch.bias,
-                                ch.mult, ch.shift, z, lo, hi, py, ws.p, ws.bytes, stream());
+                                ch.mult, ch.shift, z, lo, hi, py, ws.p, ws.bytes, s);
     });
     return y.release();
 }
@@ -606,9 +616,9 @@ PyObject *f_qdwconv2d(Args a) // x, z_x, w, stride, pad, mult, shift, z_out, act
     auto *py = static_cast<uint8_t *>(dense(y.t, at::kByte, "y"));
     const Channels ch = channels(a[10], a[5], a[6]);
     const int32_t zx = i32(a[1]), z = i32(a[7]), lo = i32(a[8]), hi = i32(a[9]);
-    call("qnn_qdwconv2d", [&] {
+    call("qnn_qdwconv2d", [&](void *s) {
         return qnn_qdwconv2d(c.px, c.N, c.H, c.W, c.Cin, zx, static_cast<const int8_t *>(c.pw), c.kh, c.kw, c.s.h, c.s.w, c.p.h, c.p.w, ch.bias,
-                             ch.mult, ch.shift, z, lo, hi, py, stream());
+                             ch.mult, ch.shift, z, lo, hi, py, s);
     });
     return y.release();
 }
@@ -621,9 +631,9 @@ PyObject *f_qdwconv2d_asym(Args a) // x, z_x, w, z_w, stride, pad, mult, shift, 
     const auto *zw = static_cast<const int32_t *>(dense(a[3], at::kInt, "z_w"));
     const Channels ch = channels(a[11], a[6], a[7]);
     const int32_t zx = i32(a[1]), z = i32(a[8]), lo = i32(a[9]), hi = i32(a[10]);
-    call("qnn_qdwconv2d_asym", [&] {
+    call("qnn_qdwconv2d_asym", [&](void *s) {
         return qnn_qdwconv2d_asym(c.px, c.N, c.H, c.W, c.Cin, zx, static_cast<const int8_t *>(c.pw), c.kh, c.kw, zw, c.s.h, c.s.w, c.p.h, c.p.w,
-                                  ch.bias, ch.mult, ch.shift, z, lo, hi, py, stream());
+                                  ch.bias, ch.mult, ch.shift, z, lo, hi, py, s);
     });
     return y.release();
 }

@@ -1,4 +1,8 @@
 """The compiled binding: argument checks that need no GPU, and (on a GPU) allocation, caller-owned outputs and errors."""
+import os
+import re
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -23,6 +27,38 @@ def test_tensors_of_the_wrong_kind_raise_type_errors(bad):
         qnn.quantize(bad, 1.0, 0)
     with pytest.raises(TypeError):
         qnn.qgemm(bad, 0, bad, bad, bad, 0, 0, 255)
+
+
+def test_nothing_that_throws_runs_without_the_interpreter_lock():
+    # an exception between the two macros would leave the lock given up; and the library is C, the stream query is not
+    src = open(os.path.join(os.path.dirname(binding.__file__), "csrc", "binding.cpp")).read()
+    assert "Py_BEGIN_ALLOW_THREADS" not in src and "~Unlocked() { PyEval_RestoreThread" in src
+    calls = re.findall(r'call\("qnn_\w+", \[&\](.*?)\}\);', src, re.S)
+    assert len(calls) > 20 and all(c.startswith("(void *s)") and "stream()" not in c for c in calls)
+
+
+@pytest.mark.gpu
+def test_calls_follow_the_thread_s_own_stream():
+    # several threads at once, each on a stream of its own
+    x = torch.randn(1 << 16, device="cuda:0")
+    want = oracle.quantize(x.cpu().numpy(), 0.03, 120)
+    bad = []
+
+    def work():
+        stream = torch.cuda.Stream()
+        stream.wait_stream(torch.cuda.default_stream())
+        with torch.cuda.stream(stream):
+            outs = [qnn.quantize(x, 0.03, 120) for _ in range(50)]
+        stream.synchronize()
+        bad.extend(i for i, o in enumerate(outs) if not np.array_equal(o.cpu().numpy(), want))
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work) for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
 
 
 @pytest.mark.gpu
