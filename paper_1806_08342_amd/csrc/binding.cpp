@@ -58,6 +58,17 @@ int64_t integer(PyObject *o)
 }
 int32_t i32(PyObject *o) { return (int32_t)integer(o); }
 
+// what Python's int() takes: floats are truncated
+int32_t whole(PyObject *o)
+{
+    if (PyLong_Check(o)) return i32(o);
+    PyObject *const v = PyNumber_Long(o);
+    if (!v) throw PythonErrorSet{};
+    const int64_t r = (int64_t)PyLong_AsUnsignedLongLongMask(v);
+    Py_DECREF(v);
+    return (int32_t)r;
+}
+
 float real(PyObject *o)
 {
     const double v = PyFloat_AsDouble(o);
@@ -327,7 +338,7 @@ PyObject *f_rescale_u8(Args a) // x, z_in, mult, shift, z_out, act_min, act_max,
     const Rows rx = rows(x, "x");
     Out y = output(a[7], x.sizes(), at::kByte, x);
     const Rows ry = rows(y.t, "y");
-    const int32_t zi = i32(a[1]), mult = i32(a[2]), shift = i32(a[3]), z = i32(a[4]), lo = i32(a[5]), hi = i32(a[6]);
+    const int32_t zi = whole(a[1]), mult = whole(a[2]), shift = whole(a[3]), z = whole(a[4]), lo = whole(a[5]), hi = whole(a[6]);
     call("qnn_rescale_u8", [&](void *s) {
         return qnn_rescale_u8(rx.p, rx.pitch, zi, mult, shift, z, lo, hi, ry.p, ry.pitch, x.size(0), x.size(1), s);
     });
@@ -342,7 +353,7 @@ PyObject *f_minmax(Args a) // x, state, momentum, bits
     const auto *px = static_cast<const float *>(dense(x, at::kFloat, "x"));
     qnn_dyn_qparams *st = range_state(a[1]);
     const float momentum = real(a[2]);
-    const int bits = i32(a[3]);
+    const int bits = whole(a[3]);
     call("qnn_minmax", [&](void *s) { return qnn_minmax(px, (size_t)x.numel(), momentum, bits, st, s); });
     Py_INCREF(a[1]);
     return a[1];
@@ -367,7 +378,7 @@ PyObject *f_simquant(Args a) // x, scale, zero_point, qmin, qmax, out
     Out y = output(a[5], x.sizes(), at::kFloat, x, false);
     auto *py = static_cast<float *>(dense(y.t, at::kFloat, "y"));
     const float scale = real(a[1]);
-    const int32_t z = i32(a[2]), lo = i32(a[3]), hi = i32(a[4]);
+    const int32_t z = whole(a[2]), lo = whole(a[3]), hi = whole(a[4]);
     call("qnn_simquant", [&](void *s) { return qnn_simquant(px, py, (size_t)x.numel(), scale, z, lo, hi, s); });
     return y.release();
 }
@@ -380,7 +391,7 @@ PyObject *f_simquant_backward(Args a) // x, grad_y, scale, zero_point, qmin, qma
     const auto *pg = static_cast<const float *>(dense(a[1], at::kFloat, "grad_y"));
     auto *po = static_cast<float *>(dense(g.t, at::kFloat, "grad_x"));
     const float scale = real(a[2]);
-    const int32_t z = i32(a[3]), lo = i32(a[4]), hi = i32(a[5]);
+    const int32_t z = whole(a[3]), lo = whole(a[4]), hi = whole(a[5]);
     call("qnn_simquant_backward", [&](void *s) { return qnn_simquant_backward(px, pg, po, (size_t)x.numel(), scale, z, lo, hi, s); });
     return g.release();
 }

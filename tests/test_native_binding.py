@@ -80,3 +80,20 @@ def test_outputs_shapes_and_status_errors():
     with pytest.raises(qnn.QnnError):
         qnn.qconv2d(img, 0, dev(np.zeros((4, 9, 9, 8), np.int8)), (1, 1), (0, 0), one, one, 0, 0, 255)
     assert qnn.quantize(x[:0], 0.1, 3).shape == (0, 7)
+
+
+@pytest.mark.gpu
+def test_numbers_that_int_takes():
+    # these four convert with int(): zero-points and ranges that come as floats, numpy scalars or tensors
+    x = torch.randn(1000, device="cuda:0")
+    g = torch.randn(1000, device="cuda:0")
+    q = qnn.quantize(x, 0.02, 120).view(10, 100)
+    mult, shift = oracle.quantize_multiplier(0.7)
+    for conv in (float, np.float32, np.int64, torch.tensor):
+        z, lo, hi = conv(120), conv(3), conv(250)
+        assert torch.equal(qnn.simquant(x, 0.02, z, lo, hi), qnn.simquant(x, 0.02, 120, 3, 250))
+        assert torch.equal(qnn.simquant_backward(x, g, 0.02, z, lo, hi), qnn.simquant_backward(x, g, 0.02, 120, 3, 250))
+        assert torch.equal(qnn.rescale_u8(q, z, mult, conv(shift), conv(128), lo, hi), qnn.rescale_u8(q, 120, mult, shift, 128, 3, 250))
+        assert torch.equal(qnn.minmax(x, qnn.new_range_state(), 0.0, conv(8)), qnn.minmax(x, qnn.new_range_state(), 0.0, 8))
+    with pytest.raises((TypeError, ValueError)):
+        qnn.simquant(x, 0.02, "no number")
