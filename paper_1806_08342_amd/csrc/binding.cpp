@@ -542,8 +542,8 @@ Conv conv(PyObject *ox, PyObject *ow, PyObject *stride, PyObject *pad, int bits,
 {
     const at::Tensor &x = tensor(ox, "x"), &w = tensor(ow, "w");
     if (x.dim() != 4) type_error("x", "a 4-D NHWC tensor");
-    if (w.dim() < 3) type_error("w", depthwise ? "a weight tensor [kh, kw, C]" : "a weight tensor [Cout, kh, kw, Cin]");
-    const int d = depthwise ? 0 : 1;
+    const int d = depthwise ? 0 : 1; // kh and kw are all that is looked at: a single channel may have [kh, kw]
+    if (w.dim() < d + 2) type_error("w", depthwise ? "a weight tensor [kh, kw, C]" : "a weight tensor [Cout, kh, kw, Cin]");
     Conv c{x,
            static_cast<const uint8_t *>(dense(x, at::kByte, "x")),
            dense(w, bits == 4 ? at::kByte : at::kChar, "w"),

@@ -97,3 +97,19 @@ def test_numbers_that_int_takes():
         assert torch.equal(qnn.minmax(x, qnn.new_range_state(), 0.0, conv(8)), qnn.minmax(x, qnn.new_range_state(), 0.0, 8))
     with pytest.raises((TypeError, ValueError)):
         qnn.simquant(x, 0.02, "no number")
+
+
+@pytest.mark.gpu
+def test_depthwise_weights_of_one_channel_without_a_channel_dimension():
+    rng = np.random.default_rng(3)
+    x = rng.integers(0, 256, (2, 9, 8, 1)).astype(np.uint8)
+    w = rng.integers(-128, 128, (3, 3)).astype(np.int8)
+    mult, shift = oracle.quantize_multipliers([0.002])
+    z_w = np.array([5], np.int32)
+    args = (dev(mult), dev(shift), 120, 0, 255)
+    want = oracle.qdwconv2d(x, 7, w[:, :, None], (1, 1), (1, 1), mult, shift, 120, 0, 255)
+    assert_same(host(qnn.qdwconv2d(dev(x), 7, dev(w), (1, 1), (1, 1), *args)), want, "symmetric")
+    want = oracle.qdwconv2d(x, 7, w[:, :, None], (1, 1), (1, 1), mult, shift, 120, 0, 255, z_w=z_w)
+    assert_same(host(qnn.qdwconv2d_asym(dev(x), 7, dev(w), dev(z_w), (1, 1), (1, 1), *args)), want, "weight zero-point")
+    with pytest.raises(TypeError):
+        qnn.qdwconv2d(dev(x), 7, dev(w[0]), (1, 1), (1, 1), *args)
