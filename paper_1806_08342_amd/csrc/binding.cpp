@@ -136,12 +136,23 @@ Rows rows(const at::Tensor &t, const char *name)
     return {static_cast<uint8_t *>(t.data_ptr()), t.size(0) > 1 ? t.stride(0) : t.size(1)};
 }
 
+// pointer of an operand that a kernel reads as many elements of as `x` has
+void *dense_like(PyObject *o, at::ScalarType type, const char *name, const at::Tensor &x)
+{
+    if (o == Py_None) return nullptr;
+    const at::Tensor &t = tensor(o, name);
+    void *const p = dense(t, type, name);
+    if (t.numel() < x.numel()) shape_error(name, t.sizes(), x.sizes());
+    return p;
+}
+
 at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like)
 {
     return at::Tensor(at::detail::empty_cuda(shape, type, like.device(), std::nullopt));
 }
 
-// the caller's `out` after a shape check (the kernels write shape-many elements), or a new tensor
+// the caller's `out` (the kernels write shape-many elements: of that shape, or, without check_shape, any tensor that
+// holds as many), or a new tensor
 struct Out {
     at::Tensor t;
     PyObject *given = nullptr; // returned as it came
@@ -162,7 +173,7 @@ Out output(PyObject *o, at::IntArrayRef shape, at::ScalarType type, const at::Te
     } else {
         out.t = tensor(o, "out");
         out.given = o;
-        if (check_shape && out.t.sizes() != shape) shape_error("out", out.t.sizes(), shape);
+        if (check_shape ? out.t.sizes() != shape : out.t.numel() < c10::multiply_integers(shape)) shape_error("out", out.t.sizes(), shape);
     }
     return out;
 }
@@ -321,7 +332,7 @@ PyObject *f_qadd(Args a) // a, z_a, b, z_b, params, z_out, act_min, act_max, out
     const auto *pa = static_cast<const uint8_t *>(dense(x, at::kByte, "a"));
     Out y = output(a[8], x.sizes(), at::kByte, x);
     const AddDict d = add_dict(a[4]);
-    const auto *pb = static_cast<const uint8_t *>(dense(a[2], at::kByte, "b"));
+    const auto *pb = static_cast<const uint8_t *>(dense_like(a[2], at::kByte, "b", x));
     auto *py = static_cast<uint8_t *>(dense(y.t, at::kByte, "y"));
     const int32_t za = i32(a[1]), zb = i32(a[3]), z = i32(a[5]), lo = i32(a[6]), hi = i32(a[7]);
     call("qnn_qadd", [&](void *s) {
@@ -388,7 +399,7 @@ PyObject *f_simquant_backward(Args a) // x, grad_y, scale, zero_point, qmin, qma
     const at::Tensor &x = tensor(a[0], "x");
     const auto *px = static_cast<const float *>(dense(x, at::kFloat, "x"));
     Out g = output(a[6], x.sizes(), at::kFloat, x, false);
-    const auto *pg = static_cast<const float *>(dense(a[1], at::kFloat, "grad_y"));
+    const auto *pg = static_cast<const float *>(dense_like(a[1], at::kFloat, "grad_y", x));
     auto *po = static_cast<float *>(dense(g.t, at::kFloat, "grad_x"));
     const float scale = real(a[2]);
     const int32_t z = whole(a[3]), lo = whole(a[4]), hi = whole(a[5]);

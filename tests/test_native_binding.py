@@ -113,3 +113,22 @@ def test_depthwise_weights_of_one_channel_without_a_channel_dimension():
     assert_same(host(qnn.qdwconv2d_asym(dev(x), 7, dev(w), dev(z_w), (1, 1), (1, 1), *args)), want, "weight zero-point")
     with pytest.raises(TypeError):
         qnn.qdwconv2d(dev(x), 7, dev(w[0]), (1, 1), (1, 1), *args)
+
+
+@pytest.mark.gpu
+def test_tensors_too_small_for_the_call_are_refused():
+    # (raised before anything is launched)
+    x = torch.randn(6, 50, device="cuda:0")
+    q = qnn.quantize(x, 0.02, 120)
+    small, small_codes = x[:5].contiguous(), q[:5].contiguous()
+    p = qnn.qadd_params(0.02, 0.03, 0.05)
+    for bad in (lambda: qnn.dequantize(q, 0.02, 120, out=small), lambda: qnn.simquant(x, 0.02, 120, out=small),
+                lambda: qnn.simquant_backward(x, x, 0.02, 120, out=small), lambda: qnn.simquant_backward(x, small, 0.02, 120),
+                lambda: qnn.qadd(q, 120, small_codes, 120, p, 120, 0, 255)):
+        with pytest.raises(ValueError, match="shape"):
+            bad()
+    # any tensor that holds the elements still does
+    flat = torch.empty(300, device="cuda:0")
+    assert qnn.dequantize(q, 0.02, 120, out=flat) is flat and torch.equal(flat.view(6, 50), qnn.dequantize(q, 0.02, 120))
+    assert torch.equal(qnn.simquant_backward(x, x.view(-1), 0.02, 120), qnn.simquant_backward(x, x, 0.02, 120))
+    assert torch.equal(qnn.qadd(q, 120, q.view(-1), 120, p, 120, 0, 255), qnn.qadd(q, 120, q, 120, p, 120, 0, 255))
