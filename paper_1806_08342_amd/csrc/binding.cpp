@@ -525,8 +525,8 @@ PyObject *f_pack_b(Args a) // B_rows
     const at::Tensor &b = tensor(a[0], "B");
     if (b.dim() != 2) type_error("B", "a 2-D device tensor of torch.int8");
     const int64_t K = b.size(0), N = b.size(1);
-    at::Tensor out = fresh({N, K}, at::kChar, b);
     const auto *src = static_cast<const int8_t *>(dense(b, at::kChar, "B"));
+    at::Tensor out = fresh({N, K}, at::kChar, b);
     auto *dst = static_cast<int8_t *>(out.data_ptr());
     call("qnn_pack_b", [&](void *s) { return qnn_pack_b(src, N, K, N, dst, K, s); });
     return THPVariable_Wrap(std::move(out));

@@ -29,6 +29,11 @@ def test_tensors_of_the_wrong_kind_raise_type_errors(bad):
         qnn.qgemm(bad, 0, bad, bad, bad, 0, 0, 255)
 
 
+def test_pack_b_looks_at_the_tensor_before_it_allocates():
+    with pytest.raises(TypeError):
+        qnn.pack_b(torch.zeros(4, 4, dtype=torch.int8))
+
+
 def test_nothing_that_throws_runs_without_the_interpreter_lock():
     # an exception between the two macros would leave the lock given up; and the library is C, the stream query is not
     src = open(os.path.join(os.path.dirname(binding.__file__), "csrc", "binding.cpp")).read()
