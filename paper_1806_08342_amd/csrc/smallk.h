@@ -190,10 +190,18 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
 #pragma unroll
     for (int t = 0; t < MT; ++t) rowsum[t] = 0;
     const bool need_colsum = g.z_a != 128;
+    // orders the wave's own row exchange for the compiler (other lanes read what a lane stores); the hardware keeps LDS
+    // accesses of a wave in order, so it costs no wait
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    };
     // one step: wv the weight rows, av the activation rows, by halves of 128 bytes
     auto multiply = [&](const u32x4 (&wv)[2], const u32x4 (&av)[HALVES][AI]) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4 *>(xb + put[i]) = wv[i];
+        wave_sync();
         u32x4 w[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) w[h] = *reinterpret_cast<const u32x4 *>(xb + get_b[h]);
@@ -219,12 +227,14 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
                     if (2 * t + i < AI) *reinterpret_cast<u32x4 *>(xa + put[i]) = av[p][2 * t + i] ^ 0x80808080u; // code -> signed (code - 128)
+                wave_sync();
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const i32x4 xs = *reinterpret_cast<const i32x4 *>(xa + get_a[h]); // (AI odd: rows 8..15 of the tile are nobody's)
                     acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[h], xs, acc[t], 0, 0, 0);
                     if constexpr (ZW) add_rowsum(rowsum[t], xs);
                 }
+                wave_sync(); // before the next rows take the place of these
             }
         }
     };

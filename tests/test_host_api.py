@@ -245,3 +245,11 @@ def test_rescale_u8_takes_tensors_of_any_size(rows, cols):
     for ld in (cols, cols + 3):
         rc = qnn.load_library().qnn_rescale_u8(far, ld, 9, 1 << 30, 1, 128, 0, 255, far + (1 << 43), ld, rows, cols, None)
         assert qnn.binding.STATUS[rc] == "QNN_ELAUNCH"
+
+
+def test_wave_private_exchange_is_ordered_for_the_compiler():
+    # what lanes store into the wave's rows of LDS is read by others and overwritten by the next step: a fence each time
+    src = open(os.path.join(os.path.dirname(qnn.binding.__file__), "csrc", "smallk.h")).read()
+    body = src[src.index("auto multiply"):src.index("const int steps")]
+    assert re.findall(r"x[ab] \+ put|x[ab] \+ get|wave_sync\(\)", body) == [
+        "xb + put", "wave_sync()", "xb + get", "xa + put", "wave_sync()", "xa + get", "wave_sync()"]
