@@ -201,9 +201,9 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
     };
     {
         qnn_status st;
+        if (try_small(g, a_mode, b_mode, s, &st)) return st;
         IgemmArgs plain = g;
         plain.R = nullptr;
-        if (try_small(plain, a_mode, b_mode, s, &st)) return add_pass(st);
         if (a_mode == A_MATRIX && shortk_eligible(g, b_mode, false)) return launch_shortk(g, b_mode, false, s);
         if (try_bres(plain, a_mode, b_mode, s, &st)) return add_pass(st);
     }

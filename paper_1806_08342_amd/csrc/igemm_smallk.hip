@@ -17,16 +17,16 @@ bool small_shape(int64_t M, int64_t N, int64_t K, bool conv, bool int4)
     return ((N + 15) / 16) * ((M + 31) / 32) <= 800;
 }
 
-template <int AI, bool INT4, int A_MODE, bool ZW> static void launch_rows(const SmallArgs &a, int waves, hipStream_t s)
+template <int AI, bool INT4, int A_MODE, SmallExtra EXTRA> static void launch_rows(const SmallArgs &a, int waves, hipStream_t s)
 {
     const dim3 grid((unsigned)((a.g.N + 15) / 16), (unsigned)((a.g.M + 8 * AI - 1) / (8 * AI)));
     // (64 rows in 16 waves do not fit the register file)
-    if (waves == 4) hipLaunchKernelGGL((smallk_kernel<AI, INT4, 4, A_MODE, ZW>), grid, dim3(256), 0, s, a);
-    else if (waves == 8 || AI == 8) hipLaunchKernelGGL((smallk_kernel<AI, INT4, 8, A_MODE, ZW>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((smallk_kernel<AI, INT4, AI == 8 ? 8 : 16, A_MODE, ZW>), grid, dim3(1024), 0, s, a);
+    if (waves == 4) hipLaunchKernelGGL((smallk_kernel<AI, INT4, 4, A_MODE, EXTRA>), grid, dim3(256), 0, s, a);
+    else if (waves == 8 || AI == 8) hipLaunchKernelGGL((smallk_kernel<AI, INT4, 8, A_MODE, EXTRA>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((smallk_kernel<AI, INT4, AI == 8 ? 8 : 16, A_MODE, EXTRA>), grid, dim3(1024), 0, s, a);
 }
 
-template <bool INT4, bool ZW> static void launch_small(const SmallArgs &a, bool conv, hipStream_t s)
+template <bool INT4, SmallExtra EXTRA> static void launch_small(const SmallArgs &a, bool conv, hipStream_t s)
 {
     const IgemmArgs &g = a.g;
     const int64_t cols = (g.N + 15) / 16, wgs32 = cols * ((g.M + 31) / 32);
@@ -39,15 +39,15 @@ template <bool INT4, bool ZW> static void launch_small(const SmallArgs &a, bool 
     const bool several = wgs > (ai == 8 ? 256 : 512) && ai >= 4;
     const int waves = several || steps <= 4 ? 4 : (ai < 8 && wgs <= 256 && steps > 8 ? 16 : 8);
     if (conv) {
-        launch_rows<4, INT4, A_CONV, ZW>(a, waves, s);
+        launch_rows<4, INT4, A_CONV, EXTRA>(a, waves, s);
     } else if (ai == 1) {
-        launch_rows<1, INT4, A_MATRIX, ZW>(a, waves, s);
+        launch_rows<1, INT4, A_MATRIX, EXTRA>(a, waves, s);
     } else if (ai == 2) {
-        launch_rows<2, INT4, A_MATRIX, ZW>(a, waves, s);
+        launch_rows<2, INT4, A_MATRIX, EXTRA>(a, waves, s);
     } else if (ai == 4) {
-        launch_rows<4, INT4, A_MATRIX, ZW>(a, waves, s);
+        launch_rows<4, INT4, A_MATRIX, EXTRA>(a, waves, s);
     } else {
-        launch_rows<8, INT4, A_MATRIX, ZW>(a, waves, s);
+        launch_rows<8, INT4, A_MATRIX, EXTRA>(a, waves, s);
     }
 }
 
@@ -62,8 +62,10 @@ bool try_small(const IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_st
         fast_division((uint32_t)(g.Ho * g.Wo), a.magic_hw, a.shift_hw);
         fast_division((uint32_t)g.Wo, a.magic_wo, a.shift_wo);
     }
-    if (g.zw) b_mode == B_INT4 ? launch_small<true, true>(a, conv, s) : launch_small<false, true>(a, conv, s);
-    else b_mode == B_INT4 ? launch_small<true, false>(a, conv, s) : launch_small<false, false>(a, conv, s);
+    const bool i4 = b_mode == B_INT4;
+    if (g.zw) i4 ? launch_small<true, SMALL_ZW>(a, conv, s) : launch_small<false, SMALL_ZW>(a, conv, s);
+    else if (g.R) i4 ? launch_small<true, SMALL_ADD>(a, conv, s) : launch_small<false, SMALL_ADD>(a, conv, s);
+    else i4 ? launch_small<true, SMALL_PLAIN>(a, conv, s) : launch_small<false, SMALL_PLAIN>(a, conv, s);
     *status = launch_status(hipGetLastError());
     return true;
 }

@@ -88,11 +88,16 @@ __device__ __forceinline__ i32x4 widen_int4(uint32_t r0, uint32_t r1)
 
 // AI: load instructions per 128 bytes of the activation rows, 8 rows each (a workgroup owns 8 * AI rows).
 // A_CONV: the 16-byte chunks of a row are gathered from the image; Cin % 16 == 0, so a chunk lies inside one tap.
-// ZW: per-column weight zero-points (see igemm_epilogue_impl).
-template <int AI, bool INT4, int NW, int A_MODE, bool ZW>
+// SMALL_ZW: per-column weight zero-points (see igemm_epilogue_impl).
+// SMALL_ADD: the rescaling add with g.R.  A lane ends up with 4 codes of one row, so it needs one dword of the residual,
+// requested with the per-column parameters; the tables of the add are filled while these are on their way.
+enum SmallExtra { SMALL_PLAIN, SMALL_ZW, SMALL_ADD };
+
+template <int AI, bool INT4, int NW, int A_MODE, SmallExtra EXTRA>
 __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
 {
     const IgemmArgs &g = args.g;
+    constexpr bool ZW = EXTRA == SMALL_ZW, ADD = EXTRA == SMALL_ADD;
     constexpr int MT = (AI + 1) / 2, BN = 16, STEP = INT4 ? 256 : 128, HALVES = STEP / 128;
     constexpr int STEP_REGS = 4 * (2 + AI * HALVES);
     constexpr int UNROLL = STEP_REGS <= 16 ? 4 : (STEP_REGS <= (NW > 8 ? 24 : 40) ? 2 : 1); // steps in flight per wave (what the registers hold)
@@ -101,6 +106,7 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
     __shared__ __attribute__((aligned(16))) uint8_t smem[NW * 4096];
     __shared__ int32_t csum[NW][BN];
     __shared__ int32_t rsum[ZW ? NW : 1][MT][16];
+    __shared__ int32_t add_tab[ADD ? 512 : 1];
     i32x4(*const part)[MT][64] = reinterpret_cast<i32x4(*)[MT][64]>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform
@@ -181,6 +187,19 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
             p_mult[e] = g.mult[n];
             p_shift[e] = g.shift[n];
         }
+    }
+    uint32_t residual = 0;
+    if constexpr (ADD) {
+        if (wave < MT) {
+            const int64_t m = m0 + wave * 16 + frow;
+            const uint8_t *const r = g.R + (m < g.M ? m : g.M - 1) * g.ldr;
+            if (nb + 4 <= g.N) {
+                __builtin_memcpy(&residual, r + nb, 4);
+            } else {
+                for (int e = 0; nb + e < g.N; ++e) residual |= (uint32_t)r[nb + e] << (8 * e);
+            }
+        }
+        add_fill_tables(add_tab, g.add, tid, NW * 64);
     }
 
     i32x4 acc[MT];
@@ -330,6 +349,10 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
         if constexpr (ZW) a = (int32_t)((uint32_t)a - (uint32_t)g.zw[nb + e < g.N ? nb + e : g.N - 1] * (uint32_t)rs);
         const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general(a, make_rescale(p_mult[e], p_shift[e]))) + g.z_out;
         packed |= (uint32_t)y << (8 * e);
+    }
+    if constexpr (ADD) {
+        const AddOut ao = make_add_out(g.add);
+        packed = ao.fused ? add_codes4<true>(packed, residual, add_tab, ao) : add_codes4<false>(packed, residual, add_tab, ao);
     }
     uint8_t *dst = g.C + m * g.ldc + nb;
     if (nb + 4 <= g.N) {

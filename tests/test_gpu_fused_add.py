@@ -167,3 +167,67 @@ def test_fused_add_equals_two_calls_on_the_gpu():
     t = qnn.qgemm(dev(A), z_a, dev(Bo), dev(mult), dev(shift), z_mid, 0, 255, bias=dev(bias))
     two = host(qnn.qadd(t, z_mid, dev(R), z_r, p, z_o, lo, hi))
     assert_same(two, want, "qgemm then qadd")
+
+
+def _launches(fn):
+    """Number of nodes that `fn` leaves in a captured graph."""
+    import ctypes
+
+    fn()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        fn()
+    n = ctypes.c_size_t()
+    assert ctypes.CDLL("libamdhip64.so").hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+# rows per workgroup 8, 16, 32 and 64; 4, 8 and 16 waves; N and K that are no multiple of 4; misaligned residual rows
+@pytest.mark.parametrize("M,N,K,bits", [(1, 16, 64, 8), (8, 33, 2048, 8), (9, 21, 1030, 4), (16, 64, 4096, 4), (31, 47, 129, 8), (50, 4099, 300, 8),
+                                        (64, 4112, 514, 4), (65, 18, 2304, 8), (97, 66, 6000, 4), (333, 35, 77, 8), (1570, 162, 960, 4), (3137, 25, 144, 4),
+                                        (1571, 127, 1000, 8)])
+def test_small_launches_add_in_one_kernel(M, N, K, bits):
+    rng = np.random.default_rng(M + N + K)
+    A, Bt, bias, mult, shift = _gemm_inputs(rng, M, N, K, bits)
+    Bo = oracle.pack_int4(Bt) if bits == 4 else Bt
+    for odd, act, spaced in ((False, "relu", 0), (False, "none", 3), (True, "none", 5)):
+        Rw, z_mid, z_r, p, z_o, lo, hi = _add_setup(rng, (M, N + spaced), act, odd)
+        R = Rw[:, spaced:]
+        t = oracle.qgemm(A, 77, Bo, mult, shift, z_mid, 2, 252, bias=bias, weight_bits=bits)
+        want = oracle.qadd(t, z_mid, np.ascontiguousarray(R), z_r, p, z_o, lo, hi)
+        out = torch.full((M, N + spaced), 9, dtype=torch.uint8, device="cuda:0")
+        args = [dev(v) for v in (A, Bo, mult, shift, Rw, bias)]
+
+        def run():
+            qnn.qgemm_add(args[0], 77, args[1], args[2], args[3], z_mid, 2, 252, args[4][:, spaced:], z_r, p, z_o, lo, hi, bias=args[5],
+                          weight_bits=bits, out=out[:, spaced:])
+
+        assert _launches(run) == 1
+        out.fill_(9)
+        run()
+        assert_same(host(out[:, spaced:].contiguous()), want, f"{M}x{N}x{K} bits={bits} odd={odd} spaced={spaced}")
+        assert spaced == 0 or bool((out[:, :spaced] == 9).all())
+    assert M == 1 or len(np.unique(want)) > 8
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("batch,H,W,cin,cout,k,s", [(1, 7, 7, 512, 130, 3, 1), (2, 9, 11, 32, 33, 3, 2), (1, 28, 28, 32, 32, 3, 1), (2, 20, 20, 272, 63, 1, 2)])
+def test_small_convolutions_add_in_one_kernel(batch, H, W, cin, cout, k, s, bits):
+    layer = workloads.Layer("t", "conv", H, W, cin, cout, k=k, stride=s, pad=k // 2, act="none", weight_bits=bits)
+    c = synth.conv_case(layer, batch, 4950 + cin + cout, oracle)
+    w_o = c.get("w_packed", c["w"])
+    t = oracle.qconv2d(c["x"], c["z_x"], w_o, c["stride"], c["pad"], c["mult"], c["shift"], c["z_out"], 0, 255, bias=c["bias"], weight_bits=bits)
+    R, _, z_r, p, z_o, lo, hi = _add_setup(np.random.default_rng(cout), t.shape)
+    want = oracle.qadd(t, c["z_out"], R, z_r, p, z_o, lo, hi)
+    args = [dev(v) for v in (c["x"], w_o, c["mult"], c["shift"], R, c["bias"])]
+    out = torch.empty(t.shape, dtype=torch.uint8, device="cuda:0")
+
+    def run():
+        qnn.qconv2d_add(args[0], c["z_x"], args[1], c["stride"], c["pad"], args[2], args[3], c["z_out"], 0, 255, args[4], z_r, p, z_o, lo, hi,
+                        bias=args[5], weight_bits=bits, out=out)
+
+    assert _launches(run) == 1
+    out.fill_(9)
+    run()
+    assert_same(host(out), want, f"conv {batch}x{H}x{W}x{cin}->{cout} k{k} s{s} bits={bits}")
