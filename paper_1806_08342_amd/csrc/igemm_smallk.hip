@@ -14,7 +14,12 @@ bool small_shape(int64_t M, int64_t N, int64_t K, bool conv, bool int4)
     if (M <= 64 && !conv) return true;
     if (!tuning().small || tuning().bres == 1) return false; // tuning aids: reach the other kernels on small shapes
     if (!conv && !int4 && K >= 4096) return false;
-    return ((N + 15) / 16) * ((M + 31) / 32) <= 800;
+    const int64_t wgs = ((N + 15) / 16) * ((M + 31) / 32);
+    // 4-bit weights: a fourth workgroup does not fit a CU, and past 768 the last few run alone.  With a partial K-step on
+    // top the tiles win where they take K as it is and it is not long (784 workgroups: K = 288 5.3 us against 6.7 here, 384
+    // 5.4 / 6.4, 576 6.1 / 7.1, 704 6.6 / 7.1; but K = 512 5.9 / 5.4, 768 6.9 / 5.7, 264 7.9 / 7.1; 768: 5.4 / 4.7 for 384)
+    if (int4 && wgs > 768 && K > 256 && K <= 704 && (K % 32) == 0 && (K % 256) != 0) return false;
+    return wgs <= 800;
 }
 
 template <int AI, bool INT4, int A_MODE, SmallExtra EXTRA> static void launch_rows(const SmallArgs &a, int waves, hipStream_t s)
