@@ -147,8 +147,9 @@ static size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int weight_b
     if (M <= 0 || N <= 0 || K <= 0) return 0;
     if (asym) return rowsum_bytes(M);
     const int64_t padded = repack_length((int)K, weight_bits);
+    if (!tuning().forced() && small_shape(M, N, K, false, weight_bits == 4)) return 0; // that kernel takes none
     if (padded == K) return split_bytes_for(M, N, K, weight_bits);
-    if (small_shape(M, N, K, false, weight_bits == 4) || !repack_pays(M, N, K) || (K <= 256 && (K % 8) == 0)) return 0; // these take it as it is
+    if (!repack_pays(M, N, K) || (K <= 256 && (K % 8) == 0)) return 0; // these take it as it is
     const size_t copies = repack_bytes(M, N, (int)K, weight_bits);
     return copies ? copies + split_bytes_for(M, N, padded, weight_bits) : 0;
 }

@@ -253,3 +253,15 @@ def test_wave_private_exchange_is_ordered_for_the_compiler():
     body = src[src.index("auto multiply"):src.index("const int steps")]
     assert re.findall(r"x[ab] \+ put|x[ab] \+ get|wave_sync\(\)", body) == [
         "xb + put", "wave_sync()", "xb + get", "xa + put", "wave_sync()", "xa + get", "wave_sync()"]
+
+
+def test_small_launches_ask_for_no_scratch():
+    # they run on a kernel that takes none
+    for bits in (8, 4):
+        assert qnn.qgemm_workspace_bytes(196, 512, 2048, bits) == 0
+        assert qnn.qconv2d_workspace_bytes(1, 14, 14, 2048, 512, 1, 1, (1, 1), (0, 0), bits) == 0
+    qnn.tuning_set("QNN_SMALL", 0)
+    try:
+        assert qnn.qgemm_workspace_bytes(196, 512, 2048) == 2 * 196 * 512 * 4
+    finally:
+        qnn.tuning_set("QNN_SMALL")
