@@ -15,6 +15,7 @@
 #include <ATen/core/Tensor.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
+#include <c10/util/Exception.h>
 #include <c10/util/SmallVector.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -185,7 +186,7 @@ struct Workspace {
     void *p = nullptr;
     size_t bytes = 0;
 };
-template <class Query> Workspace workspace(PyObject *o, const at::Tensor &like, Query query)
+template <class Query> Workspace workspace(PyObject *o, const at::Tensor &like, bool required, Query query)
 {
     Workspace w;
     if (o != Py_None) {
@@ -196,8 +197,13 @@ template <class Query> Workspace workspace(PyObject *o, const at::Tensor &like, 
     }
     w.bytes = query();
     if (w.bytes) {
-        w.t = fresh({(int64_t)w.bytes}, at::kByte, like);
-        w.p = w.t.data_ptr();
+        try {
+            w.t = fresh({(int64_t)w.bytes}, at::kByte, like);
+            w.p = w.t.data_ptr();
+        } catch (const c10::OutOfMemoryError &) {
+            if (required) throw;
+            w.bytes = 0; // padded copies can be as large as the operands: without room for them the library takes another route
+        }
     }
     return w;
 }
@@ -440,7 +446,7 @@ Product product(PyObject *oa, PyObject *ob, int bits, int layout)
 }
 Workspace gemm_workspace(PyObject *o, const Product &p, bool asym)
 {
-    return workspace(o, p.A, [&] { return qnn_qgemm_workspace_bytes(p.M, p.N, p.K, p.bits, asym); });
+    return workspace(o, p.A, asym, [&] { return qnn_qgemm_workspace_bytes(p.M, p.N, p.K, p.bits, asym); });
 }
 
 PyObject *f_qgemm(Args a) // A, z_a, B, mult, shift, z_out, act_min, act_max, bias, weight_bits, b_layout, out, workspace
@@ -574,7 +580,7 @@ Conv conv(PyObject *ox, PyObject *ow, PyObject *stride, PyObject *pad, int bits,
 }
 Workspace conv_workspace(PyObject *o, const Conv &c, bool asym)
 {
-    return workspace(o, c.x, [&] {
+    return workspace(o, c.x, asym, [&] {
         return qnn_qconv2d_workspace_bytes(c.N, c.H, c.W, c.Cin, c.Cout, c.kh, c.kw, c.bits, c.s.h, c.s.w, c.p.h, c.p.w, asym);
     });
 }

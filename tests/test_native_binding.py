@@ -137,3 +137,27 @@ def test_tensors_too_small_for_the_call_are_refused():
     assert qnn.dequantize(q, 0.02, 120, out=flat) is flat and torch.equal(flat.view(6, 50), qnn.dequantize(q, 0.02, 120))
     assert torch.equal(qnn.simquant_backward(x, x.view(-1), 0.02, 120), qnn.simquant_backward(x, x, 0.02, 120))
     assert torch.equal(qnn.qadd(q, 120, q.view(-1), 120, p, 120, 0, 255), qnn.qadd(q, 120, q, 120, p, 120, 0, 255))
+
+
+@pytest.mark.gpu
+def test_products_run_where_their_scratch_does_not_fit():
+    rng = np.random.default_rng(5)
+    M, N, K = 3000, 1500, 4099
+    A, B = dev(rng.integers(0, 256, (M, K)).astype(np.uint8)), dev(rng.integers(-128, 128, (N, K)).astype(np.int8))
+    mult, shift = (dev(v) for v in oracle.quantize_multipliers(rng.uniform(40.0, 120.0, N) / (K * 255.0 * 128)))
+    assert qnn.qgemm_workspace_bytes(M, N, K) > (M + N) * K
+    want = qnn.qgemm(A, 9, B, mult, shift, 120, 0, 255)
+    out, z_w = torch.zeros_like(want), torch.zeros(N, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    filler = []
+    try:
+        torch.cuda.set_per_process_memory_fraction(1e-6)  # no new memory from here on ...
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            while True:  # ... nor what the allocator still holds
+                filler.append(torch.empty(4 << 20, dtype=torch.uint8, device="cuda:0"))
+        qnn.qgemm(A, 9, B, mult, shift, 120, 0, 255, out=out)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert_same(host(out), host(want), "without scratch")
+    assert_same(host(qnn.qgemm_asym(A, 9, B, z_w, mult, shift, 120, 0, 255)), host(want), "afterwards")
