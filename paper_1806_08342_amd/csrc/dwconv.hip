@@ -90,6 +90,15 @@ __device__ __forceinline__ void dw_direct_block(const DwArgs &g, int n, int ho0,
             for (int c = c0; c < c1; ++c) g.y[(((int64_t)n * g.Ho + ho) * g.Wo + wo) * g.C + c] = dw_direct(g, n, ho, wo, c);
 }
 
+// One dword of the output.  NT: non-temporal.  What is left in the L2s is written back when the kernel ends, 10-15 % of a
+// 12 us launch; but a cache line that several waves fill piece by piece goes out in pieces once much else passes
+// through the caches (see dw_stream_out).
+template <bool NT> __device__ __forceinline__ void dw_store(uint8_t *p, uint32_t v)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<uint32_t *>(p));
+    else *reinterpret_cast<uint32_t *>(p) = v;
+}
+
 // 3x3 kernel, stride S (same in h and w).  One lane owns 4 consecutive channels and an
 // RH x RW patch of output pixels; the ((RH-1)S+3) x ((RW-1)S+3) input window is loaded once
 // (one dword = 4 channels per pixel), each byte is unpacked once and multiplied into every
@@ -251,7 +260,7 @@ __device__ __forceinline__ DwZeroPoint dw_zero_point(int32_t zw)
 // address) followed by a select of the padding code: no branches around memory operations.
 // ZW: weight zero-points, see DwZeroPoint.  (One lane per output, as such layers ran before: 17.6 us on
 // 16 x 14 x 14 x 512, 7.2 us here; 57 against 14.3 us on 16 x 112 x 112 x 32 with the matrix-unit kernel below.)
-template <int S, int RH, bool ZW>
+template <int S, int RH, bool ZW, bool NT>
 __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
 {
     constexpr int RW = 4;
@@ -431,8 +440,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
                         packed |= (uint32_t)y << (8 * j);
                     }
                 }
-                // (non-temporal: what is left in the L2s is written back when the kernel ends, 10-15 % of a 12 us launch)
-                if (wo0 + p < g.Wo) __builtin_nontemporal_store(packed, reinterpret_cast<uint32_t *>(out + (out_off + (uint32_t)(p * g.C))));
+                if (wo0 + p < g.Wo) dw_store<NT>(out + (out_off + (uint32_t)(p * g.C)), packed);
             }
         }
     };
@@ -475,7 +483,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
 using dw_i32x4 = int32_t __attribute__((ext_vector_type(4)));
 using dw_i32x16 = int32_t __attribute__((ext_vector_type(16)));
 
-template <int S, int MODE, bool ZW> // ZW: weight zero-points, see DwZeroPoint
+template <int S, int MODE, bool ZW, bool NT> // ZW: weight zero-points, see DwZeroPoint; NT: see dw_store
 __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, const int seg_rows, const int tiles_w,
                                                                 const int cblocks)
 {
@@ -653,7 +661,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
             uint32_t v = __builtin_amdgcn_perm(o, x[q], sel1);
             o = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);
             v = __builtin_amdgcn_perm(o, v, sel2);
-            if (o_ok[q]) __builtin_nontemporal_store(v, reinterpret_cast<uint32_t *>(out + o_off[q]));
+            if (o_ok[q]) dw_store<NT>(out + o_off[q], v);
         }
         out_row += out_row_bytes;
     };
@@ -837,6 +845,20 @@ __global__ void __launch_bounds__(256) dwconv_generic_kernel(const DwArgs g)
 
 using namespace qnn;
 
+// Non-temporal output stores?  A wave of the matrix-unit kernel writes 32 channels of its pixels, one of the patch kernel
+// 256: with just as many channels in a pixel (or fewer) it fills whole cache lines, else these stores pay only while
+// input and output together are small enough that the other waves' pieces come in time.  Measured, non-temporal over
+// plain time, inputs from the cache / from HBM, outputs of 4, 16, 32 and 80 MB:
+//   matrix unit, 56x56x32: 0.99/0.94, 0.96/0.93, 0.92/0.95, 0.96/0.93;  112x112x64: 0.99/0.93, 0.93/0.93, 0.93/0.92, 1.04/1.02
+//                56x56x128: 0.98/0.93, 0.93/0.93, 1.03/1.04, 1.29/1.27;  112x112x128, stride 2: 0.98/0.98, 1.05/1.05, 1.15/1.16, 1.24/1.28
+//   patch, 28x28x256: 0.97/0.92, 0.90/0.90, 0.95/0.91, 0.98/0.95;  28x28x144, stride 2: 0.98/0.97, 1.00/1.01, 1.01/1.04, 1.05/1.05
+static bool dw_stream_out(const DwArgs &g, bool matrix_unit)
+{
+    const int64_t mb = ((int64_t)g.N * g.C * ((int64_t)g.H * g.W + (int64_t)g.Ho * g.Wo)) >> 20;
+    if (matrix_unit) return g.C <= 32 || mb < (g.C <= 64 ? 128 : 42);
+    return g.C >= 256 || mb < 128;
+}
+
 static qnn_status qdwconv2d_impl(const uint8_t *x, int N, int H, int W, int C, int32_t z_x, const int8_t *w, int kh, int kw,
                                  int stride_h, int stride_w, int pad_h, int pad_w, const int32_t *bias, const int32_t *mult,
                                  const int32_t *shift, int32_t z_out, int32_t act_min, int32_t act_max, uint8_t *y,
@@ -903,15 +925,16 @@ static qnn_status qdwconv2d_impl(const uint8_t *x, int N, int H, int W, int C, i
             const int segs = (g.Ho + seg_rows - 1) / seg_rows;
             const dim3 grid((unsigned)((waves_x + 3) / 4), (unsigned)segs, (unsigned)N);
             g.xcd_remap = tuning().dw_xcd != 0 && (int64_t)grid.x * grid.y * grid.z < (1ll << 31);
-            auto launch = [&](auto zw) {
-                constexpr bool ZW = decltype(zw)::value;
+            auto launch = [&](auto zw, auto nt) {
+                constexpr bool ZW = decltype(zw)::value, NT = decltype(nt)::value;
                 const bool absorbs = g.lo_rel >= 0; // the clamp absorbs the tie term
-                if (stride_h == 1 && absorbs) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 2, ZW>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-                else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 1, ZW>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-                else if (absorbs) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 2, ZW>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-                else hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 1, ZW>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                if (stride_h == 1 && absorbs) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 2, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 1, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                else if (absorbs) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 2, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                else hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 1, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
             };
-            z_w ? launch(std::true_type{}) : launch(std::false_type{});
+            if (dw_stream_out(g, true)) z_w ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
+            else z_w ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
             return launch_status(hipGetLastError());
         }
         // taller patches (4 output rows per lane) reuse more of the window, but need enough lanes to
@@ -922,14 +945,15 @@ static qnn_status qdwconv2d_impl(const uint8_t *x, int N, int H, int W, int C, i
         if (tall) g.hruns = (g.Ho + 3) / 4;
         const dim3 grid((unsigned)((lanes_x + 255) / 256), (unsigned)g.hruns, (unsigned)N);
         g.xcd_remap = tuning().dw_xcd != 0 && (int64_t)grid.x * grid.y * grid.z < (1ll << 31);
-        auto launch = [&](auto zw) {
-            constexpr bool ZW = decltype(zw)::value;
-            if (tall && stride_h == 1) hipLaunchKernelGGL((dwconv3x3_dot_kernel<1, 4, ZW>), grid, dim3(256), 0, s, g);
-            else if (tall) hipLaunchKernelGGL((dwconv3x3_dot_kernel<2, 4, ZW>), grid, dim3(256), 0, s, g);
-            else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_dot_kernel<1, RH, ZW>), grid, dim3(256), 0, s, g);
-            else hipLaunchKernelGGL((dwconv3x3_dot_kernel<2, RH, ZW>), grid, dim3(256), 0, s, g);
+        auto launch = [&](auto zw, auto nt) {
+            constexpr bool ZW = decltype(zw)::value, NT = decltype(nt)::value;
+            if (tall && stride_h == 1) hipLaunchKernelGGL((dwconv3x3_dot_kernel<1, 4, ZW, NT>), grid, dim3(256), 0, s, g);
+            else if (tall) hipLaunchKernelGGL((dwconv3x3_dot_kernel<2, 4, ZW, NT>), grid, dim3(256), 0, s, g);
+            else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_dot_kernel<1, RH, ZW, NT>), grid, dim3(256), 0, s, g);
+            else hipLaunchKernelGGL((dwconv3x3_dot_kernel<2, RH, ZW, NT>), grid, dim3(256), 0, s, g);
         };
-        z_w ? launch(std::true_type{}) : launch(std::false_type{});
+        if (dw_stream_out(g, false)) z_w ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
+        else z_w ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
     } else if (c4 && stride_h == 1)
         hipLaunchKernelGGL((dwconv3x3_kernel<1, RH, RW>), dim3((unsigned)blocks), dim3(256), 0, s, g);
     else if (c4)

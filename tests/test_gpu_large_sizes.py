@@ -120,3 +120,24 @@ def test_qdwconv2d_with_tensors_beyond_4gib():
                                     c["z_out"], c["act_min"], c["act_max"], bias=c["bias"])
             assert_same(host(y[n:n + 1, 50:54]), want, f"qdwconv2d stride {stride} image {n} rows 50..53")
         del y
+
+
+@pytest.mark.parametrize("N,H,W,C,stride", [
+    (90, 57, 56, 80, 1), (40, 113, 112, 96, 2),        # matrix-unit kernel: beyond 42 MB of inputs and outputs with plain stores
+    (2100, 24, 24, 112, 1), (900, 28, 27, 176, 2),     # patch kernel: beyond 128 MB
+])
+def test_depthwise_layers_with_plain_stores(N, H, W, C, stride):
+    # too large for the oracle as a whole: the first, middle and last images
+    rng = np.random.default_rng(N + C)
+    w = rng.integers(-128, 128, (3, 3, C)).astype(np.int8)
+    z_w = rng.integers(-128, 128, C).astype(np.int32)
+    mult, shift = oracle.quantize_multipliers(rng.uniform(40.0, 120.0, C) / (9 * 255.0 * 128))
+    bias = rng.integers(-2000, 2000, C).astype(np.int32)
+    x = torch.randint(0, 256, (N, H, W, C), dtype=torch.uint8, device="cuda:0")
+    some = torch.tensor([0, N // 2, N - 1], device="cuda:0")
+    tail = ((stride, stride), (1, 1), dev(mult), dev(shift), 120, 0, 255)
+    for zw in (None, z_w):
+        want = oracle.qdwconv2d(host(x[some]), 131, w, (stride, stride), (1, 1), mult, shift, 120, 0, 255, bias=bias, z_w=zw)
+        got = qnn.qdwconv2d(x, 131, dev(w), *tail, bias=dev(bias)) if zw is None else qnn.qdwconv2d_asym(x, 131, dev(w), dev(zw), *tail, bias=dev(bias))
+        assert_same(host(got[some]), want, f"{N}x{H}x{W}x{C} stride {stride}, z_w {zw is not None}")
+    assert len(np.unique(want)) > 16
