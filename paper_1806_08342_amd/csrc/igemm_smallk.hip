@@ -15,10 +15,12 @@ bool small_shape(int64_t M, int64_t N, int64_t K, bool conv, bool int4)
     if (!tuning().small || tuning().bres == 1) return false; // tuning aids: reach the other kernels on small shapes
     if (!conv && !int4 && K >= 4096) return false;
     const int64_t wgs = ((N + 15) / 16) * ((M + 31) / 32);
-    // 4-bit weights: a fourth workgroup does not fit a CU, and past 768 the last few run alone.  With a partial K-step on
-    // top the tiles win where they take K as it is and it is not long (784 workgroups: K = 288 5.3 us against 6.7 here, 384
-    // 5.4 / 6.4, 576 6.1 / 7.1, 704 6.6 / 7.1; but K = 512 5.9 / 5.4, 768 6.9 / 5.7, 264 7.9 / 7.1; 768: 5.4 / 4.7 for 384)
-    if (int4 && wgs > 768 && K > 256 && K <= 704 && (K % 32) == 0 && (K % 256) != 0) return false;
+    // 4-bit weights: rows of 8 bytes take a branch around every load (5.3-9.4 us against 4.2-4.9 of the short-K kernel)
+    if (int4 && K < 32) return false;
+    // ... and a fourth workgroup does not fit a CU, so that past 768 the last few run alone: for some K the other kernels
+    // are ahead then (784 workgroups, here / there: K = 32 5.4-5.7 / 4.3-4.9, 288 5.6 / 5.3, 384 5.6 / 5.3; but 64 5.7-5.9 /
+    // 5.4-6.2, 264 7.3 / 7.9, 448 5.6 / 5.6, 512 5.4 / 5.9, 704 6.0 / 6.7)
+    if (int4 && wgs > 768 && (K <= 48 || (K > 256 && K <= 384 && (K % 32) == 0))) return false;
     return wgs <= 800;
 }
 

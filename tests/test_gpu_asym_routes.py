@@ -73,10 +73,11 @@ def test_depthwise_zero_points_beyond_a_byte(N, H, W, C, stride, pad):
 
 @pytest.mark.parametrize("M,N,K,bits", [
     (1, 16, 16, 8), (64, 70, 129, 8), (33, 40, 258, 4), (700, 48, 384, 8),      # few rows, with tails in K
+    (9, 20, 208, 8), (500, 48, 80, 8), (90, 33, 96, 4), (40, 50, 1120, 4),       # ... of whole 16-byte pieces
     (5000, 30, 8, 8), (5001, 33, 24, 4), (4100, 96, 40, 8), (3000, 200, 72, 4), (2999, 130, 120, 8), (7001, 260, 256, 8),
     (6000, 131, 248, 4),                                                         # short K, partial steps
     (3000, 700, 320, 8), (2500, 900, 640, 4), (9000, 2100, 448, 8),              # large tiles
-    (1500, 1100, 323, 8), (2100, 1300, 402, 4),                                  # staged tiles, zero-padded K
+    (1500, 1100, 323, 8), (2100, 1300, 402, 4),                                  # staged tiles
 ])
 def test_matrix_routes(M, N, K, bits):
     rng = np.random.default_rng(M + N + K)

@@ -41,6 +41,7 @@ def test_few_rows_misaligned_row_pitch():
 @pytest.mark.parametrize("small", ["1", "0"])
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(65, 16, 64), (300, 130, 256), (1000, 40, 72), (97, 100, 514), (800, 256, 1152), (129, 90, 2306),
+                                   (200, 70, 16), (333, 50, 48), (90, 33, 176), (70, 20, 1056),  # partial K-steps of whole 16-byte pieces
                                    (6272, 64, 384), (6145, 60, 352), (6144, 64, 384), (1570, 250, 512)])  # around 768 workgroups of 4-bit weights
 def test_small_launches_and_the_kernels_they_replace(tuning, small, M, N, K, bits):
     tuning.setenv("QNN_SMALL", small)
