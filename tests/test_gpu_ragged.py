@@ -1,6 +1,6 @@
 """Products and convolutions whose sizes divide nothing: K that is no multiple of 64 (chunks beyond K), rows that are no
-whole 16-byte chunks (zero-padded copies in the workspace, and the route without a workspace), K groups inside a
-workgroup, stems on images of any width."""
+whole 16-byte chunks (zero-padded copies in the workspace, and the route without a workspace), stems on images of any
+width."""
 import numpy as np
 import pytest
 import torch
@@ -73,3 +73,45 @@ def test_stems_of_any_width(H, W, cin, k, stride):
         got = qnn.qconv2d(x, c["z_x"], dev(c["w"]), c["stride"], c["pad"], dev(c["mult"]), dev(c["shift"]), c["z_out"], c["act_min"], c["act_max"],
                           bias=dev(c["bias"]))
         assert_same(host(got), want, f"stem {H}x{W}x{cin} k{k} s{stride}")
+
+
+@pytest.mark.parametrize("z_a", [128, 7])
+def test_split_products_with_a_partial_last_step(z_a):
+    # the last of the K ranges ends in a partial step
+    assert qnn.qgemm_workspace_bytes(66, 2000, 8016) > 0
+    _gemm(66, 2000, 8016, 8, z_a)
+
+
+@pytest.mark.parametrize("bits,K", [(8, 528), (8, 1056), (8, 1072), (4, 544), (4, 1056)])
+@pytest.mark.parametrize("tile", ["dma64x64", "dma128x128", "dma256x256", "dma256x128", "dma256x64"])
+def test_every_pipelined_tile_with_a_partial_step(tuning, tile, bits, K):
+    tuning.setenv("QNN_FORCE_TILE", tile)
+    _gemm(300, 270, K, bits, 9)
+    if bits == 8 and tile in ("dma64x64", "dma128x128"):
+        tuning.setenv("QNN_FORCE_SPLIT", "3")
+        assert qnn.qgemm_workspace_bytes(300, 270, K) > 0
+        _gemm(300, 270, K, bits, 9)
+
+
+@pytest.mark.parametrize("tile", ["dma64x64", "dma128x128", "dma256x256", "dma256x128", "dma256x64"])
+@pytest.mark.parametrize("bits,cin,split", [(8, 48, 1), (8, 112, 2), (4, 32, 1), (4, 96, 1)])
+def test_convolutions_on_every_pipelined_tile_with_a_partial_step(tuning, tile, bits, cin, split):
+    tuning.setenv("QNN_FORCE_TILE", tile)
+    tuning.setenv("QNN_FORCE_SPLIT", str(split))
+    layer = workloads.Layer("t", "conv", 13, 15, cin, 130, k=3, stride=1, pad=1, act="relu6", weight_bits=bits)
+    c = synth.conv_case(layer, 2, 7300 + cin, oracle)
+    assert (9 * cin) % 64 != 0
+    for z_x in (c["z_x"], 131):
+        want = oracle.qconv2d(c["x"], z_x, c["w"], c["stride"], c["pad"], c["mult"], c["shift"], c["z_out"], c["act_min"], c["act_max"], bias=c["bias"])
+        got = qnn.qconv2d(dev(c["x"]), z_x, dev(c.get("w_packed", c["w"])), c["stride"], c["pad"], dev(c["mult"]), dev(c["shift"]), c["z_out"],
+                          c["act_min"], c["act_max"], bias=dev(c["bias"]), weight_bits=bits)
+        assert_same(host(got), want, f"{tile} bits={bits} cin={cin} z_x={z_x}")
+
+
+@pytest.mark.parametrize("M,N,K", [(2600, 2100, 352), (5000, 2300, 544)])  # 4-bit weights on the 128x128 and 256x256 tiles by default
+def test_ragged_4bit_products_on_the_large_tiles(M, N, K):
+    c = synth.gemm_case(M, N, K, 6100 + M, oracle, weight_bits=4)
+    rows = np.r_[0:8, M // 2:M // 2 + 8, M - 8:M]
+    want = oracle.qgemm(c["A"][rows], 9, c["Bt"], c["mult"], c["shift"], c["z_out"], 0, 255)
+    got = qnn.qgemm(dev(c["A"]), 9, dev(c["Bt_packed"]), dev(c["mult"]), dev(c["shift"]), c["z_out"], 0, 255, weight_bits=4)
+    assert_same(host(got[torch.from_numpy(rows).to("cuda:0")]), want, f"{M}x{N}x{K}")
