@@ -128,9 +128,10 @@ qnn_status qnn_qgemm(const uint8_t *A, int64_t lda, int32_t z_a, const void *B, 
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and same
  * result as qnn_qgemm; the scratch memory (partial sums of products whose K is divided over several
  * workgroups) is a static 16 MiB device array inside the library, which every GPU the library runs on
- * holds until the process ends.  The call allocates nothing.  A product whose plan asks for more than
- * 16 MiB of scratch (qnn_qgemm_workspace_bytes) is rejected with QNN_EUNSUPPORTED and a message in
- * qnn_last_error().  The array is shared by all calls on one GPU and keeps the last call's contents
+ * holds until the process ends.  The call allocates nothing.  A product whose partial sums ask for more than
+ * 16 MiB is rejected with QNN_EUNSUPPORTED and a message in qnn_last_error() (only tuning switches lead there); the
+ * padded copies of ragged operands that qnn_qgemm_workspace_bytes also counts are not made here, such a product takes the
+ * route without them.  The array is shared by all calls on one GPU and keeps the last call's contents
  * (every call writes what it reads, nothing needs clearing): calls that overlap on one GPU -- other
  * streams, concurrent graph branches -- race on it; order them, or use qnn_qgemm with separate
  * workspaces.  The device address of the array is looked up at the first call on each device (make
@@ -253,10 +254,10 @@ qnn_status qnn_qconv2d_add(const uint8_t *x, int N, int H, int W, int Cin, int32
  * post-training experiments of Sec. 3.1 find most accurate).  The sum becomes
  *   sum_k (A[m][k] - z_a) * (B[k][n] - z_w[n])
  * = sum_k A*B - z_a * sum_k B[k][n] - z_w[n] * sum_k A[m][k] + K * z_a * z_w[n]        (eq. 5-6)
- * The activation sums of the third term are shared by all channels: one extra pass over A forms
- * them per output row (for a convolution: over the taps inside the image; padding holds the code
- * z_x and adds nothing), into the caller's workspace (required here: QNN_EINVAL when it is NULL,
- * misaligned or smaller than the workspace query says).
+ * The activation sums of the third term are shared by all channels; the kernels form them while they read A
+ * (for a convolution: over the taps inside the image; padding holds the code z_x and adds nothing).
+ * workspace is required here (QNN_EINVAL when it is NULL, misaligned or smaller than the workspace query says),
+ * though nothing is written to it at present.
  * z_w: DEVICE int32[N] (resp. [Cout]), each in [-128, 127] for 8-bit and [-8, 7] for 4-bit weights.
  * K (resp. kh*kw*Cin) <= 32768, which keeps |sum| below 2^31.  Everything else as in qnn_qgemm /
  * qnn_qconv2d. */

@@ -122,9 +122,9 @@ static Plan choose_plan(int64_t M, int64_t N, int64_t K, bool dma_ok, bool int4,
     return Plan{(N <= 64 || M <= 64) ? TILE_64x64 : TILE_128x128, 1};
 }
 
-// Scratch memory comes from the caller (`workspace` of the entry points): the int32 activation row
-// sums of the asymmetric-weight entry points (M values; asked for, no longer used), or zero-padded copies of operands that are no whole
-// 16-byte chunks, and behind them the partial sums of split-K (splits x M x N values).
+// Scratch memory comes from the caller (`workspace` of the entry points): zero-padded copies of operands that are no
+// whole 16-byte chunks, and behind them the partial sums of split-K (splits x M x N values).  The asymmetric-weight entry
+// points ask for 4 bytes per row and write nothing there.
 constexpr uint64_t kMaxSplitBytes = (uint64_t)1 << 40;
 static size_t rowsum_bytes(int64_t M) { return (size_t)((M * 4 + 255) / 256 * 256); }
 

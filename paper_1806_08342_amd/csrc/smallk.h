@@ -5,7 +5,7 @@
 // organised around memory-level parallelism, not MFMA rate: one workgroup owns 16 output columns of up to
 // 64 rows, its 4, 8 or 16 waves split K between them, and every wave keeps a whole batch of K-steps in flight.
 // On 64x64 tiles the same K loop is a serial chain of barriers, 0.2 us per 64 k behind 4 us of set-up (7x7x512
-// -> 512, 3x3: 31 us; 196 x 512 x 512: 5.8 us; here 4 and 3.4).
+// -> 512, 3x3: 31 us; 196 x 512 x 512: 5.8 us; here 6.0 and 3.0).
 // The roles of the operands are swapped with respect to the big kernel: the weights are the A operand of
 // v_mfma_i32_16x16x64_i8 (16 columns n x 64 k) and the activations the B operand (16 rows m), so a lane
 // ends up with 4 consecutive output columns of one row m: one dword store, no transposition.
