@@ -199,10 +199,9 @@ __device__ __forceinline__ AddOut make_add_out(const AddParams &p)
     return o;
 }
 
-// one code of the product + one of the residual -> one output code
-template <bool FUSED> __device__ __forceinline__ uint32_t add_code1(uint32_t m, uint32_t r, const int32_t *tab, const AddOut &o)
+// the add of two rescaled values -> one output code
+template <bool FUSED> __device__ __forceinline__ uint32_t add_value1(int32_t tm, int32_t tr, const AddOut &o)
 {
-    const int32_t tm = tab[m], tr = tab[256 + r];
     if constexpr (FUSED) {
         return (uint32_t)rescale_fused(tm + tr, o.fo);
     } else {
@@ -212,6 +211,24 @@ template <bool FUSED> __device__ __forceinline__ uint32_t add_code1(uint32_t m, 
     }
 }
 
+// one rescaled value of the product + four of the residual -> four output codes
+template <bool FUSED> __device__ __forceinline__ uint32_t add_values4(int32_t tm, const int32_t (&tr)[4], const AddOut &o)
+{
+    uint32_t x = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if constexpr (FUSED) x = shift_into_byte(x, rescale_fused_w(tm + tr[e], o.fo), o.fo.n1, e);
+        else x |= add_value1<false>(tm, tr[e], o) << (8 * e);
+    }
+    return x;
+}
+
+// one code of the product + one of the residual -> one output code
+template <bool FUSED> __device__ __forceinline__ uint32_t add_code1(uint32_t m, uint32_t r, const int32_t *tab, const AddOut &o)
+{
+    return add_value1<FUSED>(tab[m], tab[256 + r], o);
+}
+
 // four codes of the product (bytes of m) + four of the residual (bytes of r) -> four output codes
 template <bool FUSED> __device__ __forceinline__ uint32_t add_codes4(uint32_t m, uint32_t r, const int32_t *tab, const AddOut &o)
 {
@@ -219,13 +236,8 @@ template <bool FUSED> __device__ __forceinline__ uint32_t add_codes4(uint32_t m,
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int32_t tm = tab[(m >> (8 * e)) & 0xffu], tr = tab[256 + ((r >> (8 * e)) & 0xffu)];
-        if constexpr (FUSED) {
-            x = shift_into_byte(x, rescale_fused_w(tm + tr, o.fo), o.fo.n1, e);
-        } else {
-            int64_t u = (int64_t)tm + (int64_t)tr;
-            u = u > INT32_MAX ? INT32_MAX : (u < INT32_MIN ? INT32_MIN : u);
-            x |= (uint32_t)(clamp_i32(o.lo_rel, o.hi_rel, rescale_general((int32_t)u, o.po)) + o.z_out) << (8 * e);
-        }
+        if constexpr (FUSED) x = shift_into_byte(x, rescale_fused_w(tm + tr, o.fo), o.fo.n1, e);
+        else x |= add_value1<false>(tm, tr, o) << (8 * e);
     }
     return x;
 }

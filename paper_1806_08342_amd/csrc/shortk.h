@@ -100,13 +100,21 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         __syncthreads();
         if constexpr (use_pairs) {
             const AddOut ao = make_add_out(g.add);
-            // entry [m][r] = code of the sum; a lane fills 4 consecutive r of one m per step
-            for (int q = threadIdx.x; q < 65536 / 4; q += 512) {
-                const uint32_t m = (uint32_t)q >> 6, r0 = ((uint32_t)q & 63u) * 4u;
-                const uint32_t mm = m * 0x01010101u, rr = (r0 * 0x01010101u) + 0x03020100u;
-                reinterpret_cast<uint32_t *>(pair_tab)[q] =
-                    ao.fused ? add_codes4<true>(mm, rr, tab, ao) : add_codes4<false>(mm, rr, tab, ao);
-            }
+            // Entry [m][r] = code of the sum, at byte 256 m + (r ^ 4 (m % 64)): the bank of a gather then depends on both
+            // codes.  (With r alone choosing the bank, the lanes whose residual is the code of zero, half of them behind a
+            // ReLU, met in one bank.)  A lane fills the same 4 consecutive r for every m of its wave, so that the value of
+            // m is one broadcast read and those of r stay in registers.
+            const int r0 = (int)(threadIdx.x & 63u) * 4;
+            int32_t tr[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tr[e] = tab[256 + r0 + e];
+            auto fill = [&](auto fused_tag) {
+                for (int m = threadIdx.x >> 6; m < 256; m += WAVES)
+                    reinterpret_cast<uint32_t *>(pair_tab)[m * 64 + ((threadIdx.x ^ (uint32_t)m) & 63u)] =
+                        add_values4<decltype(fused_tag)::value>(tab[m], tr, ao);
+            };
+            if (ao.fused) fill(std::true_type{});
+            else fill(std::false_type{});
             __syncthreads();
         }
     }
@@ -279,7 +287,8 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         if constexpr (use_pairs) {
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                const uint32_t i01 = __builtin_amdgcn_perm(v[d], r[d], 0x05010400u), i23 = __builtin_amdgcn_perm(v[d], r[d], 0x07030602u);
+                const uint32_t rs = r[d] ^ ((v[d] << 2) & 0xfcfcfcfcu); // the table's order
+                const uint32_t i01 = __builtin_amdgcn_perm(v[d], rs, 0x05010400u), i23 = __builtin_amdgcn_perm(v[d], rs, 0x07030602u);
                 const uint32_t t0 = pair_tab[i01 & 0xffffu], t1 = pair_tab[i01 >> 16], t2 = pair_tab[i23 & 0xffffu], t3 = pair_tab[i23 >> 16];
                 y[d] = t0 | (t1 << 8) | (t2 << 16) | (t3 << 24);
             }
