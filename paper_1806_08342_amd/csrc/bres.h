@@ -73,7 +73,9 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
     __syncthreads(); // the only workgroup barrier
 
     // ---- per-column epilogue constants (as in shortk.h)
-    int32_t c_mult[NB], c_corr[NB], c_c[NB], c_n1[NB], c_lo[NB], c_hi[NB], c_shift[NB];
+    ChannelRescale c_r[NB];
+    int32_t c_mult[NB], c_corr[NB], c_shift[NB]; // general form
+    const bool ties = rescale_ties(g.lo_rel);
     bool fused_ok = g.small_acc >= 2;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -89,15 +91,10 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
             colsum += __shfl_xor(colsum, 32);
         }
         const int32_t b = g.bias ? g.bias[n] : 0, mu = g.mult[n], sf = g.shift[n];
-        fused_ok = fused_ok && sf >= 1 && sf <= 20 && b > -(1 << 27) && b < (1 << 27);
-        const int nn = (sf >= 1 && sf <= 20) ? sf : 1;
-        c_mult[j] = mu;
+        fused_ok = fused_ok && channel_rescale_ok(mu, sf, ties) && b > -(1 << 27) && b < (1 << 27);
         c_corr[j] = b + (128 - g.z_a) * colsum;
-        c_n1[j] = nn + 1;
-        c_c[j] = 2 * ((1 << (nn - 1)) + (g.z_out << nn)) + 1;
-        c_lo[j] = (g.lo_rel + g.z_out) << (nn + 1);
-        c_hi[j] = ((g.hi_rel + g.z_out + 1) << (nn + 1)) - 1;
-        c_shift[j] = sf;
+        c_mult[j] = mu, c_shift[j] = sf;
+        c_r[j] = make_channel_rescale(mu, sf, c_corr[j], g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     }
     const bool fused = __all(fused_ok);
 
@@ -212,7 +209,7 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
     };
 
     auto walk = [&](auto fused_tag) {
-        constexpr bool FUSED = decltype(fused_tag)::value > 0, TIES = decltype(fused_tag)::value == 1; // 2: without the tie term
+        using Mode = RescaleModeTraits<decltype(fused_tag)::value>;
         const int chunks = (KS + KC - 1) / KC;
         i32x4 fa0[KC], fa1[KC], fa2[KC]; // the chunk being computed and the next two, in flight
         i32x16 acc[NB];
@@ -299,18 +296,14 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
                     const RescaleParams rp = make_rescale(c_mult[j], c_shift[j]);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
+                        const int32_t a[4] = {acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
                         uint32_t x = 0;
+                        if constexpr (Mode::kFused) {
+                            x = channel_codes4<Mode::kTies, Mode::kFull>(a, c_r[j]);
+                        } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int32_t a = acc[j][4 * q + e];
-                            if constexpr (FUSED) {
-                                const int32_t t = __mulhi((int32_t)((uint32_t)(a + c_corr[j]) << 2), c_mult[j]);
-                                const int32_t w = fused_w_from_t<TIES>(t, c_c[j]);
-                                x = shift_into_byte(x, med3_i32(w, c_lo[j], c_hi[j]), c_n1[j], e);
-                            } else {
-                                const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general(a + c_corr[j], rp)) + g.z_out;
-                                x |= (uint32_t)y << (8 * e);
-                            }
+                            for (int e = 0; e < 4; ++e)
+                                x |= (uint32_t)(clamp_i32(g.lo_rel, g.hi_rel, rescale_general(a[e] + c_corr[j], rp)) + g.z_out) << (8 * e);
                         }
                         put(j, q, x);
                     }
@@ -331,9 +324,7 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
         }
         if (rb_stored >= 0) store_block(rb_stored);
     };
-    if (!fused) walk(std::integral_constant<int, 0>{});
-    else if (g.lo_rel < 0) walk(std::integral_constant<int, 1>{});
-    else walk(std::integral_constant<int, 2>{}); // act_min >= z_out: the clamp absorbs the tie term
+    with_rescale_mode(fused, g.z_out, g.lo_rel, g.hi_rel, walk);
 }
 
 } // namespace qnn

@@ -58,8 +58,8 @@ __global__ void __launch_bounds__(256) calibrate_copy_kernel(const u32x4 *__rest
 }
 
 // Every lane rescales 16 independent accumulators per round with the instruction sequence the
-// epilogues use when act_min >= z_out (add + shift, high multiply, add, 3-way median, shift into a
-// byte of the packed dword) and feeds the packed dwords back into the accumulators, so that nothing
+// epilogues use when act_min >= z_out and the output range is 0 ... 255 (64-bit multiply-add per value, shift,
+// saturation and packing two at a time) and feeds the packed dwords back into the accumulators, so that nothing
 // can be hoisted out of the loop.  No memory traffic inside the loop.
 __global__ void __launch_bounds__(256) calibrate_rescale_kernel(int iters, int32_t mult, int32_t shift, int32_t *sink)
 {
@@ -71,17 +71,13 @@ __global__ void __launch_bounds__(256) calibrate_rescale_kernel(int iters, int32
         h ^= h >> 15, h *= 2246822519u, h ^= h >> 13;
         acc[i] = (int32_t)(h >> 10) - (1 << 21); // |acc| < 2^21, as after a K <= 256 reduction
     }
-    const FusedRescale p = make_fused(mult, shift, (int32_t)(id & 1023u), 3, 3, 255);
+    const ChannelRescale p = make_channel_rescale(mult, shift, (int32_t)(id & 1023u), 0, 0, 255, false);
     for (int it = 0; it < iters; ++it) {
         uint32_t packed[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            uint32_t x = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                x = shift_into_byte(x, rescale_fused_w<false>(acc[4 * q + e], p), p.n1, e);
-            }
-            packed[q] = x;
+            const int32_t a[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+            packed[q] = channel_codes4<false, true>(a, p);
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = (acc[i] ^ (int32_t)(packed[i & 3] >> (i & 12))) & 0x3fffff; // next round's inputs

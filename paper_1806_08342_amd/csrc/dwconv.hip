@@ -390,21 +390,17 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
         }
     }
 
-    // ---- epilogue: exact rescale in its cheapest form when every channel of the wave allows it
-    // (see the comment at rescale_fused; here clamped before the final shift so that the shift
-    // writes its byte into the packed dword), else the general form
-    int32_t mu[4], cc[4], n1[4], lo[4], hi_[4], sf[4];
+    // ---- epilogue: the fused form of the rescale when every channel of the wave allows it, else the general form
+    int32_t mu[4], sf[4];
+    ChannelRescale cr[4];
+    const bool ties = rescale_ties(g.lo_rel);
     bool fused_ok = true;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         mu[j] = g.mult[c0 + j], sf[j] = g.shift[c0 + j];
         const int32_t b = g.bias ? g.bias[c0 + j] : 0;
-        fused_ok = fused_ok && sf[j] >= 1 && sf[j] <= 20 && b > -(1 << 28) && b < (1 << 28);
-        const int nn = (sf[j] >= 1 && sf[j] <= 20) ? sf[j] : 1;
-        n1[j] = nn + 1;
-        cc[j] = 2 * ((1 << (nn - 1)) + (g.z_out << nn)) + 1;
-        lo[j] = (g.lo_rel + g.z_out) << (nn + 1);
-        hi_[j] = ((g.hi_rel + g.z_out + 1) << (nn + 1)) - 1;
+        fused_ok = fused_ok && channel_rescale_ok(mu[j], sf[j], ties) && b > -(1 << 28) && b < (1 << 28);
+        cr[j] = make_channel_rescale(mu[j], sf[j], 0, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     }
     if constexpr (ZW) {
         if (!zw_bytes) return dw_direct_block(g, n, ho0, ho0 + RH, wo0, wo0 + RW, 1, c0, c0 + 4);
@@ -418,35 +414,43 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
     const bool fused = __all(fused_ok);
     uint8_t *const out_img = g.y + (int64_t)n * g.Ho * g.Wo * g.C; // scalar
     const uint32_t out_off = (uint32_t)(wo0 * g.C + c0);            // inside an output row (Wo * C < 2^31)
-    auto finish = [&](auto fused_tag) {
+    auto finish = [&](auto mode_tag) {
+        using Mode = RescaleModeTraits<decltype(mode_tag)::value>;
 #pragma unroll
         for (int r = 0; r < RH; ++r) {
             if (ho0 + r >= g.Ho) break; // scalar
             uint8_t *out = out_img + (int64_t)(ho0 + r) * g.Wo * g.C; // scalar
+            uint32_t pixel[4]; // four channels of a pixel
+            if constexpr (Mode::kFused) {
+                // the four pixels of a channel share its shift and are packed together; the 4x4 bytes are transposed then
+                uint32_t ch[4];
 #pragma unroll
-            for (int p = 0; p < RW; ++p) {
-                uint32_t packed = 0;
-                if constexpr (decltype(fused_tag)::value > 0) {
+                for (int j = 0; j < 4; ++j) {
+                    const int32_t a[4] = {acc[r][0][j], acc[r][1][j], acc[r][2][j], acc[r][3][j]};
+                    ch[j] = channel_codes4<Mode::kTies, Mode::kFull>(a, cr[j]);
+                }
+                const uint32_t lo01 = __builtin_amdgcn_perm(ch[1], ch[0], 0x05010400u), hi01 = __builtin_amdgcn_perm(ch[1], ch[0], 0x07030602u);
+                const uint32_t lo23 = __builtin_amdgcn_perm(ch[3], ch[2], 0x05010400u), hi23 = __builtin_amdgcn_perm(ch[3], ch[2], 0x07030602u);
+                pixel[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u), pixel[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+                pixel[2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), pixel[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+            } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int32_t tt = __mulhi((int32_t)((uint32_t)acc[r][p][j] << 2), mu[j]);
-                        const int32_t w = fused_w_from_t<decltype(fused_tag)::value == 1>(tt, cc[j]); // 2: without the tie term
-                        packed = shift_into_byte(packed, med3_i32(w, lo[j], hi_[j]), n1[j], j);
-                    }
-                } else {
+                for (int p = 0; p < RW; ++p) {
+                    pixel[p] = 0;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general(acc[r][p][j], make_rescale(mu[j], sf[j]))) + g.z_out;
-                        packed |= (uint32_t)y << (8 * j);
+                        pixel[p] |= (uint32_t)y << (8 * j);
                     }
                 }
-                if (wo0 + p < g.Wo) dw_store<NT>(out + (out_off + (uint32_t)(p * g.C)), packed);
             }
+#pragma unroll
+            for (int p = 0; p < RW; ++p)
+                if (wo0 + p < g.Wo) dw_store<NT>(out + (out_off + (uint32_t)(p * g.C)), pixel[p]);
         }
     };
-    if (!fused) finish(std::integral_constant<int, 0>{});
-    else if (g.lo_rel < 0) finish(std::integral_constant<int, 1>{});
-    else finish(std::integral_constant<int, 2>{}); // act_min >= z_out: the clamp absorbs the tie term
+    static_assert(RW == 4, "four pixels of a channel are packed together");
+    with_rescale_mode(fused, g.z_out, g.lo_rel, g.hi_rel, finish);
 }
 
 // Depthwise 3x3 with the multiplies on the matrix unit.
@@ -571,15 +575,12 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     const int32_t bias = (ch_ok && g.bias) ? g.bias[ch] : 0;
     const int32_t init = bias + (128 - g.z_x) * wsum;
 
-    // ---- epilogue constants of this lane's channel (see rescale_fused_w)
-    const int32_t mu = ch_ok ? g.mult[ch] : 0, sf = ch_ok ? g.shift[ch] : 1;
-    const bool fused_ok = sf >= 1 && sf <= 20 && bias > -(1 << 28) && bias < (1 << 28);
-    const int nn = (sf >= 1 && sf <= 20) ? sf : 1;
-    const int32_t n1 = nn + 1;
-    const int32_t cc = 2 * ((1 << (nn - 1)) + (g.z_out << nn)) + 1;
-    const int32_t lo = (g.lo_rel + g.z_out) << (nn + 1);
-    const int32_t hi_ = ((g.hi_rel + g.z_out + 1) << (nn + 1)) - 1;
-    const bool fused = MODE != 0 && __all(fused_ok); // wave-uniform
+    // ---- epilogue constants of this lane's channel
+    using Mode = RescaleModeTraits<MODE>;
+    const int32_t mu = ch_ok ? g.mult[ch] : 1 << 30, sf = ch_ok ? g.shift[ch] : 1;
+    const bool fused_ok = channel_rescale_ok(mu, sf, Mode::kTies) && bias > -(1 << 28) && bias < (1 << 28);
+    const ChannelRescale cr = make_channel_rescale(mu, sf, init, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, Mode::kTies);
+    const bool fused = __all(fused_ok); // wave-uniform
     if (ZW && !__all(zw_bytes)) { // the whole wave: its lanes share the matrix instructions
         dw_direct_block(g, n, hb, hb + rows, w0 + half, w0 + TP, 2, ch, ch_ok ? ch + 1 : ch);
         __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8)); // vmcnt(0): no copy may land in LDS after the wave is gone
@@ -619,7 +620,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     }
 
     // accumulators start at zero (an inline constant of the matrix instruction); bias and zero-point term join in
-    // the rescale, inside the add-and-shift that the 32-bit form needs anyway
+    // the addend of the rescale
     dw_i32x16 acc[SLOTS];
     auto reset = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
@@ -627,7 +628,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     };
     auto finish = [&](int slot) __attribute__((always_inline)) {
         // wave-uniform row base (scalar registers) + 32-bit lane offsets
-        auto with_init = [&](int32_t a) { return ZW ? __mul24(a, zp.sign) + init : (int32_t)((uint32_t)a + (uint32_t)init); };
+        auto signed_sum = [&](int32_t a) { return ZW ? __mul24(a, zp.sign) : a; };
         const int64_t row_off = ((int64_t)__builtin_amdgcn_readfirstlane((int)(out_row >> 32)) << 32) |
                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)out_row);
         uint8_t *out = g.y + row_off;
@@ -635,12 +636,10 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
         if (fused) { // one test per output row; the general form below is the rare case
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                x[q] = 0;
+                int32_t a[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int32_t tt = __mulhi((int32_t)((uint32_t)with_init(acc[slot][4 * q + e]) << 2), mu);
-                    x[q] = shift_into_byte(x[q], med3_i32(fused_w_from_t<MODE == 1>(tt, cc), lo, hi_), n1, e);
-                }
+                for (int e = 0; e < 4; ++e) a[e] = signed_sum(acc[slot][4 * q + e]);
+                x[q] = channel_codes4<Mode::kTies, Mode::kFull>(a, cr);
             }
         } else {
             const RescaleParams rp = make_rescale(mu, sf);
@@ -649,7 +648,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
                 x[q] = 0;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general(with_init(acc[slot][4 * q + e]), rp)) + g.z_out;
+                    const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general((int32_t)((uint32_t)signed_sum(acc[slot][4 * q + e]) + (uint32_t)init), rp)) + g.z_out;
                     x[q] |= (uint32_t)y << (8 * e);
                 }
             }
@@ -927,11 +926,13 @@ static qnn_status qdwconv2d_impl(const uint8_t *x, int N, int H, int W, int C, i
             g.xcd_remap = tuning().dw_xcd != 0 && (int64_t)grid.x * grid.y * grid.z < (1ll << 31);
             auto launch = [&](auto zw, auto nt) {
                 constexpr bool ZW = decltype(zw)::value, NT = decltype(nt)::value;
-                const bool absorbs = g.lo_rel >= 0; // the clamp absorbs the tie term
-                if (stride_h == 1 && absorbs) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 2, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-                else if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, 1, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-                else if (absorbs) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 2, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
-                else hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, 1, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                with_rescale_mode(true, g.z_out, g.lo_rel, g.hi_rel, [&](auto mode) {
+                    constexpr int MODE = decltype(mode)::value;
+                    if constexpr (MODE != RESCALE_GENERAL) { // (channels that need that form are found in the kernel)
+                        if (stride_h == 1) hipLaunchKernelGGL((dwconv3x3_mfma_kernel<1, MODE, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                        else hipLaunchKernelGGL((dwconv3x3_mfma_kernel<2, MODE, ZW, NT>), grid, dim3(256), 0, s, g, seg_rows, tiles_w, cblocks);
+                    }
+                });
             };
             if (dw_stream_out(g, true)) z_w ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
             else z_w ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});

@@ -137,6 +137,21 @@ __device__ __forceinline__ void load_a_chunk(const IgemmArgs &g, const ARow &r, 
     }
 }
 
+// 16 weights from 8 packed bytes, each times 16
+__device__ __forceinline__ i32x4 expand_int4(u32x2 raw)
+{
+    // byte j of raw holds element 2j in its low and element 2j+1 in its high nibble; each element
+    // becomes one byte holding 16 times its value (the nibble in the high half of the byte)
+    i32x4 w;
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        const uint32_t even = (raw[d] << 4) & 0xF0F0F0F0u, odd = raw[d] & 0xF0F0F0F0u;
+        w[2 * d] = (int32_t)__builtin_amdgcn_perm(odd, even, 0x05010400u);
+        w[2 * d + 1] = (int32_t)__builtin_amdgcn_perm(odd, even, 0x07030602u);
+    }
+    return w;
+}
+
 // 16 consecutive k of one B column as 4 dwords of int8 (B_INT4: the values times 16)
 template <int B_MODE, int VEC>
 __device__ __forceinline__ void load_b_chunk(const IgemmArgs &g, int n, int kc, uint32_t *w)
@@ -244,7 +259,8 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
     bool fast_ok = g.small_acc >= 1 && (!ZW || g.K <= 4096), fused_ok = g.small_acc >= 2 && (!ZW || g.K <= 2048);
     int32_t corr[TN];
     RescaleParams rp[TN];
-    FusedRescale fr[TN];
+    ChannelRescale fr[TN];
+    const bool ties = rescale_ties(g.lo_rel);
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         int32_t cs = colsum[j] + __shfl_xor(colsum[j], 32);
@@ -253,10 +269,10 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
         corr[j] = b + (128 - g.z_a) * cs;
         if constexpr (ZW) corr[j] = (int32_t)((uint32_t)corr[j] - (uint32_t)cp.zw[j] * (uint32_t)(k_counted * (128 - g.z_a))); // rowsum counts code - 128
         rp[j] = make_rescale(mu, sf);
-        // |acc + corr| < 2^30 for the 64-bit fast form, < 2^29 for the fused 32-bit form
+        // |acc + corr| < 2^30 for the fast form, < 2^29 for the fused forms
         fast_ok = fast_ok && sf >= 0 && b > -(1 << 28) && b < (1 << 28);
-        fused_ok = fused_ok && sf >= 1 && sf <= 20 && b > -(1 << 27) && b < (1 << 27);
-        fr[j] = make_fused(mu, sf, corr[j], g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out);
+        fused_ok = fused_ok && channel_rescale_ok(mu, sf, ties) && b > -(1 << 27) && b < (1 << 27);
+        fr[j] = make_channel_rescale(mu, sf, corr[j], g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     }
     const bool fast = __all(fast_ok), fused = __all(fused_ok);
     // A lane holds, for one column, the rows 8q + 4*half + {0,1,2,3} (q = 0..3) of each 32x32
@@ -312,19 +328,10 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
     auto pack_values = [&](const int32_t (&y)[4]) {
         return (uint32_t)y[0] | ((uint32_t)y[1] << 8) | ((uint32_t)y[2] << 16) | ((uint32_t)y[3] << 24);
     };
-    if (fused && g.lo_rel >= 0) { // act_min >= z_out: the clamp absorbs the tie term
-        run([&](const int32_t (&a)[4], int j) {
-            uint32_t x = 0;
-#pragma clang loop unroll(full)
-            for (int e = 0; e < 4; ++e) x = shift_into_byte(x, rescale_fused_w<false>(a[e], fr[j]), fr[j].n1, e);
-            return x;
-        });
-    } else if (fused) {
-        run([&](const int32_t (&a)[4], int j) {
-            uint32_t x = 0;
-#pragma clang loop unroll(full)
-            for (int e = 0; e < 4; ++e) x = shift_into_byte(x, rescale_fused_w<true>(a[e], fr[j]), fr[j].n1, e);
-            return x;
+    if (fused) {
+        with_rescale_mode(true, g.z_out, g.lo_rel, g.hi_rel, [&](auto mode_tag) {
+            using Mode = RescaleModeTraits<decltype(mode_tag)::value>;
+            if constexpr (Mode::kFused) run([&](const int32_t (&a)[4], int j) { return channel_codes4<Mode::kTies, Mode::kFull>(a, fr[j]); });
         });
     } else if (fast) {
         run([&](const int32_t (&a)[4], int j) {

@@ -110,20 +110,6 @@ __device__ __forceinline__ bool assign_tile(int slot, int tiles_m, int tiles_n, 
 // consecutive rows conflict-free.  Waves without a B segment of their own (narrow tiles) fetch
 // the constant chunk into the unused half of the B area, so that every wave issues the same
 // number of loads per K-step.
-__device__ __forceinline__ i32x4 expand_int4(u32x2 raw)
-{
-    // byte j of raw holds element 2j in its low and element 2j+1 in its high nibble; each element
-    // becomes one byte holding 16 times its value (the nibble in the high half of the byte)
-    i32x4 w;
-#pragma unroll
-    for (int d = 0; d < 2; ++d) {
-        const uint32_t even = (raw[d] << 4) & 0xF0F0F0F0u, odd = raw[d] & 0xF0F0F0F0u;
-        w[2 * d] = (int32_t)__builtin_amdgcn_perm(odd, even, 0x05010400u);
-        w[2 * d + 1] = (int32_t)__builtin_amdgcn_perm(odd, even, 0x07030602u);
-    }
-    return w;
-}
-
 // KTAIL: K need not be a multiple of 64.  Chunks of B beyond K are fetched from a chunk of zeros, chunks
 // of A from the row's last chunk (any bytes do: they meet zero weights).
 template <int BM, int BN, int WM, int WN, int A_MODE, int NSTAGE, bool SPLIT = false, bool ZW = false, bool B4 = false,

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/qnn.h"
 
 namespace qnn {
@@ -156,6 +158,87 @@ __device__ __forceinline__ int32_t med3_i32(int32_t v, int32_t lo, int32_t hi)
     return r;
 }
 
+// The epilogues' form of the rescale, per output channel.  With a = acc + corr and n = shift as above, the two nested
+// floors are one: out = floor((a * mult + c * 2^30) / 2^(31 + n)), so that
+//   no tie term (see fused_w_from_t):  w = hi32(acc * mult + (corr * mult + c * 2^30)),               out = w >> (n - 1)
+//   tie term:  w = hi32(2 a * mult + c * 2^31 - 2^32 [a < 0]),                                         out = w >> n
+// with everything that does not depend on acc in one 64-bit addend of the multiply-add (v_mad_i64_i32 runs at the rate of
+// v_mul_hi_i32).  2 mult as a signed 32-bit factor is 2 mult - 2^32 (mult >= 2^30, as the encoding has it), which the
+// extra `acc` in the high half makes up for; the tie term comes in as the carry of that addition:
+//   w = hi32(acc * (2 mult - 2^32) + (2 corr * mult + c * 2^31 - 2^32)) + acc + [acc >= -corr].
+// v_ashr_pk_u8_i32 shifts, saturates to 0 ... 255 and packs two values; a narrower output range is clamped before it.
+// Cycles per wave and output: 8.6 without tie term, 17.1 with it, 4.4 more for a narrower range; as add / mul_hi / add /
+// med3 / shift into a byte they were 20.6 and 27.
+// Valid under the conditions of FusedRescale, with the tie term for mult >= 2^30 only.
+struct ChannelRescale {
+    int32_t mult, ncorr, sh, lo, hi; // lo / hi: bounds of w
+    int64_t add;
+};
+
+__device__ __forceinline__ bool channel_rescale_ok(int32_t mult, int32_t shift, bool ties) { return shift >= 1 && shift <= 20 && (!ties || mult >= (1 << 30)); }
+
+__device__ __forceinline__ ChannelRescale make_channel_rescale(int32_t mult, int32_t shift, int32_t corr, int32_t z_out, int32_t act_min,
+                                                               int32_t act_max, bool ties)
+{
+    const int nn = (shift >= 1 && shift <= 20) ? shift : 1; // callers check the range; keep shifts defined
+    const int32_t c = (1 << nn) + (z_out << (nn + 1)) + 1; // below 2^30
+    const int64_t at_t = (int64_t)corr * mult + (int64_t)(((uint64_t)(uint32_t)(c >> 2) << 32) | (uint32_t)((uint32_t)c << 30));
+    ChannelRescale r;
+    r.mult = ties ? (int32_t)((uint32_t)mult << 1) : mult;
+    r.ncorr = -corr;
+    r.add = ties ? 2 * at_t - ((int64_t)1 << 32) : at_t;
+    r.sh = ties ? nn : nn - 1;
+    r.lo = act_min << r.sh;
+    r.hi = ((act_max + 1) << r.sh) - 1;
+    return r;
+}
+
+template <bool TIES> __device__ __forceinline__ int32_t channel_w(int32_t acc, const ChannelRescale &r)
+{
+    const int32_t hi = (int32_t)(((int64_t)acc * (int64_t)r.mult + r.add) >> 32);
+    if constexpr (TIES) return (int32_t)((uint32_t)hi + (uint32_t)acc + (acc >= r.ncorr ? 1u : 0u));
+    else return hi;
+}
+
+// four values w of one channel -> four packed codes.  FULL: the output range is 0 ... 255
+template <bool FULL> __device__ __forceinline__ uint32_t channel_pack4(int32_t w0, int32_t w1, int32_t w2, int32_t w3, const ChannelRescale &r)
+{
+    if constexpr (!FULL) w0 = med3_i32(w0, r.lo, r.hi), w1 = med3_i32(w1, r.lo, r.hi), w2 = med3_i32(w2, r.lo, r.hi), w3 = med3_i32(w3, r.lo, r.hi);
+    uint32_t x;
+    asm("v_ashr_pk_u8_i32 %0, %1, %2, %3" : "=v"(x) : "v"(w0), "v"(w1), "v"(r.sh));
+    asm("v_ashr_pk_u8_i32 %0, %1, %2, %3 op_sel:[0,0,0,1]" : "+v"(x) : "v"(w2), "v"(w3), "v"(r.sh)); // the upper half
+    return x;
+}
+
+// four accumulators of one channel -> four packed codes, in a fused form
+template <bool TIES, bool FULL> __device__ __forceinline__ uint32_t channel_codes4(const int32_t (&acc)[4], const ChannelRescale &r)
+{
+    return channel_pack4<FULL>(channel_w<TIES>(acc[0], r), channel_w<TIES>(acc[1], r), channel_w<TIES>(acc[2], r), channel_w<TIES>(acc[3], r), r);
+}
+
+// Forms of an epilogue: the choice is made once per wave (or launch), outside its loops.
+enum RescaleMode { RESCALE_GENERAL, RESCALE_TIES, RESCALE_PLAIN, RESCALE_TIES_FULL, RESCALE_PLAIN_FULL };
+template <int MODE> struct RescaleModeTraits {
+    static constexpr bool kFused = MODE != RESCALE_GENERAL;
+    static constexpr bool kTies = MODE == RESCALE_TIES || MODE == RESCALE_TIES_FULL;
+    static constexpr bool kFull = MODE == RESCALE_TIES_FULL || MODE == RESCALE_PLAIN_FULL;
+};
+template <int MODE> using RescaleTag = std::integral_constant<int, MODE>;
+
+// act_min >= z_out (lo_rel >= 0): the clamp absorbs the tie term
+__host__ __device__ __forceinline__ bool rescale_ties(int32_t lo_rel) { return lo_rel < 0; }
+__host__ __device__ __forceinline__ bool rescale_full(int32_t z_out, int32_t lo_rel, int32_t hi_rel) { return lo_rel + z_out == 0 && hi_rel + z_out == 255; }
+// calls f with the tag of the form for an output range; `fused`: every channel allows the fused forms
+template <class F> __host__ __device__ __forceinline__ void with_rescale_mode(bool fused, int32_t z_out, int32_t lo_rel, int32_t hi_rel, F f)
+{
+    const bool ties = rescale_ties(lo_rel), full = rescale_full(z_out, lo_rel, hi_rel);
+    if (!fused) f(RescaleTag<RESCALE_GENERAL>{});
+    else if (ties && full) f(RescaleTag<RESCALE_TIES_FULL>{});
+    else if (ties) f(RescaleTag<RESCALE_TIES>{});
+    else if (full) f(RescaleTag<RESCALE_PLAIN_FULL>{});
+    else f(RescaleTag<RESCALE_PLAIN>{});
+}
+
 __device__ __forceinline__ int32_t clamp_i32(int32_t lo, int32_t hi, int32_t v)
 {
     return v < lo ? lo : (v > hi ? hi : v);
@@ -209,18 +292,6 @@ template <bool FUSED> __device__ __forceinline__ uint32_t add_value1(int32_t tm,
         u = u > INT32_MAX ? INT32_MAX : (u < INT32_MIN ? INT32_MIN : u);
         return (uint32_t)(clamp_i32(o.lo_rel, o.hi_rel, rescale_general((int32_t)u, o.po)) + o.z_out);
     }
-}
-
-// one rescaled value of the product + four of the residual -> four output codes
-template <bool FUSED> __device__ __forceinline__ uint32_t add_values4(int32_t tm, const int32_t (&tr)[4], const AddOut &o)
-{
-    uint32_t x = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if constexpr (FUSED) x = shift_into_byte(x, rescale_fused_w(tm + tr[e], o.fo), o.fo.n1, e);
-        else x |= add_value1<false>(tm, tr[e], o) << (8 * e);
-    }
-    return x;
 }
 
 // one code of the product + one of the residual -> one output code

@@ -50,16 +50,85 @@ template <int VEC> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t 
     return v;
 }
 
-// Epilogue constants of one column in the cheapest exact form (valid for 1 <= shift <= 20 and
-// |acc + corr| < 2^29).  With a = acc + corr, n = shift:
-//   T = hi32(4a * mult),  s = T >> 31,  w = T + 2s + c,  c = 2*(2^(n-1) + (z_out << n)) + 1
-//   out = clamp(w, act_min << (n+1), ((act_max + 1) << (n+1)) - 1) >> (n + 1)
-// which equals clamp(z_out + RESCALE(a)) bit for bit: the rounding-doubling high multiply
-// (ties up) and the rounding shift (ties away from zero) collapse into one floor division, and
-// clamping before the final shift lets that shift write its byte straight into the packed dword.
+// Epilogue constants of one column (ChannelRescale: fused forms; the rest: general form and weight zero-points)
 struct ShortKColumn {
-    int32_t mult, corr, c, n1, lo, hi, shift, zw;
+    ChannelRescale r;
+    int32_t corr, mult, shift, zw;
 };
+
+// Constants of a column from the sum of its weights and its parameters; k_loaded: the k that a weight zero-point's
+// activation sums run over (those from K on read as the code 0).  Returns whether the column allows the fused form.
+__device__ __forceinline__ bool shortk_column(ShortKColumn &c, const IgemmArgs &g, int32_t colsum, int32_t bias, int32_t mult, int32_t shift,
+                                              int32_t zw, int k_loaded)
+{
+    const bool ties = rescale_ties(g.lo_rel);
+    c.corr = bias + (128 - g.z_a) * colsum - zw * (g.K * (128 - g.z_a) + 128 * (k_loaded - g.K));
+    c.mult = mult, c.shift = shift, c.zw = zw;
+    c.r = make_channel_rescale(mult, shift, c.corr, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
+    return channel_rescale_ok(mult, shift, ties) && bias > -(1 << 27) && bias < (1 << 27);
+}
+
+// All 65536 results of an add from its tables of rescaled codes (add_fill_tables).  Entry [m][r] = code of the sum, at
+// byte 256 m + (r ^ 4 (m % 64)): the bank of a gather then depends on both codes.  (With r alone choosing the bank, the
+// lanes whose residual is the code of zero, half of them behind a ReLU, met in one bank.)  A lane fills the same 4
+// consecutive r for every m of its wave, so that the value of m is one broadcast read and those of r stay in registers.
+template <int WAVES> __device__ __forceinline__ void fill_pair_table(uint8_t *pair_tab, const int32_t *tab, const AddParams &add)
+{
+    const int r0 = (int)(threadIdx.x & 63u) * 4;
+    int32_t tr[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tr[e] = tab[256 + r0 + e];
+    uint32_t *const out = reinterpret_cast<uint32_t *>(pair_tab);
+    const AddParams &p = add;
+    const bool ties = rescale_ties(p.act_min - p.z_out);
+    const ChannelRescale r = make_channel_rescale(p.mult_o, p.shift_o, 0, p.z_out, p.act_min, p.act_max, ties);
+    const AddOut ao = make_add_out(p);
+    with_rescale_mode(ao.fused && channel_rescale_ok(p.mult_o, p.shift_o, ties), p.z_out, p.act_min - p.z_out, p.act_max - p.z_out, [&](auto mode_tag) {
+        using Mode = RescaleModeTraits<decltype(mode_tag)::value>;
+#pragma unroll 4
+        for (int i = 0; i < 256 / WAVES; ++i) {
+            const int m = i * WAVES + (int)(threadIdx.x >> 6);
+            const int32_t tm = tab[m];
+            uint32_t x = 0;
+            if constexpr (Mode::kFused) {
+                const int32_t sum[4] = {tm + tr[0], tm + tr[1], tm + tr[2], tm + tr[3]};
+                x = channel_codes4<Mode::kTies, Mode::kFull>(sum, r);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x |= add_value1<false>(tm, tr[e], ao) << (8 * e);
+            }
+            out[m * 64 + ((threadIdx.x ^ (uint32_t)m) & 63u)] = x;
+        }
+    });
+}
+
+// 4 codes of the layer (v) and of the residual (r): the byte pairs are interleaved into 16-bit indices of the table, one
+// byte gather each
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void pairs_lookup(const uint8_t *pair_tab, uint32_t v, uint32_t r, u16x2 (&t)[2])
+{
+    const uint32_t rs = r ^ ((v << 2) & 0xfcfcfcfcu); // the table's order
+    const uint32_t i01 = __builtin_amdgcn_perm(v, rs, 0x05010400u), i23 = __builtin_amdgcn_perm(v, rs, 0x07030602u);
+    t[0] = u16x2{pair_tab[i01 & 0xffffu], pair_tab[i23 & 0xffffu]};
+    t[1] = u16x2{pair_tab[i01 >> 16], pair_tab[i23 >> 16]};
+}
+__device__ __forceinline__ uint32_t pairs_combine(const u16x2 (&t)[2])
+{
+    return __builtin_bit_cast(uint32_t, t[0]) | (__builtin_bit_cast(uint32_t, t[1]) << 8);
+}
+
+// 16 codes of the layer and of the residual -> 16 output codes
+__device__ __forceinline__ u32x4 add_pairs16(const uint8_t *pair_tab, u32x4 v, u32x4 r)
+{
+    u32x4 y;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        u16x2 t[2];
+        pairs_lookup(pair_tab, v[d], r[d], t);
+        y[d] = pairs_combine(t);
+    }
+    return y;
+}
 
 // ADD: the rescaling add with a residual tensor (g.R) is applied to the output tile on its way
 // from LDS to global memory; the residual chunks of a row block are requested one round ahead.
@@ -99,22 +168,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         add_fill_tables(tab, g.add, threadIdx.x, WAVES * 64);
         __syncthreads();
         if constexpr (use_pairs) {
-            const AddOut ao = make_add_out(g.add);
-            // Entry [m][r] = code of the sum, at byte 256 m + (r ^ 4 (m % 64)): the bank of a gather then depends on both
-            // codes.  (With r alone choosing the bank, the lanes whose residual is the code of zero, half of them behind a
-            // ReLU, met in one bank.)  A lane fills the same 4 consecutive r for every m of its wave, so that the value of
-            // m is one broadcast read and those of r stay in registers.
-            const int r0 = (int)(threadIdx.x & 63u) * 4;
-            int32_t tr[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) tr[e] = tab[256 + r0 + e];
-            auto fill = [&](auto fused_tag) {
-                for (int m = threadIdx.x >> 6; m < 256; m += WAVES)
-                    reinterpret_cast<uint32_t *>(pair_tab)[m * 64 + ((threadIdx.x ^ (uint32_t)m) & 63u)] =
-                        add_values4<decltype(fused_tag)::value>(tab[m], tr, ao);
-            };
-            if (ao.fused) fill(std::true_type{});
-            else fill(std::false_type{});
+            fill_pair_table<WAVES>(pair_tab, tab, g.add);
             __syncthreads();
         }
     }
@@ -155,17 +209,10 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
             const int k = ks * 32 + fhalf * 16;
             if constexpr (INT4) {
                 const uint8_t *p = g.B + (((int64_t)n * g.ldb) >> 1);
-                uint32_t r2[2] = {0u, 0u};
-                if (k + 8 <= g.K) r2[0] = *reinterpret_cast<const uint32_t *>(p + (k >> 1));
-                if (k + 16 <= g.K) r2[1] = *reinterpret_cast<const uint32_t *>(p + (k >> 1) + 4);
-#pragma unroll
-                for (int d = 0; d < 2; ++d) { // r2[d] holds elements 8d .. 8d+7, two per byte, low nibble first
-                    const uint32_t even = (r2[d] << 4) & 0xF0F0F0F0u, odd = r2[d] & 0xF0F0F0F0u;
-                    fb[ks][j][2 * d] = (int32_t)((even & 0xFFu) | ((odd & 0xFFu) << 8) | ((even & 0xFF00u) << 8) |
-                                                 ((odd & 0xFF00u) << 16));
-                    fb[ks][j][2 * d + 1] = (int32_t)(((even >> 16) & 0xFFu) | (((odd >> 16) & 0xFFu) << 8) |
-                                                     (((even >> 24) & 0xFFu) << 16) | ((odd >> 24) << 24));
-                }
+                u32x2 raw = {0u, 0u}; // (rows are 4-byte aligned: K and ldb are multiples of 8)
+                if (k + 16 <= g.K) __builtin_memcpy(&raw, p + (k >> 1), 8);
+                else if (k + 8 <= g.K) raw[0] = *reinterpret_cast<const uint32_t *>(p + (k >> 1));
+                fb[ks][j] = expand_int4(raw);
             } else {
                 fb[ks][j] = shortk_load16<BVEC>(g.B + (int64_t)n * g.ldb, k, g.K);
             }
@@ -174,22 +221,8 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         }
         colsum += __shfl_xor(colsum, 32);
         if (INT4) colsum >>= 4; // weights are kept times 16; exact
-        const int32_t b = g.bias ? g.bias[n] : 0, mu = g.mult[n], sf = g.shift[n];
-        fused_ok = fused_ok && sf >= 1 && sf <= 20 && b > -(1 << 27) && b < (1 << 27);
-        const int nn = (sf >= 1 && sf <= 20) ? sf : 1;
-        col[j].mult = mu;
-        col[j].corr = b + (128 - g.z_a) * colsum;
-        col[j].zw = 0;
-        if constexpr (ZW) {
-            col[j].zw = g.zw[n];
-            // the sums count code - 128, and -128 for every k from K to KS * 32 (loaded as zeros)
-            col[j].corr -= col[j].zw * (g.K * (128 - g.z_a) + 128 * (KS * 32 - g.K));
-        }
-        col[j].n1 = nn + 1;
-        col[j].c = 2 * ((1 << (nn - 1)) + (g.z_out << nn)) + 1;
-        col[j].lo = (g.lo_rel + g.z_out) << (nn + 1);
-        col[j].hi = ((g.hi_rel + g.z_out + 1) << (nn + 1)) - 1;
-        col[j].shift = sf; // the general path
+        // (the sums of ZW count code - 128, and -128 for every k from K to KS * 32, loaded as zeros)
+        fused_ok = shortk_column(col[j], g, colsum, g.bias ? g.bias[n] : 0, g.mult[n], g.shift[n], ZW ? g.zw[n] : 0, KS * 32) && fused_ok;
     }
     const bool fused = __all(fused_ok);
     const i32x4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101}; // ZW
@@ -279,19 +312,12 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         for (int i = 0; i < NB; ++i)
             if (st_col_ok[i] && rbx * 32 + st_row[i] < M) rres[i] = *reinterpret_cast<const u32x4 *>(r_block + st_roff[i]);
     };
-    // 16 codes of the layer (v) and of the residual (r) -> 16 output codes: the byte pairs are
-    // interleaved into 16-bit table indices [m << 8 | r], one byte gather each
+    // 16 codes of the layer (v) and of the residual (r) -> 16 output codes
     const AddOut ao = make_add_out(g.add);
     auto add16 = [&](u32x4 v, u32x4 r) __attribute__((always_inline)) {
         u32x4 y;
         if constexpr (use_pairs) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const uint32_t rs = r[d] ^ ((v[d] << 2) & 0xfcfcfcfcu); // the table's order
-                const uint32_t i01 = __builtin_amdgcn_perm(v[d], rs, 0x05010400u), i23 = __builtin_amdgcn_perm(v[d], rs, 0x07030602u);
-                const uint32_t t0 = pair_tab[i01 & 0xffffu], t1 = pair_tab[i01 >> 16], t2 = pair_tab[i23 & 0xffffu], t3 = pair_tab[i23 >> 16];
-                y[d] = t0 | (t1 << 8) | (t2 << 16) | (t3 << 24);
-            }
+            y = add_pairs16(pair_tab, v, r);
         } else if (ao.fused) {
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
@@ -360,8 +386,8 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
 
     // the row loop exists twice (fast and general epilogue) and the choice is made once, outside:
     // inside the loop the compiler would evaluate both forms for every output and select
-    auto walk = [&](auto mode_tag) { // 0: general rescale, 1: fused form, 2: fused form without the tie term
-    constexpr bool FUSED = decltype(mode_tag)::value > 0, TIES = decltype(mode_tag)::value == 1;
+    auto walk = [&](auto mode_tag) {
+    using Mode = RescaleModeTraits<decltype(mode_tag)::value>;
     i32x4 fa[KS];
     int rb = walker, rb_stored = -1, turn = 0;
     if constexpr (ALDS) { // two copies in flight; the first block's fragments are in registers before the loop
@@ -422,42 +448,28 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
             x = __builtin_amdgcn_perm(o, x, sel2);
             *reinterpret_cast<uint32_t *>(stage + put_base + q * 8 * PITCH + j * 32) = x;
         };
-        if constexpr (FUSED) {
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                if (j >= blocks_here) break;
+        for (int j = 0; j < NB; ++j) {
+            if (j >= blocks_here) break;
+            const RescaleParams rp = make_rescale(col[j].mult, col[j].shift); // general form
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    uint32_t x = 0;
+            for (int q = 0; q < 4; ++q) {
+                int32_t a[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        int32_t a = acc[j][4 * q + e];
-                        if (INT4) a >>= 4;
-                        if constexpr (ZW) a -= __mul24(col[j].zw, sums[4 * q + e]);
-                        const int32_t t = __mulhi((int32_t)((uint32_t)(a + col[j].corr) << 2), col[j].mult);
-                        x = shift_into_byte(x, med3_i32(fused_w_from_t<TIES>(t, col[j].c), col[j].lo, col[j].hi), col[j].n1, e);
-                    }
-                    put(j, q, x);
+                for (int e = 0; e < 4; ++e) {
+                    a[e] = acc[j][4 * q + e];
+                    if (INT4) a[e] >>= 4;
+                    if constexpr (ZW) a[e] -= __mul24(col[j].zw, sums[4 * q + e]);
                 }
-            }
-        } else { // any multiplier / shift / bias: the general form
+                uint32_t x = 0;
+                if constexpr (Mode::kFused) {
+                    x = channel_codes4<Mode::kTies, Mode::kFull>(a, col[j].r);
+                } else {
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                if (j >= blocks_here) break;
-                const RescaleParams rp = make_rescale(col[j].mult, col[j].shift);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    uint32_t x = 0;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        int32_t a = acc[j][4 * q + e];
-                        if (INT4) a >>= 4;
-                        if constexpr (ZW) a -= __mul24(col[j].zw, sums[4 * q + e]);
-                        const int32_t y = clamp_i32(lo_rel, hi_rel, rescale_general(a + col[j].corr, rp)) + z_out;
-                        x |= (uint32_t)y << (8 * e);
-                    }
-                    put(j, q, x);
+                    for (int e = 0; e < 4; ++e)
+                        x |= (uint32_t)(clamp_i32(lo_rel, hi_rel, rescale_general(a[e] + col[j].corr, rp)) + z_out) << (8 * e);
                 }
+                put(j, q, x);
             }
         }
         // the tile is private to the wave and LDS operations of one wave complete in order:
@@ -470,9 +482,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
     }
     if (rb_stored >= 0) store_block(rb_stored);
     };
-    if (!fused) walk(std::integral_constant<int, 0>{});
-    else if (g.lo_rel < 0) walk(std::integral_constant<int, 1>{});
-    else walk(std::integral_constant<int, 2>{}); // act_min >= z_out: the clamp absorbs the tie term
+    with_rescale_mode(fused, z_out, lo_rel, hi_rel, walk);
 }
 
 } // namespace qnn

@@ -72,20 +72,6 @@ __device__ __forceinline__ u32x4 load_tail16(const uint8_t *row, int k, int len)
     return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
 }
 
-// 16 weights from 8 packed bytes (element 2j in the low nibble of byte j), each times 16
-__device__ __forceinline__ i32x4 widen_int4(uint32_t r0, uint32_t r1)
-{
-    const uint32_t r[2] = {r0, r1};
-    i32x4 w;
-#pragma unroll
-    for (int d = 0; d < 2; ++d) {
-        const uint32_t even = (r[d] << 4) & 0xF0F0F0F0u, odd = r[d] & 0xF0F0F0F0u;
-        w[2 * d] = (int32_t)__builtin_amdgcn_perm(odd, even, 0x05010400u);
-        w[2 * d + 1] = (int32_t)__builtin_amdgcn_perm(odd, even, 0x07030602u);
-    }
-    return w;
-}
-
 // AI: load instructions per 128 bytes of the activation rows, 8 rows each (a workgroup owns 8 * AI rows).
 // A_CONV: the 16-byte chunks of a row are gathered from the image; Cin % 16 == 0, so a chunk lies inside one tap.
 // SMALL_ZW: per-column weight zero-points (see igemm_epilogue_impl).
@@ -257,7 +243,7 @@ __global__ void __launch_bounds__(NW * 64) smallk_kernel(const SmallArgs args)
             i32x4 fb[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                if constexpr (INT4) fb[h] = widen_int4(w[p][2 * h], w[p][2 * h + 1]);
+                if constexpr (INT4) fb[h] = expand_int4(u32x2{w[p][2 * h], w[p][2 * h + 1]});
                 else fb[h] = i32x4{(int32_t)w[h].x, (int32_t)w[h].y, (int32_t)w[h].z, (int32_t)w[h].w};
             }
             if (need_colsum) {
