@@ -163,8 +163,12 @@ static qnn_status run_igemm_zw(IgemmArgs &g, int a_mode, int b_mode, int vec, vo
     if (try_small(g, a_mode, b_mode, s, &st)) return st;
     if (a_mode == A_MATRIX && shortk_eligible(g, b_mode, false)) return launch_shortk(g, b_mode, false, s);
     const bool i4 = b_mode == B_INT4;
-    const bool aligned_for_dma = vec == 16 && (g.K % 64) == 0 && g.lda < (1 << 23) && g.ldb < (1 << 23) &&
-                                 (!i4 || (aligned_to(g.B, 16) && (g.ldb % 32) == 0));
+    const bool chunks = vec == 16 && (b_mode == B_INT8 || (i4 && aligned_to(g.B, 16) && (g.ldb % 32) == 0 && (g.K % 32) == 0));
+    const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
+    // few tiles (two workgroups of 64x64 per CU), or a K that the larger tiles do not take: 3136 x 512 x 512 6.4 us on
+    // 64x64 tiles, 9.5 on 128x128
+    if (chunks && tiles64 <= 0x7ffffff && (tiles64 <= 512 || (g.K % 64) != 0)) return launch_status(launch_tile64(g, a_mode == A_MATRIX, i4, SplitK{1, 0, nullptr}, s));
+    const bool aligned_for_dma = chunks && (g.K % 64) == 0 && g.lda < (1 << 23) && g.ldb < (1 << 23);
     if ((b_mode == B_INT8 || i4) && aligned_for_dma && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 0x7ffffff) {
         // large products: the 256x256 tile once it fills most of the chip, else 128x128
         const bool big = ((g.M + 255) / 256) * ((g.N + 255) / 256) >= 160 && g.K > 256;
@@ -247,10 +251,10 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
             hipError_t e;
             IgemmArgs plain = g; // the reduction kernel writes the product's code; the add follows
             plain.R = nullptr;
-            if (tail)
+            if (cfg == TILE_DMA_64x64)
+                e = launch_tile64(plain, mat, false, sk, s);
+            else if (tail)
                 e = launch_tail_tile(plain, (int)bm, (int)bn, mat, false, sk, s);
-            else if (cfg == TILE_DMA_64x64)
-                e = mat ? launch_dma<64, 64, 2, 2, A_MATRIX, 4, true>(plain, s, sk) : launch_dma<64, 64, 2, 2, A_CONV, 4, true>(plain, s, sk);
             else
                 e = mat ? launch_dma<128, 128, 2, 2, A_MATRIX, 4, true>(plain, s, sk) : launch_dma<128, 128, 2, 2, A_CONV, 4, true>(plain, s, sk);
             return add_pass(launch_status(e));
@@ -258,6 +262,7 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
     }
     if (((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) > max_tiles) return QNN_EINVAL;
     const SplitK one{1, 0, nullptr};
+    if (cfg == TILE_DMA_64x64) return launch_status(launch_tile64(g, mat, i4, one, s));
     if (tail && cfg >= TILE_DMA_128x128) return launch_status(launch_tail_tile(g, (int)bm, (int)bn, mat, i4, one, s));
     switch (cfg) {
     case TILE_64x64:
@@ -278,9 +283,6 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
         return launch_status(mat ? launch_dma<256, 256, 4, 2, A_MATRIX, 4>(g, s, one, 1, 1) : launch_dma<256, 256, 4, 2, A_CONV, 4>(g, s, one, 1, 1));
     case TILE_DMA_256x64:
         return launch_status(mat ? launch_dma<256, 64, 4, 1, A_MATRIX, 4>(g, s) : launch_dma<256, 64, 4, 1, A_CONV, 4>(g, s));
-    case TILE_DMA_64x64:
-        if (i4) return launch_status(mat ? launch_dma<64, 64, 2, 2, A_MATRIX, 4, false, false, true>(g, s) : launch_dma<64, 64, 2, 2, A_CONV, 4, false, false, true>(g, s));
-        return launch_status(mat ? launch_dma<64, 64, 2, 2, A_MATRIX, 4>(g, s) : launch_dma<64, 64, 2, 2, A_CONV, 4>(g, s));
     case TILE_DMA_256x128:
         return launch_status(mat ? launch_dma<256, 128, 4, 2, A_MATRIX, 4>(g, s, one, 1, 0) : launch_dma<256, 128, 4, 2, A_CONV, 4>(g, s, one, 1, 0));
     case TILE_DMA_256x64_S3:

@@ -40,6 +40,10 @@ __device__ __forceinline__ void block_barrier()
     asm volatile("" ::: "memory");
 }
 
+// barrier over the LDS traffic of the workgroup: what was written is visible, what was read may be overwritten;
+// requests to memory stay in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 __device__ __forceinline__ void dma16(const uint8_t *src, uint8_t *lds_wave_base)
 {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,

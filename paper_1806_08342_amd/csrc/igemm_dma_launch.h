@@ -26,6 +26,14 @@ inline void choose_xcd_cut(const IgemmArgs &g, int tiles_m, int tiles_n, int64_t
     }
 }
 
+// second pass of split-K
+inline hipError_t launch_splitk_reduce(const IgemmArgs &g, const SplitK &sk, hipStream_t s)
+{
+    const int64_t threads = g.M * (((int64_t)g.N + 3) / 4);
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, g, sk);
+    return hipGetLastError();
+}
+
 // `per_cu` > 0: persistent launch with that many workgroups per CU (each walks its XCD's tile
 // sequence); 0: one workgroup per tile.  `prio`: issue-priority scheme of the main loop (see the kernel).
 template <int BM, int BN, int WM, int WN, int A_MODE, int NSTAGE, bool SPLIT = false, bool ZW = false, bool B4 = false,
@@ -52,9 +60,7 @@ hipError_t launch_dma(const IgemmArgs &g, hipStream_t s, SplitK sk = SplitK{1, 0
                        sk, prio);
     hipError_t e = hipGetLastError();
     if (SPLIT && e == hipSuccess) {
-        const int64_t threads = g.M * (((int64_t)g.N + 3) / 4);
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, g, sk);
-        e = hipGetLastError();
+        e = launch_splitk_reduce(g, sk, s);
     }
     return e;
 }

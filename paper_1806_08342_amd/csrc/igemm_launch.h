@@ -54,6 +54,9 @@ struct SplitK;
 // Pipelined tiles bm x bn for K % 64 != 0 (igemm_tail.hip)
 hipError_t launch_tail_tile(const IgemmArgs &g, int bm, int bn, bool mat, bool i4, const SplitK &sk, hipStream_t s);
 
+// 64x64 tiles for few output tiles, any K of whole chunks; g.zw and sk (8-bit weights) as set
+hipError_t launch_tile64(const IgemmArgs &g, bool mat, bool i4, const SplitK &sk, hipStream_t s);
+
 // Zero-padded copies of operands that are no whole, aligned 16-byte chunks (igemm_repack.hip).  `length`: K of a
 // matrix, Cin of a convolution.  launch_repack points g at the copies in `workspace` (repack_bytes of it).
 int repack_length(int length, int weight_bits);

@@ -11,13 +11,9 @@ template <int A_MODE> static hipError_t launch_tail(const IgemmArgs &g, int bm, 
     if (i4) {
         if constexpr (A_MODE == A_MATRIX)
             if (bm == 256) return launch_dma<256, 256, 4, 2, A_MODE, 4, false, false, true, 1, true>(g, s);
-        if (bm == 64) return launch_dma<64, 64, 2, 2, A_MODE, 4, false, false, true, 1, true>(g, s);
         return launch_dma<128, 128, 2, 2, A_MODE, 4, false, false, true, 1, true>(g, s);
     }
-    if (sk.splits > 1)
-        return bm == 64 ? launch_dma<64, 64, 2, 2, A_MODE, 4, true, false, false, 1, true>(g, s, sk)
-                        : launch_dma<128, 128, 2, 2, A_MODE, 4, true, false, false, 1, true>(g, s, sk);
-    if (bm == 64) return launch_dma<64, 64, 2, 2, A_MODE, 4, false, false, false, 1, true>(g, s);
+    if (sk.splits > 1) return launch_dma<128, 128, 2, 2, A_MODE, 4, true, false, false, 1, true>(g, s, sk);
     if constexpr (A_MODE == A_MATRIX)
         if (bn == 256) {
             if (bm == 256) return launch_dma<256, 256, 4, 2, A_MODE, 4, false, false, false, 1, true>(g, s, one, 1, 1);

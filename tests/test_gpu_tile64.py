@@ -1,0 +1,68 @@
+"""GPU parity of the 64x64 tiles (tile64.h): partial last stages of 128 k, one stage and fewer than the ring holds, weight
+zero-points, 4-bit weights, convolutions, and both depths of the ring (at most 512 tiles, and more)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1806_08342_amd as qnn
+
+from gpu_util import assert_same, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _only_tiles():
+    for name, value in (("QNN_SMALL", "0"), ("QNN_BRES", "0")):
+        qnn.tuning_set(name, value)
+    yield
+    for name in ("QNN_SMALL", "QNN_BRES", "QNN_FORCE_TILE"):
+        qnn.tuning_set(name)
+
+
+def _weights(rng, shape, bits):
+    return rng.integers(-8 if bits == 4 else -128, 8 if bits == 4 else 128, shape).astype(np.int8)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("asym", [False, True])
+@pytest.mark.parametrize("z_a", [128, 9])
+@pytest.mark.parametrize("M,N,K", [(65, 64, 320), (131, 66, 288), (70, 129, 384), (200, 31, 512), (97, 80, 608), (2373, 976, 288), (129, 65, 1056)])
+def test_product(bits, asym, z_a, M, N, K):
+    rng = np.random.default_rng(M + N + K + bits)
+    A = rng.integers(0, 256, (M, K)).astype(np.uint8)
+    B = _weights(rng, (N, K), bits)
+    mult, shift = oracle.quantize_multipliers(10 ** rng.uniform(-4.2, -3.4, N) * (16 if bits == 4 else 1))
+    bias = rng.integers(-20000, 20000, N).astype(np.int32)
+    zw = rng.integers(-100, 101, N).astype(np.int32)
+    Bo = oracle.pack_int4(B) if bits == 4 else B
+    rows = np.arange(M) if M < 1000 else np.sort(rng.choice(M, 300, replace=False))
+    if asym:
+        want = oracle.qgemm(A[rows], z_a, Bo, mult, shift, 120, 0, 255, bias=bias, weight_bits=bits, z_w=zw)
+        got = host(qnn.qgemm_asym(dev(A), z_a, dev(Bo), dev(zw), dev(mult), dev(shift), 120, 0, 255, bias=dev(bias), weight_bits=bits))
+    else:
+        qnn.tuning_set("QNN_FORCE_TILE", "dma64x64")
+        want = oracle.qgemm(A[rows], z_a, Bo, mult, shift, 120, 0, 255, bias=bias, weight_bits=bits)
+        got = host(qnn.qgemm(dev(A), z_a, dev(Bo), dev(mult), dev(shift), 120, 0, 255, bias=dev(bias), weight_bits=bits))
+    assert_same(got[rows], want, f"{M}x{N}x{K} {bits}-bit")
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("asym", [False, True])
+@pytest.mark.parametrize("H,W,cin,cout,stride", [(9, 11, 32, 70, 1), (13, 10, 96, 33, 2), (7, 7, 160, 64, 1)])
+def test_convolution(bits, asym, H, W, cin, cout, stride):
+    rng = np.random.default_rng(H + cin + bits)
+    x = rng.integers(0, 256, (2, H, W, cin)).astype(np.uint8)
+    w = _weights(rng, (cout, 3, 3, cin), bits)
+    wo = oracle.pack_int4(w) if bits == 4 else w
+    mult, shift = oracle.quantize_multipliers(10 ** rng.uniform(-4.2, -3.4, cout) * (16 if bits == 4 else 1))
+    bias = rng.integers(-20000, 20000, cout).astype(np.int32)
+    zw = rng.integers(-100, 101, cout).astype(np.int32)
+    if asym:
+        want = oracle.qconv2d(x, 37, wo, (stride, stride), (1, 1), mult, shift, 120, 0, 255, bias=bias, weight_bits=bits, z_w=zw)
+        got = host(qnn.qconv2d_asym(dev(x), 37, dev(wo), dev(zw), (stride, stride), (1, 1), dev(mult), dev(shift), 120, 0, 255, bias=dev(bias), weight_bits=bits))
+    else:
+        qnn.tuning_set("QNN_FORCE_TILE", "dma64x64")
+        want = oracle.qconv2d(x, 37, wo, (stride, stride), (1, 1), mult, shift, 120, 0, 255, bias=bias, weight_bits=bits)
+        got = host(qnn.qconv2d(dev(x), 37, dev(wo), (stride, stride), (1, 1), dev(mult), dev(shift), 120, 0, 255, bias=dev(bias), weight_bits=bits))
+    assert_same(got, want, f"3x3 {cin}->{cout} {bits}-bit")
