@@ -112,8 +112,8 @@ struct QuantizeOp {
 
 // Sec. 2.5: activation ranges come from the minimum and maximum of the tensor (their moving average
 // across batches during training); Sec. 2.1 turns a range into (scale, zero_point).  Everything stays on
-// the device: a reduction with one atomic pair per workgroup on order-preserving integer keys, a
-// one-lane kernel that updates the range and derives the parameters in double precision exactly as
+// the device: a reduction with one atomic pair per workgroup on order-preserving integer keys, behind it one
+// lane that updates the range and derives the parameters in double precision exactly as
 // qnn_choose_qparams does on the host, and a quantize kernel that reads them from memory.
 __device__ __forceinline__ uint32_t float_key(float v) // monotonic: a < b  <=>  key(a) < key(b)
 {
@@ -126,17 +126,54 @@ __device__ __forceinline__ float key_float(uint32_t k)
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
+// The work words of the reduction; the workgroups that are done are counted in the place of the scale, which is written last.
+__device__ __forceinline__ uint32_t *done_counter(qnn_dyn_qparams *st) { return reinterpret_cast<uint32_t *>(&st->scale); }
 __global__ void minmax_init_kernel(qnn_dyn_qparams *st)
 {
     st->key_min = 0xffffffffu;
     st->key_max = 0u;
+    *done_counter(st) = 0u;
+}
+
+__device__ __forceinline__ double nearest_away_dev(double v) { return v < 0.0 ? -floor(-v + 0.5) : floor(v + 0.5); }
+
+// range update (momentum 0: the batch range; else moving average) and quantizer parameters
+__device__ __forceinline__ void finish_range(qnn_dyn_qparams *st, float bmin, float bmax, float momentum, int bits)
+{
+    if (momentum != 0.0f) { // m * old + (1 - m) * batch, each operation rounded once in double, then to binary32
+        const double m = (double)momentum, om = __dsub_rn(1.0, m);
+        bmin = (float)__dadd_rn(__dmul_rn(m, (double)st->xmin), __dmul_rn(om, (double)bmin));
+        bmax = (float)__dadd_rn(__dmul_rn(m, (double)st->xmax), __dmul_rn(om, (double)bmax));
+    }
+    st->xmin = bmin, st->xmax = bmax;
+    const double lo = fmin((double)bmin, 0.0), hi = fmax((double)bmax, 0.0);
+    const double steps = (double)((1 << bits) - 1);
+    if (hi - lo == 0.0) {
+        st->scale = 1.0f, st->zero_point = 0;
+        return;
+    }
+    const float sc = (float)__ddiv_rn(__dsub_rn(hi, lo), steps);
+    double z = nearest_away_dev(__ddiv_rn(-lo, (double)sc));
+    z = fmin(fmax(z, 0.0), steps);
+    st->scale = sc, st->zero_point = (int32_t)z;
+}
+
+__device__ __forceinline__ void finish_keys(qnn_dyn_qparams *st, uint32_t kmin, uint32_t kmax, float momentum, int bits)
+{
+    const bool any = kmin <= kmax;
+    finish_range(st, any ? key_float(kmin) : 0.0f, any ? key_float(kmax) : 0.0f, momentum, bits);
 }
 
 // Bound by reading x and, behind that, by the atomics: about 10 ns each on one address, and the workgroups end
 // together, so that none finds the other's result already there.  One workgroup of 16 waves per CU: 25.7 M values
-// in 22 us where 2048 workgroups of 4 waves took 59.
-constexpr int kMinmaxThreads = 1024, kMinmaxBlocks = 256;
-template <bool NT> __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__restrict__ x, size_t n, qnn_dyn_qparams *st)
+// in 22 us where 2048 workgroups of 4 waves took 59.  Launches saved at the smaller sizes, where they are most of the time:
+// up to kMinmaxAlone values one workgroup does it all (65536 values 7.2 -> 5.1 us, 16384 6.6 -> 3.3), and up to
+// kMinmaxCounted workgroups the last one to arrive finishes the range (0.5 M values, called one by one 8.6 -> 7.2 us; with
+// 256 workgroups the count, one more atomic on one address each, takes 3 us longer than the launch it saves).
+constexpr int kMinmaxThreads = 1024, kMinmaxBlocks = 256, kMinmaxCounted = 64;
+constexpr size_t kMinmaxAlone = (size_t)4 * kMinmaxThreads * kUnroll * 4;
+template <bool NT>
+__global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__restrict__ x, size_t n, qnn_dyn_qparams *st, float momentum, int bits)
 {
     float lo = INFINITY, hi = -INFINITY; // values that are not finite take no part in the range
     auto take = [&](float v) {
@@ -156,8 +193,9 @@ template <bool NT> __global__ void __launch_bounds__(kMinmaxThreads) minmax_kern
     __shared__ float s_lo[kMinmaxThreads / 64], s_hi[kMinmaxThreads / 64];
     if ((threadIdx.x & 63) == 0) s_lo[threadIdx.x >> 6] = lo, s_hi[threadIdx.x >> 6] = hi;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kMinmaxThreads / 64; ++w) lo = fminf(lo, s_lo[w]), hi = fmaxf(hi, s_hi[w]);
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < kMinmaxThreads / 64; ++w) lo = fminf(lo, s_lo[w]), hi = fmaxf(hi, s_hi[w]);
+    if (gridDim.x > 1) {
         if (lo <= hi) { // at least one finite value in this block
             // atomics on one address serialise across the chip: skip them when the value seen so far is
             // already as good (a stale read only costs an atomic that changes nothing)
@@ -165,33 +203,23 @@ template <bool NT> __global__ void __launch_bounds__(kMinmaxThreads) minmax_kern
             if (klo < __hip_atomic_load(&st->key_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&st->key_min, klo);
             if (khi > __hip_atomic_load(&st->key_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&st->key_max, khi);
         }
+        if (gridDim.x > kMinmaxCounted) return; // range_finalize_kernel comes behind
+        // The last one to arrive sees the atomics of all: they carry all that is shared and are performed where all XCDs meet, so
+        // it is enough that a workgroup's own are done before it is counted.  (As a release / acquire pair the count writes
+        // back and invalidates an L2 in every workgroup: 27 us instead of 21 on 25.7 M values.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (__hip_atomic_fetch_add(done_counter(st), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u != gridDim.x) return;
+        asm volatile("" ::: "memory");
+        finish_keys(st, __hip_atomic_load(&st->key_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                    __hip_atomic_load(&st->key_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), momentum, bits);
+    } else if (lo <= hi) {
+        finish_range(st, lo, hi, momentum, bits);
+    } else { // no finite value at all
+        finish_range(st, 0.0f, 0.0f, momentum, bits);
     }
 }
 
-__device__ __forceinline__ double nearest_away_dev(double v) { return v < 0.0 ? -floor(-v + 0.5) : floor(v + 0.5); }
-
-// range update (momentum 0: the batch range; else moving average) and quantizer parameters
-__global__ void range_finalize_kernel(qnn_dyn_qparams *st, float momentum, int bits)
-{
-    float bmin = 0.0f, bmax = 0.0f;
-    if (st->key_min <= st->key_max) bmin = key_float(st->key_min), bmax = key_float(st->key_max);
-    if (momentum != 0.0f) { // m * old + (1 - m) * batch, each operation rounded once in double, then to binary32
-        const double m = (double)momentum, om = __dsub_rn(1.0, m);
-        bmin = (float)__dadd_rn(__dmul_rn(m, (double)st->xmin), __dmul_rn(om, (double)bmin));
-        bmax = (float)__dadd_rn(__dmul_rn(m, (double)st->xmax), __dmul_rn(om, (double)bmax));
-    }
-    st->xmin = bmin, st->xmax = bmax;
-    const double lo = fmin((double)bmin, 0.0), hi = fmax((double)bmax, 0.0);
-    const double steps = (double)((1 << bits) - 1);
-    if (hi - lo == 0.0) {
-        st->scale = 1.0f, st->zero_point = 0;
-        return;
-    }
-    const float sc = (float)__ddiv_rn(__dsub_rn(hi, lo), steps);
-    double z = nearest_away_dev(__ddiv_rn(-lo, (double)sc));
-    z = fmin(fmax(z, 0.0), steps);
-    st->scale = sc, st->zero_point = (int32_t)z;
-}
+__global__ void range_finalize_kernel(qnn_dyn_qparams *st, float momentum, int bits) { finish_keys(st, st->key_min, st->key_max, momentum, bits); }
 
 // quantize with parameters that live in device memory (8-bit codes)
 struct QuantizeWithOp {
@@ -616,14 +644,12 @@ qnn_status qnn_minmax(const float *x, size_t n, float momentum, int bits, qnn_dy
 {
     if (!state || (n && !x) || bits < 2 || bits > 16 || !(momentum >= 0.0f) || !(momentum < 1.0f)) return QNN_EINVAL;
     const hipStream_t s = as_stream(stream);
-    hipLaunchKernelGGL(minmax_init_kernel, dim3(1), dim3(1), 0, s, state);
-    if (n) {
-        const size_t tiles = (n / 4 + kMinmaxThreads * kUnroll - 1) / (kMinmaxThreads * kUnroll);
-        const dim3 grid((unsigned)(tiles < 1 ? 1 : (tiles < kMinmaxBlocks ? tiles : kMinmaxBlocks)));
-        if (n * 4 > kCacheBytes) hipLaunchKernelGGL(minmax_kernel<true>, grid, dim3(kMinmaxThreads), 0, s, x, n, state);
-        else hipLaunchKernelGGL(minmax_kernel<false>, grid, dim3(kMinmaxThreads), 0, s, x, n, state);
-    }
-    hipLaunchKernelGGL(range_finalize_kernel, dim3(1), dim3(1), 0, s, state, momentum, bits);
+    const size_t tiles = (n / 4 + kMinmaxThreads * kUnroll - 1) / (kMinmaxThreads * kUnroll);
+    const dim3 grid((unsigned)(n <= kMinmaxAlone ? 1 : (tiles < kMinmaxBlocks ? tiles : kMinmaxBlocks)));
+    if (grid.x > 1) hipLaunchKernelGGL(minmax_init_kernel, dim3(1), dim3(1), 0, s, state);
+    if (n * 4 > kCacheBytes) hipLaunchKernelGGL(minmax_kernel<true>, grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
+    else hipLaunchKernelGGL(minmax_kernel<false>, grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
+    if (grid.x > kMinmaxCounted) hipLaunchKernelGGL(range_finalize_kernel, dim3(1), dim3(1), 0, s, state, momentum, bits);
     return launch_status(hipGetLastError());
 }
 

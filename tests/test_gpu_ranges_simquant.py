@@ -160,3 +160,21 @@ def test_rescale_u8_writes_a_channel_slice_of_a_concatenation():
     got = host(qnn.rescale_u8(dev(wide)[:, 3:70], 50, mult, shift, 60, 0, 255))
     assert_same(got, oracle.requantize(wide[:, 3:70].astype(np.int32) - 50, np.array([mult]), np.array([shift]), False, 60, 0, 255),
                 "rescale_u8 from a slice")
+
+
+@pytest.mark.parametrize("n", [1, 4097, 65536, 65537, 16384 * 5 + 3, 16384 * 64, 16384 * 64 + 4, 16384 * 65])
+@pytest.mark.parametrize("momentum", [0.0, 0.75])
+def test_range_on_one_workgroup_counted_workgroups_and_more(n, momentum):
+    """The edges between the three ways in which the reduction ends; the work words of the state start as anything."""
+    rng = np.random.default_rng(n)
+    x = rng.normal(0, 2, n).astype(np.float32)
+    x[rng.integers(0, n)] = np.float32(np.nan) if n > 1 else x[0]
+    x[n - 1] = np.float32(17.5)
+    st = qnn.new_range_state(-1.0, 3.0)
+    st[4:] = torch.tensor([-7, 12345], dtype=torch.int32, device=st.device)
+    lo, hi = -1.0, 3.0
+    for _ in range(2): # a second pass finds the words as the first one left them
+        qnn.minmax(dev(x), st, momentum=momentum)
+        s, z, lo, hi = oracle.dynamic_qparams(x, state=(lo, hi), momentum=momentum) if momentum else oracle.dynamic_qparams(x)
+        r = qnn.read_range_state(st)
+        assert (r["scale"], r["zero_point"], r["xmin"], r["xmax"]) == (float(s), z, float(lo), float(hi))
