@@ -27,12 +27,15 @@ struct ShortKArgs {
     int stream_out;    // non-temporal output stores
 };
 
-// 16 consecutive k of one row / column as 4 dwords, zero beyond K.  VEC = bytes per load.
-template <int VEC> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t *p, int k, int K)
+// 16 consecutive k of one row / column as 4 dwords, zero beyond K (ZERO = false, VEC 16: any bytes there, where the other
+// operand is zero).  VEC = bytes per load; whole 16-byte pieces are loaded without a branch, from a clamped address.
+template <int VEC, bool ZERO = true> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t *p, int k, int K)
 {
     i32x4 v = {0, 0, 0, 0};
     if constexpr (VEC == 16) {
-        if (k + 16 <= K) v = *reinterpret_cast<const i32x4 *>(p + k);
+        const bool in = k + 16 <= K;
+        v = *reinterpret_cast<const i32x4 *>(p + (in ? k : K - 16));
+        if constexpr (ZERO) v = i32x4{in ? v.x : 0, in ? v.y : 0, in ? v.z : 0, in ? v.w : 0};
     } else if constexpr (VEC == 8) {
         if (k + 8 <= K) {
             const u32x2 a = *reinterpret_cast<const u32x2 *>(p + k);
@@ -53,7 +56,7 @@ template <int VEC> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t 
 // Epilogue constants of one column (ChannelRescale: fused forms; the rest: general form and weight zero-points)
 struct ShortKColumn {
     ChannelRescale r;
-    int32_t corr, mult, shift, zw;
+    int32_t mult, shift, zw;
 };
 
 // Constants of a column from the sum of its weights and its parameters; k_loaded: the k that a weight zero-point's
@@ -62,9 +65,9 @@ __device__ __forceinline__ bool shortk_column(ShortKColumn &c, const IgemmArgs &
                                               int32_t zw, int k_loaded)
 {
     const bool ties = rescale_ties(g.lo_rel);
-    c.corr = bias + (128 - g.z_a) * colsum - zw * (g.K * (128 - g.z_a) + 128 * (k_loaded - g.K));
+    const int32_t corr = bias + (128 - g.z_a) * colsum - zw * (g.K * (128 - g.z_a) + 128 * (k_loaded - g.K));
     c.mult = mult, c.shift = shift, c.zw = zw;
-    c.r = make_channel_rescale(mult, shift, c.corr, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
+    c.r = make_channel_rescale(mult, shift, corr, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     return channel_rescale_ok(mult, shift, ties) && bias > -(1 << 27) && bias < (1 << 27);
 }
 
@@ -194,62 +197,77 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
     const int n0 = cg * 32 * NB;
     const int blocks_here = (g.N - n0 + 31) / 32 < NB ? (g.N - n0 + 31) / 32 : NB; // column blocks that exist
 
-    // ---- weights: B fragments of all K sub-steps, for good
+    // ---- weights: B fragments of all K sub-steps, for good.  The parameters of the columns, all weights and the rows of the
+    // first block are requested before any of them is waited for.
     i32x4 fb[KS][NB];
+    u32x2 packed[INT4 ? KS : 1][INT4 ? NB : 1];
     ShortKColumn col[NB];
-    bool fused_ok = g.small_acc >= 2;
+    int32_t p_bias[NB], p_mult[NB], p_shift[NB], p_zw[NB];
+    const int32_t *const bias_or_any = g.bias ? g.bias : g.mult; // no branch around the load; the value is dropped below
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         int n = n0 + j * 32 + frow;
-        const bool real = n < g.N;
-        n = real ? n : g.N - 1;
-        int32_t colsum = 0;
+        n = n < g.N ? n : g.N - 1;
+        p_bias[j] = bias_or_any[n], p_mult[j] = g.mult[n], p_shift[j] = g.shift[n];
+        p_zw[j] = ZW ? g.zw[n] : 0;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const int k = ks * 32 + fhalf * 16;
             if constexpr (INT4) {
                 const uint8_t *p = g.B + (((int64_t)n * g.ldb) >> 1);
-                u32x2 raw = {0u, 0u}; // (rows are 4-byte aligned: K and ldb are multiples of 8)
-                if (k + 16 <= g.K) __builtin_memcpy(&raw, p + (k >> 1), 8);
-                else if (k + 8 <= g.K) raw[0] = *reinterpret_cast<const uint32_t *>(p + (k >> 1));
-                fb[ks][j] = expand_int4(raw);
+                if constexpr (VEC == 16) { // K % 16 == 0 (rows are 4-byte aligned)
+                    __builtin_memcpy(&packed[ks][j], p + ((k + 16 <= g.K ? k : g.K - 16) >> 1), 8);
+                } else {
+                    packed[ks][j] = u32x2{0u, 0u};
+                    if (k + 16 <= g.K) __builtin_memcpy(&packed[ks][j], p + (k >> 1), 8);
+                    else if (k + 8 <= g.K) packed[ks][j][0] = *reinterpret_cast<const uint32_t *>(p + (k >> 1));
+                }
             } else {
-                fb[ks][j] = shortk_load16<BVEC>(g.B + (int64_t)n * g.ldb, k, g.K);
+                fb[ks][j] = shortk_load16<BVEC, false>(g.B + (int64_t)n * g.ldb, k, g.K);
+            }
+        }
+    }
+    const int M = (int)g.M; // (the dispatcher guarantees M < 2^31)
+    const int row_blocks = (M + 31) / 32;
+    // ---- rows
+    auto load_rows = [&](int rb, i32x4 (&fa)[KS]) __attribute__((always_inline)) {
+        const uint8_t *p;
+        int m = rb * 32 + frow;
+        m = m < M ? m : M - 1;
+        if (s.strided) {
+            const uint32_t per_image = (uint32_t)g.Ho * (uint32_t)g.Wo;
+            const uint32_t img = (uint32_t)m / per_image, rem = (uint32_t)m - img * per_image;
+            const uint32_t ho = rem / (uint32_t)g.Wo, wo = rem - ho * (uint32_t)g.Wo;
+            p = g.A + (((int64_t)img * g.H + ho * g.sh) * g.W + wo * g.sw) * g.Cin + fhalf * 16;
+        } else {
+            p = g.A + (int64_t)m * g.lda + fhalf * 16;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) fa[ks] = shortk_load16<VEC, false>(p, ks * 32, g.K - fhalf * 16); // (beyond K the weights are zero)
+    };
+    i32x4 first[KS];
+    if constexpr (!ALDS && !ZW) load_rows(walker < row_blocks ? walker : row_blocks - 1, first);
+
+    bool fused_ok = g.small_acc >= 2;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        int32_t colsum = 0;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if constexpr (INT4) fb[ks][j] = expand_int4(packed[ks][j]);
+            if constexpr (INT4 ? VEC == 16 : BVEC == 16) {
+                if (ks * 32 + fhalf * 16 + 16 > g.K) fb[ks][j] = i32x4{0, 0, 0, 0};
             }
 #pragma unroll
             for (int d = 0; d < 4; ++d) colsum = __builtin_amdgcn_sdot4(fb[ks][j][d], 0x01010101, colsum, false);
         }
         colsum += __shfl_xor(colsum, 32);
         if (INT4) colsum >>= 4; // weights are kept times 16; exact
-        // (the sums of ZW count code - 128, and -128 for every k from K to KS * 32, loaded as zeros)
-        fused_ok = shortk_column(col[j], g, colsum, g.bias ? g.bias[n] : 0, g.mult[n], g.shift[n], ZW ? g.zw[n] : 0, KS * 32) && fused_ok;
+        // (the sums of ZW count code - 128; where pieces of 8 are loaded, also -128 for every k from K to KS * 32, read as zeros)
+        fused_ok = shortk_column(col[j], g, colsum, g.bias ? p_bias[j] : 0, p_mult[j], p_shift[j], p_zw[j], VEC == 16 ? g.K : KS * 32) && fused_ok;
     }
-    const bool fused = __all(fused_ok);
-    const i32x4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101}; // ZW
-
-    // ---- rows (the dispatcher guarantees M < 2^31)
-    const int M = (int)g.M;
-    const int row_blocks = (M + 31) / 32;
-    const int64_t lane_row_off = (int64_t)frow * g.lda + fhalf * 16; // A_MATRIX: offset of this lane's fragment inside a row block
-    auto load_rows = [&](int rb, i32x4 (&fa)[KS]) {
-        const uint8_t *p;
-        if (s.strided) {
-            int m = rb * 32 + frow;
-            m = m < M ? m : M - 1;
-            const uint32_t per_image = (uint32_t)g.Ho * (uint32_t)g.Wo;
-            const uint32_t img = (uint32_t)m / per_image, rem = (uint32_t)m - img * per_image;
-            const uint32_t ho = rem / (uint32_t)g.Wo, wo = rem - ho * (uint32_t)g.Wo;
-            p = g.A + (((int64_t)img * g.H + ho * g.sh) * g.W + wo * g.sw) * g.Cin + fhalf * 16;
-        } else if (rb * 32 + 32 <= M) {
-            p = g.A + (int64_t)rb * 32 * g.lda + lane_row_off; // uniform base + invariant lane offset
-        } else {
-            int m = rb * 32 + frow;
-            m = m < M ? m : M - 1;
-            p = g.A + (int64_t)m * g.lda + fhalf * 16;
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) fa[ks] = shortk_load16<VEC>(p, ks * 32, g.K - fhalf * 16);
-    };
+    const bool fused = __all(fused_ok), k_tail = VEC == 16 && g.K != KS * 32;
+    const i32x4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 
     // ALDS: copy of row block rbx into a_tiles[buf]; wave w, pass i moves LDS chunks (i * WAVES + w) * 64 + lane:
     // LDS chunk q = (row, position p) holds global chunk p ^ swz(row) of that row
@@ -336,8 +354,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
     // K = 256: 84 us and 93 with non-temporal ones, 70 and 76; 51 MB, K = 256: 57 and 54, but the 3x3 layer that reads
     // them then takes 67 instead of 64.)
     // the output tile of row block rbx, from the wave's LDS area to global memory.  Called one
-    // round late, right after the next block's MFMAs are issued and before the loads of the block
-    // after it: the stores then never sit between a load and the wait for that load.
+    // round late, right after the next block's MFMAs and the loads of the block after it are issued.
     auto store_block = [&](int rbx) __attribute__((always_inline)) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -400,7 +417,9 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
             read_tile(0, fa);
         }
     } else {
-        if (rb < row_blocks) load_rows(rb, fa);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) fa[ks] = first[ks];
+        if constexpr (ZW) load_rows(rb < row_blocks ? rb : row_blocks - 1, fa);
     }
     for (; rb < row_blocks; rb += s.walkers, turn ^= 1) {
         i32x16 acc[NB];
@@ -411,8 +430,11 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         i32x16 sums = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}; // ZW: sum_k (code - 128) of the rows
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const i32x4 xs = fa[ks] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
-            if constexpr (ZW) sums = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, ones, sums, 0, 0, 0);
+            i32x4 xs = fa[ks] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
+            if constexpr (ZW) {
+                if (k_tail && ks * 32 + fhalf * 16 >= g.K) xs = i32x4{0, 0, 0, 0}; // counts in the sum
+                sums = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, ones, sums, 0, 0, 0);
+            }
 #pragma unroll
             for (int j = 0; j < NB; ++j)
                 acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, fb[ks][j], acc[j], 0, 0, 0); // columns past N: clamped loads, never stored
@@ -431,13 +453,12 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
                 if (rb + 2 * s.walkers < row_blocks) issue_tile(rb + 2 * s.walkers, turn);
             }
         }
+        // The fragments are consumed: the next block's are requested into the same registers now, ahead of the stores, so that
+        // the wait for them is no wait for these (requests retire in order), and past the last block too (the last one's again:
+        // without a branch the wait is for the exact number of requests).
+        if constexpr (!ALDS) load_rows(rb + s.walkers < row_blocks ? rb + s.walkers : row_blocks - 1, fa);
         if (rb_stored >= 0) store_block(rb_stored);
         if constexpr (ADD) load_res(rb); // used one round from now, when this block is stored
-        // the fragments are consumed: fetch the next block's into the same registers now, so that
-        // the loads are in flight during the epilogue
-        if constexpr (!ALDS) {
-            if (rb + s.walkers < row_blocks) load_rows(rb + s.walkers, fa);
-        }
 
         // ---- epilogue into the wave's LDS tile: after the 4x4 byte transposition inside each
         // quad of lanes a lane holds 4 consecutive columns of one row
@@ -467,7 +488,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        x |= (uint32_t)(clamp_i32(lo_rel, hi_rel, rescale_general(a[e] + col[j].corr, rp)) + z_out) << (8 * e);
+                        x |= (uint32_t)(clamp_i32(lo_rel, hi_rel, rescale_general(a[e] - col[j].r.ncorr, rp)) + z_out) << (8 * e);
                 }
                 put(j, q, x);
             }
