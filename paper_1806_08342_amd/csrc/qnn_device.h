@@ -112,23 +112,13 @@ __device__ __forceinline__ FusedRescale make_fused(int32_t mult, int32_t shift, 
     return f;
 }
 
-// w of the comment above from T.  TIES = false drops the term 2s (two instructions fewer).  That
-// is exact whenever act_min >= z_out (every ReLU-like output range): the term only acts for T < 0,
-// where both T + c and T - 2 + c stay below (z_out + 1) << (n+1) <= (act_min + 1) << (n+1), so
-// after the clamp from below the shifted result is act_min either way.
-template <bool TIES> __device__ __forceinline__ int32_t fused_w_from_t(int32_t t, int32_t c)
-{
-    if constexpr (TIES) return (int32_t)(((uint32_t)(t >> 31) << 1) + (uint32_t)t + (uint32_t)c);
-    else return (int32_t)((uint32_t)t + (uint32_t)c);
-}
-
 // w of the comment above, clamped; the caller shifts it right by n1
 __device__ __forceinline__ int32_t med3_i32(int32_t v, int32_t lo, int32_t hi);
-template <bool TIES = true> __device__ __forceinline__ int32_t rescale_fused_w(int32_t acc, const FusedRescale &p)
+__device__ __forceinline__ int32_t rescale_fused_w(int32_t acc, const FusedRescale &p)
 {
     const int32_t a4 = (int32_t)(((uint32_t)acc << 2) + (uint32_t)p.corr4);
     const int32_t t = __mulhi(a4, p.mult);
-    return med3_i32(fused_w_from_t<TIES>(t, p.c), p.lo, p.hi);
+    return med3_i32((int32_t)(((uint32_t)(t >> 31) << 1) + (uint32_t)t + (uint32_t)p.c), p.lo, p.hi);
 }
 
 // complete value (already clamped to [act_min, act_max])
@@ -160,10 +150,12 @@ __device__ __forceinline__ int32_t med3_i32(int32_t v, int32_t lo, int32_t hi)
 
 // The epilogues' form of the rescale, per output channel.  With a = acc + corr and n = shift as above, the two nested
 // floors are one: out = floor((a * mult + c * 2^30) / 2^(31 + n)), so that
-//   no tie term (see fused_w_from_t):  w = hi32(acc * mult + (corr * mult + c * 2^30)),               out = w >> (n - 1)
-//   tie term:  w = hi32(2 a * mult + c * 2^31 - 2^32 [a < 0]),                                         out = w >> n
-// with everything that does not depend on acc in one 64-bit addend of the multiply-add (v_mad_i64_i32 runs at the rate of
-// v_mul_hi_i32).  2 mult as a signed 32-bit factor is 2 mult - 2^32 (mult >= 2^30, as the encoding has it), which the
+//   no tie term:  w = hi32(acc * mult + (corr * mult + c * 2^30)),               out = w >> (n - 1)
+//   tie term:     w = hi32(2 a * mult + c * 2^31 - 2^32 [a < 0]),                out = w >> n
+// Without the tie term (2s above) whenever act_min >= z_out, every ReLU-like output range: it only acts for T < 0, where
+// both T + c and T - 2 + c stay below (z_out + 1) << (n+1) <= (act_min + 1) << (n+1), so that the clamp from below
+// gives act_min either way.  Everything that does not depend on acc is in the 64-bit addend of one multiply-add
+// (v_mad_i64_i32 runs at the rate of v_mul_hi_i32).  2 mult as a signed 32-bit factor is 2 mult - 2^32 (mult >= 2^30, as the encoding has it), which the
 // extra `acc` in the high half makes up for; the tie term comes in as the carry of that addition:
 //   w = hi32(acc * (2 mult - 2^32) + (2 corr * mult + c * 2^31 - 2^32)) + acc + [acc >= -corr].
 // v_ashr_pk_u8_i32 shifts, saturates to 0 ... 255 and packs two values; a narrower output range is clamped before it.
