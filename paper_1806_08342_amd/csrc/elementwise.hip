@@ -442,6 +442,36 @@ __global__ void __launch_bounds__(kThreads) qadd_kernel(const uint8_t *__restric
     }
 }
 
+// The same with one vector of 4 W codes per lane, requested ahead of the tables.  Small tensors are bound by latencies (a
+// lane of the kernel above waits for its tables, then for its codes, and looks up 128 of them one after another, on 15
+// workgroups where a layer has 250880), larger ones by how many requests are in flight.  16 codes per lane against the kernel
+// above, us: 250880 codes 2.4 and 3.7, 2408448 3.7 and 4.4, 38.5 M 22.7 and 24.1, 51 M 29.5 and 31.7, 77 M 40-44 and 42; then
+// the tables of ever more workgroups cost more: 150 M 81 and 77.  8 codes per lane: 250880 2.2, 2408448 3.7, 9.6 M 8.2 (16: 7.3).
+constexpr size_t kQaddLanes = (size_t)64 << 20;
+template <bool FUSED, int W>
+__global__ void __launch_bounds__(kThreads) qadd_lane_kernel(const uint8_t *a, const uint8_t *b, uint8_t *y, size_t n, QaddArgs g)
+{
+    typedef uint32_t Vec __attribute__((ext_vector_type(W)));
+    __shared__ int32_t tab[512];
+    const AddParams p = {g.z_a, g.mult_a, g.shift_a, g.z_b, g.mult_b, g.shift_b, g.left_shift, g.mult_o, g.shift_o, g.z_out, g.act_min, g.act_max};
+    const size_t nvec = n / (4 * W), v = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    const size_t at = 4 * W * (v < nvec ? v : nvec - 1); // (the dispatcher guarantees one vector)
+    const Vec va = load_any<Vec, false>(a + at), vb = load_any<Vec, false>(b + at);
+    asm volatile("" ::: "memory"); // the loads stay here
+    add_fill_tables(tab, p, threadIdx.x, kThreads);
+    __syncthreads();
+    const AddOut ao = make_add_out(p);
+    if (v < nvec) {
+        Vec o;
+#pragma unroll
+        for (int d = 0; d < W; ++d) o[d] = add_codes4<FUSED>(va[d], vb[d], tab, ao);
+        store_any(y + at, o);
+    }
+    if (blockIdx.x == 0 && threadIdx.x < n - nvec * (4 * W)) {
+        const size_t i = nvec * (4 * W) + threadIdx.x;
+        y[i] = (uint8_t)add_code1<FUSED>(a[i], b[i], tab, ao);
+    }
+}
 
 // ------------------------------------------------------ rescale of uint8 codes (concat)
 
@@ -726,6 +756,15 @@ qnn_status qnn_qadd(const uint8_t *a, int32_t z_a, int32_t mult_a, int32_t shift
     QaddArgs g = {z_a, mult_a, shift_a, z_b, mult_b, shift_b, left_shift, mult_o, shift_o, z_out, act_min, act_max};
     const bool fused = shift_o >= 1 && shift_o <= 20 && shift_a >= 0 && shift_b >= 0 && left_shift <= 20;
     const hipStream_t s = as_stream(stream);
+    if (n >= 8 && n <= kQaddLanes) { // see kQaddLanes; 8 codes per lane while that is no more than a workgroup per CU
+        const bool narrow = n <= (size_t)256 * kThreads * 8;
+        const dim3 grid((unsigned)((n / (narrow ? 8 : 16) + kThreads - 1) / kThreads));
+        if (fused && narrow) hipLaunchKernelGGL((qadd_lane_kernel<true, 2>), grid, dim3(kThreads), 0, s, a, b, y, n, g);
+        else if (fused) hipLaunchKernelGGL((qadd_lane_kernel<true, 4>), grid, dim3(kThreads), 0, s, a, b, y, n, g);
+        else if (narrow) hipLaunchKernelGGL((qadd_lane_kernel<false, 2>), grid, dim3(kThreads), 0, s, a, b, y, n, g);
+        else hipLaunchKernelGGL((qadd_lane_kernel<false, 4>), grid, dim3(kThreads), 0, s, a, b, y, n, g);
+        return launch_status(hipGetLastError());
+    }
     const dim3 grid((unsigned)grid_for(n / 16));
     const bool nt = n * 3 > kCacheBytes;
     if (fused && nt) hipLaunchKernelGGL((qadd_kernel<true, true>), grid, dim3(kThreads), 0, s, a, b, y, n, g);

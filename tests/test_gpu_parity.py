@@ -124,6 +124,25 @@ def test_qadd_all_code_pairs_and_odd_parameters():
         assert_same(got, want, f"qadd all pairs {s_a},{s_b},{s_o}")
 
 
+@pytest.mark.parametrize("n", [7, 8, 9, 15, 16, 2047, 2049, (1 << 19) - 1, 1 << 19, (1 << 19) + 1, (1 << 19) + 15, 64 << 20, (64 << 20) + 3])
+@pytest.mark.parametrize("left_shift", [20, 22])
+@pytest.mark.parametrize("offset,in_place", [(0, False), (1, True)])
+def test_qadd_widths(n, left_shift, offset, in_place):
+    """The edges between 8 codes per lane, 16, and the loop over tiles; left_shift 22 takes the general form.  The ends of
+    the larger tensors and every 4099th code are compared, and no byte beyond the tensor is written."""
+    rng = np.random.default_rng(n)
+    a, b = (rng.integers(0, 256, n + 3, dtype=np.uint8) for _ in range(2))
+    p = dict(oracle.qadd_params(0.02, 0.031, 0.04), left_shift=left_shift)
+    da, db = dev(a)[offset:offset + n], dev(b)[offset:offset + n]
+    y = da if in_place else dev(np.full(n + 64, 77, np.uint8))[:n]
+    a, b = a[offset:offset + n], b[offset:offset + n]
+    tail = None if in_place else y.as_strided((64,), (1,), n)
+    got = host(qnn.qadd(da, 120, db, 131, p, 128, 0, 255, out=y))
+    pick = np.arange(n) if n < 10000 else np.unique(np.concatenate([np.arange(5000), np.arange(n - 5000, n), np.arange(0, n, 4099)]))
+    assert_same(got[pick], oracle.qadd(a[pick], 120, b[pick], 131, p, 128, 0, 255), f"qadd n={n}")
+    assert tail is None or (host(tail) == 77).all()
+
+
 # ----------------------------------------------------------------------------------- qgemm
 
 def _gemm_params(rng, N, K, spread=True):
