@@ -436,7 +436,7 @@ def calibrate(torch, qnn):
             cnt[0] = qnn.calibrate_rescale(256 * w, 2048, sink)
         t = graph_time(torch, [fn], min_launches=4)
         out[f"rescale_loop_{w}_waves_per_simd"] = dict(us=round(t * 1e6, 1), outputs_per_s=round(cnt[0] / t, -9),
-                                                        lane_ops_per_output="5 + 1 (feedback)")
+                                                        lane_ops_per_output="1.5 (64-bit multiply-add, half a shift-and-pack) + 1 (feedback)")
     n = 1 << 30
     srcs = [_device_uint8(torch, (n,), 12345 + i) for i in range(2)]
     dsts = [torch.empty_like(srcs[0]) for _ in range(2)]
