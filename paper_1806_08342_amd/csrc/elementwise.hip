@@ -126,13 +126,12 @@ __device__ __forceinline__ float key_float(uint32_t k)
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-// The work words of the reduction; the workgroups that are done are counted in the place of the scale, which is written last.
-__device__ __forceinline__ uint32_t *done_counter(qnn_dyn_qparams *st) { return reinterpret_cast<uint32_t *>(&st->scale); }
+// key_min / key_max are all of the state that is work space: scale, zero-point and range are those of the call before until
+// the one lane at the end writes them.
 __global__ void minmax_init_kernel(qnn_dyn_qparams *st)
 {
     st->key_min = 0xffffffffu;
     st->key_max = 0u;
-    *done_counter(st) = 0u;
 }
 
 __device__ __forceinline__ double nearest_away_dev(double v) { return v < 0.0 ? -floor(-v + 0.5) : floor(v + 0.5); }
@@ -158,20 +157,19 @@ __device__ __forceinline__ void finish_range(qnn_dyn_qparams *st, float bmin, fl
     st->scale = sc, st->zero_point = (int32_t)z;
 }
 
-__device__ __forceinline__ void finish_keys(qnn_dyn_qparams *st, uint32_t kmin, uint32_t kmax, float momentum, int bits)
+__global__ void range_finalize_kernel(qnn_dyn_qparams *st, float momentum, int bits)
 {
-    const bool any = kmin <= kmax;
-    finish_range(st, any ? key_float(kmin) : 0.0f, any ? key_float(kmax) : 0.0f, momentum, bits);
+    const bool any = st->key_min <= st->key_max;
+    finish_range(st, any ? key_float(st->key_min) : 0.0f, any ? key_float(st->key_max) : 0.0f, momentum, bits);
 }
 
 // Bound by reading x and, behind that, by the atomics: about 10 ns each on one address, and the workgroups end
 // together, so that none finds the other's result already there.  One workgroup of 16 waves per CU: 25.7 M values
-// in 22 us where 2048 workgroups of 4 waves took 59.  Launches saved at the smaller sizes, where they are most of the time:
-// up to kMinmaxAlone values one workgroup does it all (65536 values 7.2 -> 5.1 us, 16384 6.6 -> 3.3), and up to
-// kMinmaxCounted workgroups the last one to arrive finishes the range (0.5 M values, called one by one 8.6 -> 7.2 us; with
-// 256 workgroups the count, one more atomic on one address each, takes 3 us longer than the launch it saves).
-constexpr int kMinmaxThreads = 1024, kMinmaxBlocks = 256, kMinmaxCounted = 64;
-constexpr size_t kMinmaxAlone = (size_t)4 * kMinmaxThreads * kUnroll * 4;
+// in 22 us where 2048 workgroups of 4 waves took 59.  Up to kMinmaxAlone values the three launches are most of the time: one
+// workgroup does it all (us in a graph and called one by one, against three launches: 16384 values 3.1 and 3.6 (6.6), 65536 5.0
+// and 4.9 (7.2), 114688 7.0 and 6.7 (7.4, 7.7), 131072 7.6 and 7.4 (7.5, 7.7), 163840 8.9 and 8.7 (7.4, 7.7)).
+constexpr int kMinmaxThreads = 1024, kMinmaxBlocks = 256;
+constexpr size_t kMinmaxAlone = (size_t)7 * kMinmaxThreads * kUnroll * 4;
 template <bool NT>
 __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__restrict__ x, size_t n, qnn_dyn_qparams *st, float momentum, int bits)
 {
@@ -203,23 +201,12 @@ __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__r
             if (klo < __hip_atomic_load(&st->key_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&st->key_min, klo);
             if (khi > __hip_atomic_load(&st->key_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&st->key_max, khi);
         }
-        if (gridDim.x > kMinmaxCounted) return; // range_finalize_kernel comes behind
-        // The last one to arrive sees the atomics of all: they carry all that is shared and are performed where all XCDs meet, so
-        // it is enough that a workgroup's own are done before it is counted.  (As a release / acquire pair the count writes
-        // back and invalidates an L2 in every workgroup: 27 us instead of 21 on 25.7 M values.)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (__hip_atomic_fetch_add(done_counter(st), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u != gridDim.x) return;
-        asm volatile("" ::: "memory");
-        finish_keys(st, __hip_atomic_load(&st->key_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                    __hip_atomic_load(&st->key_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), momentum, bits);
     } else if (lo <= hi) {
         finish_range(st, lo, hi, momentum, bits);
     } else { // no finite value at all
         finish_range(st, 0.0f, 0.0f, momentum, bits);
     }
 }
-
-__global__ void range_finalize_kernel(qnn_dyn_qparams *st, float momentum, int bits) { finish_keys(st, st->key_min, st->key_max, momentum, bits); }
 
 // quantize with parameters that live in device memory (8-bit codes)
 struct QuantizeWithOp {
@@ -679,7 +666,7 @@ qnn_status qnn_minmax(const float *x, size_t n, float momentum, int bits, qnn_dy
     if (grid.x > 1) hipLaunchKernelGGL(minmax_init_kernel, dim3(1), dim3(1), 0, s, state);
     if (n * 4 > kCacheBytes) hipLaunchKernelGGL(minmax_kernel<true>, grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
     else hipLaunchKernelGGL(minmax_kernel<false>, grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
-    if (grid.x > kMinmaxCounted) hipLaunchKernelGGL(range_finalize_kernel, dim3(1), dim3(1), 0, s, state, momentum, bits);
+    if (grid.x > 1) hipLaunchKernelGGL(range_finalize_kernel, dim3(1), dim3(1), 0, s, state, momentum, bits);
     return launch_status(hipGetLastError());
 }
 

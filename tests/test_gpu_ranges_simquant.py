@@ -162,10 +162,10 @@ def test_rescale_u8_writes_a_channel_slice_of_a_concatenation():
                 "rescale_u8 from a slice")
 
 
-@pytest.mark.parametrize("n", [1, 4097, 65536, 65537, 16384 * 5 + 3, 16384 * 64, 16384 * 64 + 4, 16384 * 65])
+@pytest.mark.parametrize("n", [1, 4097, 65536, 65537, 16384 * 5 + 3, 16384 * 7, 16384 * 7 + 1, 16384 * 64, 16384 * 64 + 4, 16384 * 65])
 @pytest.mark.parametrize("momentum", [0.0, 0.75])
 def test_range_on_one_workgroup_counted_workgroups_and_more(n, momentum):
-    """The edges between the three ways in which the reduction ends; the work words of the state start as anything."""
+    """The edges between one workgroup and several, whole tiles and parts; the work words of the state start as anything."""
     rng = np.random.default_rng(n)
     x = rng.normal(0, 2, n).astype(np.float32)
     x[rng.integers(0, n)] = np.float32(np.nan) if n > 1 else x[0]
@@ -178,3 +178,23 @@ def test_range_on_one_workgroup_counted_workgroups_and_more(n, momentum):
         s, z, lo, hi = oracle.dynamic_qparams(x, state=(lo, hi), momentum=momentum) if momentum else oracle.dynamic_qparams(x)
         r = qnn.read_range_state(st)
         assert (r["scale"], r["zero_point"], r["xmin"], r["xmax"]) == (float(s), z, float(lo), float(hi))
+
+
+@pytest.mark.parametrize("n,calls", [(65536, 400), (16384 * 7 + 1, 400), (500000, 400), (16384 * 64 + 4, 200), (1 << 26, 20)])
+def test_parameters_stand_while_a_range_is_reduced(n, calls):
+    """Only key_min / key_max are work space: whoever reads the parameters meanwhile, on another stream, finds those of the
+    last range (which are those of the present one here, so that every sample has to be the same)."""
+    x = torch.linspace(-1.5, 4.0, n, device="cuda:0")
+    st = qnn.new_range_state()
+    qnn.minmax(x, st)
+    want = st[:4].clone()
+    samples = torch.zeros((300, 4), dtype=torch.int32, device="cuda:0")
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(calls):
+        qnn.minmax(x, st)
+    with torch.cuda.stream(other):
+        for i in range(samples.shape[0]):
+            samples[i].copy_(st[:4])
+    torch.cuda.synchronize()
+    assert (samples == want).all(), samples[(samples != want).any(1)][:4].tolist()
