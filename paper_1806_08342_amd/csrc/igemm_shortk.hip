@@ -1,61 +1,13 @@
-// Launch routine of the weight-stationary short-K kernel.
-#include "igemm_launch.h"
+// Launch routine of the weight-stationary short-K kernel; its forms for 8-bit weights.
+#include "shortk_launch.h"
 #include "tuning.h"
-#include "shortk.h"
 
 namespace qnn {
 
-// Short reduction (K <= 256): weight-stationary kernel of shortk.h.  Returns false when the
-// operands do not meet its alignment rules (the caller then takes the general route).
-template <int NB, int KS, bool INT4, int VEC, int BVEC, int ADD>
-static void launch_shortk_add(const ShortKArgs &a, int64_t waves, hipStream_t s)
+void launch_shortk_int8(const ShortKArgs &a, int ks, int64_t waves, hipStream_t s, bool v16, bool alds)
 {
-    // the waves of a workgroup (8 with the 64 KB table of code pairs, else 4) share the table(s); their tiles behind
-    constexpr int kWaves = ADD == 2 ? 8 : 4;
-    constexpr int kLds = (ADD == 2 ? 65536 : 2048) + kWaves * 32 * (32 * NB + 32);
-    auto kernel = shortk_kernel<NB, KS, INT4, VEC, BVEC, ADD>;
-    static LdsOptIn opt_in; // per instantiation
-    if (opt_in.ensure(reinterpret_cast<const void *>(kernel), kLds) != hipSuccess) return; // the error stays pending for the caller
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kWaves * 64), kLds, s, a);
-}
-
-template <int KS, bool INT4, int VEC> static void launch_shortk_one(const ShortKArgs &a, int64_t waves, hipStream_t s, bool alds)
-{
-    constexpr int NB = KS <= 4 ? 4 : 2;
-    // weights: 16-byte loads when every 16-element piece of a column is 16-byte aligned, else dwords
-    const bool b16 = !INT4 && aligned_to(a.g.B, 16) && (a.g.ldb % 16) == 0 && (a.g.K % 16) == 0;
-    if constexpr (VEC == 16 && (KS == 4 || KS == 8)) {
-        if (alds) { // A rows through LDS, shared by the waves of a workgroup (the caller sized `waves` in workgroups)
-            if (b16) hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 16, 0, true>), dim3((unsigned)waves), dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 4, 0, true>), dim3((unsigned)waves), dim3(256), 0, s, a);
-            return;
-        }
-    }
-    if constexpr (VEC == 16) {
-        if (a.g.R) { // residual add in the store phase (the launcher only leaves R set for VEC == 16)
-            // from 2^24 outputs on the 65536-entry pair table pays for itself; below, two 256-entry tables
-            const bool pairs = a.g.M * (int64_t)a.g.N >= ((int64_t)1 << 24);
-            if (b16) pairs ? launch_shortk_add<NB, KS, INT4, VEC, 16, 2>(a, waves, s) : launch_shortk_add<NB, KS, INT4, VEC, 16, 1>(a, waves, s);
-            else pairs ? launch_shortk_add<NB, KS, INT4, VEC, 4, 2>(a, waves, s) : launch_shortk_add<NB, KS, INT4, VEC, 4, 1>(a, waves, s);
-            return;
-        }
-    }
-    const unsigned blocks = (unsigned)((waves + 3) / 4);
-    if (a.g.zw) {
-        if (b16) hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 16, 0, false, true>), dim3(blocks), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 4, 0, false, true>), dim3(blocks), dim3(256), 0, s, a);
-        return;
-    }
-    if (b16) hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 16>), dim3(blocks), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((shortk_kernel<NB, KS, INT4, VEC, 4>), dim3(blocks), dim3(256), 0, s, a);
-}
-
-template <bool INT4, int VEC> static void launch_shortk_ks(const ShortKArgs &a, int ks, int64_t waves, hipStream_t s, bool alds)
-{
-    if (ks <= 1) launch_shortk_one<1, INT4, VEC>(a, waves, s, false);
-    else if (ks <= 2) launch_shortk_one<2, INT4, VEC>(a, waves, s, false);
-    else if (ks <= 4) launch_shortk_one<4, INT4, VEC>(a, waves, s, alds);
-    else launch_shortk_one<8, INT4, VEC>(a, waves, s, alds);
+    if (v16) launch_shortk_ks<false, 16>(a, ks, waves, s, alds);
+    else launch_shortk_ks<false, 8>(a, ks, waves, s, false);
 }
 
 bool shortk_eligible(const IgemmArgs &g, int b_mode, bool strided)
@@ -113,13 +65,8 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
         a.walkers = (int)wk;
         waves = groups * wk; // workgroups
     }
-    if (b_mode == B_INT4) {
-        if (v16) launch_shortk_ks<true, 16>(a, ks, waves, s, alds);
-        else launch_shortk_ks<true, 8>(a, ks, waves, s, false);
-    } else {
-        if (v16) launch_shortk_ks<false, 16>(a, ks, waves, s, alds);
-        else launch_shortk_ks<false, 8>(a, ks, waves, s, false);
-    }
+    if (b_mode == B_INT4) launch_shortk_int4(a, ks, waves, s, v16, alds);
+    else launch_shortk_int8(a, ks, waves, s, v16, alds);
     const qnn_status st = launch_status(hipGetLastError());
     if (st != QNN_OK || !add_pass) return st;
     return launch_add_inplace(g.C, g.ldc, g.R, g.ldr, g.M, g.N, g.add, s);
