@@ -165,9 +165,16 @@ static qnn_status run_igemm_zw(IgemmArgs &g, int a_mode, int b_mode, int vec, vo
     const bool i4 = b_mode == B_INT4;
     const bool chunks = vec == 16 && (b_mode == B_INT8 || (i4 && aligned_to(g.B, 16) && (g.ldb % 32) == 0 && (g.K % 32) == 0));
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
-    // few tiles (two workgroups of 64x64 per CU), or a K that the larger tiles do not take: 3136 x 512 x 512 6.4 us on
-    // 64x64 tiles, 9.5 on 128x128
-    if (chunks && tiles64 <= 0x7ffffff && (tiles64 <= 512 || (g.K % 64) != 0)) return launch_status(launch_tile64(g, a_mode == A_MATRIX, i4, SplitK{1, 0, nullptr}, s));
+    // K % 64 == 0: 64x64 tiles while one round of two workgroups per CU holds them all, 128x128 and 256x256 beyond (us, 64x64 and
+    // 128x128: 1024 x 1024 x 512 7.5 and 11.7, 4096 x 512 x 4096 26 and 31).
+    // Other K: the staged 64x64 tile, whose four workgroups per CU hide each other's latencies, is ahead where the pipeline
+    // hardly fills, and where its single round meets a second one of three workgroups per CU (staged and pipelined: 25088 x 256 x
+    // 288 9 and 11, 4096 x 4096 x 544 34 and 38, 1056 54 and 55, 4064 195 and 166; 2048 x 2048 x 1568 22 and 24, 4064 52 and 51;
+    // with 4-bit weights 4096 x 4096 x 288 26 and 29, 544 37 and 37, 1056 60 and 54; 2048 x 1024 x 352 9.0 and 8.2).
+    const bool pipelined = (g.K % 64) == 0 ? tiles64 <= 512
+                           : i4            ? g.K >= 512 || tiles64 <= 768
+                                           : g.K >= 1024 && (tiles64 <= 768 || tiles64 > 1024 || g.K >= 4032);
+    if (chunks && tiles64 <= 0x7ffffff && pipelined) return launch_status(launch_tile64(g, a_mode == A_MATRIX, i4, SplitK{1, 0, nullptr}, s));
     const bool aligned_for_dma = chunks && (g.K % 64) == 0 && g.lda < (1 << 23) && g.ldb < (1 << 23);
     if ((b_mode == B_INT8 || i4) && aligned_for_dma && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 0x7ffffff) {
         // large products: the 256x256 tile once it fills most of the chip, else 128x128

@@ -27,7 +27,8 @@ def _weights(rng, shape, bits):
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("asym", [False, True])
 @pytest.mark.parametrize("z_a", [128, 9])
-@pytest.mark.parametrize("M,N,K", [(65, 64, 320), (131, 66, 288), (70, 129, 384), (200, 31, 512), (97, 80, 608), (2373, 976, 288), (129, 65, 1056)])
+@pytest.mark.parametrize("M,N,K", [(65, 64, 320), (131, 66, 288), (70, 129, 384), (200, 31, 512), (97, 80, 608), (2373, 976, 288), (129, 65, 1056),
+                                   (1403, 1400, 1056), (3130, 1150, 1056), (5000, 1001, 1056)]) # one round, none of tile64.h's, several
 def test_product(bits, asym, z_a, M, N, K):
     rng = np.random.default_rng(M + N + K + bits)
     A = rng.integers(0, 256, (M, K)).astype(np.uint8)
