@@ -223,7 +223,7 @@ __device__ __forceinline__ ChannelParams<TN> load_channel_params(const IgemmArgs
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int n = n0 + wave_n * WTN + j * 32 + (lane & 31);
-        p.bias[j] = 0, p.mult[j] = 0, p.shift[j] = 1, p.zw[j] = 0;
+        p.bias[j] = 0, p.mult[j] = 1 << 30, p.shift[j] = 1, p.zw[j] = 0; // columns beyond N: what every form of the rescale takes
         if (n < g.N) {
             p.bias[j] = g.bias ? g.bias[n] : 0;
             p.zw[j] = g.zw ? g.zw[n] : 0;
