@@ -430,11 +430,13 @@ __global__ void __launch_bounds__(kThreads) qadd_kernel(const uint8_t *__restric
 }
 
 // The same with one vector of 4 W codes per lane, requested ahead of the tables.  Small tensors are bound by latencies (a
-// lane of the kernel above waits for its tables, then for its codes, and looks up 128 of them one after another, on 15
+// lane of the kernel above waits for its tables, then for its codes, and looks up 128 of them one after another, on 16
 // workgroups where a layer has 250880), larger ones by how many requests are in flight.  16 codes per lane against the kernel
 // above, us: 250880 codes 2.4 and 3.7, 2408448 3.7 and 4.4, 38.5 M 22.7 and 24.1, 51 M 29.5 and 31.7, 77 M 40-44 and 42; then
 // the tables of ever more workgroups cost more: 150 M 81 and 77.  8 codes per lane: 250880 2.2, 2408448 3.7, 9.6 M 8.2 (16: 7.3).
-constexpr size_t kQaddLanes = (size_t)64 << 20;
+// In the general form a workgroup's arithmetic weighs more than its latencies from 12 M codes on: 4.2 M 5.9 and 7.1, 9.6 M 10.6
+// and 12.0, 12.6 M 12.2 and 12.2, 25 M 22.7 and 21.5, 50 M 43.3 and 38.8.
+constexpr size_t kQaddLanes = (size_t)64 << 20, kQaddLanesGeneral = (size_t)12 << 20;
 template <bool FUSED, int W>
 __global__ void __launch_bounds__(kThreads) qadd_lane_kernel(const uint8_t *a, const uint8_t *b, uint8_t *y, size_t n, QaddArgs g)
 {
@@ -743,7 +745,7 @@ qnn_status qnn_qadd(const uint8_t *a, int32_t z_a, int32_t mult_a, int32_t shift
     QaddArgs g = {z_a, mult_a, shift_a, z_b, mult_b, shift_b, left_shift, mult_o, shift_o, z_out, act_min, act_max};
     const bool fused = shift_o >= 1 && shift_o <= 20 && shift_a >= 0 && shift_b >= 0 && left_shift <= 20;
     const hipStream_t s = as_stream(stream);
-    if (n >= 8 && n <= kQaddLanes) { // see kQaddLanes; 8 codes per lane while that is no more than a workgroup per CU
+    if (n >= 8 && n <= (fused ? kQaddLanes : kQaddLanesGeneral)) { // see kQaddLanes; 8 codes per lane while that is no more than a workgroup per CU
         const bool narrow = n <= (size_t)256 * kThreads * 8;
         const dim3 grid((unsigned)((n / (narrow ? 8 : 16) + kThreads - 1) / kThreads));
         if (fused && narrow) hipLaunchKernelGGL((qadd_lane_kernel<true, 2>), grid, dim3(kThreads), 0, s, a, b, y, n, g);

@@ -124,7 +124,8 @@ def test_qadd_all_code_pairs_and_odd_parameters():
         assert_same(got, want, f"qadd all pairs {s_a},{s_b},{s_o}")
 
 
-@pytest.mark.parametrize("n", [7, 8, 9, 15, 16, 2047, 2049, (1 << 19) - 1, 1 << 19, (1 << 19) + 1, (1 << 19) + 15, 64 << 20, (64 << 20) + 3])
+@pytest.mark.parametrize("n", [7, 8, 9, 15, 16, 2047, 2049, (1 << 19) - 1, 1 << 19, (1 << 19) + 1, (1 << 19) + 15, 12 << 20, (12 << 20) + 5,
+                               64 << 20, (64 << 20) + 3])
 @pytest.mark.parametrize("left_shift", [20, 22])
 @pytest.mark.parametrize("offset,in_place", [(0, False), (1, True)])
 def test_qadd_widths(n, left_shift, offset, in_place):
