@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
     ChannelRescale c_r[NB];
     int32_t c_mult[NB], c_corr[NB], c_shift[NB]; // general form
     const bool ties = rescale_ties(g.lo_rel);
-    bool fused_ok = g.small_acc >= 2;
+    bool range_ok = g.small_acc >= 2, fused_ok = true;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         int n = n0 + j * 32 + frow;
@@ -91,12 +91,13 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
             colsum += __shfl_xor(colsum, 32);
         }
         const int32_t b = g.bias ? g.bias[n] : 0, mu = g.mult[n], sf = g.shift[n];
-        fused_ok = fused_ok && channel_rescale_ok(mu, sf, ties) && b > -(1 << 27) && b < (1 << 27);
+        range_ok = range_ok && rescale_in_range(sf) && b > -(1 << 27) && b < (1 << 27);
+        fused_ok = fused_ok && range_ok && channel_rescale_ok(mu, sf, ties);
         c_corr[j] = b + (128 - g.z_a) * colsum;
         c_mult[j] = mu, c_shift[j] = sf;
         c_r[j] = make_channel_rescale(mu, sf, c_corr[j], g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     }
-    const bool fused = __all(fused_ok);
+    const bool fused = __all(fused_ok), in_range = __all(range_ok);
 
     // ---- rows (the dispatcher guarantees M < 2^31 and 32-bit offsets inside one image / matrix)
     const int M = (int)g.M;
@@ -293,19 +294,11 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
                     if (j >= blocks_here) break;
-                    const RescaleParams rp = make_rescale(c_mult[j], c_shift[j]);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int32_t a[4] = {acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
-                        uint32_t x = 0;
-                        if constexpr (Mode::kFused) {
-                            x = channel_codes4<Mode::kTies, Mode::kFull>(a, c_r[j]);
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                x |= (uint32_t)(clamp_i32(g.lo_rel, g.hi_rel, rescale_general(a[e] + c_corr[j], rp)) + g.z_out) << (8 * e);
-                        }
-                        put(j, q, x);
+                        if constexpr (Mode::kFused) put(j, q, channel_codes4<Mode::kTies, Mode::kFull>(a, c_r[j]));
+                        else put(j, q, other_codes4(a, c_mult[j], c_shift[j], c_corr[j], in_range, g.z_out, g.lo_rel, g.hi_rel));
                     }
                 }
                 wave_sync();

@@ -277,9 +277,9 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
     const int ho0 = ph * RH, wo0 = (int)pw * RW;
 
     // ---- Everything that the lane needs from memory is requested before anything is waited for: the window (whole where
-    // the registers hold it; the tall patch of stride 2 goes row by row), the weights and the parameters of the rescale.  As a chain of four round trips, weights, bias,
-    // window, rescale, a 14 x 14 x 512 layer took 4.3 us on one image, 6.0 on 16 with weight zero-points and 7.6 on 64,
-    // now 3.8, 5.5 and 6.4.
+    // the registers hold it; the tall patch of stride 2 goes row by row), the weights and the parameters of the
+    // rescale.  As a chain of four round trips, weights, bias, window, rescale, a 14 x 14 x 512 layer took 4.3 us on one
+    // image, 6.0 on 16 with weight zero-points and 7.6 on 64, now 3.8, 5.5 and 6.4.
     const int hi0 = ho0 * S - g.ph, wi0 = wo0 * S - g.pw;
     const uint8_t *img = g.x + (int64_t)n * g.H * g.W * g.C; // scalar
     const uint32_t fill = (uint32_t)g.z_x * 0x01010101u;
@@ -425,10 +425,11 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
     // ---- epilogue: the fused form of the rescale when every channel of the wave allows it, else the general form
     ChannelRescale cr[4];
     const bool ties = rescale_ties(g.lo_rel);
-    bool fused_ok = true;
+    bool range_ok = true, fused_ok = true;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        fused_ok = fused_ok && channel_rescale_ok(mu[j], sf[j], ties) && bias[j] > -(1 << 28) && bias[j] < (1 << 28);
+        range_ok = range_ok && rescale_in_range(sf[j]) && bias[j] > -(1 << 28) && bias[j] < (1 << 28);
+        fused_ok = fused_ok && range_ok && channel_rescale_ok(mu[j], sf[j], ties);
         cr[j] = make_channel_rescale(mu[j], sf[j], 0, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     }
     if constexpr (ZW) {
@@ -440,7 +441,7 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc[r][p][j] = __mul24(acc[r][p][j], sign[j]) + init[j];
     }
-    const bool fused = __all(fused_ok);
+    const bool fused = __all(fused_ok), in_range = __all(range_ok);
     uint8_t *const out_img = g.y + (int64_t)n * g.Ho * g.Wo * g.C; // scalar
     const uint32_t out_off = (uint32_t)(wo0 * g.C + c0);            // inside an output row (Wo * C < 2^31)
     auto finish = [&](auto mode_tag) {
@@ -449,30 +450,18 @@ __global__ void __launch_bounds__(256) dwconv3x3_dot_kernel(const DwArgs g)
         for (int r = 0; r < RH; ++r) {
             if (ho0 + r >= g.Ho) break; // scalar
             uint8_t *out = out_img + (int64_t)(ho0 + r) * g.Wo * g.C; // scalar
-            uint32_t pixel[4]; // four channels of a pixel
-            if constexpr (Mode::kFused) {
-                // the four pixels of a channel share its shift and are packed together; the 4x4 bytes are transposed then
-                uint32_t ch[4];
+            // the four pixels of a channel share its shift and are packed together; the 4x4 bytes are transposed then
+            uint32_t ch[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int32_t a[4] = {acc[r][0][j], acc[r][1][j], acc[r][2][j], acc[r][3][j]};
-                    ch[j] = channel_codes4<Mode::kTies, Mode::kFull>(a, cr[j]);
-                }
-                const uint32_t lo01 = __builtin_amdgcn_perm(ch[1], ch[0], 0x05010400u), hi01 = __builtin_amdgcn_perm(ch[1], ch[0], 0x07030602u);
-                const uint32_t lo23 = __builtin_amdgcn_perm(ch[3], ch[2], 0x05010400u), hi23 = __builtin_amdgcn_perm(ch[3], ch[2], 0x07030602u);
-                pixel[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u), pixel[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
-                pixel[2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), pixel[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
-            } else {
-#pragma unroll
-                for (int p = 0; p < RW; ++p) {
-                    pixel[p] = 0;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general(acc[r][p][j], make_rescale(mu[j], sf[j]))) + g.z_out;
-                        pixel[p] |= (uint32_t)y << (8 * j);
-                    }
-                }
+            for (int j = 0; j < 4; ++j) {
+                const int32_t a[4] = {acc[r][0][j], acc[r][1][j], acc[r][2][j], acc[r][3][j]};
+                if constexpr (Mode::kFused) ch[j] = channel_codes4<Mode::kTies, Mode::kFull>(a, cr[j]);
+                else ch[j] = other_codes4(a, mu[j], sf[j], 0, in_range, g.z_out, g.lo_rel, g.hi_rel);
             }
+            const uint32_t lo01 = __builtin_amdgcn_perm(ch[1], ch[0], 0x05010400u), hi01 = __builtin_amdgcn_perm(ch[1], ch[0], 0x07030602u);
+            const uint32_t lo23 = __builtin_amdgcn_perm(ch[3], ch[2], 0x05010400u), hi23 = __builtin_amdgcn_perm(ch[3], ch[2], 0x07030602u);
+            const uint32_t pixel[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                                       __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
 #pragma unroll
             for (int p = 0; p < RW; ++p)
                 if (wo0 + p < g.Wo) dw_store<NT>(out + (out_off + (uint32_t)(p * g.C)), pixel[p]);
@@ -607,9 +596,9 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
     // ---- epilogue constants of this lane's channel
     using Mode = RescaleModeTraits<MODE>;
     const int32_t mu = ch_ok ? g.mult[ch] : 1 << 30, sf = ch_ok ? g.shift[ch] : 1;
-    const bool fused_ok = channel_rescale_ok(mu, sf, Mode::kTies) && bias > -(1 << 28) && bias < (1 << 28);
+    const bool range_ok = rescale_in_range(sf) && bias > -(1 << 28) && bias < (1 << 28);
     const ChannelRescale cr = make_channel_rescale(mu, sf, init, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, Mode::kTies);
-    const bool fused = __all(fused_ok); // wave-uniform
+    const bool in_range = __all(range_ok), fused = __all(range_ok && channel_rescale_ok(mu, sf, Mode::kTies)); // wave-uniform
     if (ZW && !__all(zw_bytes)) { // the whole wave: its lanes share the matrix instructions
         dw_direct_block(g, n, hb, hb + rows, w0 + half, w0 + TP, 2, ch, ch_ok ? ch + 1 : ch);
         __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8)); // vmcnt(0): no copy may land in LDS after the wave is gone
@@ -662,7 +651,7 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)out_row);
         uint8_t *out = g.y + row_off;
         uint32_t x[4];
-        if (fused) { // one test per output row; the general form below is the rare case
+        if (fused) { // one test per output row; the forms below are the rare case
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 int32_t a[4];
@@ -670,16 +659,21 @@ __global__ void __launch_bounds__(256, 2) dwconv3x3_mfma_kernel(const DwArgs g, 
                 for (int e = 0; e < 4; ++e) a[e] = signed_sum(acc[slot][4 * q + e]);
                 x[q] = channel_codes4<Mode::kTies, Mode::kFull>(a, cr);
             }
+        } else if (in_range) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                int32_t a[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[e] = signed_sum(acc[slot][4 * q + e]);
+                x[q] = other_codes4(a, mu, sf, init, true, g.z_out, g.lo_rel, g.hi_rel);
+            }
         } else {
-            const RescaleParams rp = make_rescale(mu, sf);
 #pragma nounroll
             for (int q = 0; q < 4; ++q) {
-                x[q] = 0;
+                int32_t a[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int32_t y = clamp_i32(g.lo_rel, g.hi_rel, rescale_general((int32_t)((uint32_t)signed_sum(acc[slot][4 * q + e]) + (uint32_t)init), rp)) + g.z_out;
-                    x[q] |= (uint32_t)y << (8 * e);
-                }
+                for (int e = 0; e < 4; ++e) a[e] = signed_sum(acc[slot][4 * q + e]);
+                x[q] = other_codes4(a, mu, sf, init, false, g.z_out, g.lo_rel, g.hi_rel);
             }
         }
 #pragma unroll

@@ -256,7 +256,7 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
     const int wave_m = wave / WN, wave_n = wave % WN;
     const int frag_row = lane & 31, frag_half = lane >> 5;
     // with weight zero-points |z_w * rowsum| <= 2^15 * K joins the sum: the 32-bit forms stay exact for K <= 2048
-    bool fast_ok = g.small_acc >= 1 && (!ZW || g.K <= 4096), fused_ok = g.small_acc >= 2 && (!ZW || g.K <= 2048);
+    bool fast_ok = g.small_acc >= 1 && (!ZW || g.K <= 4096), range_ok = g.small_acc >= 2 && (!ZW || g.K <= 2048), fused_ok = true;
     int32_t corr[TN];
     RescaleParams rp[TN];
     ChannelRescale fr[TN];
@@ -271,10 +271,11 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
         rp[j] = make_rescale(mu, sf);
         // |acc + corr| < 2^30 for the fast form, < 2^29 for the fused forms
         fast_ok = fast_ok && sf >= 0 && b > -(1 << 28) && b < (1 << 28);
-        fused_ok = fused_ok && channel_rescale_ok(mu, sf, ties) && b > -(1 << 27) && b < (1 << 27);
+        range_ok = range_ok && rescale_in_range(sf) && b > -(1 << 27) && b < (1 << 27);
+        fused_ok = fused_ok && range_ok && channel_rescale_ok(mu, sf, ties);
         fr[j] = make_channel_rescale(mu, sf, corr[j], g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     }
-    const bool fast = __all(fast_ok), fused = __all(fused_ok);
+    const bool fast = __all(fast_ok), in_range = __all(range_ok), fused = __all(fused_ok);
     // A lane holds, for one column, the rows 8q + 4*half + {0,1,2,3} (q = 0..3) of each 32x32
     // tile.  The four bytes of a row group are packed into a dword and the 4x4 byte blocks are
     // transposed across the four lanes of a quad (two DPP exchanges + byte permutes), so that
@@ -333,6 +334,8 @@ __device__ __forceinline__ void igemm_epilogue_impl(const IgemmArgs &g, i32x16 (
             using Mode = RescaleModeTraits<decltype(mode_tag)::value>;
             if constexpr (Mode::kFused) run([&](const int32_t (&a)[4], int j) { return channel_codes4<Mode::kTies, Mode::kFull>(a, fr[j]); });
         });
+    } else if (in_range) {
+        run([&](const int32_t (&a)[4], int j) { return other_codes4(a, cp.mult[j], cp.shift[j], corr[j], true, g.z_out, g.lo_rel, g.hi_rel); });
     } else if (fast) {
         run([&](const int32_t (&a)[4], int j) {
             int32_t y[4];

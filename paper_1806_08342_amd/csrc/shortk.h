@@ -60,15 +60,13 @@ struct ShortKColumn {
 };
 
 // Constants of a column from the sum of its weights and its parameters; k_loaded: the k that a weight zero-point's
-// activation sums run over (those from K on read as the code 0).  Returns whether the column allows the fused form.
-__device__ __forceinline__ bool shortk_column(ShortKColumn &c, const IgemmArgs &g, int32_t colsum, int32_t bias, int32_t mult, int32_t shift,
+// activation sums run over (those from K on read as the code 0).
+__device__ __forceinline__ void shortk_column(ShortKColumn &c, const IgemmArgs &g, int32_t colsum, int32_t bias, int32_t mult, int32_t shift,
                                               int32_t zw, int k_loaded)
 {
-    const bool ties = rescale_ties(g.lo_rel);
     const int32_t corr = bias + (128 - g.z_a) * colsum - zw * (g.K * (128 - g.z_a) + 128 * (k_loaded - g.K));
     c.mult = mult, c.shift = shift, c.zw = zw;
-    c.r = make_channel_rescale(mult, shift, corr, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
-    return channel_rescale_ok(mult, shift, ties) && bias > -(1 << 27) && bias < (1 << 27);
+    c.r = make_channel_rescale(mult, shift, corr, g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, rescale_ties(g.lo_rel));
 }
 
 // All 65536 results of an add from its tables of rescaled codes (add_fill_tables).  Entry [m][r] = code of the sum, at
@@ -98,7 +96,7 @@ template <int WAVES> __device__ __forceinline__ void fill_pair_table(uint8_t *pa
                 x = channel_codes4<Mode::kTies, Mode::kFull>(sum, r);
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) x |= add_value1<false>(tm, tr[e], ao) << (8 * e);
+                for (int e = 0; e < 4; ++e) x |= (ao.fused ? add_value1<true>(tm, tr[e], ao) : add_value1<false>(tm, tr[e], ao)) << (8 * e);
             }
             out[m * 64 + ((threadIdx.x ^ (uint32_t)m) & 63u)] = x;
         }
@@ -251,7 +249,8 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
     i32x4 first[KS];
     if constexpr (FIRST_AHEAD) load_rows(walker < row_blocks ? walker : row_blocks - 1, first);
 
-    bool fused_ok = g.small_acc >= 2;
+    bool range_ok = g.small_acc >= 2, fused_ok = true;
+    const bool ties = rescale_ties(g.lo_rel);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         int32_t colsum = 0;
@@ -267,9 +266,12 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         colsum += __shfl_xor(colsum, 32);
         if (INT4) colsum >>= 4; // weights are kept times 16; exact
         // (the sums of ZW count code - 128; where pieces of 8 are loaded, also -128 for every k from K to KS * 32, read as zeros)
-        fused_ok = shortk_column(col[j], g, colsum, g.bias ? p_bias[j] : 0, p_mult[j], p_shift[j], p_zw[j], VEC == 16 ? g.K : KS * 32) && fused_ok;
+        const int32_t b = g.bias ? p_bias[j] : 0;
+        shortk_column(col[j], g, colsum, b, p_mult[j], p_shift[j], p_zw[j], VEC == 16 ? g.K : KS * 32);
+        range_ok = range_ok && rescale_in_range(p_shift[j]) && b > -(1 << 27) && b < (1 << 27);
+        fused_ok = fused_ok && range_ok && channel_rescale_ok(p_mult[j], p_shift[j], ties);
     }
-    const bool fused = __all(fused_ok), k_tail = VEC == 16 && g.K != KS * 32;
+    const bool fused = __all(fused_ok), in_range = __all(range_ok), k_tail = VEC == 16 && g.K != KS * 32;
     const i32x4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 
     // ALDS: copy of row block rbx into a_tiles[buf]; wave w, pass i moves LDS chunks (i * WAVES + w) * 64 + lane:
@@ -476,7 +478,6 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             if (j >= blocks_here) break;
-            const RescaleParams rp = make_rescale(col[j].mult, col[j].shift); // general form
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 int32_t a[4];
@@ -486,15 +487,8 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
                     if (INT4) a[e] >>= 4;
                     if constexpr (ZW) a[e] -= __mul24(col[j].zw, sums[4 * q + e]);
                 }
-                uint32_t x = 0;
-                if constexpr (Mode::kFused) {
-                    x = channel_codes4<Mode::kTies, Mode::kFull>(a, col[j].r);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        x |= (uint32_t)(clamp_i32(lo_rel, hi_rel, rescale_general(a[e] - col[j].r.ncorr, rp)) + z_out) << (8 * e);
-                }
-                put(j, q, x);
+                if constexpr (Mode::kFused) put(j, q, channel_codes4<Mode::kTies, Mode::kFull>(a, col[j].r));
+                else put(j, q, other_codes4(a, col[j].mult, col[j].shift, -col[j].r.ncorr, in_range, z_out, lo_rel, hi_rel));
             }
         }
         // the tile is private to the wave and LDS operations of one wave complete in order:

@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
     ChannelRescale c_r[NB];
     int32_t c_mult[NB], c_corr[NB], c_shift[NB]; // general form
     const bool ties = rescale_ties(g.lo_rel);
-    bool fused_ok = true;
+    bool range_ok = true, fused_ok = true;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         int co = j * 32 + frow;
@@ -113,13 +113,14 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
         }
         colsum += __shfl_xor(colsum, 32);
         const int32_t b = g.bias ? g.bias[co] : 0, mu = g.mult[co], sf = g.shift[co];
-        fused_ok = fused_ok && channel_rescale_ok(mu, sf, ties) && b > -(1 << 27) && b < (1 << 27);
+        range_ok = range_ok && rescale_in_range(sf) && b > -(1 << 27) && b < (1 << 27);
+        fused_ok = fused_ok && range_ok && channel_rescale_ok(mu, sf, ties);
         c_corr[j] = b + (128 - g.z_a) * colsum;
         if constexpr (ZW) c_corr[j] -= g.zw[co] * KH * s.run * (128 - g.z_a);
         c_mult[j] = mu, c_shift[j] = sf;
         c_r[j] = make_channel_rescale(mu, sf, c_corr[j], g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     }
-    const bool fused = __all(fused_ok);
+    const bool fused = __all(fused_ok), in_range = __all(range_ok);
     // ZW (per-column weight zero-points): the activation sums as one more accumulator, see shortk.h
     i32x4 ones;
 #pragma unroll
@@ -266,7 +267,6 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
             };
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                const RescaleParams rp = make_rescale(c_mult[j], c_shift[j]);
                 int32_t zw = 0;
                 if constexpr (ZW) zw = g.zw[j * 32 + frow < g.N ? j * 32 + frow : g.N - 1];
 #pragma unroll
@@ -277,15 +277,8 @@ __global__ void __launch_bounds__(256) stemwave_kernel(const StemWaveArgs s)
                         a[e] = acc[j][4 * q + e];
                         if constexpr (ZW) a[e] -= __mul24(zw, sums[4 * q + e]);
                     }
-                    uint32_t x = 0;
-                    if constexpr (Mode::kFused) {
-                        x = channel_codes4<Mode::kTies, Mode::kFull>(a, c_r[j]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            x |= (uint32_t)(clamp_i32(g.lo_rel, g.hi_rel, rescale_general(a[e] + c_corr[j], rp)) + g.z_out) << (8 * e);
-                    }
-                    put(j, q, x);
+                    if constexpr (Mode::kFused) put(j, q, channel_codes4<Mode::kTies, Mode::kFull>(a, c_r[j]));
+                    else put(j, q, other_codes4(a, c_mult[j], c_shift[j], c_corr[j], in_range, g.z_out, g.lo_rel, g.hi_rel));
                 }
             }
             wave_sync();

@@ -104,3 +104,60 @@ def test_table_of_code_pairs(z_out, lo, hi, mult_o, shift_o):
     want = oracle.qadd(np.ascontiguousarray(mid), 0, R, 5, p, z_out, lo, hi)
     got = host(qnn.qgemm_add(dev(A), 0, dev(B), dev(mult), dev(shift), 0, 0, 255, dev(R), 5, p, z_out, lo, hi))
     assert_same(got, want, "pairs")
+
+
+SMALL = [((1 << 30) - 1, 9), (5, 3), (0, 1), (-(1 << 30), 9), (1 << 29, 20), (-(1 << 31), 12), (1 << 30, 9), ((1 << 31) - 1, 10)]
+
+
+def _small_params(n, rng):
+    """Shifts inside the fused forms' range, multipliers of any size and sign: channels beyond N aside, all waves meet both kinds"""
+    pick = [SMALL[i] for i in rng.integers(0, len(SMALL), n)]
+    return np.array([p[0] for p in pick], np.int32), np.array([p[1] for p in pick], np.int32)
+
+
+@pytest.mark.parametrize("z_out,lo,hi", RANGES)
+@pytest.mark.parametrize("kind", ["few", "shortk", "shortk8", "bres", "tile64", "dma128", "dma256", "p256x128", "staged", "patch", "patch2",
+                                  "matrix", "matrix2", "patch_asym", "matrix_asym", "stem", "stem7"])
+def test_multipliers_below_the_encoding(kind, z_out, lo, hi):
+    """Multipliers that are no encoding of a real number in [0.5, 1): the tie term's form does not take them"""
+    rng = np.random.default_rng(z_out + lo + len(kind))
+    products = dict(few=(9, 48, 64, ""), shortk=(2085, 272, 64, ""), shortk8=(1063, 272, 200, ""), bres=(33000, 80, 288, ""), tile64=(700, 190, 320, "dma64x64"),
+                    dma128=(300, 272, 320, "dma128x128"), dma256=(300, 272, 320, "dma256x256"), p256x128=(257, 144, 320, "p256x128"),
+                    staged=(200, 80, 72, "64x64"))
+    if kind in products:
+        M, N, K, tile = products[kind]
+        A, B = rng.integers(0, 256, (M, K)).astype(np.uint8), rng.integers(-2, 3, (N, K)).astype(np.int8)
+        mult, shift = _small_params(N, rng)
+        bias = _bias(N, shift, rng)
+        rows = np.arange(M) if M < 4000 else np.sort(rng.choice(M, 500, replace=False))
+        want = oracle.qgemm(A[rows], 77, B, mult, shift, z_out, lo, hi, bias=bias)
+        if tile:
+            qnn.tuning_set("QNN_FORCE_TILE", tile)
+        try:
+            got = host(qnn.qgemm(dev(A), 77, dev(B), dev(mult), dev(shift), z_out, lo, hi, bias=dev(bias)))[rows]
+        finally:
+            qnn.tuning_set("QNN_FORCE_TILE")
+    elif kind.startswith("stem"):
+        k, cout = (7, 48) if kind == "stem7" else (3, 32)
+        x, w = rng.integers(0, 256, (2, 37, 45, 3)).astype(np.uint8), rng.integers(-8, 9, (cout, k, k, 3)).astype(np.int8)
+        mult, shift = _small_params(cout, rng)
+        bias = _bias(cout, shift, rng)
+        want = oracle.qconv2d(x, 90, w, (2, 2), (k // 2, k // 2), mult, shift, z_out, lo, hi, bias=bias)
+        got = host(qnn.qconv2d(dev(x), 90, dev(w), (2, 2), (k // 2, k // 2), dev(mult), dev(shift), z_out, lo, hi, bias=dev(bias)))
+    else:
+        s, C = (2 if "2" in kind else 1), (48 if "matrix" in kind else 20)
+        x, w = rng.integers(0, 256, (2, 11, 61, C)).astype(np.uint8), rng.integers(-20, 21, (3, 3, C)).astype(np.int8)
+        mult, shift = _small_params(C, rng)
+        bias = _bias(C, shift, rng)
+        zw = rng.integers(-3, 4, C).astype(np.int32)
+        qnn.tuning_set("QNN_DW_VARIANT", "3" if "matrix" in kind else "0")
+        try:
+            if "asym" in kind:
+                want = oracle.qdwconv2d(x, 31, w, (s, s), (1, 1), mult, shift, z_out, lo, hi, bias=bias, z_w=zw)
+                got = host(qnn.qdwconv2d_asym(dev(x), 31, dev(w), dev(zw), (s, s), (1, 1), dev(mult), dev(shift), z_out, lo, hi, bias=dev(bias)))
+            else:
+                want = oracle.qdwconv2d(x, 31, w, (s, s), (1, 1), mult, shift, z_out, lo, hi, bias=bias)
+                got = host(qnn.qdwconv2d(dev(x), 31, dev(w), (s, s), (1, 1), dev(mult), dev(shift), z_out, lo, hi, bias=dev(bias)))
+        finally:
+            qnn.tuning_set("QNN_DW_VARIANT")
+    assert_same(got, want, kind)
