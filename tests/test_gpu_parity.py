@@ -134,14 +134,16 @@ def test_qadd_widths(n, left_shift, offset, in_place):
     rng = np.random.default_rng(n)
     a, b = (rng.integers(0, 256, n + 3, dtype=np.uint8) for _ in range(2))
     p = dict(oracle.qadd_params(0.02, 0.031, 0.04), left_shift=left_shift)
-    da, db = dev(a)[offset:offset + n], dev(b)[offset:offset + n]
-    y = da if in_place else dev(np.full(n + 64, 77, np.uint8))[:n]
-    a, b = a[offset:offset + n], b[offset:offset + n]
-    tail = None if in_place else y.as_strided((64,), (1,), n)
+    whole = dev(a) if in_place else dev(np.full(n + 64, 77, np.uint8))
+    around = np.concatenate([a[:offset], a[offset + n:]]) if in_place else np.full(64, 77, np.uint8)
+    a, b, db = a[offset:offset + n], b[offset:offset + n], dev(b)[offset:offset + n]
+    y = whole[offset:offset + n] if in_place else whole[:n]
+    da = y if in_place else dev(a)
     got = host(qnn.qadd(da, 120, db, 131, p, 128, 0, 255, out=y))
     pick = np.arange(n) if n < 10000 else np.unique(np.concatenate([np.arange(5000), np.arange(n - 5000, n), np.arange(0, n, 4099)]))
     assert_same(got[pick], oracle.qadd(a[pick], 120, b[pick], 131, p, 128, 0, 255), f"qadd n={n}")
-    assert tail is None or (host(tail) == 77).all()
+    whole = host(whole)
+    assert_same(np.concatenate([whole[:offset], whole[offset + n:]]), around, "bytes around the tensor")
 
 
 # ----------------------------------------------------------------------------------- qgemm
