@@ -20,7 +20,9 @@ stream the kernels run on:
   * the streaming kernels on configuration 5's tensor;
   * two calibration kernels (register-only MFMA loop, 1 GiB copy) that say what this machine
     sustains;
-and the CPU oracle on a bounded sample, and prints ONE JSON line.
+and the CPU oracle on a bounded sample, and prints ONE JSON line: the headline with the roofline of its dominant kernel and
+one figure per conv stack, short enough for a log that keeps the last 2000 characters.  The rows behind it, one JSON
+line of some 40 KB, go to the file of --details, without it to stderr.
 """
 from __future__ import annotations
 
@@ -536,6 +538,20 @@ def cpu_baseline():
     return out
 
 
+def headline(result):
+    """The line that is printed: what the rows add up to, without the rows."""
+    line = {k: v for k, v in result.items() if not isinstance(v, (list, dict))}
+    line["config"] = result["config"]
+    keep = ("bound", "kernel", "achieved", "peak", "unit", "frac", "launches_per_step", "avg_launch_us")
+    line["roofline"] = {k: result["roofline"][k] for k in keep}
+    stacks = {k: v["images_per_s"] for k, v in result.get("secondary", {}).items() if "images_per_s" in v}
+    if stacks:
+        line["stacks_images_per_s"] = stacks
+    if "cpu_baseline" in result:
+        line["cpu_baseline"] = {k: result["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind", "sample")}
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -543,6 +559,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=2)
     ap.add_argument("--no-secondary", action="store_true", help="skip the conv stacks, streaming kernels and calibration")
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--details", default=None, help="file for the per-shape and per-layer rows (default: stderr)")
     ap.add_argument("--eager", action="store_true", help="time the sweep as single launches instead of a graph replay")
     ap.add_argument("--streams", type=int, default=4,
                     help="streams the independent products of a sweep pass are spread over inside the graph (1: one after another)")
@@ -658,7 +675,12 @@ def main():
         result["secondary"] = sec
     if not args.no_cpu_baseline:
         result["cpu_baseline"] = cpu_baseline()
-    print(json.dumps(result))
+    if args.details:
+        with open(args.details, "w") as f:
+            f.write(json.dumps(result) + "\n")
+    else:
+        print(json.dumps(result), file=sys.stderr, flush=True)
+    print(json.dumps(headline(result)))
 
 
 if __name__ == "__main__":
