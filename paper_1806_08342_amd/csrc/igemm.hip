@@ -62,7 +62,9 @@ static Plan choose_plan(int64_t M, int64_t N, int64_t K, bool dma_ok, bool int4,
                 return Plan{(TileConfig)t, splits};
             }
     }
-    if (dma_ok && int4) { // the pipelined kernel expands nibbles for three tile shapes
+    // 4-bit weights: 256x256, 128x128 and 64x64 tiles (us, 64x64 / 128x128: 2048 x 1024 x 1024 11.3 / 14.5, 1792 x 1792 x 1024
+    // 16.0 / 15.1; 128x128 / 256x256: 4096 x 2048 x 4096 49 / 62)
+    if (dma_ok && int4) {
         const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
         if (K > 256 && M >= 128 && N >= 128 && t256 >= 160) return Plan{TILE_DMA_256x256, 1};
         if (M >= 128 && N >= 128 && t128 >= 192) return Plan{TILE_DMA_128x128, 1};

@@ -111,9 +111,7 @@ __device__ __forceinline__ bool assign_tile(int slot, int tiles_m, int tiles_n, 
 // bytes, two 16-byte chunks (one per 32-deep sub-step), a wave-level load covers 32 rows -- and
 // are expanded to int8 (times 16, see expand_int4) in registers after the fragment read.  Chunk c
 // of row r sits at position c ^ ((r / 8) % 2), which makes the 8-byte fragment reads of 32
-// consecutive rows conflict-free.  Waves without a B segment of their own (narrow tiles) fetch
-// the constant chunk into the unused half of the B area, so that every wave issues the same
-// number of loads per K-step.
+// consecutive rows conflict-free.  They take the first half of the stage's B area.
 // KTAIL: K need not be a multiple of 64.  Chunks of B beyond K are fetched from a chunk of zeros, chunks
 // of A from the row's last chunk (any bytes do: they meet zero weights).
 template <int BM, int BN, int WM, int WN, int A_MODE, int NSTAGE, bool SPLIT = false, bool ZW = false, bool B4 = false,
@@ -126,9 +124,8 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int TM = WTM / 32, TN = WTN / 32;
     constexpr int B_SEG_ROWS = B4 ? 32 : 16;                // B rows per wave-level load (1 KB)
-    constexpr int B_SEGS = BN / B_SEG_ROWS;                 // wave-level loads per stage that carry B rows
-    constexpr int A_LOADS = BM / 16 / NW, B_LOADS = (B_SEGS + NW - 1) / NW; // wave-level loads per stage and wave
-    static_assert(BM % (16 * NW) == 0 && (B4 || BN % (16 * NW) == 0), "whole 16-row segments per wave");
+    constexpr int A_LOADS = BM / 16 / NW, B_LOADS = BN / B_SEG_ROWS / NW; // wave-level loads per stage and wave
+    static_assert(BM % (16 * NW) == 0 && BN % (B_SEG_ROWS * NW) == 0, "whole segments per wave");
     static_assert(!B4 || !SPLIT, "4-bit weights run unsplit");
     constexpr int STAGE_BYTES = (BM + BN) * BK;
     constexpr int LOADS = A_LOADS + B_LOADS;
@@ -249,13 +246,10 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
             } else {
                 const int j = idx - A_LOADS;
                 if constexpr (B4) {
-                    const int seg = wave * B_LOADS + j; // wave-uniform
-                    const bool mine = seg < B_SEGS;
-                    const uint8_t *src = (live && mine) ? (b_tile + (k0 >> 1)) + b_lane_off[j] : fill_a;
+                    const uint8_t *src = live ? (b_tile + (k0 >> 1)) + b_lane_off[j] : fill_a;
                     if constexpr (KTAIL)
                         if (k0 + b_k[j] >= g.K) src = zero_b;
-                    // segments beyond the tile: into the unused second half of the B area
-                    dma16(src, stage + BM * BK + (mine ? seg * 1024 : BN * 32));
+                    dma16(src, stage + BM * BK + (wave * B_LOADS + j) * 1024);
                 } else {
                     const uint8_t *src = live ? (b_tile + k0) + b_lane_off[j] : fill_a;
                     if constexpr (KTAIL)

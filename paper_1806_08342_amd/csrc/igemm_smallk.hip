@@ -18,8 +18,9 @@ bool small_shape(int64_t M, int64_t N, int64_t K, bool conv, bool int4)
     // 4-bit weights: rows of 8 bytes take a branch around every load (5.3-9.4 us against 4.2-4.9 of the short-K kernel)
     if (int4 && K < 32) return false;
     // ... and a fourth workgroup does not fit a CU, so that past 768 the last few run alone: for some K the other kernels
-    // are ahead then (784 workgroups, here / there: K = 32 5.4-5.7 / 4.3-4.9, 288 5.6 / 5.3, 384 5.6 / 5.3; but 64 5.7-5.9 /
-    // 5.4-6.2, 264 7.3 / 7.9, 448 5.6 / 5.6, 512 5.4 / 5.9, 704 6.0 / 6.7)
+    // are ahead then (784 workgroups, here / there: K = 32 5.4-5.7 / 4.4-4.9, 64 6.3 / 4.8-5.3, 128 6.3 / 5.3-6.1, 192 6.3 / 4.8,
+    // 288 and 384 5.6 / 5.5, 448 6.5 / 6.0; but 256 5.9 / 6.2, 264 8.1 / 7.9, 512 6.2 / 6.0, 704 6.8 / 7.0, 2048 8.7 / 12.0).  The
+    // line was drawn when the short-K kernel took 5.4-6.2 at K = 64 and the 64x64 tile 5.6 and more from 448 on.
     if (int4 && wgs > 768 && (K <= 48 || (K > 256 && K <= 384 && (K % 32) == 0))) return false;
     return wgs <= 800;
 }

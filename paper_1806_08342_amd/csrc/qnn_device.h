@@ -85,7 +85,8 @@ __device__ __forceinline__ int32_t rescale_fast(int32_t a, const RescaleParams &
 }
 
 // Fused form for any multiplier (the adds, requantize, the second pass of split-K, and the epilogues where ChannelRescale
-// below does not take a multiplier), valid when 1 <= shift <= 20 (rescale_in_range), |acc + corr| < 2^29 and 0 <= act_min <= act_max <= 255.  With a = acc + corr, n = shift:
+// below does not take a multiplier), valid when 1 <= shift <= 20 (rescale_in_range), |acc + corr| < 2^29 and
+// 0 <= act_min <= act_max <= 255.  With a = acc + corr, n = shift:
 //   T = hi32(4a * mult) = floor(a*mult / 2^30)     so  nearest(a*mult/2^31), ties up  = (T + 1) >> 1
 //   s = T >> 31 (0 or -1)                          and z_out + nearest(h/2^n), ties away from zero,
 //   w = T + 2s + c,  c = 2*(2^(n-1) + (z_out << n)) + 1            is  w >> (n + 1)
@@ -155,8 +156,8 @@ __device__ __forceinline__ int32_t med3_i32(int32_t v, int32_t lo, int32_t hi)
 // Without the tie term (2s above) whenever act_min >= z_out, every ReLU-like output range: it only acts for T < 0, where
 // both T + c and T - 2 + c stay below (z_out + 1) << (n+1) <= (act_min + 1) << (n+1), so that the clamp from below
 // gives act_min either way.  Everything that does not depend on acc is in the 64-bit addend of one multiply-add
-// (v_mad_i64_i32 runs at the rate of v_mul_hi_i32).  2 mult as a signed 32-bit factor is 2 mult - 2^32 (mult >= 2^30, as the encoding has it), which the
-// extra `acc` in the high half makes up for; the tie term comes in as the carry of that addition:
+// (v_mad_i64_i32 runs at the rate of v_mul_hi_i32).  2 mult as a signed 32-bit factor is 2 mult - 2^32 (mult >= 2^30, as the
+// encoding has it), which the extra `acc` in the high half makes up for; the tie term comes in as the carry of that addition:
 //   w = hi32(acc * (2 mult - 2^32) + (2 corr * mult + c * 2^31 - 2^32)) + acc + [acc >= -corr].
 // v_ashr_pk_u8_i32 shifts, saturates to 0 ... 255 and packs two values; a narrower output range is clamped before it.
 // Cycles per wave and output: 8.6 without tie term, 17.1 with it, 4.4 more for a narrower range; as add / mul_hi / add /
