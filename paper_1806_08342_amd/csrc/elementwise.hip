@@ -9,7 +9,10 @@
 // what the 256 MB cache could hold for the next pass over them (25 MB copies: 6.0 TB/s with plain loads, 5.5 with
 // non-temporal ones; a training step's three passes over 103 MB: 99 us and 106 us).
 // Pointers may have any alignment their element type allows (gfx950 loads and stores 16 bytes at any address).
+#include <atomic>
+
 #include "qnn_device.h"
+#include "tuning.h"
 
 namespace qnn {
 
@@ -41,12 +44,13 @@ static int grid_for(size_t vectors)
     return (int)(b < 1 ? 1 : (b > (size_t)kMaxBlocks ? (size_t)kMaxBlocks : b));
 }
 
-// tiles of kUnroll x kThreads consecutive vectors: item = load(v) for a whole tile, then use(v, item)
+// tiles of kUnroll x kThreads consecutive vectors, every `step`-th from `first` on: item = load(v) for a whole tile, then
+// use(v, item)
 template <int THREADS = kThreads, class Load, class Use>
-__device__ __forceinline__ void for_tiles(size_t nvec, Load load, Use use)
+__device__ __forceinline__ void for_tiles(size_t nvec, Load load, Use use, uint32_t first, uint32_t step)
 {
     constexpr size_t kTile = (size_t)THREADS * kUnroll;
-    for (size_t base = (size_t)blockIdx.x * kTile; base < nvec; base += (size_t)gridDim.x * kTile) {
+    for (size_t base = (size_t)first * kTile; base < nvec; base += (size_t)step * kTile) {
         const size_t v = base + threadIdx.x;
         if (base + kTile <= nvec) { // uniform
             decltype(load(v)) item[kUnroll];
@@ -59,6 +63,10 @@ __device__ __forceinline__ void for_tiles(size_t nvec, Load load, Use use)
                 if (v + u * THREADS < nvec) use(v + u * THREADS, load(v + u * THREADS));
         }
     }
+}
+template <int THREADS = kThreads, class Load, class Use> __device__ __forceinline__ void for_tiles(size_t nvec, Load load, Use use)
+{
+    for_tiles<THREADS>(nvec, load, use, blockIdx.x, gridDim.x);
 }
 
 // An element-wise pass: Op::kWidth elements per vector, load / store of a vector, one(i) for the last n % kWidth.
@@ -134,6 +142,28 @@ __global__ void minmax_init_kernel(qnn_dyn_qparams *st)
     st->key_max = 0u;
 }
 
+// Up to kMinmaxCounted workgroups the last one to arrive finishes the range.  key_min / key_max leave no room to count, so the
+// keys and the count are in a slot of the library, claimed on the device for the time of one call; key_min holds its number.
+// The host passes the slots round.  A call that finds its own taken (that of 1024 calls ago still runs, or a captured graph
+// brings the same number) has none: its workgroup 0 then does it all.
+struct RangeSlot {
+    uint32_t key_min, key_max, done, busy;
+};
+constexpr uint32_t kRangeSlots = 1024, kNoSlot = kRangeSlots;
+static __device__ RangeSlot g_range_slots[kRangeSlots];
+
+__global__ void minmax_claim_kernel(qnn_dyn_qparams *st, uint32_t number)
+{
+    RangeSlot &slot = g_range_slots[number < kRangeSlots ? number : 0];
+    const bool claimed = number < kRangeSlots && __hip_atomic_exchange(&slot.busy, 1u, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+    if (claimed) {
+        __hip_atomic_store(&slot.key_min, 0xffffffffu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&slot.key_max, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&slot.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    st->key_min = claimed ? number : kNoSlot;
+}
+
 __device__ __forceinline__ double nearest_away_dev(double v) { return v < 0.0 ? -floor(-v + 0.5) : floor(v + 0.5); }
 
 // range update (momentum 0: the batch range; else moving average) and quantizer parameters
@@ -157,18 +187,24 @@ __device__ __forceinline__ void finish_range(qnn_dyn_qparams *st, float bmin, fl
     st->scale = sc, st->zero_point = (int32_t)z;
 }
 
-__global__ void range_finalize_kernel(qnn_dyn_qparams *st, float momentum, int bits)
+__device__ __forceinline__ void finish_keys(qnn_dyn_qparams *st, uint32_t kmin, uint32_t kmax, float momentum, int bits)
 {
-    const bool any = st->key_min <= st->key_max;
-    finish_range(st, any ? key_float(st->key_min) : 0.0f, any ? key_float(st->key_max) : 0.0f, momentum, bits);
+    const bool any = kmin <= kmax;
+    finish_range(st, any ? key_float(kmin) : 0.0f, any ? key_float(kmax) : 0.0f, momentum, bits);
 }
+
+__global__ void range_finalize_kernel(qnn_dyn_qparams *st, float momentum, int bits) { finish_keys(st, st->key_min, st->key_max, momentum, bits); }
 
 // Bound by reading x and, behind that, by the atomics: about 10 ns each on one address, and the workgroups end
 // together, so that none finds the other's result already there.  One workgroup of 16 waves per CU: 25.7 M values
-// in 22 us where 2048 workgroups of 4 waves took 59.  Up to kMinmaxAlone values the three launches are most of the time: one
-// workgroup does it all (us in a graph and called one by one, against three launches: 16384 values 3.1 and 3.6 (6.6), 65536 5.0
-// and 4.9 (7.2), 114688 7.0 and 6.7 (7.4, 7.7), 131072 7.6 and 7.4 (7.5, 7.7), 163840 8.9 and 8.7 (7.4, 7.7)).
-constexpr int kMinmaxThreads = 1024, kMinmaxBlocks = 256;
+// in 22 us where 2048 workgroups of 4 waves took 59.  Launches are most of the time of smaller tensors: up to
+// kMinmaxAlone values one workgroup does it all, up to kMinmaxCounted workgroups the last one to arrive finishes the range (see
+// RangeSlot).  us in a graph / called one by one: one workgroup 65536 values 5.1 / 4.9 (three launches 7.2), 98304 6.3 / 6.2,
+// 114688 7.0 / 6.7, 131072 7.6 / 7.4, 163840 8.9 / 8.7; counted 114689 7.2 / 6.8-7.8, 131072 7.0 / 6.9-7.6, 262144 7.5 / 7.0-7.9,
+// 524288 7.8 / 7.4-8.2, 1048576 8.7 / 8.4-9.2; three launches 131072 7.4 / 7.5-9.0, 262144 7.5 / 7.5-9.9, 524288 7.8 / 7.6-10.1,
+// 1048576 8.5 / 8.3-10.1.  With 256 workgroups the count, one more atomic on one address each, takes 3 us longer than the launch
+// it saves.
+constexpr int kMinmaxThreads = 1024, kMinmaxBlocks = 256, kMinmaxCounted = 64;
 constexpr size_t kMinmaxAlone = (size_t)7 * kMinmaxThreads * kUnroll * 4;
 template <bool NT>
 __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__restrict__ x, size_t n, qnn_dyn_qparams *st, float momentum, int bits)
@@ -180,8 +216,16 @@ __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__r
         lo = fminf(lo, ok ? v : INFINITY), hi = fmaxf(hi, ok ? v : -INFINITY);
     };
     const size_t nvec = n / 4;
-    for_tiles<kMinmaxThreads>(nvec, [&](size_t v) { return load_any<f32x4, NT>(x + 4 * v); },
-              [&](size_t, f32x4 a) { take(a.x), take(a.y), take(a.z), take(a.w); });
+    auto load = [&](size_t v) { return load_any<f32x4, NT>(x + 4 * v); };
+    auto use = [&](size_t, f32x4 a) { take(a.x), take(a.y), take(a.z), take(a.w); };
+    const bool counted = gridDim.x > 1 && gridDim.x <= kMinmaxCounted;
+    const uint32_t number = counted ? st->key_min : 0u; // requested here, used behind the loads
+    for_tiles<kMinmaxThreads>(nvec, load, use);
+    const bool alone = gridDim.x == 1 || (counted && number >= kNoSlot);
+    if (alone && gridDim.x > 1) {
+        if (blockIdx.x != 0) return;
+        for_tiles<kMinmaxThreads>(nvec, load, use, 0, 1);
+    }
     if (blockIdx.x == 0 && threadIdx.x < n - nvec * 4) take(x[nvec * 4 + threadIdx.x]);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -193,19 +237,27 @@ __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__r
     __syncthreads();
     if (threadIdx.x != 0) return;
     for (int w = 1; w < kMinmaxThreads / 64; ++w) lo = fminf(lo, s_lo[w]), hi = fmaxf(hi, s_hi[w]);
-    if (gridDim.x > 1) {
-        if (lo <= hi) { // at least one finite value in this block
-            // atomics on one address serialise across the chip: skip them when the value seen so far is
-            // already as good (a stale read only costs an atomic that changes nothing)
-            const uint32_t klo = float_key(lo), khi = float_key(hi);
-            if (klo < __hip_atomic_load(&st->key_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&st->key_min, klo);
-            if (khi > __hip_atomic_load(&st->key_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&st->key_max, khi);
-        }
-    } else if (lo <= hi) {
-        finish_range(st, lo, hi, momentum, bits);
-    } else { // no finite value at all
-        finish_range(st, 0.0f, 0.0f, momentum, bits);
+    if (alone) {
+        finish_range(st, lo <= hi ? lo : 0.0f, lo <= hi ? hi : 0.0f, momentum, bits); // (no finite value at all: 0, 0)
+        return;
     }
+    RangeSlot *const slot = counted ? &g_range_slots[number] : nullptr;
+    uint32_t *const key_min = counted ? &slot->key_min : &st->key_min, *const key_max = counted ? &slot->key_max : &st->key_max;
+    if (lo <= hi) { // at least one finite value in this block
+        // atomics on one address serialise across the chip: skip them when the value seen so far is
+        // already as good (a stale read only costs an atomic that changes nothing)
+        const uint32_t klo = float_key(lo), khi = float_key(hi);
+        if (klo < __hip_atomic_load(key_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(key_min, klo);
+        if (khi > __hip_atomic_load(key_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(key_max, khi);
+    }
+    if (!counted) return; // range_finalize_kernel comes behind
+    // release: this workgroup's keys come before its count; acquire: the last one sees those of all (with a relaxed count, which
+    // no rule orders behind the keys, 0.1-0.4 us less)
+    if (__hip_atomic_fetch_add(&slot->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u != gridDim.x) return;
+    const uint32_t kmin = __hip_atomic_load(key_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t kmax = __hip_atomic_load(key_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&slot->busy, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    finish_keys(st, kmin, kmax, momentum, bits);
 }
 
 // quantize with parameters that live in device memory (8-bit codes)
@@ -665,10 +717,17 @@ qnn_status qnn_minmax(const float *x, size_t n, float momentum, int bits, qnn_dy
     const hipStream_t s = as_stream(stream);
     const size_t tiles = (n / 4 + kMinmaxThreads * kUnroll - 1) / (kMinmaxThreads * kUnroll);
     const dim3 grid((unsigned)(n <= kMinmaxAlone ? 1 : (tiles < kMinmaxBlocks ? tiles : kMinmaxBlocks)));
-    if (grid.x > 1) hipLaunchKernelGGL(minmax_init_kernel, dim3(1), dim3(1), 0, s, state);
+    const bool counted = grid.x > 1 && grid.x <= kMinmaxCounted;
+    if (counted) {
+        static std::atomic<uint32_t> calls{0};
+        const uint32_t number = tuning().range_slot >= 0 ? (uint32_t)tuning().range_slot : calls.fetch_add(1, std::memory_order_relaxed) % kRangeSlots;
+        hipLaunchKernelGGL(minmax_claim_kernel, dim3(1), dim3(1), 0, s, state, number);
+        // without it the reduction would take whatever the state holds for its slot
+        if (const qnn_status st = launch_status(hipGetLastError()); st != QNN_OK) return st;
+    } else if (grid.x > 1) hipLaunchKernelGGL(minmax_init_kernel, dim3(1), dim3(1), 0, s, state);
     if (n * 4 > kCacheBytes) hipLaunchKernelGGL(minmax_kernel<true>, grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
     else hipLaunchKernelGGL(minmax_kernel<false>, grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
-    if (grid.x > 1) hipLaunchKernelGGL(range_finalize_kernel, dim3(1), dim3(1), 0, s, state, momentum, bits);
+    if (grid.x > kMinmaxCounted) hipLaunchKernelGGL(range_finalize_kernel, dim3(1), dim3(1), 0, s, state, momentum, bits);
     return launch_status(hipGetLastError());
 }
 

@@ -20,6 +20,7 @@ struct Tuning {
     int shortk_alds = 1;      // QNN_SHORTK_ALDS: short-K kernel with the A rows staged in LDS per workgroup (K = 128, 256)
     int small = 1;            // QNN_SMALL: 0 = small launches (more than 64 rows) on the kernels for large ones
     int dw_xcd = 1;           // QNN_DW_XCD: depthwise workgroups renumbered so that an XCD gets neighbouring patches
+    int range_slot = -1;      // QNN_RANGE_SLOT: slot of the counted range reductions (-1 = the next one, 1024 = none)
     bool forced() const { return force_tile[0] != 0; }
 };
 

@@ -165,7 +165,7 @@ def test_rescale_u8_writes_a_channel_slice_of_a_concatenation():
 @pytest.mark.parametrize("n", [1, 4097, 65536, 65537, 16384 * 5 + 3, 16384 * 7, 16384 * 7 + 1, 16384 * 64, 16384 * 64 + 4, 16384 * 65])
 @pytest.mark.parametrize("momentum", [0.0, 0.75])
 def test_range_on_one_workgroup_counted_workgroups_and_more(n, momentum):
-    """The edges between one workgroup and several, whole tiles and parts; the work words of the state start as anything."""
+    """The edges between the three ways in which the reduction ends; the work words of the state start as anything."""
     rng = np.random.default_rng(n)
     x = rng.normal(0, 2, n).astype(np.float32)
     x[rng.integers(0, n)] = np.float32(np.nan) if n > 1 else x[0]
@@ -198,3 +198,43 @@ def test_parameters_stand_while_a_range_is_reduced(n, calls):
             samples[i].copy_(st[:4])
     torch.cuda.synchronize()
     assert (samples == want).all(), samples[(samples != want).any(1)][:4].tolist()
+
+
+@pytest.mark.parametrize("n", [16384 * 7 + 1, 500003, 16384 * 64 + 3])
+@pytest.mark.parametrize("slot", ["1024", "5"])
+def test_range_without_a_slot_of_its_own(n, slot):
+    """1024: none, one workgroup does it all; 5: all calls, on streams side by side, want the same one, and some get none"""
+    rng = np.random.default_rng(n)
+    xs = [(rng.normal(0, 1 + i, n)).astype(np.float32) for i in range(6)]
+    dx, states = [dev(x) for x in xs], [qnn.new_range_state() for _ in xs]
+    streams = [torch.cuda.Stream() for _ in xs]
+    torch.cuda.synchronize()
+    qnn.tuning_set("QNN_RANGE_SLOT", slot)
+    try:
+        for _ in range(20):
+            for x, st, stream in zip(dx, states, streams):
+                with torch.cuda.stream(stream):
+                    qnn.minmax(x, st)
+    finally:
+        qnn.tuning_set("QNN_RANGE_SLOT")
+    torch.cuda.synchronize()
+    for x, st in zip(xs, states):
+        s, z, lo, hi = oracle.dynamic_qparams(x)
+        r = qnn.read_range_state(st)
+        assert (r["scale"], r["zero_point"], r["xmin"], r["xmax"]) == (float(s), z, float(lo), float(hi))
+
+
+def test_counted_range_replayed_from_a_graph_beside_eager_calls():
+    x = [torch.randn(300000, device="cuda:0") for _ in range(2)]
+    states = [qnn.new_range_state() for _ in range(2)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        qnn.minmax(x[0], states[0])
+    for _ in range(5):
+        x[0].mul_(1.25)
+        graph.replay()
+        qnn.minmax(x[1], states[1])
+        for xi, st in zip(x, states):
+            s, z, lo, hi = oracle.dynamic_qparams(host(xi))
+            r = qnn.read_range_state(st)
+            assert (r["scale"], r["zero_point"], r["xmin"], r["xmax"]) == (float(s), z, float(lo), float(hi))
