@@ -243,8 +243,10 @@ static qnn_status run_igemm(IgemmArgs &g, int a_mode, int b_mode, int vec, void 
     const TileConfig cfg = plan.tile;
     const int64_t bm = kTileM[cfg], bn = kTileN[cfg];
     // Large outputs on the pipelined tiles: the add as a pass of its own is faster than the add inside the tile
-    // epilogue (measured 36 + 16 us against 57 us on 12544 x 2048 x 512: the epilogue looks both codes up in LDS
-    // tables, and a streaming pass hides that behind its loads); small layers keep the single launch.
+    // epilogue (the epilogue looks both codes up in LDS tables, and a streaming pass hides that behind its loads; us, both
+    // launches / epilogue: 12544 x 2048 x 512 48.9 / 52.2, 25088 x 1024 x 512 47.4 / 51.4, 8192 x 8192 x 2048 188 / 193); small
+    // layers keep the single launch.  (Drawn with an earlier epilogue: at 2^24 outputs themselves 34.0 / 28.9, on 8192 x 2048 x
+    // 512, and 42.9 / 41.4, on 12544 x 1344 x 512.)
     if (g.R && cfg >= TILE_DMA_128x128 && g.M * (int64_t)g.N >= ((int64_t)1 << 24)) {
         IgemmArgs plain = g;
         plain.R = nullptr;
