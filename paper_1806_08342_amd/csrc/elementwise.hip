@@ -206,7 +206,7 @@ __global__ void range_finalize_kernel(qnn_dyn_qparams *st, float momentum, int b
 // it saves.
 constexpr int kMinmaxThreads = 1024, kMinmaxBlocks = 256, kMinmaxCounted = 64;
 constexpr size_t kMinmaxAlone = (size_t)7 * kMinmaxThreads * kUnroll * 4;
-template <bool NT>
+template <bool NT, bool MANY> // MANY: more than kMinmaxCounted workgroups
 __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__restrict__ x, size_t n, qnn_dyn_qparams *st, float momentum, int bits)
 {
     float lo = INFINITY, hi = -INFINITY; // values that are not finite take no part in the range
@@ -218,10 +218,10 @@ __global__ void __launch_bounds__(kMinmaxThreads) minmax_kernel(const float *__r
     const size_t nvec = n / 4;
     auto load = [&](size_t v) { return load_any<f32x4, NT>(x + 4 * v); };
     auto use = [&](size_t, f32x4 a) { take(a.x), take(a.y), take(a.z), take(a.w); };
-    const bool counted = gridDim.x > 1 && gridDim.x <= kMinmaxCounted;
+    const bool counted = !MANY && gridDim.x > 1;
     const uint32_t number = counted ? st->key_min : 0u; // requested here, used behind the loads
     for_tiles<kMinmaxThreads>(nvec, load, use);
-    const bool alone = gridDim.x == 1 || (counted && number >= kNoSlot);
+    const bool alone = !MANY && (gridDim.x == 1 || number >= kNoSlot);
     if (alone && gridDim.x > 1) {
         if (blockIdx.x != 0) return;
         for_tiles<kMinmaxThreads>(nvec, load, use, 0, 1);
@@ -725,8 +725,10 @@ qnn_status qnn_minmax(const float *x, size_t n, float momentum, int bits, qnn_dy
         // without it the reduction would take whatever the state holds for its slot
         if (const qnn_status st = launch_status(hipGetLastError()); st != QNN_OK) return st;
     } else if (grid.x > 1) hipLaunchKernelGGL(minmax_init_kernel, dim3(1), dim3(1), 0, s, state);
-    if (n * 4 > kCacheBytes) hipLaunchKernelGGL(minmax_kernel<true>, grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
-    else hipLaunchKernelGGL(minmax_kernel<false>, grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
+    static_assert((kMinmaxBlocks + 1) * (size_t)kMinmaxThreads * kUnroll * 16 < kCacheBytes, "only launches of many workgroups exceed the cache");
+    if (n * 4 > kCacheBytes) hipLaunchKernelGGL((minmax_kernel<true, true>), grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
+    else if (grid.x > kMinmaxCounted) hipLaunchKernelGGL((minmax_kernel<false, true>), grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
+    else hipLaunchKernelGGL((minmax_kernel<false, false>), grid, dim3(kMinmaxThreads), 0, s, x, n, state, momentum, bits);
     if (grid.x > kMinmaxCounted) hipLaunchKernelGGL(range_finalize_kernel, dim3(1), dim3(1), 0, s, state, momentum, bits);
     return launch_status(hipGetLastError());
 }
