@@ -1,14 +1,12 @@
-// Launch routine of the weight-stationary short-K kernel; its forms for 8-bit weights.
+// Launch routine of the short-K kernels (shortk_ring.h, and shortk.h for operands that are whole 8-byte pieces only); forms of
+// the latter for 8-bit weights.
 #include "shortk_launch.h"
+#include "shortk_ring_launch.h"
 #include "tuning.h"
 
 namespace qnn {
 
-void launch_shortk_int8(const ShortKArgs &a, int ks, int64_t waves, hipStream_t s, bool v16, bool alds)
-{
-    if (v16) launch_shortk_ks<false, 16>(a, ks, waves, s, alds);
-    else launch_shortk_ks<false, 8>(a, ks, waves, s, false);
-}
+void launch_shortk_int8(const ShortKArgs &a, int ks, int64_t waves, hipStream_t s) { launch_shortk_ks<false>(a, ks, waves, s); }
 
 bool shortk_eligible(const IgemmArgs &g, int b_mode, bool strided)
 {
@@ -20,6 +18,25 @@ bool shortk_eligible(const IgemmArgs &g, int b_mode, bool strided)
     return true;
 }
 
+// Rows of whole, aligned 16-byte pieces, weights of any alignment, offsets within 32 rows (weights: 128) of 31 bits.  A strided
+// convolution has its forms without weight zero-points and without the add.
+static bool ring_eligible(const IgemmArgs &g, bool strided)
+{
+    if (tuning().shortk_alds == 0) return false; // tuning aid: fragments from global memory
+    const int64_t row_pitch = strided ? g.Cin : g.lda;
+    if (!aligned_to(g.A, 16) || (row_pitch % 16) != 0 || (g.K % 16) != 0 || g.M >= (1 << 30) || g.ldb >= (1 << 23)) return false;
+    if (g.N > (1 << 21)) return false; // sets of column groups: a dimension of the grid
+    if (!strided) return g.lda < (1 << 26);
+    return !g.zw && (32 / ((int64_t)g.Ho * g.Wo) + 2) * g.H * g.W * g.Cin < (1ll << 31);
+}
+
+// us with fragments from global memory (as in shortk.h, in forms for 16-byte pieces, and K = 128 and 256 with four and more
+// column groups with their rows in a ring of two blocks) and with the ring kernel: 802816 x 128 x 256 80 and 66, 200704 x 128 x 128
+// 17.1 and 12.2, 50176 x 256 x 128 11.7 and 8.2, 50176 x 256 x 256 14.2 and 11.1, with weight zero-points on 12544 x 256 x 256 10.3
+// and 6.6, 50176 x 1024 x 256 with the add 50.3 and 42.1, stride 2 on 256 x 56 x 56 x 256 -> 512 67 and 55; 4-bit weights,
+// 100352 x 24 x 96 10.6 and 6.4.  K <= 64 is level to 4 % ahead.  Behind: launches of one step with K no power of two (4-bit
+// weights, 6272 x 576 x 96 5.2 and 5.9, 1568 x 960 x 160 4.2 and 4.8) and the pair table with K = 128 (200704 x 512 59 and 62: the
+// gathers and the ring share the LDS).
 qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
 {
     g.small_acc = 2; // K <= 256: |acc| <= 2^22
@@ -31,42 +48,32 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
     a.strided = strided ? 1 : 0;
     a.stream_out = g.M * (int64_t)g.N <= ((int64_t)32 << 20); // between 26 MB (gains) and 51 MB (the next layer loses more)
     a.col_groups = (g.N + 32 * nb - 1) / (32 * nb);
-    const int64_t row_blocks = (g.M + 31) / 32;
-    // as many waves as stay resident together (3 per SIMD for K <= 32 without weight zero-points, else 2, on 256 CUs), spread
-    // over the column groups, then trimmed so that every wave walks the same number of row blocks
-    const int64_t row_pitch0 = strided ? g.Cin : g.lda;
-    const bool add_fused = g.R != nullptr && aligned_to(g.A, 16) && (row_pitch0 % 16) == 0 && (g.K % 16) == 0 && g.c_vec16 &&
-                           g.r_vec16 && (g.N % 16) == 0; // the variant with the add built in: 8-wave workgroups, one per CU
-    const int64_t resident = 256 * 4 * ((ks <= 1 && !add_fused && !g.zw) ? 3 : 2);
-    int64_t walkers = resident / a.col_groups;
-    walkers = walkers < 1 ? 1 : (walkers > row_blocks ? row_blocks : walkers);
-    const int64_t per_walker = (row_blocks + walkers - 1) / walkers;
-    walkers = (row_blocks + per_walker - 1) / per_walker;
-    a.walkers = (int)walkers;
-    int64_t waves = walkers * a.col_groups;
-    if (waves > 0x7fffffff) return QNN_EINVAL;
-    const int64_t row_pitch = strided ? g.Cin : g.lda;
-    const bool v16 = aligned_to(g.A, 16) && (row_pitch % 16) == 0 && (g.K % 16) == 0;
-    // the add is built into the 16-byte variants only, for outputs and residuals made of whole aligned chunks
-    const bool add_pass = g.R != nullptr && !add_fused;
+    const bool ring = ring_eligible(g, strided), whole = g.c_vec16 && g.ldc < (1 << 26);
+    // the add is built into the ring kernel only, for outputs and residuals made of whole aligned chunks
+    const bool add_pass = g.R != nullptr && !(ring && !strided && whole && g.r_vec16 && g.ldr < (1 << 26) && (g.N % 16) == 0);
     if (add_pass) a.g.R = nullptr;
-    // K = 128 / 256 with enough column groups to fill a workgroup: the A rows go through LDS once per workgroup.
-    // Not with the add built in: its 8-wave workgroups (one per CU, sharing the table of code pairs) lose more at
-    // the barrier of every row block than the shared rows save (measured 65 against 58 us on 50176 x 1024 x 256).
-    const int wg_waves = 4;
-    const bool alds = tuning().shortk_alds != 0 && !strided && v16 && !a.g.R && !g.zw && (g.K == 128 || g.K == 256) && a.col_groups >= wg_waves;
-    if (alds) {
-        const int64_t groups = (a.col_groups + wg_waves - 1) / wg_waves;
-        const int64_t resident_wgs = 256 * 2;
-        int64_t wk = resident_wgs / groups;
-        wk = wk < 1 ? 1 : (wk > row_blocks ? row_blocks : wk);
-        const int64_t per = (row_blocks + wk - 1) / wk;
-        wk = (row_blocks + per - 1) / per;
-        a.walkers = (int)wk;
-        waves = groups * wk; // workgroups
+    if (ring) {
+        ShortKRingArgs r = {};
+        r.s = a;
+        r.whole = whole ? 1 : 0;
+        if (strided) r.magic_image = magic_for((uint32_t)(g.Ho * g.Wo)), r.magic_row = magic_for((uint32_t)g.Wo);
+        if (b_mode == B_INT4) ks <= 4 ? launch_ring_int4_low(r, ks, s) : launch_ring_int4_high(r, ks, s);
+        else ks <= 4 ? launch_ring_int8_low(r, ks, s) : launch_ring_int8_high(r, ks, s);
+    } else {
+        const int64_t row_blocks = (g.M + 31) / 32;
+        // as many waves as stay resident together (3 per SIMD for K <= 32 without weight zero-points, else 2, on 256 CUs), spread
+        // over the column groups, then trimmed so that every wave walks the same number of row blocks
+        const int64_t resident = 256 * 4 * ((ks <= 1 && !g.zw) ? 3 : 2);
+        int64_t walkers = resident / a.col_groups;
+        walkers = walkers < 1 ? 1 : (walkers > row_blocks ? row_blocks : walkers);
+        const int64_t per_walker = (row_blocks + walkers - 1) / walkers;
+        walkers = (row_blocks + per_walker - 1) / per_walker;
+        a.walkers = (int)walkers;
+        const int64_t waves = walkers * a.col_groups;
+        if (waves > 0x7fffffff) return QNN_EINVAL;
+        if (b_mode == B_INT4) launch_shortk_int4(a, ks, waves, s);
+        else launch_shortk_int8(a, ks, waves, s);
     }
-    if (b_mode == B_INT4) launch_shortk_int4(a, ks, waves, s, v16, alds);
-    else launch_shortk_int8(a, ks, waves, s, v16, alds);
     const qnn_status st = launch_status(hipGetLastError());
     if (st != QNN_OK || !add_pass) return st;
     return launch_add_inplace(g.C, g.ldc, g.R, g.ldr, g.M, g.N, g.add, s);

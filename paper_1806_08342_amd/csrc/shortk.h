@@ -1,5 +1,6 @@
-// Dense quantized layer with a short reduction (K <= 256): 1x1 convolutions and GEMMs whose
-// cost is the epilogue and the memory streams, not the MFMAs.
+// Dense quantized layer with a short reduction (K <= 256, K % 8 == 0) where shortk_ring.h does not apply: rows that are whole
+// 8-byte pieces only, or pitches beyond its 32-bit offsets.  Here also: what the two kernels share, the epilogue constants of a
+// column and the add of two codes by table.
 //
 // Weight-stationary and barrier-free: a wave owns up to 32*NB output columns, loads their weights
 // ONCE into registers as MFMA B fragments (4-bit weights are unpacked there, kept times 16),
@@ -27,16 +28,11 @@ struct ShortKArgs {
     int stream_out;    // non-temporal output stores
 };
 
-// 16 consecutive k of one row / column as 4 dwords, zero beyond K (ZERO = false, VEC 16: any bytes there, where the other
-// operand is zero).  VEC = bytes per load; whole 16-byte pieces are loaded without a branch, from a clamped address.
-template <int VEC, bool ZERO = true> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t *p, int k, int K)
+// 16 consecutive k of one row / column as 4 dwords, zero beyond K (K % 8 == 0).  VEC = bytes per load
+template <int VEC> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t *p, int k, int K)
 {
     i32x4 v = {0, 0, 0, 0};
-    if constexpr (VEC == 16) {
-        const bool in = k + 16 <= K;
-        v = *reinterpret_cast<const i32x4 *>(p + (in ? k : K - 16));
-        if constexpr (ZERO) v = i32x4{in ? v.x : 0, in ? v.y : 0, in ? v.z : 0, in ? v.w : 0};
-    } else if constexpr (VEC == 8) {
+    if constexpr (VEC == 8) {
         if (k + 8 <= K) {
             const u32x2 a = *reinterpret_cast<const u32x2 *>(p + k);
             v[0] = (int32_t)a.x, v[1] = (int32_t)a.y;
@@ -118,80 +114,38 @@ __device__ __forceinline__ uint32_t pairs_combine(const u16x2 (&t)[2])
     return __builtin_bit_cast(uint32_t, t[0]) | (__builtin_bit_cast(uint32_t, t[1]) << 8);
 }
 
-// 16 codes of the layer and of the residual -> 16 output codes
+// 16 codes of the layer and of the residual -> 16 output codes.  All 16 gathers are on their way before the first is combined.
 __device__ __forceinline__ u32x4 add_pairs16(const uint8_t *pair_tab, u32x4 v, u32x4 r)
 {
+    u16x2 t[4][2];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) pairs_lookup(pair_tab, v[d], r[d], t[d]);
+    __builtin_amdgcn_sched_barrier(0);
     u32x4 y;
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        u16x2 t[2];
-        pairs_lookup(pair_tab, v[d], r[d], t);
-        y[d] = pairs_combine(t);
-    }
+    for (int d = 0; d < 4; ++d) y[d] = pairs_combine(t[d]);
     return y;
 }
 
-// ADD: the rescaling add with a residual tensor (g.R) is applied to the output tile on its way
-// from LDS to global memory; the residual chunks of a row block are requested one round ahead.
-// The add is a function of two 8-bit codes, so the workgroup (8 waves here, to share it) first
-// tabulates all 65536 results in LDS; combining a pair of codes is then one byte gather.
-// ALDS (K = 128 or 256, plain matrices, 16-byte aligned rows): the A rows of a row block are shared by the waves
-// of a workgroup, which then own neighbouring column groups of the SAME rows.  The block's 32 x K bytes are
-// copied once per workgroup straight into LDS (global_load_lds_dwordx4, whole 128-byte lines per 8 lanes, next
-// block's copy in flight during the current block) and every wave reads its fragments from there.  Fetching the
-// fragments from global memory costs one vector-cache access per lane and instruction (every lane is on a row
-// of its own): counters showed the address unit busy for 58 % and the vector cache for 70-80 % of that kernel's
-// time, on a par with the vector ALU.  LDS positions are XOR-swizzled on the global-address side, so that the
-// 16 lanes that share a cycle of a 16-byte LDS read hit 16 different bank groups.
 // ZW: per-column weight zero-points (see igemm_epilogue_impl): the activation sum of a row is one more accumulator,
 // fed by one matrix instruction per K sub-step whose B fragment is all ones, which leaves the sums in the registers
 // and lanes where the rescale of the same rows needs them.
-template <int NB, int KS, bool INT4, int VEC, int BVEC, int ADD = 0, bool ALDS = false, bool ZW = false> // ADD: 0 none, 1 two 256-entry tables, 2 pair table
-__global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 && !ZW ? 3 : 2)) shortk_kernel(const ShortKArgs s)
+template <int NB, int KS, bool INT4, bool ZW = false>
+__global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(const ShortKArgs s)
 {
     constexpr int PITCH = 32 * NB + 32; // bytes per staged output row: the 8 rows a store instruction touches fall in distinct banks
-    constexpr int WAVES = ADD == 2 ? 8 : 4; // the pair table is shared by 8 waves (one workgroup per CU)
-    constexpr int KBYTES = KS * 32, CPR = KBYTES / 16; // ALDS: bytes and 16-byte chunks of an A row (K == KS * 32)
-    constexpr int ATILE = 32 * KBYTES;
-    static_assert(!ALDS || (KS == 4 || KS == 8), "the staged form exists for K = 128 and K = 256");
-    __shared__ __attribute__((aligned(16))) uint8_t a_tiles[ALDS ? 2 * ATILE : 16];
-    __shared__ __attribute__((aligned(16))) uint8_t stage_static[ADD ? 16 : 4 * 32 * PITCH];
-    extern __shared__ __attribute__((aligned(16))) uint8_t dyn_lds[]; // ADD: [table(s)][output tiles of the waves]
-    uint8_t *const pair_tab = dyn_lds;
-    constexpr int TAB_BYTES = ADD == 2 ? 65536 : 2048; // pair table, or the two 256-entry tables
-    uint8_t *const stage_all = ADD ? dyn_lds + TAB_BYTES : stage_static;
+    constexpr int WAVES = 4;
+    __shared__ __attribute__((aligned(16))) uint8_t stage_all[WAVES * 32 * PITCH];
     const IgemmArgs &g = s.g;
-    // small layers skip the pair table (building it would cost more than it saves) and combine through
-    // the two 256-entry tables of rescaled codes instead
-    constexpr bool use_pairs = ADD == 2;
-    int32_t *const tab = reinterpret_cast<int32_t *>(use_pairs ? stage_all : pair_tab); // pairs: in the tile area for now
-    if constexpr (ADD) { // the only workgroup barriers, before any wave may leave
-        add_fill_tables(tab, g.add, threadIdx.x, WAVES * 64);
-        __syncthreads();
-        if constexpr (use_pairs) {
-            fill_pair_table<WAVES>(pair_tab, tab, g.add);
-            __syncthreads();
-        }
-    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // wave-uniform: row-block arithmetic stays scalar
     uint8_t *stage = stage_all + wave * (32 * PITCH);
     const int frow = lane & 31, fhalf = lane >> 5;
 
     // wave -> (column group, walker): neighbouring waves take neighbouring column groups of the same rows
-    int cg, walker;
-    bool active = true; // ALDS: a wave beyond the last column group only helps with the copies and the barriers
-    if constexpr (ALDS) {
-        const int groups = (s.col_groups + WAVES - 1) / WAVES; // workgroups side by side; the grid is groups x walkers
-        cg = (int)(blockIdx.x % groups) * WAVES + wave;
-        walker = (int)(blockIdx.x / groups);
-        active = cg < s.col_groups;
-        cg = active ? cg : s.col_groups - 1;
-    } else {
-        const int64_t gw = (int64_t)blockIdx.x * WAVES + wave;
-        cg = (int)(gw % s.col_groups), walker = (int)(gw / s.col_groups);
-        if (walker >= s.walkers) return; // no barriers below: a wave may leave alone
-    }
+    const int64_t gw = (int64_t)blockIdx.x * WAVES + wave;
+    const int cg = (int)(gw % s.col_groups), walker = (int)(gw / s.col_groups);
+    if (walker >= s.walkers) return; // no barriers below: a wave may leave alone
     const int n0 = cg * 32 * NB;
     const int blocks_here = (g.N - n0 + 31) / 32 < NB ? (g.N - n0 + 31) / 32 : NB; // column blocks that exist
 
@@ -213,15 +167,11 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
             const int k = ks * 32 + fhalf * 16;
             if constexpr (INT4) {
                 const uint8_t *p = g.B + (((int64_t)n * g.ldb) >> 1);
-                if constexpr (VEC == 16) { // K % 16 == 0 (rows are 4-byte aligned)
-                    __builtin_memcpy(&packed[ks][j], p + ((k + 16 <= g.K ? k : g.K - 16) >> 1), 8);
-                } else {
-                    packed[ks][j] = u32x2{0u, 0u};
-                    if (k + 16 <= g.K) __builtin_memcpy(&packed[ks][j], p + (k >> 1), 8);
-                    else if (k + 8 <= g.K) packed[ks][j][0] = *reinterpret_cast<const uint32_t *>(p + (k >> 1));
-                }
+                packed[ks][j] = u32x2{0u, 0u};
+                if (k + 16 <= g.K) __builtin_memcpy(&packed[ks][j], p + (k >> 1), 8);
+                else if (k + 8 <= g.K) packed[ks][j][0] = *reinterpret_cast<const uint32_t *>(p + (k >> 1));
             } else {
-                fb[ks][j] = shortk_load16<BVEC, false>(g.B + (int64_t)n * g.ldb, k, g.K);
+                fb[ks][j] = shortk_load16<4>(g.B + (int64_t)n * g.ldb, k, g.K);
             }
         }
     }
@@ -241,13 +191,10 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
             p = g.A + (int64_t)m * g.lda + fhalf * 16;
         }
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) fa[ks] = shortk_load16<VEC, false>(p, ks * 32, g.K - fhalf * 16); // (beyond K the weights are zero)
+        for (int ks = 0; ks < KS; ++ks) fa[ks] = shortk_load16<8>(p, ks * 32, g.K - fhalf * 16);
     };
-    // (Not where these rows and the weights as loaded do not fit the registers together: the forms for K <= 128 with the add
-    // spilled 12 to 52 bytes, 20000 x 144 x 112 11.5 us, not 11.0.)
-    constexpr bool FIRST_AHEAD = !ALDS && !ZW && !(ADD && KS == 4);
     i32x4 first[KS];
-    if constexpr (FIRST_AHEAD) load_rows(walker < row_blocks ? walker : row_blocks - 1, first);
+    load_rows(walker < row_blocks ? walker : row_blocks - 1, first);
 
     bool range_ok = g.small_acc >= 2, fused_ok = true;
     const bool ties = rescale_ties(g.lo_rel);
@@ -257,47 +204,19 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             if constexpr (INT4) fb[ks][j] = expand_int4(packed[ks][j]);
-            if constexpr (INT4 ? VEC == 16 : BVEC == 16) {
-                if (ks * 32 + fhalf * 16 + 16 > g.K) fb[ks][j] = i32x4{0, 0, 0, 0};
-            }
 #pragma unroll
             for (int d = 0; d < 4; ++d) colsum = __builtin_amdgcn_sdot4(fb[ks][j][d], 0x01010101, colsum, false);
         }
         colsum += __shfl_xor(colsum, 32);
         if (INT4) colsum >>= 4; // weights are kept times 16; exact
-        // (the sums of ZW count code - 128; where pieces of 8 are loaded, also -128 for every k from K to KS * 32, read as zeros)
+        // (the sums of ZW count code - 128, also -128 for every k from K to KS * 32, read as zeros)
         const int32_t b = g.bias ? p_bias[j] : 0;
-        shortk_column(col[j], g, colsum, b, p_mult[j], p_shift[j], p_zw[j], VEC == 16 ? g.K : KS * 32);
+        shortk_column(col[j], g, colsum, b, p_mult[j], p_shift[j], p_zw[j], KS * 32);
         range_ok = range_ok && rescale_in_range(p_shift[j]) && b > -(1 << 27) && b < (1 << 27);
         fused_ok = fused_ok && range_ok && channel_rescale_ok(p_mult[j], p_shift[j], ties);
     }
-    const bool fused = __all(fused_ok), in_range = __all(range_ok), k_tail = VEC == 16 && g.K != KS * 32;
+    const bool fused = __all(fused_ok), in_range = __all(range_ok);
     const i32x4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
-
-    // ALDS: copy of row block rbx into a_tiles[buf]; wave w, pass i moves LDS chunks (i * WAVES + w) * 64 + lane:
-    // LDS chunk q = (row, position p) holds global chunk p ^ swz(row) of that row
-    auto swz = [](int row) { return CPR == 16 ? (row & 15) : ((row >> 1) & 7); };
-    auto issue_tile = [&](int rbx, int buf) __attribute__((always_inline)) {
-        constexpr int PASSES = (32 * CPR + WAVES * 64 - 1) / (WAVES * 64);
-#pragma unroll
-        for (int i = 0; i < PASSES; ++i) {
-            const int q0 = (i * WAVES + wave) * 64; // wave-uniform
-            if (q0 >= 32 * CPR) break;
-            const int q = q0 + lane;
-            const int row = q / CPR, pos = q % CPR;
-            int m = rbx * 32 + row;
-            m = m < M ? m : M - 1;
-            const uint8_t *src = g.A + (int64_t)m * g.lda + ((pos ^ swz(row)) * 16);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                             (__attribute__((address_space(3))) void *)(a_tiles + buf * ATILE + q0 * 16), 16, 0, 0);
-        }
-    };
-    auto read_tile = [&](int buf, i32x4 (&fa)[KS]) __attribute__((always_inline)) {
-        const uint8_t *base = a_tiles + buf * ATILE + frow * KBYTES;
-        const int sw = swz(frow);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) fa[ks] = *reinterpret_cast<const i32x4 *>(base + (((2 * ks + fhalf) ^ sw) * 16));
-    };
 
     // lane-invariant parts of the LDS and global addresses of the output tile
     int st_lds[NB], st_row[NB];
@@ -308,7 +227,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         const int idx = i * 64 + lane;
         st_row[i] = idx / (2 * NB);
         const int col0 = n0 + (idx % (2 * NB)) * 16;
-        st_col_ok[i] = col0 < g.N && active;
+        st_col_ok[i] = col0 < g.N;
         st_lds[i] = st_row[i] * PITCH + (idx % (2 * NB)) * 16;
         st_off[i] = (int64_t)st_row[i] * g.ldc + col0;
     }
@@ -321,39 +240,6 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
     const uint32_t sel2 = (quad_lane & 2) ? 0x03020706u : 0x05040100u;
     const int32_t lo_rel = g.lo_rel, hi_rel = g.hi_rel, z_out = g.z_out;
 
-    // residual chunks of a row block (ADD): same lanes and addresses as the stores of that block
-    int64_t st_roff[NB];
-    u32x4 rres[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        st_roff[i] = (int64_t)st_row[i] * g.ldr + (n0 + (i * 64 + lane) % (2 * NB) * 16);
-        rres[i] = u32x4{0u, 0u, 0u, 0u};
-    }
-    auto load_res = [&](int rbx) __attribute__((always_inline)) {
-        const uint8_t *const r_block = g.R + (int64_t)rbx * 32 * g.ldr; // wave-uniform
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-            if (st_col_ok[i] && rbx * 32 + st_row[i] < M) rres[i] = *reinterpret_cast<const u32x4 *>(r_block + st_roff[i]);
-    };
-    // 16 codes of the layer (v) and of the residual (r) -> 16 output codes
-    const AddOut ao = make_add_out(g.add);
-    auto add16 = [&](u32x4 v, u32x4 r) __attribute__((always_inline)) {
-        u32x4 y;
-        if constexpr (use_pairs) {
-            y = add_pairs16(pair_tab, v, r);
-        } else if (ao.fused) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                y[d] = add_codes4<true>(v[d], r[d], tab, ao);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma nounroll
-            for (int d = 0; d < 4; ++d) y[d] = add_codes4<false>(v[d], r[d], tab, ao);
-        }
-        return y;
-    };
-
     // (Non-temporal stores, s.stream_out: 4-9 % on 6-26 MB outputs -- what is left in the L2s is written back when the
     // kernel ends.  Larger outputs and the add built in are faster with plain ones: ResNet-50 at batch 256, 103 MB,
     // K = 256: 84 us and 93 with non-temporal ones, 70 and 76; 51 MB, K = 256: 57 and 54, but the 3x3 layer that reads
@@ -365,15 +251,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         uint8_t *const c_block = g.C + (int64_t)rbx * 32 * g.ldc; // wave-uniform
-        if constexpr (ADD) { // the launcher uses ADD only when every output chunk is a whole, aligned 16-byte chunk
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                if (st_col_ok[i] && rbx * 32 + st_row[i] < M)
-                    *reinterpret_cast<u32x4 *>(c_block + st_off[i]) =
-                        add16(*reinterpret_cast<const u32x4 *>(stage + st_lds[i]), rres[i]);
-                __builtin_amdgcn_sched_barrier(0); // one chunk at a time: the table reads of all chunks at once would spill
-            }
-        } else if (chunks_whole && rbx * 32 + 32 <= M && s.stream_out) { // the common case: only the lane-invariant column test
+        if (chunks_whole && rbx * 32 + 32 <= M && s.stream_out) { // the common case: only the lane-invariant column test
 #pragma unroll
             for (int i = 0; i < NB; ++i)
                 if (st_col_ok[i])
@@ -411,22 +289,10 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
     auto walk = [&](auto mode_tag) {
     using Mode = RescaleModeTraits<decltype(mode_tag)::value>;
     i32x4 fa[KS];
-    int rb = walker, rb_stored = -1, turn = 0;
-    if constexpr (ALDS) { // two copies in flight; the first block's fragments are in registers before the loop
-        if (rb < row_blocks) {
-            issue_tile(rb, 0);
-            if (rb + s.walkers < row_blocks) issue_tile(rb + s.walkers, 1);
-            __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8)); // vmcnt(0)
-            asm volatile("" ::: "memory");
-            __syncthreads();
-            read_tile(0, fa);
-        }
-    } else {
+    int rb = walker, rb_stored = -1;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) fa[ks] = first[ks];
-        if constexpr (!FIRST_AHEAD) load_rows(rb < row_blocks ? rb : row_blocks - 1, fa);
-    }
-    for (; rb < row_blocks; rb += s.walkers, turn ^= 1) {
+    for (int ks = 0; ks < KS; ++ks) fa[ks] = first[ks];
+    for (; rb < row_blocks; rb += s.walkers) {
         i32x16 acc[NB];
 #pragma unroll
         for (int j = 0; j < NB; ++j)
@@ -435,36 +301,18 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 
         i32x16 sums = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}; // ZW: sum_k (code - 128) of the rows
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            i32x4 xs = fa[ks] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
+            const i32x4 xs = fa[ks] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
             if constexpr (ZW) {
-                if (k_tail && ks * 32 + fhalf * 16 >= g.K) xs = i32x4{0, 0, 0, 0}; // counts in the sum
                 sums = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, ones, sums, 0, 0, 0);
             }
 #pragma unroll
             for (int j = 0; j < NB; ++j)
                 acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, fb[ks][j], acc[j], 0, 0, 0); // columns past N: clamped loads, never stored
         }
-        if constexpr (ALDS) {
-            // The fragments are consumed.  The next block's copy (issued one round ago, like every store still
-            // outstanding) has landed in this wave's part; after the barrier in all parts, and every wave has read
-            // the current block (one round ago), whose buffer the copy of the block after next may overwrite.
-            // The read-back of the next block's fragments then passes under the epilogue below.
-            if (rb + s.walkers < row_blocks) { // uniform over the workgroup
-                __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8)); // vmcnt(0)
-                asm volatile("" ::: "memory");
-                __syncthreads();
-                read_tile(turn ^ 1, fa);
-                asm volatile("" ::: "memory");
-                if (rb + 2 * s.walkers < row_blocks) issue_tile(rb + 2 * s.walkers, turn);
-            }
-        }
         // The fragments are consumed: the next block's are requested into the same registers now, ahead of the stores, so that
         // the wait for them is no wait for these (requests retire in order).
-        if constexpr (!ALDS) {
-            if (rb + s.walkers < row_blocks) load_rows(rb + s.walkers, fa);
-        }
+        if (rb + s.walkers < row_blocks) load_rows(rb + s.walkers, fa);
         if (rb_stored >= 0) store_block(rb_stored);
-        if constexpr (ADD) load_res(rb); // used one round from now, when this block is stored
 
         // ---- epilogue into the wave's LDS tile: after the 4x4 byte transposition inside each
         // quad of lanes a lane holds 4 consecutive columns of one row
