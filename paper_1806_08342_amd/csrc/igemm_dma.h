@@ -1,24 +1,30 @@
 // Pipelined variant of the implicit-GEMM kernel for the aligned, MFMA-bound cases.
 //
 // Same arithmetic and LDS tile layout as igemm.h, but the operand tiles go from global
-// memory straight into LDS (global_load_lds_dwordx4, no register staging) through a ring
+// memory straight into LDS (buffer_load_dwordx4 ... lds, no register staging) through a ring
 // of NSTAGE stages, so that loads run NSTAGE-1 K-steps ahead of the MFMAs that consume
 // them.  One barrier per K-step, placed between the two 32-deep MFMA batches of the step;
 // the fragments of the next batch are read from LDS while the current batch executes.
 //
-// A wave-level global_load_lds_dwordx4 writes the 64 lanes' 16-byte chunks to 1024
-// consecutive LDS bytes in lane order, i.e. 16 tile rows of 64 bytes.  Lane p therefore
-// fetches, for row p/4 of its segment, the logical chunk (p%4) ^ swizzle(row): the XOR
-// swizzle of the tile is applied on the global-address side.
+// A wave-level load writes the 64 lanes' 16-byte chunks to 1024 consecutive LDS bytes in lane
+// order, i.e. 16 tile rows of 64 bytes.  Lane p therefore fetches, for row p/4 of its segment, the
+// logical chunk (p%4) ^ swizzle(row): the XOR swizzle of the tile is applied on the global-address
+// side.  The loads are buffer loads: a scalar base that advances with k, a 32-bit lane offset that does not change (matrices)
+// or is one add and one test away (convolutions), and nothing selected for K-steps past the end, whose buffer is empty.
+// As global_load_lds from 64-bit lane addresses, and all in the second half of a K-step, they held the matrix
+// instructions up: us before and now 8192 x 8192 x 2048 157.8 and 148.0, 50176 x 256 x 2304 48.2 and 44.2, 12544 x 2048 x 512
+// 30.9 and 29.1, 12544 x 512 x 4608 53.9 and 51.4.
 //
 // Requirements (checked by the dispatcher): every 16-byte chunk is 16-byte aligned (pitches
 // and base pointers multiples of 16; for convolutions Cin % 16 == 0), K % 64 == 0 (KTAIL: whole
 // 16-byte chunks of B, i.e. K % 16 == 0, 4-bit weights K % 32 == 0), and the
 // byte offsets inside one tile fit 32 bits.  Rows beyond M / columns beyond N are clamped to
-// the last valid one (their results are never stored); out-of-image taps of a convolution
-// read a constant chunk holding the code z_x.
+// the last valid one (their results are never stored).  Out-of-image taps of a convolution
+// read zeros, outside the buffer (A_CONV_ZERO: the code z_x is 0, or there are no such taps; Cin % 64 == 0, at most 32
+// taps, and the images of a tile within 31 bits), or else a constant chunk holding the code z_x (A_CONV, by global_load_lds).
 #pragma once
 
+#include "buffer_ops.h"
 #include "fill_table.h"
 #include "igemm.h"
 #include "lds_ring.h"
@@ -93,8 +99,7 @@ __device__ __forceinline__ bool assign_tile(int slot, int tiles_m, int tiles_n, 
 // are expanded to int8 (times 16, see expand_int4) in registers after the fragment read.  Chunk c
 // of row r sits at position c ^ ((r / 8) % 2), which makes the 8-byte fragment reads of 32
 // consecutive rows conflict-free.  They take the first half of the stage's B area.
-// KTAIL: K need not be a multiple of 64.  Chunks of B beyond K are fetched from a chunk of zeros, chunks
-// of A from the row's last chunk (any bytes do: they meet zero weights).
+// KTAIL: K need not be a multiple of 64.  Chunks beyond K read as zero.
 template <int BM, int BN, int WM, int WN, int A_MODE, int NSTAGE, bool SPLIT = false, bool ZW = false, bool B4 = false,
           int MINW = 1, bool KTAIL = false>
 __global__ void __launch_bounds__(WM *WN * 64, MINW)
@@ -131,9 +136,10 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
         // change from K-step to K-step (the K advance goes into the uniform part).
         const uint8_t *a_src[A_LOADS], *a_pix[A_LOADS];
         int a_koff[A_LOADS], a_hi0[A_LOADS], a_wi0[A_LOADS];
-        uint32_t a_lane_off[A_LOADS], b_lane_off[B_LOADS];
+        uint32_t a_lane_off[A_LOADS], b_lane_off[B_LOADS], a_taps[A_LOADS]; // a_taps: bit t is set where tap t lies inside the image
         int b_k[B_LOADS]; // KTAIL: k of the chunk within its K-step
-        const uint8_t *const a_tile = g.A + m0 * g.lda;                 // A_MATRIX only
+        const int64_t img_bytes = (int64_t)g.H * g.W * g.Cin;
+        const uint8_t *const a_tile = A_MODE == A_MATRIX ? g.A + m0 * g.lda : g.A + m0 / ((int64_t)g.Ho * g.Wo) * img_bytes; // (not A_CONV)
         const uint8_t *const b_tile = g.B + (B4 ? ((int64_t)n0 * g.ldb) >> 1 : (int64_t)n0 * g.ldb);
 #pragma unroll
         for (int j = 0; j < A_LOADS; ++j) {
@@ -142,7 +148,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
             int64_t m = m0 + row;
             m = m < g.M ? m : g.M - 1;
             a_hi0[j] = a_wi0[j] = 0;
-            a_lane_off[j] = 0;
+            a_lane_off[j] = a_taps[j] = 0;
             a_src[j] = a_pix[j] = nullptr;
             if constexpr (A_MODE == A_MATRIX) {
                 a_lane_off[j] = (uint32_t)((m - m0) * g.lda) + (uint32_t)a_koff[j];
@@ -156,6 +162,13 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
                 // address of tap (0,0), channel koff of this row's window (may lie outside the image:
                 // only dereferenced after the bounds check)
                 a_pix[j] = a_src[j] + ((int64_t)a_hi0[j] * g.W + a_wi0[j]) * g.Cin + a_koff[j];
+                if constexpr (A_MODE == A_CONV_ZERO) {
+                    a_lane_off[j] = (uint32_t)(int32_t)(a_pix[j] - a_tile);
+                    const int kh = g.K / (g.kw * g.Cin);
+                    for (int a = 0, t = 0; a < kh; ++a)
+                        for (int b = 0; b < g.kw; ++b, ++t)
+                            a_taps[j] |= (uint32_t)((unsigned)(a_hi0[j] + a) < (unsigned)g.H && (unsigned)(a_wi0[j] + b) < (unsigned)g.W) << t;
+                }
             }
         }
 #pragma unroll
@@ -183,30 +196,35 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
         const int ksteps_all = KTAIL ? (g.K + BK - 1) / BK : g.K / BK;
         const int kt_first = SPLIT ? split * sk.ksteps : 0;
         const int ktiles = SPLIT ? ((ksteps_all - kt_first) < sk.ksteps ? (ksteps_all - kt_first) : sk.ksteps) : ksteps_all;
-        const uint8_t *zero_b = &g_fill_table.v[0][0];
         const bool tap_uniform = A_MODE == A_CONV && (g.Cin % BK) == 0;
 
         // load number `idx` (0 .. LOADS-1) of K-step kt: A segments first, then B segments.
-        // K-steps past the end fetch one constant 16-byte chunk instead (into a buffer nobody reads
-        // any more): no extra memory traffic, and the number of loads per K-step stays uniform,
-        // which the vmcnt-based waits rely on.
-        auto issue_load = [&](int kt, int idx) {
+        // K-steps past the end read an empty buffer (into a stage nobody reads any more): no memory
+        // traffic, and the number of loads per K-step stays uniform, which the vmcnt-based waits
+        // rely on.
+        auto issue_load = [&](int kt, int idx) __attribute__((always_inline)) {
             uint8_t *stage = smem + (kt % NSTAGE) * STAGE_BYTES;
             const bool live = kt < ktiles; // wave-uniform
+            const int bytes = live ? 0x7fffffff : 0;
             const int k0 = (kt_first + kt) * BK;
+            constexpr uint32_t NOWHERE = 0x80000000u;
             if (idx < A_LOADS) {
                 const int j = idx;
-                const uint8_t *src = fill_a;
-                if constexpr (A_MODE == A_MATRIX && KTAIL) {
-                    const int over = k0 + a_koff[j] - (g.K - 16); // beyond the row's last chunk: take that one
-                    if (live) src = (a_tile + k0) + (a_lane_off[j] - (uint32_t)(over > 0 ? over : 0));
-                } else if constexpr (A_MODE == A_MATRIX) {
-                    if (live) src = (a_tile + k0) + a_lane_off[j]; // K % 64 == 0: no tail
+                uint8_t *const dst = stage + (wave * A_LOADS + j) * 1024;
+                if constexpr (A_MODE == A_MATRIX) {
+                    // KTAIL: beyond K zeros, which meet zero weights
+                    buffer_to_lds16(a_tile + k0, bytes, KTAIL && k0 + a_koff[j] >= g.K ? NOWHERE : a_lane_off[j], dst);
+                } else if constexpr (A_MODE == A_CONV_ZERO) {
+                    // Cin % 64 == 0: the whole K-step lies inside one tap, so the tap decomposition is wave-uniform
+                    // (scalar unit) and only the test of the tap is per lane
+                    const uint32_t tap = __umulhi((uint32_t)k0, g.magic_cin);
+                    const uint32_t ta = __umulhi(tap, g.magic_kw) + (g.kw == 1 ? tap : 0u);
+                    const uint32_t delta = (ta * (uint32_t)g.W + (tap - ta * (uint32_t)g.kw)) * (uint32_t)g.Cin + ((uint32_t)k0 - tap * (uint32_t)g.Cin);
+                    buffer_to_lds16(a_tile, bytes, (a_taps[j] >> (tap & 31u)) & 1u ? a_lane_off[j] + delta : NOWHERE, dst);
                 } else {
+                    const uint8_t *src = fill_a;
                     const int k = k0 + a_koff[j];
                     if (live && tap_uniform) {
-                        // Cin % 64 == 0: the whole K-step lies inside one tap, so the tap decomposition
-                        // is wave-uniform (scalar unit) and only the bounds check is per lane
                         const uint32_t tap = fast_div((uint32_t)k0, (uint32_t)g.Cin, g.magic_cin);
                         const int ci0 = k0 - (int)tap * g.Cin;
                         const uint32_t ta = fast_div(tap, (uint32_t)g.kw, g.magic_kw);
@@ -222,28 +240,14 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
                         const int hi = a_hi0[j] + (int)ta, wi = a_wi0[j] + tb;
                         if (hi >= 0 && hi < g.H && wi >= 0 && wi < g.W) src = a_src[j] + ((int64_t)hi * g.W + wi) * g.Cin + ci;
                     }
+                    dma16(src, dst);
                 }
-                dma16(src, stage + (wave * A_LOADS + j) * 1024);
             } else {
                 const int j = idx - A_LOADS;
-                if constexpr (B4) {
-                    const uint8_t *src = live ? (b_tile + (k0 >> 1)) + b_lane_off[j] : fill_a;
-                    if constexpr (KTAIL)
-                        if (k0 + b_k[j] >= g.K) src = zero_b;
-                    dma16(src, stage + BM * BK + (wave * B_LOADS + j) * 1024);
-                } else {
-                    const uint8_t *src = live ? (b_tile + k0) + b_lane_off[j] : fill_a;
-                    if constexpr (KTAIL)
-                        if (k0 + b_k[j] >= g.K) src = zero_b;
-                    dma16(src, stage + BM * BK + (wave * B_LOADS + j) * 1024);
-                }
+                buffer_to_lds16(B4 ? b_tile + (k0 >> 1) : b_tile + k0, bytes, KTAIL && k0 + b_k[j] >= g.K ? NOWHERE : b_lane_off[j],
+                                stage + BM * BK + (wave * B_LOADS + j) * 1024);
             }
         };
-        auto issue_stage = [&](int kt) {
-#pragma unroll
-            for (int idx = 0; idx < LOADS; ++idx) issue_load(kt, idx);
-        };
-
         i32x16 acc[TM][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -287,11 +291,16 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
 #pragma unroll
         for (int i = 0; i < TM; ++i) rowsum[i] = 0;
         constexpr int PIECES = TM + TN, MMAS = TM * TN;
-        // MFMAs of one K sub-step with the LDS reads of the next fragment set (and optionally the
-        // DMA loads of a later stage) spread evenly between them, so that neither the LDS nor
-        // the texture-address queue sees a burst that would stall MFMA issue
+        // Loads of a stage that are issued in the first half of the K-step after the one that freed its buffer: the loads are
+        // then spread over the whole step.  (Not with two workgroups per CU, whose other workgroup fills the gaps:
+        // 200704 x 128 x 1152 72.2 us, split 75.6.)
+        constexpr int LATE = MINW == 1 ? LOADS / 2 : 0;
+        // MFMAs of one K sub-step with the LDS reads of the next fragment set and this half's loads of a later
+        // stage spread evenly between them, so that neither the LDS nor the texture-address queue sees a
+        // burst that would stall MFMA issue
         auto mma_interleaved = [&](i32x4 (&fa)[TM], i32x4 (&fb)[TN], const uint8_t *next_stage, int next_ks,
-                                   i32x4 (&na)[TM], i32x4 (&nb)[TN], bool do_read, int dma_kt, bool sum_rows) {
+                                   i32x4 (&na)[TM], i32x4 (&nb)[TN], int dma_kt, auto first_tag, auto end_tag, bool sum_rows) __attribute__((always_inline)) {
+            constexpr int FIRST = decltype(first_tag)::value, COUNT = decltype(end_tag)::value - FIRST; // loads of this half
             i32x4 xs[TM];
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
@@ -306,23 +315,34 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
                 for (int j = 0; j < TN; ++j) {
                     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs[i], fb[j], acc[i][j], 0, 0, 0);
                     const int done = i * TN + j + 1;
-                    // after every MMAS/PIECES MFMAs issue one fragment read (and one DMA load)
-                    while (do_read && piece < PIECES && done * PIECES >= (piece + 1) * MMAS) {
+                    // after every MMAS/PIECES MFMAs issue one fragment read (and one load of a later stage)
+                    while (piece < PIECES && done * PIECES >= (piece + 1) * MMAS) {
                         read_piece(next_stage, next_ks, piece, na, nb);
                         ++piece;
                     }
-                    while (dma_kt >= 0 && load < LOADS && done * LOADS >= (load + 1) * MMAS) {
-                        issue_load(dma_kt, load);
+                    while (load < COUNT && done * COUNT >= (load + 1) * MMAS) {
+                        issue_load(dma_kt, FIRST + load);
                         ++load;
                     }
                 }
-        };
-
-        // ---- prologue: NSTAGE-1 stages in flight
 #pragma unroll
-        for (int s = 0; s < NSTAGE - 1; ++s) issue_stage(s);
+            for (int q = 0; q < PIECES; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, MMAS / PIECES, 0); // MFMA
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // DS read
+                if (q < COUNT) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0); // VMEM read (LDS DMA)
+            }
+        };
+        using AllLoads = std::integral_constant<int, LOADS>;
+        using EarlyLoads = std::integral_constant<int, LOADS - LATE>;
+        using NoLoads = std::integral_constant<int, 0>;
+
+        // ---- prologue: NSTAGE-1 stages in flight, but for the late loads of the last one
+#pragma unroll
+        for (int s = 0; s < NSTAGE - 1; ++s)
+#pragma unroll
+            for (int idx = 0; idx < (s == NSTAGE - 2 ? LOADS - LATE : LOADS); ++idx) issue_load(s, idx);
         // stage 0 has landed when at most the later stages' loads are outstanding
-        wait_vmcnt<(NSTAGE - 2) * LOADS>();
+        wait_vmcnt<(NSTAGE - 2) * LOADS - LATE>();
         block_barrier();
 
         i32x4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
@@ -341,12 +361,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
             const uint8_t *stage = smem + (kt % NSTAGE) * STAGE_BYTES;
             // sub-step 0: MFMAs on (fa0, fb0) while (fa1, fb1) are read from the same stage
             if (need_colsum && (0 % WM) == wave_m) add_colsum(fb0);
-            mma_interleaved(fa0, fb0, stage, 1, fa1, fb1, true, -1, (0 % WN) == wave_n);
-#pragma unroll
-            for (int q = 0; q < PIECES; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, MMAS / PIECES, 0); // MFMA
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // DS read
-            }
+            mma_interleaved(fa0, fb0, stage, 1, fa1, fb1, kt + NSTAGE - 2, EarlyLoads{}, AllLoads{}, (0 % WN) == wave_n);
             // stage kt+1 must have landed: only the NSTAGE-3 stages issued after it may be in flight
             // (every K-step issues exactly LOADS loads, real or fill, so the count is uniform)
             static_assert(NSTAGE >= 3, "the refilled buffer must not be the one still being read");
@@ -355,15 +370,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
             // sub-step 1: MFMAs on (fa1, fb1) while the first fragments of stage kt+1 are read and the
             // loads of stage kt+NSTAGE-1 are issued (past the last stage: stale data, never used)
             if (need_colsum && (1 % WM) == wave_m) add_colsum(fb1);
-            mma_interleaved(fa1, fb1, smem + ((kt + 1) % NSTAGE) * STAGE_BYTES, 0, fa0, fb0, true, kt + NSTAGE - 1, (1 % WN) == wave_n);
-            if constexpr (LOADS == PIECES) {
-#pragma unroll
-                for (int q = 0; q < PIECES; ++q) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, MMAS / PIECES, 0); // MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // DS read
-                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);             // VMEM read (LDS DMA)
-                }
-            }
+            mma_interleaved(fa1, fb1, smem + ((kt + 1) % NSTAGE) * STAGE_BYTES, 0, fa0, fb0, kt + NSTAGE - 1, NoLoads{}, EarlyLoads{}, (1 % WN) == wave_n);
         }
         __builtin_amdgcn_s_setprio(0);
         wait_vmcnt<0>(); // drain the fill loads of the last K-steps before the tile memory is reused

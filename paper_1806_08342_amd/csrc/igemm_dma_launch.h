@@ -34,12 +34,22 @@ inline hipError_t launch_splitk_reduce(const IgemmArgs &g, const SplitK &sk, hip
     return hipGetLastError();
 }
 
+// Whether taps outside the image may read as zero, by offsets within the images of a tile (A_CONV_ZERO, see igemm_dma.h)
+inline bool zero_taps(const IgemmArgs &g, int bm)
+{
+    const int kh = g.K / (g.kw * g.Cin);
+    return (g.z_a == 0 || (g.ph == 0 && g.pw == 0)) && g.Cin % 64 == 0 && kh * g.kw <= 32 &&
+           (bm / ((int64_t)g.Ho * g.Wo) + 2) * g.H * g.W * g.Cin < (1ll << 31);
+}
+
 // `per_cu` > 0: persistent launch with that many workgroups per CU (each walks its XCD's tile
 // sequence); 0: one workgroup per tile.  `prio`: issue-priority scheme of the main loop (see the kernel).
 template <int BM, int BN, int WM, int WN, int A_MODE, int NSTAGE, bool SPLIT = false, bool ZW = false, bool B4 = false,
           int MINW = 1, bool KTAIL = false>
 hipError_t launch_dma(const IgemmArgs &g, hipStream_t s, SplitK sk = SplitK{1, 0, nullptr}, int per_cu = 0, int prio = 0)
 {
+    if constexpr (A_MODE == A_CONV && !ZW && !KTAIL) // (Cin % 64 == 0: no tail)
+        if (zero_taps(g, BM)) return launch_dma<BM, BN, WM, WN, A_CONV_ZERO, NSTAGE, SPLIT, ZW, B4, MINW, KTAIL>(g, s, sk, per_cu, prio);
     constexpr int kStages = NSTAGE * (BM + BN) * 64;
     constexpr int kOut = BM * (BN + 16) + 4 * WM * WN * (BN / WN / 32) * 64 + 2048 + (ZW ? 4 * BM * WN : 0); // + add tables + row sums
     constexpr int kLds = kStages > kOut ? kStages : kOut; // operand ring, reused for the output tile + column sums + add tables
