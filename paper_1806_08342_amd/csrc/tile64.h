@@ -7,8 +7,10 @@
 // 6272 x 64 x 384 with 4-bit weights 5.6 -> 5.0.  (The waves dividing K instead of the tile, each on a ring of its own, and
 // exchanging quadrants at the end: 784 x 1024 x 1024 7.6 -> 7.1, but 3136 x 512 x 512 6.6 and the 4-bit layer 5.6.)
 //
-// Any K that is whole chunks (K % 16 == 0, 4-bit weights K % 32 == 0): weights beyond K come from a chunk of zeros,
-// activations from a chunk of the code 128, so that they add nothing to the row sums of weight zero-points either.
+// Any K that is whole chunks (K % 16 == 0, 4-bit weights K % 32 == 0): what lies beyond K reads as zero, outside the bounds
+// of a buffer; the row sums of weight zero-points are corrected for the codes 0 there.  (A convolution's activations, by
+// global_load_lds, come from a chunk of the code 128 there, which adds nothing to the row sums.)
+// The copies are buffer loads with 32-bit lane offsets (the dispatcher guarantees pitches below 2^23): see igemm_dma.h.
 #pragma once
 
 #include "igemm_dma.h"
@@ -47,7 +49,9 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
     // the fragment reads of 32 rows are free of bank conflicts
     auto swz_a = [](int row) { return (row >> 1) & 7; };
     auto swz_b = [](int row) { return B4 ? (row >> 2) & 3 : (row >> 1) & 7; };
-    const uint8_t *a_src[A_LOADS], *b_src[B_LOADS];
+    const uint8_t *a_src[A_LOADS];
+    const uint8_t *const a_tile = g.A + m0 * g.lda, *const b_tile = g.B + ((int64_t)n0 * g.ldb >> (B4 ? 1 : 0));
+    uint32_t a_off[A_LOADS], b_off[B_LOADS];
     int a_k[A_LOADS], b_k[B_LOADS], a_hi0[A_LOADS], a_wi0[A_LOADS];
 #pragma unroll
     for (int i = 0; i < A_LOADS; ++i) {
@@ -56,8 +60,9 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
         int64_t m = m0 + row;
         m = m < g.M ? m : g.M - 1;
         a_hi0[i] = a_wi0[i] = 0;
+        a_off[i] = 0;
         if constexpr (A_MODE == A_MATRIX) {
-            a_src[i] = g.A + m * g.lda + a_k[i] + k_begin;
+            a_off[i] = (uint32_t)((int)(m - m0) * (int)g.lda + a_k[i] + k_begin);
         } else {
             const int64_t img = m / ((int64_t)g.Ho * g.Wo);
             const int rem = (int)(m - img * ((int64_t)g.Ho * g.Wo));
@@ -74,19 +79,22 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
         b_k[i] = ((q % BCPR) ^ swz_b(row)) * (B4 ? 32 : 16);
         int n = n0 + row;
         n = n < g.N ? n : g.N - 1;
-        b_src[i] = g.B + (((int64_t)n * g.ldb + b_k[i] + k_begin) >> (B4 ? 1 : 0));
+        b_off[i] = (uint32_t)(((n - n0) * (int)g.ldb + b_k[i] + k_begin) >> (B4 ? 1 : 0));
     }
-    const uint8_t *const zero_xs = &g_fill_table.v[128][0], *const zero_w = &g_fill_table.v[0][0], *const outside = &g_fill_table.v[g.z_a][0];
+    const uint8_t *const zero_xs = &g_fill_table.v[128][0], *const outside = &g_fill_table.v[g.z_a][0];
+    constexpr uint32_t NOWHERE = 0x80000000u;
     auto request = [&](int st) __attribute__((always_inline)) {
         uint8_t *const stage = smem + (st % STAGES) * G::kStageBytes;
         const int k0 = st * BK;
 #pragma unroll
         for (int i = 0; i < A_LOADS; ++i) {
             const int k = k_begin + k0 + a_k[i];
-            const uint8_t *src = zero_xs;
             if constexpr (A_MODE == A_MATRIX) {
-                if (k < k_end) src = a_src[i] + k0;
-            } else if (k < k_end) {
+                buffer_to_lds16(a_tile + k0, 0x7fffffff, k < k_end ? a_off[i] : NOWHERE, stage + (wave * A_LOADS + i) * 1024);
+                continue;
+            }
+            const uint8_t *src = zero_xs;
+            if (k < k_end) {
                 const uint32_t tap = fast_div((uint32_t)k, (uint32_t)g.Cin, g.magic_cin);
                 const uint32_t ta = fast_div(tap, (uint32_t)g.kw, g.magic_kw);
                 const int a = (int)ta, b = (int)(tap - ta * (uint32_t)g.kw);
@@ -97,7 +105,8 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
         }
 #pragma unroll
         for (int i = 0; i < B_LOADS; ++i)
-            dma16(k_begin + k0 + b_k[i] < k_end ? b_src[i] + (B4 ? k0 >> 1 : k0) : zero_w, stage + 64 * BK + (wave * B_LOADS + i) * 1024);
+            buffer_to_lds16(b_tile + (B4 ? k0 >> 1 : k0), 0x7fffffff, k_begin + k0 + b_k[i] < k_end ? b_off[i] : NOWHERE,
+                            stage + 64 * BK + (wave * B_LOADS + i) * 1024);
     };
 #pragma unroll
     for (int st = 0; st < STAGES - 1; ++st)
@@ -105,12 +114,12 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
     ChannelParams<1> cparams = {};
     if constexpr (!SPLIT) cparams = load_channel_params<64, 2, 1>(g, n0);
 
-    int a_off[4], b_off[4];
+    int a_at[4], b_at[4];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
         const int ra = wave_m * 32 + frow, rb = wave_n * 32 + frow;
-        a_off[ks] = ra * BK + (((2 * ks + fhalf) ^ swz_a(ra)) & 7) * 16;
-        b_off[ks] = 64 * BK + rb * G::kBRow + (B4 ? ((ks ^ swz_b(rb)) & 3) * 16 + fhalf * 8 : (((2 * ks + fhalf) ^ swz_b(rb)) & 7) * 16);
+        a_at[ks] = ra * BK + (((2 * ks + fhalf) ^ swz_a(ra)) & 7) * 16;
+        b_at[ks] = 64 * BK + rb * G::kBRow + (B4 ? ((ks ^ swz_b(rb)) & 3) * 16 + fhalf * 8 : (((2 * ks + fhalf) ^ swz_b(rb)) & 7) * 16);
     }
     i32x16 acc0, acc1; // two chains
 #pragma unroll
@@ -130,9 +139,9 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
         i32x4 fa[4], fb[4];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            fa[ks] = *reinterpret_cast<const i32x4 *>(stage + a_off[ks]);
-            if constexpr (B4) fb[ks] = expand_int4(*reinterpret_cast<const u32x2 *>(stage + b_off[ks]));
-            else fb[ks] = *reinterpret_cast<const i32x4 *>(stage + b_off[ks]);
+            fa[ks] = *reinterpret_cast<const i32x4 *>(stage + a_at[ks]);
+            if constexpr (B4) fb[ks] = expand_int4(*reinterpret_cast<const u32x2 *>(stage + b_at[ks]));
+            else fb[ks] = *reinterpret_cast<const i32x4 *>(stage + b_at[ks]);
         }
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
@@ -148,6 +157,11 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
 #pragma unroll
                 for (int d = 0; d < 4; ++d) colsum[0] = __builtin_amdgcn_sdot4(fb[ks][d], 0x01010101, colsum[0], false);
         }
+    }
+    if constexpr (ZW && A_MODE == A_MATRIX) { // the codes 0 beyond K counted as -128
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            if ((ks & 1) == wave_n && k_begin + (steps - 1) * BK + (2 * ks + fhalf) * 16 >= k_end) rowsum[0] += 16 * 128;
     }
     i32x16 acc[1][1];
 #pragma unroll
