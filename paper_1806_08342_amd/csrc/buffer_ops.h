@@ -1,5 +1,5 @@
 // 16-byte buffer accesses: a base and a size that are the same in the whole wave, a 32-bit offset per lane; what lies beyond the
-// size is dropped (stores), reads as zero (loads) and costs no traffic.  The bodies exist in the device pass only: the
+// size is dropped (stores), reads as zero (loads) and costs no traffic.  And the division for the rows that such offsets address.  The bodies exist in the device pass only: the
 // resource type does.
 #pragma once
 
@@ -51,6 +51,16 @@ __device__ __forceinline__ void buffer_to_lds16(const uint8_t *base, int bytes, 
 #else
     (void)base, (void)bytes, (void)offset, (void)lds;
 #endif
+}
+
+// m / d for m < 2^31: the product with ceil(2^32 / d) is at most one too high (magic 0: d = 1)
+__device__ __forceinline__ uint32_t ring_div(uint32_t m, uint32_t d, uint32_t magic, uint32_t &rem)
+{
+    uint32_t q = __umulhi(m, magic) + (magic == 0 ? m : 0u);
+    rem = m - q * d;
+    const uint32_t high = rem >> 31;
+    rem += high * d;
+    return q - high;
 }
 
 } // namespace qnn

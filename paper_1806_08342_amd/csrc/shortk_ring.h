@@ -67,38 +67,31 @@ template <int CPR> __device__ __forceinline__ int ring_place(int row, int c)
 // that have the registers for it), with the pair table one of eight waves; the ring has what is left of the LDS, up to eight
 // blocks, and its first CW blocks (with the pair table: its place) are where the weights are exchanged before.
 template <int NB, int KS, int ADD, bool WIDE, bool ZW> struct RingGeometry {
-    static constexpr int kWaves = ADD == 2 ? 8 : 4;
-    static constexpr int kCw = WIDE ? 4 : 1, kRw = kWaves / kCw; // waves side by side, and on other rows
-    static constexpr int kResident = ADD == 2 ? 1 : ADD || ZW ? 2 : KS <= 4 && NB * KS <= 4 ? (NB <= 2 ? 4 : 3) : NB == 2 && KS <= 4 ? 3 : 2; // workgroups per CU
+    static constexpr int kWaves = ADD == 3 ? 16 : ADD == 2 ? 8 : 4;
+    static constexpr int kCw = ADD == 3 ? (WIDE ? 8 : 4) : (WIDE ? 4 : 1), kRw = kWaves / kCw; // waves side by side, and on other rows
+    static constexpr int kResident = ADD >= 2 ? 1 : ADD || ZW ? 2 : KS <= 4 && NB * KS <= 4 ? (NB <= 2 ? 4 : 3) : NB == 2 && KS <= 4 ? 3 : 2; // workgroups per CU
     static constexpr int kPitch = 32 * NB + 32; // bytes per staged output row: the 8 rows a store instruction touches fall in distinct banks
-    static constexpr int kTables = ADD == 2 ? 65536 : (ADD == 1 ? 2048 : 0);
+    static constexpr int kPerSimd = ADD == 3 ? 4 : kResident; // waves that the registers have to hold, at least
+    static constexpr int kTables = ADD >= 2 ? 65536 : (ADD == 1 ? 2048 : 0);
     static constexpr int kStage = kWaves * 32 * kPitch;
     static constexpr int kBlock = ring_chunks(KS) * 512; // 32 rows
     static constexpr int kFit = (160 * 1024 / kResident - kTables - kStage) / (kRw * kBlock);
     static constexpr int kDepth = kFit < 8 ? kFit : 8;
-    static constexpr int kAhead = ADD == 2 ? kDepth : kDepth - kCw; // blocks requested before the weights are in place
+    static constexpr int kAhead = ADD >= 2 ? kDepth : kDepth - kCw; // blocks requested before the weights are in place
     static constexpr bool kFits = kDepth >= 2 && kAhead >= 1;
     static constexpr int kLds = kTables + kStage + kDepth * kRw * kBlock;
 };
 
-// m / d for m < 2^31: the product with ceil(2^32 / d) is at most one too high (magic 0: d = 1)
-__device__ __forceinline__ uint32_t ring_div(uint32_t m, uint32_t d, uint32_t magic, uint32_t &rem)
-{
-    uint32_t q = __umulhi(m, magic) + (magic == 0 ? m : 0u);
-    rem = m - q * d;
-    const uint32_t high = rem >> 31;
-    rem += high * d;
-    return q - high;
-}
-
 // ADD: the rescaling add with a residual tensor (g.R) is applied to the output tile on its way from LDS to global memory; the
 // residual chunks of a row block are requested one step ahead.  1: through two 256-entry tables of rescaled codes.  2: the add is
 // a function of two 8-bit codes, so the workgroup (8 waves here, to share it) first tabulates all 65536 results in LDS; combining
-// a pair of codes is then one byte gather.
+// a pair of codes is then one byte gather.  3: the same with 16 waves of half the columns, whose gathers, rescale
+// and memory streams overlap better, for more reads of the ring: 200704 x 512 x 128 62 -> 60 us, but 50176 x 1024 x 256 42 -> 43 and
+// 802816 x 256 x 64 level, so for 64 < K <= 128 only.
 // ZW: per-column weight zero-points, as in shortk.h.  STRIDED: rows are the pixels of a strided 1x1 convolution.
 // The set-up is kept short, small launches consist of it: 32-bit offsets, no division.
 template <int NB, int KS, bool INT4, int ADD, bool WIDE, bool ZW, bool STRIDED>
-__global__ void __launch_bounds__(ADD == 2 ? 512 : 256, (RingGeometry<NB, KS, ADD, WIDE, ZW>::kResident)) shortk_ring_kernel(const ShortKRingArgs ra)
+__global__ void __launch_bounds__((RingGeometry<NB, KS, ADD, WIDE, ZW>::kWaves * 64), (RingGeometry<NB, KS, ADD, WIDE, ZW>::kPerSimd)) shortk_ring_kernel(const ShortKRingArgs ra)
 {
     fetch_arguments<sizeof(ShortKRingArgs)>();
     using G = RingGeometry<NB, KS, ADD, WIDE, ZW>;
@@ -107,7 +100,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, (RingGeometry<NB, KS, AD
     const ShortKArgs &s = ra.s;
     const IgemmArgs &g = s.g;
     uint8_t *const pair_tab = dyn_lds, *const stage_all = dyn_lds + G::kTables, *const ring = stage_all + G::kStage;
-    constexpr bool use_pairs = ADD == 2;
+    constexpr bool use_pairs = ADD >= 2;
     int32_t *const tab = reinterpret_cast<int32_t *>(use_pairs ? stage_all : pair_tab);
 
     const int lane = threadIdx.x & 63;
@@ -233,6 +226,7 @@ __global__ void __launch_bounds__(ADD == 2 ? 512 : 256, (RingGeometry<NB, KS, AD
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) fb[ks][j] = fragment(exchange + j * COLUMNS_BYTES, ks);
     } else {
+        static_assert(!use_pairs || WAVES * G::kBlock <= G::kTables, "the place of the pair table");
         uint8_t *const exchange = (use_pairs ? pair_tab : ring) + wave * G::kBlock; // one block of 32 columns after the other
 #pragma unroll
         for (int j = 0; j < NB; ++j) {

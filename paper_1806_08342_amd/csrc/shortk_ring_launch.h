@@ -31,15 +31,16 @@ template <int NB, int KS, bool INT4, int ADD, bool WIDE, bool ZW, bool STRIDED> 
 
 template <int KS, bool INT4, int ADD, bool ZW, bool STRIDED> inline void launch_ring_width(ShortKRingArgs &a, hipStream_t s)
 {
-    constexpr int NB = KS <= 4 ? 4 : 2;
+    constexpr int NB = KS > 4 || ADD == 3 ? 2 : 4;
     const int N = a.s.g.N;
     // few columns: one wave's, no wider than they are (not with the pair table, which is for large outputs)
-    if constexpr (ADD != 2) {
+    if constexpr (ADD < 2) {
         if (N <= 32) return launch_ring_form<1, KS, INT4, ADD, false, ZW, STRIDED>(a, s);
         if (NB == 4 && N <= 64) return launch_ring_form<2, KS, INT4, ADD, false, ZW, STRIDED>(a, s);
     }
-    // four waves side by side on the same rows, unless more than an eighth of them had no columns
-    const int groups = (N + 32 * NB - 1) / (32 * NB), idle = (groups + 3) / 4 * 4 - groups;
+    // four waves side by side on the same rows, unless more than an eighth of them had no columns (ADD == 3: eight, or four)
+    constexpr int W = RingGeometry<NB, KS, ADD, true, ZW>::kCw;
+    const int groups = (N + 32 * NB - 1) / (32 * NB), idle = (groups + W - 1) / W * W - groups;
     if (idle * 8 <= groups + idle) launch_ring_form<NB, KS, INT4, ADD, true, ZW, STRIDED>(a, s);
     else launch_ring_form<NB, KS, INT4, ADD, false, ZW, STRIDED>(a, s);
 }
@@ -48,8 +49,11 @@ template <int KS, bool INT4> inline void launch_ring_ks(ShortKRingArgs &a, hipSt
 {
     if (a.s.g.R) {
         // from 2^24 outputs on the 65536-entry pair table pays for itself; below, two 256-entry tables
-        if (a.s.g.M * (int64_t)a.s.g.N >= ((int64_t)1 << 24)) launch_ring_width<KS, INT4, 2, false, false>(a, s);
-        else launch_ring_width<KS, INT4, 1, false, false>(a, s);
+        if (a.s.g.M * (int64_t)a.s.g.N >= ((int64_t)1 << 24)) {
+            if constexpr (KS == 3 || KS == 4) // 16 waves where they have columns
+                if (a.s.g.N >= 192) return launch_ring_width<KS, INT4, 3, false, false>(a, s);
+            launch_ring_width<KS, INT4, 2, false, false>(a, s);
+        } else launch_ring_width<KS, INT4, 1, false, false>(a, s);
     } else if (a.s.g.zw) {
         launch_ring_width<KS, INT4, 0, true, false>(a, s);
     } else if (a.s.strided) {
