@@ -28,26 +28,11 @@ struct BResArgs {
     int groups_walkers;  // workgroups that share one column group
 };
 
-// KC: K sub-steps (of 32) per chunk; CONV: rows of A are gathered pixels; PAD: K / 32 is not a multiple of KC
-template <int NB, int KC, bool INT4, bool CONV, bool PAD>
-__global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
+// all weights of the column blocks from n0 on -> LDS, in fragment order
+template <int NB, bool INT4, int NW>
+__device__ __forceinline__ void bres_weights_to_lds(const IgemmArgs &g, int n0, int KS, int wave, int lane, uint8_t *bfrag)
 {
-    constexpr int NW = 8;                     // waves per workgroup
-    constexpr int PITCH = 32 * NB + 32;       // staged output row (see shortk.h)
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const IgemmArgs &g = s.g;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int frow = lane & 31, fhalf = lane >> 5;
-    const int KS = g.K / 32;                  // the dispatcher guarantees K % 32 == 0
-    uint8_t *const bfrag = smem;                                   // KS * NB fragments of 1 KB
-    uint8_t *const stage = smem + KS * NB * 1024 + wave * 32 * PITCH;
-
-    const int cg = blockIdx.x % s.col_groups, wg_walker = blockIdx.x / s.col_groups;
-    const int n0 = cg * 32 * NB;
-    const int blocks_here = (g.N - n0 + 31) / 32 < NB ? (g.N - n0 + 31) / 32 : NB;
-
-    // ---- weights -> LDS, in fragment order
     for (int f = wave; f < KS * NB; f += NW) {
         const int ks = f / NB, j = f - ks * NB;
         int n = n0 + j * 32 + frow;
@@ -70,11 +55,17 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
         }
         *reinterpret_cast<u32x4 *>(bfrag + f * 1024 + lane * 16) = v;
     }
-    __syncthreads(); // the only workgroup barrier
+}
 
-    // ---- per-column epilogue constants (as in shortk.h)
-    ChannelRescale c_r[NB];
-    int32_t c_mult[NB], c_corr[NB], c_shift[NB]; // general form
+// per-column epilogue constants (as in shortk.h); mult, corr and shift: general form
+template <int NB> struct BResColumns {
+    ChannelRescale r[NB];
+    int32_t mult[NB], corr[NB], shift[NB];
+    bool fused, in_range; // the same in the whole wave
+};
+template <int NB> __device__ __forceinline__ void bres_columns(const IgemmArgs &g, int n0, int KS, int lane, const uint8_t *bfrag, BResColumns<NB> &c)
+{
+    const int frow = lane & 31;
     const bool ties = rescale_ties(g.lo_rel);
     bool range_ok = g.small_acc >= 2, fused_ok = true;
 #pragma unroll
@@ -93,11 +84,37 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
         const int32_t b = g.bias ? g.bias[n] : 0, mu = g.mult[n], sf = g.shift[n];
         range_ok = range_ok && rescale_in_range(sf) && b > -(1 << 27) && b < (1 << 27);
         fused_ok = fused_ok && range_ok && channel_rescale_ok(mu, sf, ties);
-        c_corr[j] = b + (128 - g.z_a) * colsum;
-        c_mult[j] = mu, c_shift[j] = sf;
-        c_r[j] = make_channel_rescale(mu, sf, c_corr[j], g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
+        c.corr[j] = b + (128 - g.z_a) * colsum;
+        c.mult[j] = mu, c.shift[j] = sf;
+        c.r[j] = make_channel_rescale(mu, sf, c.corr[j], g.z_out, g.lo_rel + g.z_out, g.hi_rel + g.z_out, ties);
     }
-    const bool fused = __all(fused_ok), in_range = __all(range_ok);
+    c.fused = __all(fused_ok), c.in_range = __all(range_ok);
+}
+
+// KC: K sub-steps (of 32) per chunk; CONV: rows of A are gathered pixels; PAD: K / 32 is not a multiple of KC
+template <int NB, int KC, bool INT4, bool CONV, bool PAD>
+__global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
+{
+    constexpr int NW = 8;                     // waves per workgroup
+    constexpr int PITCH = 32 * NB + 32;       // staged output row (see shortk.h)
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const IgemmArgs &g = s.g;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int frow = lane & 31, fhalf = lane >> 5;
+    const int KS = g.K / 32;                  // the dispatcher guarantees K % 32 == 0
+    uint8_t *const bfrag = smem;                                   // KS * NB fragments of 1 KB
+    uint8_t *const stage = smem + KS * NB * 1024 + wave * 32 * PITCH;
+
+    const int cg = blockIdx.x % s.col_groups, wg_walker = blockIdx.x / s.col_groups;
+    const int n0 = cg * 32 * NB;
+    const int blocks_here = (g.N - n0 + 31) / 32 < NB ? (g.N - n0 + 31) / 32 : NB;
+
+    bres_weights_to_lds<NB, INT4, NW>(g, n0, KS, wave, lane, bfrag);
+    __syncthreads(); // the only workgroup barrier
+
+    BResColumns<NB> c;
+    bres_columns<NB>(g, n0, KS, lane, bfrag, c);
 
     // ---- rows (the dispatcher guarantees M < 2^31 and 32-bit offsets inside one image / matrix)
     const int M = (int)g.M;
@@ -297,8 +314,8 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int32_t a[4] = {acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
-                        if constexpr (Mode::kFused) put(j, q, channel_codes4<Mode::kTies, Mode::kFull>(a, c_r[j]));
-                        else put(j, q, other_codes4(a, c_mult[j], c_shift[j], c_corr[j], in_range, g.z_out, g.lo_rel, g.hi_rel));
+                        if constexpr (Mode::kFused) put(j, q, channel_codes4<Mode::kTies, Mode::kFull>(a, c.r[j]));
+                        else put(j, q, other_codes4(a, c.mult[j], c.shift[j], c.corr[j], c.in_range, g.z_out, g.lo_rel, g.hi_rel));
                     }
                 }
                 wave_sync();
@@ -317,7 +334,7 @@ __global__ void __launch_bounds__(512, 2) bres_kernel(const BResArgs s)
         }
         if (rb_stored >= 0) store_block(rb_stored);
     };
-    with_rescale_mode(fused, g.z_out, g.lo_rel, g.hi_rel, walk);
+    with_rescale_mode(c.fused, g.z_out, g.lo_rel, g.hi_rel, walk);
 }
 
 } // namespace qnn

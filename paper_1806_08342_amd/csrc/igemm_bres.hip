@@ -1,7 +1,7 @@
 // Launch routine of the weight-resident kernel.
 #include "igemm_launch.h"
 #include "tuning.h"
-#include "bres.h"
+#include "bres_ring.h"
 
 namespace qnn {
 
@@ -32,6 +32,23 @@ template <int NB> static hipError_t launch_bres_nb(const BResArgs &a, bool i4, b
 {
     if (conv) return i4 ? launch_bres_kc<NB, true, true>(a, blocks, lds, s) : launch_bres_kc<NB, false, true>(a, blocks, lds, s);
     return i4 ? launch_bres_kc<NB, true, false>(a, blocks, lds, s) : launch_bres_kc<NB, false, false>(a, blocks, lds, s);
+}
+
+// the form with its rows through an LDS ring of RING slots per wave
+template <int NB, int RING, bool INT4> static hipError_t launch_ring_one(const BResArgs &a, unsigned blocks, int lds, hipStream_t s)
+{
+    auto kernel = bres_ring_kernel<NB, RING, INT4>;
+    static LdsOptIn opt_in; // per instantiation
+    if (hipError_t e = opt_in.ensure(reinterpret_cast<const void *>(kernel), lds); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(512), lds, s, a);
+    return hipGetLastError();
+}
+
+template <int NB> static hipError_t launch_ring_nb(const BResArgs &a, bool i4, int slots, unsigned blocks, int lds, hipStream_t s)
+{
+    lds += (slots >= 6 ? 6 : 3) * 8 * 2048;
+    if (slots >= 6) return i4 ? launch_ring_one<NB, 6, true>(a, blocks, lds, s) : launch_ring_one<NB, 6, false>(a, blocks, lds, s);
+    return i4 ? launch_ring_one<NB, 3, true>(a, blocks, lds, s) : launch_ring_one<NB, 3, false>(a, blocks, lds, s);
 }
 
 bool try_bres(IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *status)
@@ -66,6 +83,13 @@ bool try_bres(IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *s
     const int lds = lds_for(nb);
     const bool i4 = b_mode == B_INT4;
     hipError_t e;
+    // six slots per wave where the weights leave the room, else three
+    const int slots = (160 * 1024 - lds) / (8 * 2048);
+    if (!conv && slots >= 3 && g.K % 64 == 0 && g.M < (1 << 30) && g.lda < (1 << 26)) {
+        e = nb == 4 ? launch_ring_nb<4>(a, i4, slots, blocks, lds, s) : nb == 2 ? launch_ring_nb<2>(a, i4, slots, blocks, lds, s) : launch_ring_nb<1>(a, i4, slots, blocks, lds, s);
+        *status = launch_status(e);
+        return true;
+    }
     if (nb == 4) e = launch_bres_nb<4>(a, i4, conv, blocks, lds, s);
     else if (nb == 2) e = launch_bres_nb<2>(a, i4, conv, blocks, lds, s);
     else e = launch_bres_nb<1>(a, i4, conv, blocks, lds, s);
