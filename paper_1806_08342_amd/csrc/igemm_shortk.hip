@@ -35,8 +35,8 @@ static bool ring_eligible(const IgemmArgs &g, bool strided)
 // 17.1 and 12.2, 50176 x 256 x 128 11.7 and 8.2, 50176 x 256 x 256 14.2 and 11.1, with weight zero-points on 12544 x 256 x 256 10.3
 // and 6.6, 50176 x 1024 x 256 with the add 50.3 and 42.1, stride 2 on 256 x 56 x 56 x 256 -> 512 67 and 55; 4-bit weights,
 // 100352 x 24 x 96 10.6 and 6.4.  K <= 64 is level to 4 % ahead.  Behind: launches of one step with K no power of two (4-bit
-// weights, 6272 x 576 x 96 5.2 and 5.9, 1568 x 960 x 160 4.2 and 4.8) and the pair table with K = 128 (200704 x 512 59 and 62: the
-// gathers and the ring share the LDS).
+// weights, 6272 x 576 x 96 5.2 and 5.9, 1568 x 960 x 160 4.2 and 4.8; 8-bit, 2000 x 1000 x 208 6.3 and 6.7).  The pair table with
+// K <= 128 is level (200704 x 512 x 128 59-63 and 60-62, 802816 x 256 x 64 95-97 and 97): the gathers and the ring share the LDS.
 qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
 {
     g.small_acc = 2; // K <= 256: |acc| <= 2^22
