@@ -2,6 +2,7 @@
 #pragma once
 
 #include "igemm_launch.h"
+#include "ring_grid.h"
 #include "shortk_ring.h"
 
 namespace qnn {
@@ -18,12 +19,7 @@ template <int NB, int KS, bool INT4, int ADD, bool WIDE, bool ZW, bool STRIDED> 
         const int steps = (int)((a.s.g.M + 32 * G::kRw - 1) / (32 * G::kRw));
         a.s.col_groups = (a.s.g.N + 32 * NB - 1) / (32 * NB);
         const int sets = (a.s.col_groups + G::kCw - 1) / G::kCw;
-        // as many workgroups as stay resident together, shared out over the sets of column groups, then trimmed so that every one
-        // walks the same number of steps
-        int walkers = 256 * G::kResident / sets;
-        walkers = walkers < 1 ? 1 : (walkers > steps ? steps : walkers);
-        const int per_walker = (steps + walkers - 1) / walkers;
-        walkers = (steps + per_walker - 1) / per_walker;
+        const int walkers = ring_walkers(G::kResident, sets, steps);
         a.s.walkers = walkers, a.steps = steps / walkers, a.more = steps % walkers;
         hipLaunchKernelGGL(kernel, dim3(8, (unsigned)sets, (unsigned)((walkers + 7) / 8)), dim3(G::kWaves * 64), G::kLds, s, a);
     }

@@ -71,3 +71,18 @@ def test_strided_convolutions(batch, H, W, cin, cout, stride, bits):
     want = oracle.qconv2d(x, 5, w, (stride, stride), (0, 0), mult, shift, 0, 0, 255, bias=bias, weight_bits=bits)
     got = host(qnn.qconv2d(dev(x), 5, dev(w), (stride, stride), (0, 0), dev(mult), dev(shift), 0, 0, 255, bias=dev(bias), weight_bits=bits))
     assert_same(got, want, f"strided {batch}x{H}x{W}x{cin}->{cout}")
+
+
+@pytest.mark.parametrize("M,N,K,bits", [(26310, 640, 208, 8), (5003, 640, 208, 4), (9000, 1100, 64, 8), (3001, 2300, 32, 4), (20011, 700, 128, 8),
+                                        (300, 20000, 96, 8)])
+def test_sets_that_do_not_divide_the_cus(M, N, K, bits):
+    # three, five, seven and more sets of column groups, more sets than workgroups of an XCD: walkers of unequal numbers of steps
+    rng, A, B, mult, shift, bias, rows = _case(M, N, K, bits, 5 * M + N + K)
+    z_a, z_out = 128, 120
+    want = oracle.qgemm(A[rows], z_a, B, mult, shift, z_out, 3, 250, bias=bias, weight_bits=bits)
+    got = host(qnn.qgemm(dev(A), z_a, dev(B), dev(mult), dev(shift), z_out, 3, 250, bias=dev(bias), weight_bits=bits))
+    assert_same(got[rows], want, f"{M}x{N}x{K}")
+    R = rng.integers(0, 256, (M, N)).astype(np.uint8)
+    p = oracle.qadd_params(0.02, 0.031, 0.04)
+    got = host(qnn.qgemm_add(dev(A), z_a, dev(B), dev(mult), dev(shift), z_out, 3, 250, dev(R), 7, p, 3, 0, 255, bias=dev(bias), weight_bits=bits))
+    assert_same(got[rows], oracle.qadd(want, z_out, R[rows], 7, p, 3, 0, 255), f"{M}x{N}x{K} add")
