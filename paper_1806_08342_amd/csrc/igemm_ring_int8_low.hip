@@ -3,6 +3,6 @@
 
 namespace qnn {
 
-void launch_ring_int8_low(ShortKRingArgs &a, int ks, hipStream_t s) { launch_ring_low<false>(a, ks, s); }
+bool launch_ring_int8_low(ShortKRingArgs &a, int ks, bool always, hipStream_t s) { return launch_ring_low<false>(a, ks, always, s); }
 
 } // namespace qnn

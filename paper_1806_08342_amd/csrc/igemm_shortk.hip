@@ -1,12 +1,11 @@
-// Launch routine of the short-K kernels (shortk_ring.h, and shortk.h for operands that are whole 8-byte pieces only); forms of
-// the latter for 8-bit weights.
+// Launch routine of the short-K kernels (shortk_ring.h and shortk.h); forms of the latter for 8-bit weights.
 #include "shortk_launch.h"
 #include "shortk_ring_launch.h"
 #include "tuning.h"
 
 namespace qnn {
 
-void launch_shortk_int8(const ShortKArgs &a, int ks, int64_t waves, hipStream_t s) { launch_shortk_ks<false>(a, ks, waves, s); }
+void launch_shortk_int8(const ShortKArgs &a, int ks, bool v16, int64_t waves, hipStream_t s) { launch_shortk_ks<false>(a, ks, v16, waves, s); }
 
 bool shortk_eligible(const IgemmArgs &g, int b_mode, bool strided)
 {
@@ -30,25 +29,22 @@ static bool ring_eligible(const IgemmArgs &g, bool strided)
     return !g.zw && (32 / ((int64_t)g.Ho * g.Wo) + 2) * g.H * g.W * g.Cin < (1ll << 31);
 }
 
-// us with fragments from global memory (as in shortk.h, in forms for 16-byte pieces, and K = 128 and 256 with four and more
-// column groups with their rows in a ring of two blocks) and with the ring kernel: 802816 x 128 x 256 80 and 66, 200704 x 128 x 128
-// 17.1 and 12.2, 50176 x 256 x 128 11.7 and 8.2, 50176 x 256 x 256 14.2 and 11.1, with weight zero-points on 12544 x 256 x 256 10.3
-// and 6.6, 50176 x 1024 x 256 with the add 50.3 and 42.1, stride 2 on 256 x 56 x 56 x 256 -> 512 67 and 55; 4-bit weights,
-// 100352 x 24 x 96 10.6 and 6.4.  K <= 64 is level to 4 % ahead.  Behind: launches of one step with K no power of two (4-bit
-// weights, 6272 x 576 x 96 5.2 and 5.9, 1568 x 960 x 160 4.2 and 4.8; 8-bit, 2000 x 1000 x 208 6.3 and 6.7).  The pair table with
-// K <= 128 is level (200704 x 512 x 128 59-63 and 60-62, 802816 x 256 x 64 95-97 and 97): the gathers and the ring share the LDS.
+// The ring kernel where its rows are whole 16-byte pieces and it is ahead (ring_ahead, shortk_ring_launch.h; with the add always), else
+// shortk.h.  us with fragments from global memory and with the ring: 802816 x 128 x 256 80 and 66, 200704 x 128 x 128 17.1 and
+// 12.2, 50176 x 256 x 128 11.7 and 8.2, 50176 x 256 x 256 14.2 and 11.1, with weight zero-points on 12544 x 256 x 256 10.3 and 6.6,
+// 50176 x 1024 x 256 with the add 50.3 and 42.1, stride 2 on 256 x 56 x 56 x 256 -> 512 67 and 55; 4-bit weights, 100352 x 24 x 96
+// 10.6 and 6.4.
 qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
 {
     g.small_acc = 2; // K <= 256: |acc| <= 2^22
     g.c_vec16 = aligned_to(g.C, 16) && (g.ldc % 16 == 0);
     const int ks = (g.K + 31) / 32;
-    const int nb = ks <= 4 ? 4 : 2;
     ShortKArgs a = {};
     a.g = g;
     a.strided = strided ? 1 : 0;
     a.stream_out = g.M * (int64_t)g.N <= ((int64_t)32 << 20); // between 26 MB (gains) and 51 MB (the next layer loses more)
-    a.col_groups = (g.N + 32 * nb - 1) / (32 * nb);
-    const bool ring = ring_eligible(g, strided), whole = g.c_vec16 && g.ldc < (1 << 26);
+    bool ring = ring_eligible(g, strided);
+    const bool whole = g.c_vec16 && g.ldc < (1 << 26);
     // the add is built into the ring kernel only, for outputs and residuals made of whole aligned chunks
     const bool add_pass = g.R != nullptr && !(ring && !strided && whole && g.r_vec16 && g.ldr < (1 << 26) && (g.N % 16) == 0);
     if (add_pass) a.g.R = nullptr;
@@ -57,9 +53,14 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
         r.s = a;
         r.whole = whole ? 1 : 0;
         if (strided) r.magic_image = magic_for((uint32_t)(g.Ho * g.Wo)), r.magic_row = magic_for((uint32_t)g.Wo);
-        if (b_mode == B_INT4) ks <= 4 ? launch_ring_int4_low(r, ks, s) : launch_ring_int4_high(r, ks, s);
-        else ks <= 4 ? launch_ring_int8_low(r, ks, s) : launch_ring_int8_high(r, ks, s);
-    } else {
+        const bool always = tuning().shortk_alds == 2;
+        if (b_mode == B_INT4) ring = ks <= 4 ? launch_ring_int4_low(r, ks, always, s) : launch_ring_int4_high(r, ks, always, s);
+        else ring = ks <= 4 ? launch_ring_int8_low(r, ks, always, s) : launch_ring_int8_high(r, ks, always, s);
+    }
+    if (!ring) {
+        const int nb = ks <= 4 ? 4 : 2;
+        a.col_groups = (g.N + 32 * nb - 1) / (32 * nb);
+        const bool v16 = aligned_to(g.A, 16) && ((strided ? g.Cin : g.lda) % 16) == 0 && (g.K % 16) == 0;
         const int64_t row_blocks = (g.M + 31) / 32;
         // as many waves as stay resident together (3 per SIMD for K <= 32 without weight zero-points, else 2, on 256 CUs), spread
         // over the column groups, then trimmed so that every wave walks the same number of row blocks
@@ -71,8 +72,8 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
         a.walkers = (int)walkers;
         const int64_t waves = walkers * a.col_groups;
         if (waves > 0x7fffffff) return QNN_EINVAL;
-        if (b_mode == B_INT4) launch_shortk_int4(a, ks, waves, s);
-        else launch_shortk_int8(a, ks, waves, s);
+        if (b_mode == B_INT4) launch_shortk_int4(a, ks, v16, waves, s);
+        else launch_shortk_int8(a, ks, v16, waves, s);
     }
     const qnn_status st = launch_status(hipGetLastError());
     if (st != QNN_OK || !add_pass) return st;

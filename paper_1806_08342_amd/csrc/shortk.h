@@ -1,6 +1,6 @@
-// Dense quantized layer with a short reduction (K <= 256, K % 8 == 0) where shortk_ring.h does not apply: rows that are whole
-// 8-byte pieces only, or pitches beyond its 32-bit offsets.  Here also: what the two kernels share, the epilogue constants of a
-// column and the add of two codes by table.
+// Dense quantized layer with a short reduction (K <= 256, K % 8 == 0) where shortk_ring.h is not ahead (small launches, mostly: see
+// ring_ahead) or does not apply: rows that are whole 8-byte pieces only, or pitches beyond its 32-bit offsets.  Here also: what the
+// two kernels share, the epilogue constants of a column and the add of two codes by table.
 //
 // Weight-stationary and barrier-free: a wave owns up to 32*NB output columns, loads their weights
 // ONCE into registers as MFMA B fragments (4-bit weights are unpacked there, kept times 16),
@@ -28,11 +28,14 @@ struct ShortKArgs {
     int stream_out;    // non-temporal output stores
 };
 
-// 16 consecutive k of one row / column as 4 dwords, zero beyond K (K % 8 == 0).  VEC = bytes per load
+// 16 consecutive k of one row / column as 4 dwords, zero beyond K (K % 8 == 0).  VEC = bytes per load; 16 (K % 16 == 0, any
+// address): without a branch, from a clamped address, and beyond K any bytes (the other operand is zero there).
 template <int VEC> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t *p, int k, int K)
 {
     i32x4 v = {0, 0, 0, 0};
-    if constexpr (VEC == 8) {
+    if constexpr (VEC == 16) {
+        __builtin_memcpy(&v, p + (k + 16 <= K ? k : K - 16), 16);
+    } else if constexpr (VEC == 8) {
         if (k + 8 <= K) {
             const u32x2 a = *reinterpret_cast<const u32x2 *>(p + k);
             v[0] = (int32_t)a.x, v[1] = (int32_t)a.y;
@@ -130,7 +133,8 @@ __device__ __forceinline__ u32x4 add_pairs16(const uint8_t *pair_tab, u32x4 v, u
 // ZW: per-column weight zero-points (see igemm_epilogue_impl): the activation sum of a row is one more accumulator,
 // fed by one matrix instruction per K sub-step whose B fragment is all ones, which leaves the sums in the registers
 // and lanes where the rescale of the same rows needs them.
-template <int NB, int KS, bool INT4, bool ZW = false>
+// VEC: bytes per load of the rows, 16 or 8.
+template <int NB, int KS, bool INT4, int VEC, bool ZW = false>
 __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(const ShortKArgs s)
 {
     constexpr int PITCH = 32 * NB + 32; // bytes per staged output row: the 8 rows a store instruction touches fall in distinct banks
@@ -167,11 +171,15 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
             const int k = ks * 32 + fhalf * 16;
             if constexpr (INT4) {
                 const uint8_t *p = g.B + (((int64_t)n * g.ldb) >> 1);
+                if constexpr (VEC == 16) {
+                    __builtin_memcpy(&packed[ks][j], p + ((k + 16 <= g.K ? k : g.K - 16) >> 1), 8);
+                    continue;
+                }
                 packed[ks][j] = u32x2{0u, 0u};
                 if (k + 16 <= g.K) __builtin_memcpy(&packed[ks][j], p + (k >> 1), 8);
                 else if (k + 8 <= g.K) packed[ks][j][0] = *reinterpret_cast<const uint32_t *>(p + (k >> 1));
             } else {
-                fb[ks][j] = shortk_load16<4>(g.B + (int64_t)n * g.ldb, k, g.K);
+                fb[ks][j] = shortk_load16<VEC == 16 ? 16 : 4>(g.B + (int64_t)n * g.ldb, k, g.K);
             }
         }
     }
@@ -191,10 +199,12 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
             p = g.A + (int64_t)m * g.lda + fhalf * 16;
         }
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) fa[ks] = shortk_load16<8>(p, ks * 32, g.K - fhalf * 16);
+        for (int ks = 0; ks < KS; ++ks) fa[ks] = shortk_load16<VEC>(p, ks * 32, g.K - fhalf * 16);
     };
+    // (Not where these rows and the weights as loaded do not fit the registers together.)
+    constexpr bool FIRST_AHEAD = VEC == 8 || !ZW;
     i32x4 first[KS];
-    load_rows(walker < row_blocks ? walker : row_blocks - 1, first);
+    if constexpr (FIRST_AHEAD) load_rows(walker < row_blocks ? walker : row_blocks - 1, first);
 
     bool range_ok = g.small_acc >= 2, fused_ok = true;
     const bool ties = rescale_ties(g.lo_rel);
@@ -204,18 +214,19 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             if constexpr (INT4) fb[ks][j] = expand_int4(packed[ks][j]);
+            if (VEC == 16 && ks * 32 + fhalf * 16 + 16 > g.K) fb[ks][j] = i32x4{0, 0, 0, 0};
 #pragma unroll
             for (int d = 0; d < 4; ++d) colsum = __builtin_amdgcn_sdot4(fb[ks][j][d], 0x01010101, colsum, false);
         }
         colsum += __shfl_xor(colsum, 32);
         if (INT4) colsum >>= 4; // weights are kept times 16; exact
-        // (the sums of ZW count code - 128, also -128 for every k from K to KS * 32, read as zeros)
+        // (the sums of ZW count code - 128; where pieces of 8 are loaded, also -128 for every k from K to KS * 32, read as zeros)
         const int32_t b = g.bias ? p_bias[j] : 0;
-        shortk_column(col[j], g, colsum, b, p_mult[j], p_shift[j], p_zw[j], KS * 32);
+        shortk_column(col[j], g, colsum, b, p_mult[j], p_shift[j], p_zw[j], VEC == 16 ? g.K : KS * 32);
         range_ok = range_ok && rescale_in_range(p_shift[j]) && b > -(1 << 27) && b < (1 << 27);
         fused_ok = fused_ok && range_ok && channel_rescale_ok(p_mult[j], p_shift[j], ties);
     }
-    const bool fused = __all(fused_ok), in_range = __all(range_ok);
+    const bool fused = __all(fused_ok), in_range = __all(range_ok), k_tail = VEC == 16 && g.K != KS * 32;
     const i32x4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 
     // lane-invariant parts of the LDS and global addresses of the output tile
@@ -292,6 +303,7 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
     int rb = walker, rb_stored = -1;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) fa[ks] = first[ks];
+    if constexpr (!FIRST_AHEAD) load_rows(rb < row_blocks ? rb : row_blocks - 1, fa);
     for (; rb < row_blocks; rb += s.walkers) {
         i32x16 acc[NB];
 #pragma unroll
@@ -301,8 +313,9 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
         i32x16 sums = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}; // ZW: sum_k (code - 128) of the rows
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const i32x4 xs = fa[ks] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
+            i32x4 xs = fa[ks] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
             if constexpr (ZW) {
+                if (k_tail && ks * 32 + fhalf * 16 >= g.K) xs = i32x4{0, 0, 0, 0}; // counts in the sum
                 sums = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, ones, sums, 0, 0, 0);
             }
 #pragma unroll

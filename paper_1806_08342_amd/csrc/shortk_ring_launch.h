@@ -7,80 +7,105 @@
 
 namespace qnn {
 
-template <int NB, int KS, bool INT4, int ADD, bool WIDE, bool ZW, bool STRIDED> inline void launch_ring_form(ShortKRingArgs &a, hipStream_t s)
+// Whether a launch without the add is ahead of shortk.h, whose lanes load their fragments straight from global memory (us there and
+// here; 8-bit weights unless said).
+//  - up to 32 columns, or 64 with K <= 128: always (a form as wide as the columns; 25088 x 24 x 144 5.2 and 4.6), but for strided
+//    launches of one step with K > 128 (28800 x 32 x 176 5.7 and 6.0).
+//  - one step per walker: the launch is its set-up, and the weight exchange and its barriers lose (4-bit weights, 6272 x 576 x 96
+//    5.2 and 5.9, 1568 x 960 x 160 4.3 and 4.9; 2000 x 1000 x 208 6.3 and 6.8, 2000 x 1000 x 64 6.1 and 6.4), unless the weight
+//    rows are a multiple of 128 bytes apart, where fragment loads meet in the same channels (2000 x 1000 x 256 7.1 and 6.7,
+//    55614 x 128 x 128 10.0 and 7.3), with weight zero-points 96 < K <= 128 altogether, or K <= 128 fills the chip (94226 x 128 x 32
+//    8.1 and 7.0, 39421 x 71 x 64 7.6 and 7.5).
+//  - K <= 96, walkers with one column group each: the row streams of the sets drift apart.  Behind where the last set is mostly
+//    empty (115363 x 144 x 32 10.2 and 12.1, 239900 x 144 x 64 19.1 and 21.8), and for K > 32 beyond what the caches hold
+//    (1000000 x 128 x 64 39.2 and 44.5, 651985 x 640 x 64 118 and 133) and with outputs that leave byte by byte (174968 x 158 x 64
+//    31.5 and 36.6).
+template <int NB, int KS, bool INT4, bool WIDE, bool ZW, bool STRIDED> inline bool ring_ahead(const IgemmArgs &g, int columns, int sets, int walkers, int per_walker)
+{
+    if (NB == 1 || (NB == 2 && KS <= 4)) return !(STRIDED && KS > 4 && per_walker == 1);
+    const bool long_rows = (INT4 ? g.ldb / 2 : g.ldb) % 128 == 0;
+    if (per_walker == 1 && (KS > 4 || sets * walkers <= (KS == 1 ? 400 : 300))) return long_rows || (ZW && KS == 4);
+    if (STRIDED && KS > 4 && !WIDE) return long_rows; // 18819 x 640 x 240 12.6 and 14.8, 46400 x 176 x 176 11.2 and 13.2
+    if (KS > 3 || WIDE) return true;
+    if (sets > 1 && (int64_t)g.N * 4 < (int64_t)columns * sets * 3) return false;
+    return KS == 1 || (g.N % 16 == 0 && g.M * (g.N + g.K) < 100000000);
+}
+
+// Launches one form, unless shortk.h is ahead of it (`always`: then too); whether it did.
+template <int NB, int KS, bool INT4, int ADD, bool WIDE, bool ZW, bool STRIDED> inline bool launch_ring_form(ShortKRingArgs &a, bool always, hipStream_t s)
 {
     using G = RingGeometry<NB, KS, ADD, WIDE, ZW>;
     if constexpr (!G::kFits) {
-        launch_ring_form<NB, KS, INT4, ADD, true, ZW, STRIDED>(a, s);
+        return launch_ring_form<NB, KS, INT4, ADD, true, ZW, STRIDED>(a, always, s);
     } else {
-        auto kernel = shortk_ring_kernel<NB, KS, INT4, ADD, WIDE, ZW, STRIDED>;
-        static LdsOptIn opt_in; // per instantiation
-        if (opt_in.ensure(reinterpret_cast<const void *>(kernel), G::kLds) != hipSuccess) return; // the error stays pending for the caller
         const int steps = (int)((a.s.g.M + 32 * G::kRw - 1) / (32 * G::kRw));
         a.s.col_groups = (a.s.g.N + 32 * NB - 1) / (32 * NB);
         const int sets = (a.s.col_groups + G::kCw - 1) / G::kCw;
         const int walkers = ring_walkers(G::kResident, sets, steps);
+        if (!ADD && !always && !ring_ahead<NB, KS, INT4, WIDE, ZW, STRIDED>(a.s.g, 32 * NB * G::kCw, sets, walkers, (steps + walkers - 1) / walkers)) return false;
+        auto kernel = shortk_ring_kernel<NB, KS, INT4, ADD, WIDE, ZW, STRIDED>;
+        static LdsOptIn opt_in; // per instantiation
+        if (opt_in.ensure(reinterpret_cast<const void *>(kernel), G::kLds) != hipSuccess) return true; // the error stays pending for the caller
         a.s.walkers = walkers, a.steps = steps / walkers, a.more = steps % walkers;
         hipLaunchKernelGGL(kernel, dim3(8, (unsigned)sets, (unsigned)((walkers + 7) / 8)), dim3(G::kWaves * 64), G::kLds, s, a);
+        return true;
     }
 }
 
-template <int KS, bool INT4, int ADD, bool ZW, bool STRIDED> inline void launch_ring_width(ShortKRingArgs &a, hipStream_t s)
+template <int KS, bool INT4, int ADD, bool ZW, bool STRIDED> inline bool launch_ring_width(ShortKRingArgs &a, bool always, hipStream_t s)
 {
     constexpr int NB = KS > 4 || ADD == 3 ? 2 : 4;
     const int N = a.s.g.N;
     // few columns: one wave's, no wider than they are (not with the pair table, which is for large outputs)
     if constexpr (ADD < 2) {
-        if (N <= 32) return launch_ring_form<1, KS, INT4, ADD, false, ZW, STRIDED>(a, s);
-        if (NB == 4 && N <= 64) return launch_ring_form<2, KS, INT4, ADD, false, ZW, STRIDED>(a, s);
+        if (N <= 32) return launch_ring_form<1, KS, INT4, ADD, false, ZW, STRIDED>(a, always, s);
+        if (NB == 4 && N <= 64) return launch_ring_form<2, KS, INT4, ADD, false, ZW, STRIDED>(a, always, s);
     }
     // four waves side by side on the same rows, unless more than an eighth of them had no columns (ADD == 3: eight, or four)
     constexpr int W = RingGeometry<NB, KS, ADD, true, ZW>::kCw;
     const int groups = (N + 32 * NB - 1) / (32 * NB), idle = (groups + W - 1) / W * W - groups;
-    if (idle * 8 <= groups + idle) launch_ring_form<NB, KS, INT4, ADD, true, ZW, STRIDED>(a, s);
-    else launch_ring_form<NB, KS, INT4, ADD, false, ZW, STRIDED>(a, s);
+    if (idle * 8 <= groups + idle) return launch_ring_form<NB, KS, INT4, ADD, true, ZW, STRIDED>(a, always, s);
+    return launch_ring_form<NB, KS, INT4, ADD, false, ZW, STRIDED>(a, always, s);
 }
 
-template <int KS, bool INT4> inline void launch_ring_ks(ShortKRingArgs &a, hipStream_t s)
+template <int KS, bool INT4> inline bool launch_ring_ks(ShortKRingArgs &a, bool always, hipStream_t s)
 {
     if (a.s.g.R) {
         // from 2^24 outputs on the 65536-entry pair table pays for itself; below, two 256-entry tables
         if (a.s.g.M * (int64_t)a.s.g.N >= ((int64_t)1 << 24)) {
             if constexpr (KS == 3 || KS == 4) // 16 waves where they have columns
-                if (a.s.g.N >= 192) return launch_ring_width<KS, INT4, 3, false, false>(a, s);
-            launch_ring_width<KS, INT4, 2, false, false>(a, s);
-        } else launch_ring_width<KS, INT4, 1, false, false>(a, s);
-    } else if (a.s.g.zw) {
-        launch_ring_width<KS, INT4, 0, true, false>(a, s);
-    } else if (a.s.strided) {
-        launch_ring_width<KS, INT4, 0, false, true>(a, s);
-    } else {
-        launch_ring_width<KS, INT4, 0, false, false>(a, s);
+                if (a.s.g.N >= 192) return launch_ring_width<KS, INT4, 3, false, false>(a, always, s);
+            return launch_ring_width<KS, INT4, 2, false, false>(a, always, s);
+        }
+        return launch_ring_width<KS, INT4, 1, false, false>(a, always, s);
     }
+    if (a.s.g.zw) return launch_ring_width<KS, INT4, 0, true, false>(a, always, s);
+    if (a.s.strided) return launch_ring_width<KS, INT4, 0, false, true>(a, always, s);
+    return launch_ring_width<KS, INT4, 0, false, false>(a, always, s);
 }
 
 // the forms for ks sub-steps of 32 k (igemm_ring*.hip: 8- and 4-bit weights, up to 4 and more)
-void launch_ring_int8_low(ShortKRingArgs &a, int ks, hipStream_t s);
-void launch_ring_int8_high(ShortKRingArgs &a, int ks, hipStream_t s);
-void launch_ring_int4_low(ShortKRingArgs &a, int ks, hipStream_t s);
-void launch_ring_int4_high(ShortKRingArgs &a, int ks, hipStream_t s);
+bool launch_ring_int8_low(ShortKRingArgs &a, int ks, bool always, hipStream_t s);
+bool launch_ring_int8_high(ShortKRingArgs &a, int ks, bool always, hipStream_t s);
+bool launch_ring_int4_low(ShortKRingArgs &a, int ks, bool always, hipStream_t s);
+bool launch_ring_int4_high(ShortKRingArgs &a, int ks, bool always, hipStream_t s);
 
 // Sub-steps beyond K cost like any other, so a form for nearly every number of them
-template <bool INT4> inline void launch_ring_low(ShortKRingArgs &a, int ks, hipStream_t s)
+template <bool INT4> inline bool launch_ring_low(ShortKRingArgs &a, int ks, bool always, hipStream_t s)
 {
     switch (ks) {
-    case 1: return launch_ring_ks<1, INT4>(a, s);
-    case 2: return launch_ring_ks<2, INT4>(a, s);
-    case 3: return launch_ring_ks<3, INT4>(a, s);
-    default: return launch_ring_ks<4, INT4>(a, s);
+    case 1: return launch_ring_ks<1, INT4>(a, always, s);
+    case 2: return launch_ring_ks<2, INT4>(a, always, s);
+    case 3: return launch_ring_ks<3, INT4>(a, always, s);
+    default: return launch_ring_ks<4, INT4>(a, always, s);
     }
 }
-template <bool INT4> inline void launch_ring_high(ShortKRingArgs &a, int ks, hipStream_t s)
+template <bool INT4> inline bool launch_ring_high(ShortKRingArgs &a, int ks, bool always, hipStream_t s)
 {
     switch (ks) {
     case 5:
-    case 6: return launch_ring_ks<6, INT4>(a, s);
-    default: return launch_ring_ks<8, INT4>(a, s);
+    case 6: return launch_ring_ks<6, INT4>(a, always, s);
+    default: return launch_ring_ks<8, INT4>(a, always, s);
     }
 }
 

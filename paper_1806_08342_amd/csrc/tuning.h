@@ -17,7 +17,7 @@ struct Tuning {
     int gemm_prio = -1;       // QNN_GEMM_PRIO: issue-priority scheme of the pipelined tile kernel (-1 = per tile)
     int persist = -1;         // QNN_PERSIST: 0 = one workgroup per tile, 1 = persistent workgroups, -1 = per tile
     int dw_variant = -1;      // QNN_DW_VARIANT: depthwise kernel family (-1 = choose)
-    int shortk_alds = 1;      // QNN_SHORTK_ALDS: 0 = short-K launches never on the kernel with its rows in an LDS ring
+    int shortk_alds = 1;      // QNN_SHORTK_ALDS: short-K kernel with its rows in an LDS ring 0 = never, 1 = where it is ahead, 2 = wherever it fits
     int small = 1;            // QNN_SMALL: 0 = small launches (more than 64 rows) on the kernels for large ones
     int dw_xcd = 1;           // QNN_DW_XCD: depthwise workgroups renumbered so that an XCD gets neighbouring patches
     int range_slot = -1;      // QNN_RANGE_SLOT: slot of the counted range reductions (-1 = the next one, 1024 = none)

@@ -76,7 +76,7 @@ def test_qgemm_add_pair_table(M, N, K, bits):
                     act="none")
 
 
-@pytest.mark.parametrize("alds", [1, 0])
+@pytest.mark.parametrize("alds", [2, 1, 0])
 @pytest.mark.parametrize("M,N,K,bits", [(1000, 512, 128, 8), (4099, 520, 256, 8), (133, 1030, 128, 4), (2500, 256, 256, 4),
                                          (16400, 1024, 256, 8),   # 2^24 outputs: 8-wave workgroups with the table of code pairs
                                          (33000, 1024, 128, 4)])

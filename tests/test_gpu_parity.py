@@ -832,7 +832,7 @@ def test_qgemm_default_plan_large_shape_sampled_rows():
     assert_same(got[rows], want, "qgemm 4096x4096x512 sampled rows")
 
 
-@pytest.mark.parametrize("alds", [1, 0])
+@pytest.mark.parametrize("alds", [2, 1, 0])
 @pytest.mark.parametrize("M,N,K", [(1, 256, 256), (31, 300, 256), (100, 256, 256), (1000, 300, 256), (33, 512, 128), (5000, 1024, 128),
                                    (4097, 520, 256), (65, 8192, 256), (7000, 2100, 128)])
 @pytest.mark.parametrize("bits", [8, 4])

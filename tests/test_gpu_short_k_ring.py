@@ -1,4 +1,5 @@
-"""GPU parity of the short-K kernel with its rows in an LDS ring (shortk_ring.h): launches with fewer and with more steps per
+"""GPU parity of the short-K kernels, on the one with its rows in an LDS ring wherever it fits (shortk_ring.h), on the one with
+fragments from global memory (shortk.h), and by the dispatcher's choice: launches with fewer and with more steps per
 workgroup than the ring has blocks, in each of its widths (one wave's columns, 32 to 128 of them, and four waves side by side),
 with and without the residual add and weight zero-points; weights, row pitches and outputs that are not 16-byte aligned; strided
 1x1 convolutions whose 32 rows span several images."""
@@ -14,6 +15,10 @@ from gpu_util import assert_same, dev, host
 pytestmark = pytest.mark.gpu
 
 
+# QNN_SHORTK_ALDS: the ring kernel wherever it fits, by shape, never
+ROUTES = pytest.mark.parametrize("route", ["2", "1", "0"])
+
+
 def _case(M, N, K, bits, seed):
     rng = np.random.default_rng(seed)
     lim = 8 if bits == 4 else 128
@@ -25,10 +30,12 @@ def _case(M, N, K, bits, seed):
     return rng, A, oracle.pack_int4(B) if bits == 4 else B, mult, shift, bias, rows
 
 
+@ROUTES
 @pytest.mark.parametrize("M", [129, 2049, 300001])
-@pytest.mark.parametrize("N,K", [(16, 256), (32, 16), (64, 128), (48, 32), (128, 64), (96, 208), (512, 64), (512, 256), (224, 96)])
+@pytest.mark.parametrize("N,K", [(16, 256), (32, 16), (64, 128), (48, 32), (128, 64), (96, 208), (512, 64), (512, 256), (224, 96), (160, 224), (72, 160)])
 @pytest.mark.parametrize("bits", [8, 4])
-def test_walks(M, N, K, bits):
+def test_walks(tuning, route, M, N, K, bits):
+    tuning.setenv("QNN_SHORTK_ALDS", route)
     rng, A, B, mult, shift, bias, rows = _case(M, N, K, bits, M + 3 * N + K + bits)
     dA, dB, dm, ds, db = dev(A), dev(B), dev(mult), dev(shift), dev(bias)
     for z_a, z_out, lo in ((0, 0, 0), (128, 120, 3)):
@@ -45,9 +52,11 @@ def test_walks(M, N, K, bits):
     assert_same(got[rows], want, f"{M}x{N}x{K} asym")
 
 
+@ROUTES
 @pytest.mark.parametrize("M", [200, 150001])
 @pytest.mark.parametrize("N,K", [(40, 48), (136, 256), (512, 128)])
-def test_pitches_and_alignment(M, N, K):
+def test_pitches_and_alignment(tuning, route, M, N, K):
+    tuning.setenv("QNN_SHORTK_ALDS", route)
     rng, A, B, mult, shift, bias, rows = _case(M, N, K, 8, 77 + M + N + K)
     dm, ds, db = dev(mult), dev(shift), dev(bias)
     wide = torch.zeros((M, K + 32), dtype=torch.uint8, device="cuda:0")
@@ -61,10 +70,12 @@ def test_pitches_and_alignment(M, N, K):
     assert (got[:, :8] == 77).all() and (got[:, 8 + N:] == 77).all(), "bytes beside the output"
 
 
+@ROUTES
 @pytest.mark.parametrize("batch,H,W,cin,cout,stride", [(3, 29, 31, 64, 200, 2), (40, 3, 2, 32, 32, 2), (70, 1, 1, 256, 512, 3), (9, 56, 7, 128, 64, 3),
                                                        (2, 5, 300, 16, 96, 2), (64, 28, 28, 256, 130, 2)])
 @pytest.mark.parametrize("bits", [8, 4])
-def test_strided_convolutions(batch, H, W, cin, cout, stride, bits):
+def test_strided_convolutions(tuning, route, batch, H, W, cin, cout, stride, bits):
+    tuning.setenv("QNN_SHORTK_ALDS", route)
     rng, _, B, mult, shift, bias, _ = _case(100, cout, cin, bits, batch + H + W + cin + bits)
     x = rng.integers(0, 256, (batch, H, W, cin)).astype(np.uint8)
     w = B.reshape(cout, 1, 1, -1)
@@ -73,9 +84,11 @@ def test_strided_convolutions(batch, H, W, cin, cout, stride, bits):
     assert_same(got, want, f"strided {batch}x{H}x{W}x{cin}->{cout}")
 
 
+@ROUTES
 @pytest.mark.parametrize("M,N,K,bits", [(26310, 640, 208, 8), (5003, 640, 208, 4), (9000, 1100, 64, 8), (3001, 2300, 32, 4), (20011, 700, 128, 8),
                                         (300, 20000, 96, 8)])
-def test_sets_that_do_not_divide_the_cus(M, N, K, bits):
+def test_sets_that_do_not_divide_the_cus(tuning, route, M, N, K, bits):
+    tuning.setenv("QNN_SHORTK_ALDS", route)
     # three, five, seven and more sets of column groups, more sets than workgroups of an XCD: walkers of unequal numbers of steps
     rng, A, B, mult, shift, bias, rows = _case(M, N, K, bits, 5 * M + N + K)
     z_a, z_out = 128, 120
@@ -86,3 +99,19 @@ def test_sets_that_do_not_divide_the_cus(M, N, K, bits):
     p = oracle.qadd_params(0.02, 0.031, 0.04)
     got = host(qnn.qgemm_add(dev(A), z_a, dev(B), dev(mult), dev(shift), z_out, 3, 250, dev(R), 7, p, 3, 0, 255, bias=dev(bias), weight_bits=bits))
     assert_same(got[rows], oracle.qadd(want, z_out, R[rows], 7, p, 3, 0, 255), f"{M}x{N}x{K} add")
+
+
+@pytest.mark.parametrize("lda", [(1 << 26) - 16, 1 << 26, (1 << 26) + 8])
+@pytest.mark.parametrize("N,K", [(200, 64), (48, 240)])
+def test_rows_far_apart(tuning, lda, N, K):
+    # 32 rows at the edge of the ring kernel's 31-bit offsets and beyond it
+    tuning.setenv("QNN_SMALL", "0")  # 65 rows take the short-K kernels only on request
+    M = 65
+    rng, A, B, mult, shift, bias, rows = _case(M, N, K, 8, N + K)
+    far = torch.empty((M - 1) * lda + K, dtype=torch.uint8, device="cuda:0").as_strided((M, K), (lda, 1))
+    far.copy_(dev(A))
+    want = oracle.qgemm(A, 9, B, mult, shift, 0, 0, 255, bias=bias)
+    assert_same(host(qnn.qgemm(far, 9, dev(B), dev(mult), dev(shift), 0, 0, 255, bias=dev(bias))), want, f"lda {lda} {N}x{K}")
+    zw = rng.integers(-8, 8, N).astype(np.int32)
+    want = oracle.qgemm(A, 9, B, mult, shift, 0, 0, 255, bias=bias, z_w=zw)
+    assert_same(host(qnn.qgemm_asym(far, 9, dev(B), dev(zw), dev(mult), dev(shift), 0, 0, 255, bias=dev(bias))), want, f"lda {lda} {N}x{K} asym")
