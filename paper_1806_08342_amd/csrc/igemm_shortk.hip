@@ -18,7 +18,7 @@ bool shortk_eligible(const IgemmArgs &g, int b_mode, bool strided)
 }
 
 // Rows of whole, aligned 16-byte pieces, weights of any alignment, offsets within 32 rows (weights: 128) of 31 bits.  A strided
-// convolution has its forms without weight zero-points and without the add.
+// convolution (never with weight zero-points here) has its forms without the add.
 static bool ring_eligible(const IgemmArgs &g, bool strided)
 {
     if (tuning().shortk_alds == 0) return false; // tuning aid: fragments from global memory
@@ -26,10 +26,10 @@ static bool ring_eligible(const IgemmArgs &g, bool strided)
     if (!aligned_to(g.A, 16) || (row_pitch % 16) != 0 || (g.K % 16) != 0 || g.M >= (1 << 30) || g.ldb >= (1 << 23)) return false;
     if (g.N > (1 << 21)) return false; // sets of column groups: a dimension of the grid
     if (!strided) return g.lda < (1 << 26);
-    return !g.zw && (32 / ((int64_t)g.Ho * g.Wo) + 2) * g.H * g.W * g.Cin < (1ll << 31);
+    return (32 / ((int64_t)g.Ho * g.Wo) + 2) * g.H * g.W * g.Cin < (1ll << 31);
 }
 
-// The ring kernel where its rows are whole 16-byte pieces and it is ahead (ring_ahead, shortk_ring_launch.h; with the add always), else
+// The ring kernel where its rows are whole 16-byte pieces and it is ahead (ring_ahead and launch_ring_add, shortk_ring_launch.h), else
 // shortk.h.  us with fragments from global memory and with the ring: 802816 x 128 x 256 80 and 66, 200704 x 128 x 128 17.1 and
 // 12.2, 50176 x 256 x 128 11.7 and 8.2, 50176 x 256 x 256 14.2 and 11.1, with weight zero-points on 12544 x 256 x 256 10.3 and 6.6,
 // 50176 x 1024 x 256 with the add 50.3 and 42.1, stride 2 on 256 x 56 x 56 x 256 -> 512 67 and 55; 4-bit weights, 100352 x 24 x 96
@@ -45,9 +45,12 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
     a.stream_out = g.M * (int64_t)g.N <= ((int64_t)32 << 20); // between 26 MB (gains) and 51 MB (the next layer loses more)
     bool ring = ring_eligible(g, strided);
     const bool whole = g.c_vec16 && g.ldc < (1 << 26);
-    // the add is built into the ring kernel only, for outputs and residuals made of whole aligned chunks
-    const bool add_pass = g.R != nullptr && !(ring && !strided && whole && g.r_vec16 && g.ldr < (1 << 26) && (g.N % 16) == 0);
+    const bool v16 = aligned_to(g.A, 16) && ((strided ? g.Cin : g.lda) % 16) == 0 && (g.K % 16) == 0;
+    // the add is built into the forms for pieces of 16, for outputs and residuals made of whole aligned chunks (the ring kernel's: not
+    // strided, pitches within its 31-bit offsets)
+    const bool add_pass = g.R != nullptr && !(v16 && g.c_vec16 && g.r_vec16 && (g.N % 16) == 0);
     if (add_pass) a.g.R = nullptr;
+    if (a.g.R) ring = ring && !strided && whole && g.ldr < (1 << 26);
     if (ring) {
         ShortKRingArgs r = {};
         r.s = a;
@@ -60,11 +63,10 @@ qnn_status launch_shortk(IgemmArgs &g, int b_mode, bool strided, hipStream_t s)
     if (!ring) {
         const int nb = ks <= 4 ? 4 : 2;
         a.col_groups = (g.N + 32 * nb - 1) / (32 * nb);
-        const bool v16 = aligned_to(g.A, 16) && ((strided ? g.Cin : g.lda) % 16) == 0 && (g.K % 16) == 0;
         const int64_t row_blocks = (g.M + 31) / 32;
-        // as many waves as stay resident together (3 per SIMD for K <= 32 without weight zero-points, else 2, on 256 CUs), spread
-        // over the column groups, then trimmed so that every wave walks the same number of row blocks
-        const int64_t resident = 256 * 4 * ((ks <= 1 && !g.zw) ? 3 : 2);
+        // as many waves as stay resident together (3 per SIMD for K <= 32 without weight zero-points and without the add, else 2, on
+        // 256 CUs), spread over the column groups, then trimmed so that every wave walks the same number of row blocks
+        const int64_t resident = 256 * 4 * ((ks <= 1 && !a.g.R && !g.zw) ? 3 : 2);
         int64_t walkers = resident / a.col_groups;
         walkers = walkers < 1 ? 1 : (walkers > row_blocks ? row_blocks : walkers);
         const int64_t per_walker = (row_blocks + walkers - 1) / walkers;

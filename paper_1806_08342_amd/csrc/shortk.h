@@ -28,6 +28,10 @@ struct ShortKArgs {
     int stream_out;    // non-temporal output stores
 };
 
+// Whether the add of a launch goes through the 65536-entry table of code pairs: from 2^24 outputs on it pays for itself; below,
+// two 256-entry tables.
+inline bool shortk_pairs(const IgemmArgs &g) { return g.M * (int64_t)g.N >= ((int64_t)1 << 24); }
+
 // 16 consecutive k of one row / column as 4 dwords, zero beyond K (K % 8 == 0).  VEC = bytes per load; 16 (K % 16 == 0, any
 // address): without a branch, from a clamped address, and beyond K any bytes (the other operand is zero there).
 template <int VEC> __device__ __forceinline__ i32x4 shortk_load16(const uint8_t *p, int k, int K)
@@ -130,17 +134,50 @@ __device__ __forceinline__ u32x4 add_pairs16(const uint8_t *pair_tab, u32x4 v, u
     return y;
 }
 
+// The same with the tables of an ADD form: 1 two 256-entry tables of rescaled codes, else the table of all pairs
+template <int ADD> __device__ __forceinline__ u32x4 add_chunk(u32x4 v, u32x4 r, const uint8_t *pair_tab, const int32_t *tab, const AddOut &ao)
+{
+    u32x4 y;
+    if constexpr (ADD >= 2) {
+        y = add_pairs16(pair_tab, v, r);
+    } else if (ao.fused) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            y[d] = add_codes4<true>(v[d], r[d], tab, ao);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+#pragma nounroll
+        for (int d = 0; d < 4; ++d) y[d] = add_codes4<false>(v[d], r[d], tab, ao);
+    }
+    return y;
+}
+
 // ZW: per-column weight zero-points (see igemm_epilogue_impl): the activation sum of a row is one more accumulator,
 // fed by one matrix instruction per K sub-step whose B fragment is all ones, which leaves the sums in the registers
 // and lanes where the rescale of the same rows needs them.
 // VEC: bytes per load of the rows, 16 or 8.
-template <int NB, int KS, bool INT4, int VEC, bool ZW = false>
-__global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(const ShortKArgs s)
+// ADD (VEC 16): the rescaling add with a residual tensor (g.R), as in shortk_ring.h: 1 through two 256-entry tables, 2 through the
+// table of all pairs, which eight waves share.
+template <int NB, int KS, bool INT4, int VEC, int ADD = 0, bool ZW = false>
+__global__ void __launch_bounds__(ADD == 2 ? 512 : 256, ADD == 2 ? 1 : (KS <= 1 && !ZW ? 3 : 2)) shortk_kernel(const ShortKArgs s)
 {
     constexpr int PITCH = 32 * NB + 32; // bytes per staged output row: the 8 rows a store instruction touches fall in distinct banks
-    constexpr int WAVES = 4;
-    __shared__ __attribute__((aligned(16))) uint8_t stage_all[WAVES * 32 * PITCH];
+    constexpr int WAVES = ADD == 2 ? 8 : 4;
+    __shared__ __attribute__((aligned(16))) uint8_t stage_static[ADD ? 16 : WAVES * 32 * PITCH];
+    extern __shared__ __attribute__((aligned(16))) uint8_t shortk_lds[]; // ADD: tables, then the output tiles of the waves
+    constexpr int TABLES = ADD == 2 ? 65536 : 2048;
+    uint8_t *const stage_all = ADD ? shortk_lds + TABLES : stage_static;
     const IgemmArgs &g = s.g;
+    int32_t *const tab = reinterpret_cast<int32_t *>(ADD == 2 ? stage_all : shortk_lds);
+    if constexpr (ADD) { // the only workgroup barriers, before any wave may leave
+        add_fill_tables(tab, g.add, threadIdx.x, WAVES * 64);
+        __syncthreads();
+        if constexpr (ADD == 2) {
+            fill_pair_table<WAVES>(shortk_lds, tab, g.add);
+            __syncthreads();
+        }
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // wave-uniform: row-block arithmetic stays scalar
     uint8_t *stage = stage_all + wave * (32 * PITCH);
@@ -201,8 +238,9 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) fa[ks] = shortk_load16<VEC>(p, ks * 32, g.K - fhalf * 16);
     };
-    // (Not where these rows and the weights as loaded do not fit the registers together.)
-    constexpr bool FIRST_AHEAD = VEC == 8 || !ZW;
+    // (Not where these rows and the weights as loaded do not fit the registers together: the forms for K <= 128 with the add
+    // spilled 12 to 52 bytes, 20000 x 144 x 112 11.5 us, not 11.0.)
+    constexpr bool FIRST_AHEAD = VEC == 8 || (!ZW && !(ADD && KS == 4));
     i32x4 first[KS];
     if constexpr (FIRST_AHEAD) load_rows(walker < row_blocks ? walker : row_blocks - 1, first);
 
@@ -251,6 +289,22 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
     const uint32_t sel2 = (quad_lane & 2) ? 0x03020706u : 0x05040100u;
     const int32_t lo_rel = g.lo_rel, hi_rel = g.hi_rel, z_out = g.z_out;
 
+    // residual chunks of a row block (ADD), requested one round ahead: same lanes and addresses as the stores of that block
+    int64_t st_roff[NB];
+    u32x4 rres[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        st_roff[i] = (int64_t)st_row[i] * g.ldr + (n0 + (i * 64 + lane) % (2 * NB) * 16);
+        rres[i] = u32x4{0u, 0u, 0u, 0u};
+    }
+    auto load_res = [&](int rbx) __attribute__((always_inline)) {
+        const uint8_t *const r_block = g.R + (int64_t)rbx * 32 * g.ldr; // wave-uniform
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (st_col_ok[i] && rbx * 32 + st_row[i] < M) rres[i] = *reinterpret_cast<const u32x4 *>(r_block + st_roff[i]);
+    };
+    const AddOut ao = make_add_out(g.add);
+
     // (Non-temporal stores, s.stream_out: 4-9 % on 6-26 MB outputs -- what is left in the L2s is written back when the
     // kernel ends.  Larger outputs and the add built in are faster with plain ones: ResNet-50 at batch 256, 103 MB,
     // K = 256: 84 us and 93 with non-temporal ones, 70 and 76; 51 MB, K = 256: 57 and 54, but the 3x3 layer that reads
@@ -262,7 +316,14 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         uint8_t *const c_block = g.C + (int64_t)rbx * 32 * g.ldc; // wave-uniform
-        if (chunks_whole && rbx * 32 + 32 <= M && s.stream_out) { // the common case: only the lane-invariant column test
+        if constexpr (ADD) { // the launcher uses ADD only when every output chunk is a whole, aligned 16-byte chunk
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                if (st_col_ok[i] && rbx * 32 + st_row[i] < M)
+                    *reinterpret_cast<u32x4 *>(c_block + st_off[i]) = add_chunk<ADD>(*reinterpret_cast<const u32x4 *>(stage + st_lds[i]), rres[i], shortk_lds, tab, ao);
+                __builtin_amdgcn_sched_barrier(0); // one chunk at a time: the table reads of all chunks at once would spill
+            }
+        } else if (chunks_whole && rbx * 32 + 32 <= M && s.stream_out) { // the common case: only the lane-invariant column test
 #pragma unroll
             for (int i = 0; i < NB; ++i)
                 if (st_col_ok[i])
@@ -326,6 +387,7 @@ __global__ void __launch_bounds__(256, KS <= 1 && !ZW ? 3 : 2) shortk_kernel(con
         // the wait for them is no wait for these (requests retire in order).
         if (rb + s.walkers < row_blocks) load_rows(rb + s.walkers, fa);
         if (rb_stored >= 0) store_block(rb_stored);
+        if constexpr (ADD) load_res(rb); // used one round from now, when this block is stored
 
         // ---- epilogue into the wave's LDS tile: after the 4x4 byte transposition inside each
         // quad of lanes a lane holds 4 consecutive columns of one row

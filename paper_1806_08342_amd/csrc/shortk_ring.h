@@ -313,22 +313,6 @@ __global__ void __launch_bounds__((RingGeometry<NB, KS, ADD, WIDE, ZW>::kWaves *
         for (int i = 0; i < NB; ++i) rres[i] = buffer_load16(r_block, bytes, st_roff[i]);
     };
     const AddOut ao = make_add_out(g.add);
-    auto add16 = [&](u32x4 v, u32x4 r) __attribute__((always_inline)) {
-        u32x4 y;
-        if constexpr (use_pairs) {
-            y = add_pairs16(pair_tab, v, r);
-        } else if (ao.fused) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                y[d] = add_codes4<true>(v[d], r[d], tab, ao);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma nounroll
-            for (int d = 0; d < 4; ++d) y[d] = add_codes4<false>(v[d], r[d], tab, ao);
-        }
-        return y;
-    };
     auto tile_fence = [] { // the tile is private to the wave and LDS operations of one wave complete in order
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -345,7 +329,7 @@ __global__ void __launch_bounds__((RingGeometry<NB, KS, ADD, WIDE, ZW>::kWaves *
             if constexpr (ADD) {
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
-                    buffer_store16<false>(c_block, bytes, st_off[i], add16(chunk(i), rres[i]));
+                    buffer_store16<false>(c_block, bytes, st_off[i], add_chunk<ADD>(chunk(i), rres[i], pair_tab, tab, ao));
                     __builtin_amdgcn_sched_barrier(0); // one chunk at a time: the table reads of all chunks at once would spill
                 }
             } else if (s.stream_out) {

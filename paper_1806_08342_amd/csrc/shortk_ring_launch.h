@@ -31,57 +31,88 @@ template <int NB, int KS, bool INT4, bool WIDE, bool ZW, bool STRIDED> inline bo
     return KS == 1 || (g.N % 16 == 0 && g.M * (g.N + g.K) < 100000000);
 }
 
-// Launches one form, unless shortk.h is ahead of it (`always`: then too); whether it did.
+// Launches one form, unless shortk.h is ahead of it (`always`: then too); whether it did.  With the add: see launch_ring_add.
 template <int NB, int KS, bool INT4, int ADD, bool WIDE, bool ZW, bool STRIDED> inline bool launch_ring_form(ShortKRingArgs &a, bool always, hipStream_t s)
 {
     using G = RingGeometry<NB, KS, ADD, WIDE, ZW>;
-    if constexpr (!G::kFits) {
-        return launch_ring_form<NB, KS, INT4, ADD, true, ZW, STRIDED>(a, always, s);
-    } else {
-        const int steps = (int)((a.s.g.M + 32 * G::kRw - 1) / (32 * G::kRw));
-        a.s.col_groups = (a.s.g.N + 32 * NB - 1) / (32 * NB);
-        const int sets = (a.s.col_groups + G::kCw - 1) / G::kCw;
-        const int walkers = ring_walkers(G::kResident, sets, steps);
-        if (!ADD && !always && !ring_ahead<NB, KS, INT4, WIDE, ZW, STRIDED>(a.s.g, 32 * NB * G::kCw, sets, walkers, (steps + walkers - 1) / walkers)) return false;
-        auto kernel = shortk_ring_kernel<NB, KS, INT4, ADD, WIDE, ZW, STRIDED>;
-        static LdsOptIn opt_in; // per instantiation
-        if (opt_in.ensure(reinterpret_cast<const void *>(kernel), G::kLds) != hipSuccess) return true; // the error stays pending for the caller
-        a.s.walkers = walkers, a.steps = steps / walkers, a.more = steps % walkers;
-        hipLaunchKernelGGL(kernel, dim3(8, (unsigned)sets, (unsigned)((walkers + 7) / 8)), dim3(G::kWaves * 64), G::kLds, s, a);
-        return true;
-    }
+    const int steps = (int)((a.s.g.M + 32 * G::kRw - 1) / (32 * G::kRw));
+    a.s.col_groups = (a.s.g.N + 32 * NB - 1) / (32 * NB);
+    const int sets = (a.s.col_groups + G::kCw - 1) / G::kCw;
+    const int walkers = ring_walkers(G::kResident, sets, steps), per_walker = (steps + walkers - 1) / walkers;
+    const bool busy = per_walker > 1 && steps * 3ll >= 2ll * per_walker * ring_resident(G::kResident, sets);
+    if (!always && !(ADD ? ADD > 1 || NB < 4 || busy : ring_ahead<NB, KS, INT4, WIDE, ZW, STRIDED>(a.s.g, 32 * NB * G::kCw, sets, walkers, per_walker))) return false;
+    auto kernel = shortk_ring_kernel<NB, KS, INT4, ADD, WIDE, ZW, STRIDED>;
+    static LdsOptIn opt_in; // per instantiation
+    if (opt_in.ensure(reinterpret_cast<const void *>(kernel), G::kLds) != hipSuccess) return true; // the error stays pending for the caller
+    a.s.walkers = walkers, a.steps = steps / walkers, a.more = steps % walkers;
+    hipLaunchKernelGGL(kernel, dim3(8, (unsigned)sets, (unsigned)((walkers + 7) / 8)), dim3(G::kWaves * 64), G::kLds, s, a);
+    return true;
 }
 
-template <int KS, bool INT4, int ADD, bool ZW, bool STRIDED> inline bool launch_ring_width(ShortKRingArgs &a, bool always, hipStream_t s)
+// Column groups that W waves side by side leave without columns, of `total`
+inline int ring_idle(int N, int columns, int W, int &total)
 {
-    constexpr int NB = KS > 4 || ADD == 3 ? 2 : 4;
-    const int N = a.s.g.N;
-    // few columns: one wave's, no wider than they are (not with the pair table, which is for large outputs)
-    if constexpr (ADD < 2) {
-        if (N <= 32) return launch_ring_form<1, KS, INT4, ADD, false, ZW, STRIDED>(a, always, s);
-        if (NB == 4 && N <= 64) return launch_ring_form<2, KS, INT4, ADD, false, ZW, STRIDED>(a, always, s);
-    }
-    // four waves side by side on the same rows, unless more than an eighth of them had no columns (ADD == 3: eight, or four)
-    constexpr int W = RingGeometry<NB, KS, ADD, true, ZW>::kCw;
-    const int groups = (N + 32 * NB - 1) / (32 * NB), idle = (groups + W - 1) / W * W - groups;
-    if (idle * 8 <= groups + idle) return launch_ring_form<NB, KS, INT4, ADD, true, ZW, STRIDED>(a, always, s);
+    const int groups = (N + columns - 1) / columns;
+    total = (groups + W - 1) / W * W;
+    return total - groups;
+}
+
+// Four waves side by side on the same rows, unless more than an eighth of them had no columns
+template <int NB, int KS, bool INT4, int ADD, bool ZW, bool STRIDED> inline bool launch_ring_wide(ShortKRingArgs &a, bool always, hipStream_t s)
+{
+    int total;
+    const int idle = ring_idle(a.s.g.N, 32 * NB, 4, total);
+    if (idle * 8 <= total) return launch_ring_form<NB, KS, INT4, ADD, true, ZW, STRIDED>(a, always, s);
     return launch_ring_form<NB, KS, INT4, ADD, false, ZW, STRIDED>(a, always, s);
+}
+
+template <int KS, bool INT4, bool ZW, bool STRIDED> inline bool launch_ring_width(ShortKRingArgs &a, bool always, hipStream_t s)
+{
+    constexpr int NB = KS > 4 ? 2 : 4;
+    const int N = a.s.g.N;
+    // few columns: one wave's, no wider than they are
+    if (N <= 32) return launch_ring_form<1, KS, INT4, 0, false, ZW, STRIDED>(a, always, s);
+    if (NB == 4 && N <= 64) return launch_ring_form<2, KS, INT4, 0, false, ZW, STRIDED>(a, always, s);
+    return launch_ring_wide<NB, KS, INT4, 0, ZW, STRIDED>(a, always, s);
+}
+
+// With the add the ring kernel has the forms that are ahead of shortk.h only (us there and here):
+//  - two tables of 256 entries: up to 32 columns, or 64 with K <= 128 (22477 x 32 x 64 8.1 and 5.7 with 4-bit weights), and K <= 32 from
+//    two steps on (160166 x 96 x 32 30.3 and 23.1, 16935 x 704 x 32 22.8 and 20.1) that keep two thirds of the chip busy (9046 x
+//    816 x 16, 55 %, 13.5 and 19.5).  Other launches this small are set-up, and the
+//    tables come on top of the weight exchange (6272 x 576 x 96 8.4 and 13.8, 2000 x 1008 x 208 6.8 and 8.5).
+//  - the table of pairs, which leaves room for little besides: 96 < K <= 128 on 16 waves where less than a quarter of the columns
+//    is idle (274776 x 480 x 128 82 and 69, 205520 x 1872 x 128 255 and 207; 384 columns are behind, 186836 x 384 x 128 43 and 50);
+//    more than 160 with four waves side by side (50176 x 1024 x 256 53 and 43, 162833 x 1552 x 192 225 and 175), up to 192 for
+//    large outputs only (25088 x 1024 x 192 25.2 and 26.0).  Else behind: 400000 x 48 x 96 26 and 74, 200704 x 256 x 96 34 and 36,
+//    300000 x 144 x 160 44 and 48; level, 802816 x 256 x 64 100-106 and 101-104.
+template <int KS, bool INT4> inline bool launch_ring_add(ShortKRingArgs &a, bool always, hipStream_t s)
+{
+    const int N = a.s.g.N;
+    [[maybe_unused]] int total;
+    if (!shortk_pairs(a.s.g)) {
+        if (N <= 32) return launch_ring_form<1, KS, INT4, 1, false, false, false>(a, always, s);
+        if constexpr (KS <= 4)
+            if (N <= 64) return launch_ring_form<2, KS, INT4, 1, false, false, false>(a, always, s);
+        if constexpr (KS == 1) return launch_ring_wide<4, KS, INT4, 1, false, false>(a, always, s);
+        return false;
+    }
+    if constexpr (KS == 4) {
+        if (ring_idle(N, 64, 8, total) * 8 <= total) return launch_ring_form<2, KS, INT4, 3, true, false, false>(a, always, s);
+        if (ring_idle(N, 64, 4, total) * 4 < total) return launch_ring_form<2, KS, INT4, 3, false, false, false>(a, always, s);
+    }
+    if constexpr (KS > 4)
+        if (ring_idle(N, 64, 4, total) * 8 <= total && (always || a.s.g.K > 192 || (a.s.g.K > 160 && a.s.g.M * (int64_t)N >= ((int64_t)1 << 26))))
+            return launch_ring_form<2, KS, INT4, 2, true, false, false>(a, always, s);
+    return false;
 }
 
 template <int KS, bool INT4> inline bool launch_ring_ks(ShortKRingArgs &a, bool always, hipStream_t s)
 {
-    if (a.s.g.R) {
-        // from 2^24 outputs on the 65536-entry pair table pays for itself; below, two 256-entry tables
-        if (a.s.g.M * (int64_t)a.s.g.N >= ((int64_t)1 << 24)) {
-            if constexpr (KS == 3 || KS == 4) // 16 waves where they have columns
-                if (a.s.g.N >= 192) return launch_ring_width<KS, INT4, 3, false, false>(a, always, s);
-            return launch_ring_width<KS, INT4, 2, false, false>(a, always, s);
-        }
-        return launch_ring_width<KS, INT4, 1, false, false>(a, always, s);
-    }
-    if (a.s.g.zw) return launch_ring_width<KS, INT4, 0, true, false>(a, always, s);
-    if (a.s.strided) return launch_ring_width<KS, INT4, 0, false, true>(a, always, s);
-    return launch_ring_width<KS, INT4, 0, false, false>(a, always, s);
+    if (a.s.g.R) return launch_ring_add<KS, INT4>(a, always, s);
+    if (a.s.g.zw) return launch_ring_width<KS, INT4, true, false>(a, always, s);
+    if (a.s.strided) return launch_ring_width<KS, INT4, false, true>(a, always, s);
+    return launch_ring_width<KS, INT4, false, false>(a, always, s);
 }
 
 // the forms for ks sub-steps of 32 k (igemm_ring*.hip: 8- and 4-bit weights, up to 4 and more)

@@ -78,16 +78,20 @@ def test_qgemm_add_pair_table(M, N, K, bits):
 
 @pytest.mark.parametrize("alds", [2, 1, 0])
 @pytest.mark.parametrize("M,N,K,bits", [(1000, 512, 128, 8), (4099, 520, 256, 8), (133, 1030, 128, 4), (2500, 256, 256, 4),
-                                         (16400, 1024, 256, 8),   # 2^24 outputs: 8-wave workgroups with the table of code pairs
-                                         (33000, 1024, 128, 4)])
+                                         (9100, 320, 32, 8), (5000, 64, 128, 4), (70001, 24, 16, 4),  # tables of rescaled codes, on the ring kernel
+                                         # 2^24 outputs: the table of code pairs
+                                         (16400, 1024, 256, 8),   # 8 waves, four side by side
+                                         (24000, 720, 208, 4), (120000, 144, 192, 8),  # the same, and too few columns for it
+                                         (33000, 1024, 128, 4), (33001, 512, 112, 8),  # 16 waves, eight side by side
+                                         (82001, 208, 128, 8),    # 16 waves, four side by side
+                                         (60003, 288, 104, 4)])   # no rows of whole 16-byte pieces
 def test_qgemm_add_short_k_rows_through_lds(tuning, alds, M, N, K, bits):
-    # K = 128 / 256 with at least one workgroup's worth of column groups: without an add these shapes stage the A
-    # rows in LDS once per workgroup; with the add built in they keep the direct loads whatever the switch says,
-    # and as a second pass behind the staged kernel when the operands are not made of whole aligned chunks
+    # short-K products with the add in either kernel: the one with its rows in an LDS ring wherever it has a form (2), by shape (1),
+    # always the one with fragments from global memory (0); operands that are no whole aligned chunks take a second pass
     tuning.setenv("QNN_SHORTK_ALDS", str(alds))
     assert qnn.qgemm_plan(M, N, K) == "shortk"
-    _check_gemm_add(M, N, K, 4300 + M + N + K + bits, f"qgemm_add short-K through LDS={alds} {M}x{N}x{K} bits={bits}", bits=bits)
-    _check_gemm_add(M, N, K, 4400 + M + N + K + bits, f"qgemm_add short-K through LDS={alds} {M}x{N}x{K} bits={bits}, general add rescale",
+    _check_gemm_add(M, N, K, 4300 + M + N + K + bits, f"qgemm_add short-K route={alds} {M}x{N}x{K} bits={bits}", bits=bits)
+    _check_gemm_add(M, N, K, 4400 + M + N + K + bits, f"qgemm_add short-K route={alds} {M}x{N}x{K} bits={bits}, general add rescale",
                     bits=bits, odd=True, act="none")
 
 

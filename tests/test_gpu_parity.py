@@ -604,8 +604,7 @@ def test_qgemm_short_k_general_rescale_columns(K, N):
 
 @pytest.mark.parametrize("K,pad_a,pad_c", [(256, 16, 16), (128, 48, 32), (256, 32, 0), (256, 8, 16)])
 def test_qgemm_short_k_rows_through_lds_spaced_rows(K, pad_a, pad_c):
-    # the staged form (A rows copied to LDS per workgroup) on column slices of wider matrices: lda > K, ldc > N;
-    # pad 8 leaves the rows 8-byte aligned only, which takes the direct loads instead
+    # column slices of wider matrices: lda > K, ldc > N; pad 8 leaves the rows 8-byte aligned only
     import torch
     M, N = 1333, 576
     rng = np.random.default_rng(2100 + K + pad_a + pad_c)
@@ -837,8 +836,8 @@ def test_qgemm_default_plan_large_shape_sampled_rows():
                                    (4097, 520, 256), (65, 8192, 256), (7000, 2100, 128)])
 @pytest.mark.parametrize("bits", [8, 4])
 def test_qgemm_short_k_rows_through_lds(tuning, alds, M, N, K, bits):
-    # short-K kernel with the A rows copied to LDS once per workgroup (K = 128 / 256): ragged row blocks, column
-    # counts that leave a workgroup with idle waves, one and many walkers; the switch off = direct fragment loads
+    # short-K products on the kernel with its rows in an LDS ring wherever it fits (2), by shape (1), on the one with fragments from
+    # global memory (0): ragged row blocks, column counts that leave a workgroup with idle waves, one and many walkers
     tuning.setenv("QNN_SHORTK_ALDS", str(alds))
     if M > 64:
         assert qnn.qgemm_plan(M, N, K) == "shortk"

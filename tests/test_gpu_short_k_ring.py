@@ -72,7 +72,7 @@ def test_pitches_and_alignment(tuning, route, M, N, K):
 
 @ROUTES
 @pytest.mark.parametrize("batch,H,W,cin,cout,stride", [(3, 29, 31, 64, 200, 2), (40, 3, 2, 32, 32, 2), (70, 1, 1, 256, 512, 3), (9, 56, 7, 128, 64, 3),
-                                                       (2, 5, 300, 16, 96, 2), (64, 28, 28, 256, 130, 2)])
+                                                       (2, 5, 300, 16, 96, 2), (64, 28, 28, 256, 130, 2), (200, 27, 27, 64, 448, 2)])
 @pytest.mark.parametrize("bits", [8, 4])
 def test_strided_convolutions(tuning, route, batch, H, W, cin, cout, stride, bits):
     tuning.setenv("QNN_SHORTK_ALDS", route)
@@ -82,6 +82,11 @@ def test_strided_convolutions(tuning, route, batch, H, W, cin, cout, stride, bit
     want = oracle.qconv2d(x, 5, w, (stride, stride), (0, 0), mult, shift, 0, 0, 255, bias=bias, weight_bits=bits)
     got = host(qnn.qconv2d(dev(x), 5, dev(w), (stride, stride), (0, 0), dev(mult), dev(shift), 0, 0, 255, bias=dev(bias), weight_bits=bits))
     assert_same(got, want, f"strided {batch}x{H}x{W}x{cin}->{cout}")
+    R = rng.integers(0, 256, want.shape).astype(np.uint8)
+    p = oracle.qadd_params(0.02, 0.031, 0.04)
+    got = host(qnn.qconv2d_add(dev(x), 5, dev(w), (stride, stride), (0, 0), dev(mult), dev(shift), 0, 0, 255, dev(R), 7, p, 3, 0, 255, bias=dev(bias),
+                               weight_bits=bits))
+    assert_same(got, oracle.qadd(want, 0, R, 7, p, 3, 0, 255), f"strided {batch}x{H}x{W}x{cin}->{cout} add")
 
 
 @ROUTES
