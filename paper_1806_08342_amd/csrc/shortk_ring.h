@@ -63,9 +63,9 @@ template <int CPR> __device__ __forceinline__ int ring_place(int row, int c)
     return c ^ ((row >> kShift) & (CPR - 1));
 }
 
-// Waves of a workgroup and its dynamic LDS: tables, output tiles of the waves, ring.  Two workgroups per CU (three of the forms
-// that have the registers for it), with the pair table one of eight waves; the ring has what is left of the LDS, up to eight
-// blocks, and its first CW blocks (with the pair table: its place) are where the weights are exchanged before.
+// Waves of a workgroup and its dynamic LDS: tables, output tiles of the waves, ring.  Two workgroups of four waves per CU, three or
+// four of the forms that have the registers for it, with the pair table one of eight or sixteen waves; the ring has what is left of
+// the LDS, up to eight blocks, and its first CW blocks (with the pair table: its place) are where the weights are exchanged before.
 template <int NB, int KS, int ADD, bool WIDE, bool ZW> struct RingGeometry {
     static constexpr int kWaves = ADD == 3 ? 16 : ADD == 2 ? 8 : 4;
     static constexpr int kCw = ADD == 3 ? (WIDE ? 8 : 4) : (WIDE ? 4 : 1), kRw = kWaves / kCw; // waves side by side, and on other rows
@@ -383,13 +383,17 @@ __global__ void __launch_bounds__((RingGeometry<NB, KS, ADD, WIDE, ZW>::kWaves *
                 i32x4 xs = fa[ks] ^ (int32_t)0x80808080; // uint8 code -> signed (code - 128)
                 if constexpr (ZW) {
                     if (k_tail && ks * 32 + fhalf * 16 >= g.K) xs = i32x4{0, 0, 0, 0}; // counts in the sum
+                }
+                // in registers from here on: the LDS read is over before the barrier below, behind which its block is refilled
+                asm volatile("" : "+v"(xs));
+                if constexpr (ZW) {
                     sums = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, ones, sums, 0, 0, 0);
                 }
 #pragma unroll
                 for (int j = 0; j < NB; ++j)
-                    acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, fb[ks][j], acc[j], 0, 0, 0); // columns past N: clamped loads, never stored
+                    acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xs, fb[ks][j], acc[j], 0, 0, 0); // columns past N: zeros, never stored
             }
-            // Every wave has consumed this step's fragments (read one step ago): its block is free after the barrier.  Without
+            // Every wave has this step's fragments in registers (read one step ago): its block is free after the barrier.  Without
             // a branch for the last step, whose next one is a constant chunk: the compiler counts requests too.
             const int next = at + 1 < DEPTH ? at + 1 : 0;
             if (few) {

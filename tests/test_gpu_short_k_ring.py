@@ -120,3 +120,28 @@ def test_rows_far_apart(tuning, lda, N, K):
     zw = rng.integers(-8, 8, N).astype(np.int32)
     want = oracle.qgemm(A, 9, B, mult, shift, 0, 0, 255, bias=bias, z_w=zw)
     assert_same(host(qnn.qgemm_asym(far, 9, dev(B), dev(zw), dev(mult), dev(shift), 0, 0, 255, bias=dev(bias))), want, f"lda {lda} {N}x{K} asym")
+
+
+@pytest.mark.parametrize("N,K", [(512, 64), (512, 128), (512, 256), (1024, 96)])
+def test_waves_of_a_workgroup_in_different_rescale_forms(tuning, N, K):
+    # four waves side by side share a barrier per step: some take the fused rescale, one the general one in range (shift 25), one
+    # the one beyond (bias 2^28), one with a left shift
+    tuning.setenv("QNN_SHORTK_ALDS", "2")
+    M = 20000
+    rng, A, B, mult, shift, bias, rows = _case(M, N, K, 8, N + K)
+    mult[130], shift[130] = 2 ** 30 + 12345, -3
+    bias[150] = 2 ** 28
+    shift[300], shift[310] = 25, 31
+    bias[N - 1], bias[N - 2] = 2 ** 28, -(2 ** 28)
+    zw = rng.integers(-8, 8, N).astype(np.int32)
+    R = rng.integers(0, 256, (M, N)).astype(np.uint8)
+    p = oracle.qadd_params(0.02, 0.031, 0.04)
+    for z_a, z_out, lo, hi in ((0, 0, 0, 255), (128, 120, 3, 250)):
+        want = oracle.qgemm(A[rows], z_a, B, mult, shift, z_out, lo, hi, bias=bias)
+        got = host(qnn.qgemm(dev(A), z_a, dev(B), dev(mult), dev(shift), z_out, lo, hi, bias=dev(bias)))
+        assert_same(got[rows], want, f"{M}x{N}x{K} z_a={z_a}")
+        got = host(qnn.qgemm_add(dev(A), z_a, dev(B), dev(mult), dev(shift), z_out, lo, hi, dev(R), 7, p, 3, 0, 255, bias=dev(bias)))
+        assert_same(got[rows], oracle.qadd(want, z_out, R[rows], 7, p, 3, 0, 255), f"{M}x{N}x{K} z_a={z_a} add")
+        want = oracle.qgemm(A[rows], z_a, B, mult, shift, z_out, lo, hi, bias=bias, z_w=zw)
+        got = host(qnn.qgemm_asym(dev(A), z_a, dev(B), dev(zw), dev(mult), dev(shift), z_out, lo, hi, bias=dev(bias)))
+        assert_same(got[rows], want, f"{M}x{N}x{K} z_a={z_a} asym")
