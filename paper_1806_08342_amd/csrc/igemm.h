@@ -29,7 +29,7 @@ using i32x16 = int32_t __attribute__((ext_vector_type(16)));
 using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
 using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
 
-enum { A_MATRIX = 0, A_CONV = 1, A_CONV_ZERO = 2 }; // A_CONV_ZERO: see igemm_dma.h
+enum { A_MATRIX = 0, A_CONV = 1, A_CONV_ZERO = 2, A_FAR = 3 }; // A_CONV_ZERO: see igemm_dma.h, A_FAR: tile64.h
 enum { B_INT8 = 0, B_INT4 = 1, B_INT8_ROWS = 2 };
 
 struct IgemmArgs {

@@ -176,7 +176,8 @@ static qnn_status run_igemm_zw(IgemmArgs &g, int a_mode, int b_mode, int vec, vo
     const bool pipelined = (g.K % 64) == 0 ? tiles64 <= 512
                            : i4            ? g.K >= 512 || tiles64 <= 768
                                            : g.K >= 1024 && (tiles64 <= 768 || tiles64 > 1024 || g.K >= 4032);
-    if (chunks && tiles64 <= 0x7ffffff && pipelined && g.lda < (1 << 23) && g.ldb < (1 << 23)) return launch_status(launch_tile64(g, a_mode == A_MATRIX, i4, SplitK{1, 0, nullptr}, s));
+    // (Offsets within 64 columns of 31 bits; the rows of A may be further apart.)
+    if (chunks && tiles64 <= 0x7ffffff && pipelined && g.ldb < (1 << 25)) return launch_status(launch_tile64(g, a_mode == A_MATRIX, i4, SplitK{1, 0, nullptr}, s));
     const bool aligned_for_dma = chunks && (g.K % 64) == 0 && g.lda < (1 << 23) && g.ldb < (1 << 23);
     if ((b_mode == B_INT8 || i4) && aligned_for_dma && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 0x7ffffff) {
         // large products: the 256x256 tile once it fills most of the chip, else 128x128

@@ -42,6 +42,9 @@ template <int A_MODE> static hipError_t launch_mode(const IgemmArgs &g, bool i4,
 
 hipError_t launch_tile64(const IgemmArgs &g, bool mat, bool i4, const SplitK &sk, hipStream_t s)
 {
+    // rows of A whose offsets within 64 of them exceed 31 bits (1100 x 384 x 512 with weight zero-points, us: 5.3, rows 2^25 apart
+    // 5.7; on the staged tile 6.4 and 6.5)
+    if (mat && g.lda >= (1 << 25)) return i4 ? launch_one<A_FAR, true, true, false>(g, sk, s) : launch_one<A_FAR, false, true, false>(g, sk, s);
     return mat ? launch_mode<A_MATRIX>(g, i4, sk, s) : launch_mode<A_CONV>(g, i4, sk, s);
 }
 

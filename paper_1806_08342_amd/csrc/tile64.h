@@ -1,6 +1,6 @@
 // 64x64 tiles of the implicit GEMM for products with few output tiles: at most a few workgroups per CU.
 //
-// Four waves of 32x32 outputs; operands by global_load_lds into a ring of STAGES stages of 128 k, one barrier per stage, all
+// Four waves of 32x32 outputs; operands by buffer loads (a convolution's activations: global_load_lds) into a ring of STAGES stages of 128 k, one barrier per stage, all
 // fragments of a stage (4 + 4 reads) requested before its first matrix instruction.  A lone tile is bound by this chain
 // (barrier, LDS round trip, four matrix instructions, the next requests), about 0.45 us per 128 k however deep the ring is.
 // Against the same tile on igemm_dma.h (stages of 64 k): 3136 x 512 x 512 6.7 -> 6.2 us, 784 x 1024 x 512 5.8 -> 5.3,
@@ -10,7 +10,8 @@
 // Any K that is whole chunks (K % 16 == 0, 4-bit weights K % 32 == 0): what lies beyond K reads as zero, outside the bounds
 // of a buffer; the row sums of weight zero-points are corrected for the codes 0 there.  (A convolution's activations, by
 // global_load_lds, come from a chunk of the code 128 there, which adds nothing to the row sums.)
-// The copies are buffer loads with 32-bit lane offsets (the dispatcher guarantees pitches below 2^23): see igemm_dma.h.
+// The copies are buffer loads with 32-bit lane offsets (the dispatcher guarantees pitches below 2^25): see igemm_dma.h.  A_FAR: rows
+// of a matrix further apart, by global_load_lds (with weight zero-points; other products of such rows never come here).
 #pragma once
 
 #include "igemm_dma.h"
@@ -61,7 +62,9 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
         m = m < g.M ? m : g.M - 1;
         a_hi0[i] = a_wi0[i] = 0;
         a_off[i] = 0;
-        if constexpr (A_MODE == A_MATRIX) {
+        if constexpr (A_MODE == A_FAR) {
+            a_src[i] = g.A + m * g.lda + a_k[i] + k_begin;
+        } else if constexpr (A_MODE == A_MATRIX) {
             a_off[i] = (uint32_t)((int)(m - m0) * (int)g.lda + a_k[i] + k_begin);
         } else {
             const int64_t img = m / ((int64_t)g.Ho * g.Wo);
@@ -94,7 +97,9 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
                 continue;
             }
             const uint8_t *src = zero_xs;
-            if (k < k_end) {
+            if constexpr (A_MODE == A_FAR) {
+                if (k < k_end) src = a_src[i] + k0;
+            } else if (k < k_end) {
                 const uint32_t tap = fast_div((uint32_t)k, (uint32_t)g.Cin, g.magic_cin);
                 const uint32_t ta = fast_div(tap, (uint32_t)g.kw, g.magic_kw);
                 const int a = (int)ta, b = (int)(tap - ta * (uint32_t)g.kw);

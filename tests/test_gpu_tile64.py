@@ -2,6 +2,7 @@
 zero-points, 4-bit weights, convolutions, and both depths of the ring (at most 512 tiles, and more)."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_1806_08342_amd as qnn
@@ -67,3 +68,29 @@ def test_convolution(bits, asym, H, W, cin, cout, stride):
         want = oracle.qconv2d(x, 37, wo, (stride, stride), (1, 1), mult, shift, 120, 0, 255, bias=bias, weight_bits=bits)
         got = host(qnn.qconv2d(dev(x), 37, dev(wo), (stride, stride), (1, 1), dev(mult), dev(shift), 120, 0, 255, bias=dev(bias), weight_bits=bits))
     assert_same(got, want, f"3x3 {cin}->{cout} {bits}-bit")
+
+
+@pytest.mark.parametrize("lda,ldb", [(1 << 23, 1040), ((1 << 25) - 16, 1040), (1 << 25, 1040), ((1 << 26) + 16, 1040), (1040, 1 << 23), (1040, (1 << 25) - 16),
+                                     (1040, 1 << 25), (1 << 25, 1 << 25)])
+@pytest.mark.parametrize("K", [512, 1040])
+def test_weight_zero_points_with_rows_far_apart(lda, ldb, K):
+    # at the edges of the tile's 31-bit offsets and beyond them
+    M, N, z_a = 70, 67, 9
+    rng = np.random.default_rng(lda % 1000003 + ldb + K)
+    A = rng.integers(0, 256, (M, K)).astype(np.uint8)
+    B = rng.integers(-128, 128, (N, K)).astype(np.int8)
+    zw = rng.integers(-8, 8, N).astype(np.int32)
+    mult, shift = oracle.quantize_multipliers(10 ** rng.uniform(-4.2, -3.6, N))
+
+    def spaced(a, pitch):
+        t = torch.empty((a.shape[0] - 1) * pitch + a.shape[1], dtype=dev(a[:1]).dtype, device="cuda:0").as_strided(a.shape, (pitch, 1))
+        t.copy_(dev(a))
+        return t
+
+    dA, dB, dz, dm, ds = spaced(A, lda), spaced(B, ldb), dev(zw), dev(mult), dev(shift)
+    out = torch.empty((M, N), dtype=torch.uint8, device="cuda:0")
+    ws = torch.empty(4096, dtype=torch.uint8, device="cuda:0")
+    rc = qnn.load_library().qnn_qgemm_asym(dA.data_ptr(), lda, z_a, dB.data_ptr(), ldb, 0, 8, dz.data_ptr(), M, N, K, None, dm.data_ptr(), ds.data_ptr(),
+                                           120, 0, 255, out.data_ptr(), N, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    assert_same(host(out), oracle.qgemm(A, z_a, B, mult, shift, 120, 0, 255, z_w=zw), f"lda {lda} ldb {ldb} K {K}")
