@@ -115,6 +115,10 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
     static_assert(!B4 || !SPLIT, "4-bit weights run unsplit");
     constexpr int STAGE_BYTES = (BM + BN) * BK;
     constexpr int LOADS = A_LOADS + B_LOADS;
+    // Gathered activations and 4-bit weights with zero-points: both by global_load_lds, a stage's loads in one half of a K-step (us with
+    // the weights by buffer loads, spread over the step, and like this: 25344 x 192 x 4800 88 and 82.5, 11088 x 448 x 4608 81.6 and
+    // 75.6; 120 random shapes 1.2 % apart.  Without zero-points the former are ahead by 0.2 %, with 8-bit weights by 2 %.)
+    constexpr bool PLAIN = A_MODE == A_CONV && B4 && ZW;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
     const int tid = threadIdx.x;
@@ -244,8 +248,15 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
                 }
             } else {
                 const int j = idx - A_LOADS;
-                buffer_to_lds16(B4 ? b_tile + (k0 >> 1) : b_tile + k0, bytes, KTAIL && k0 + b_k[j] >= g.K ? NOWHERE : b_lane_off[j],
-                                stage + BM * BK + (wave * B_LOADS + j) * 1024);
+                uint8_t *const dst = stage + BM * BK + (wave * B_LOADS + j) * 1024;
+                if constexpr (PLAIN) {
+                    const uint8_t *src = live ? (B4 ? b_tile + (k0 >> 1) : b_tile + k0) + b_lane_off[j] : fill_a;
+                    if constexpr (KTAIL)
+                        if (k0 + b_k[j] >= g.K) src = &g_fill_table.v[0][0];
+                    dma16(src, dst);
+                    return;
+                }
+                buffer_to_lds16(B4 ? b_tile + (k0 >> 1) : b_tile + k0, bytes, KTAIL && k0 + b_k[j] >= g.K ? NOWHERE : b_lane_off[j], dst);
             }
         };
         i32x16 acc[TM][TN];
@@ -294,7 +305,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
         // Loads of a stage that are issued in the first half of the K-step after the one that freed its buffer: the loads are
         // then spread over the whole step.  (Not with two workgroups per CU, whose other workgroup fills the gaps:
         // 200704 x 128 x 1152 72.2 us, split 75.6.)
-        constexpr int LATE = MINW == 1 ? LOADS / 2 : 0;
+        constexpr int LATE = MINW == 1 && !PLAIN ? LOADS / 2 : 0;
         // MFMAs of one K sub-step with the LDS reads of the next fragment set and this half's loads of a later
         // stage spread evenly between them, so that neither the LDS nor the texture-address queue sees a
         // burst that would stall MFMA issue
@@ -325,6 +336,7 @@ __global__ void __launch_bounds__(WM *WN * 64, MINW)
                         ++load;
                     }
                 }
+            if constexpr (PLAIN && COUNT > 0 && LOADS != PIECES) return;
 #pragma unroll
             for (int q = 0; q < PIECES; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, MMAS / PIECES, 0); // MFMA

@@ -9,7 +9,8 @@
 //
 // Any K that is whole chunks (K % 16 == 0, 4-bit weights K % 32 == 0): what lies beyond K reads as zero, outside the bounds
 // of a buffer; the row sums of weight zero-points are corrected for the codes 0 there.  (A convolution's activations, by
-// global_load_lds, come from a chunk of the code 128 there, which adds nothing to the row sums.)
+// global_load_lds, come from a chunk of the code 128 there, which adds nothing to the row sums.  Its 4-bit
+// weights with zero-points are copied by global_load_lds too, see PLAIN in igemm_dma.h: 4312 x 192 x 5760 35.6 us, like this 34.4.)
 // The copies are buffer loads with 32-bit lane offsets (the dispatcher guarantees pitches below 2^25): see igemm_dma.h.  A_FAR: rows
 // of a matrix further apart, by global_load_lds (with weight zero-points; other products of such rows never come here).
 #pragma once
@@ -109,9 +110,13 @@ __global__ void __launch_bounds__(256, 2) tile64_kernel(const IgemmArgs g, const
             dma16(src, stage + (wave * A_LOADS + i) * 1024);
         }
 #pragma unroll
-        for (int i = 0; i < B_LOADS; ++i)
-            buffer_to_lds16(b_tile + (B4 ? k0 >> 1 : k0), 0x7fffffff, k_begin + k0 + b_k[i] < k_end ? b_off[i] : NOWHERE,
-                            stage + 64 * BK + (wave * B_LOADS + i) * 1024);
+        for (int i = 0; i < B_LOADS; ++i) {
+            const uint8_t *const b_step = b_tile + (B4 ? k0 >> 1 : k0);
+            uint8_t *const dst = stage + 64 * BK + (wave * B_LOADS + i) * 1024;
+            const bool in = k_begin + k0 + b_k[i] < k_end;
+            if constexpr (A_MODE == A_CONV && B4 && ZW) dma16(in ? b_step + b_off[i] : &g_fill_table.v[0][0], dst);
+            else buffer_to_lds16(b_step, 0x7fffffff, in ? b_off[i] : NOWHERE, dst);
+        }
     };
 #pragma unroll
     for (int st = 0; st < STAGES - 1; ++st)
