@@ -84,8 +84,9 @@ template <int KS, bool INT4, bool ZW, bool STRIDED> inline bool launch_ring_widt
 //  - the table of pairs, which leaves room for little besides: 96 < K <= 128 on 16 waves where less than a quarter of the columns
 //    is idle (274776 x 480 x 128 82 and 69, 205520 x 1872 x 128 255 and 207; 384 columns are behind, 186836 x 384 x 128 43 and 50);
 //    more than 160 with four waves side by side (50176 x 1024 x 256 53 and 43, 162833 x 1552 x 192 225 and 175), up to 192 for
-//    large outputs only (25088 x 1024 x 192 25.2 and 26.0).  Else behind: 400000 x 48 x 96 26 and 74, 200704 x 256 x 96 34 and 36,
-//    300000 x 144 x 160 44 and 48; level, 802816 x 256 x 64 100-106 and 101-104.
+//    large outputs only (25088 x 1024 x 192 25.2 and 26.0); 32 < K <= 64 with one or two full column groups and 2^25 outputs, by 1
+//    to 3 % (401408 x 256 x 64 56.8 and 55.5; in the ResNet-50 stack at batch 256, 802816 x 256 x 64, 94.6 and 91.4).  Else behind:
+//    400000 x 48 x 96 26 and 74, 200704 x 256 x 96 34 and 36, 300000 x 144 x 160 44 and 48.
 template <int KS, bool INT4> inline bool launch_ring_add(ShortKRingArgs &a, bool always, hipStream_t s)
 {
     const int N = a.s.g.N;
@@ -101,6 +102,8 @@ template <int KS, bool INT4> inline bool launch_ring_add(ShortKRingArgs &a, bool
         if (ring_idle(N, 64, 8, total) * 8 <= total) return launch_ring_form<2, KS, INT4, 3, true, false, false>(a, always, s);
         if (ring_idle(N, 64, 4, total) * 4 < total) return launch_ring_form<2, KS, INT4, 3, false, false, false>(a, always, s);
     }
+    if constexpr (KS == 2)
+        if ((N <= 128 || N == 256) && a.s.g.M * (int64_t)N >= ((int64_t)1 << 25)) return launch_ring_form<4, 2, INT4, 2, false, false, false>(a, always, s);
     if constexpr (KS > 4)
         if (ring_idle(N, 64, 4, total) * 8 <= total && (always || a.s.g.K > 192 || (a.s.g.K > 160 && a.s.g.M * (int64_t)N >= ((int64_t)1 << 26))))
             return launch_ring_form<2, KS, INT4, 2, true, false, false>(a, always, s);

@@ -80,6 +80,7 @@ def test_qgemm_add_pair_table(M, N, K, bits):
 @pytest.mark.parametrize("M,N,K,bits", [(1000, 512, 128, 8), (4099, 520, 256, 8), (133, 1030, 128, 4), (2500, 256, 256, 4),
                                          (9100, 320, 32, 8), (5000, 64, 128, 4), (70001, 24, 16, 4),  # tables of rescaled codes, on the ring kernel
                                          # 2^24 outputs: the table of code pairs
+                                         (262200, 128, 64, 8), (131080, 256, 48, 4),  # 8 waves, each on rows of its own
                                          (16400, 1024, 256, 8),   # 8 waves, four side by side
                                          (24000, 720, 208, 4), (120000, 144, 192, 8),  # the same, and too few columns for it
                                          (33000, 1024, 128, 4), (33001, 512, 112, 8),  # 16 waves, eight side by side
