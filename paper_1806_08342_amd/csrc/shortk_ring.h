@@ -64,8 +64,10 @@ template <int CPR> __device__ __forceinline__ int ring_place(int row, int c)
 }
 
 // Waves of a workgroup and its dynamic LDS: tables, output tiles of the waves, ring.  Two workgroups of four waves per CU, three or
-// four of the forms that have the registers for it, with the pair table one of eight or sixteen waves; the ring has what is left of
-// the LDS, up to eight blocks, and its first CW blocks (with the pair table: its place) are where the weights are exchanged before.
+// four of the forms that have the registers for it (us with two and with three or four: 401408 x 64 x 64 12.4 and 10.9, 100352 x 64 x
+// 128 7.3 and 6.5, 401408 x 32 x 32 8.5 and 8.0; small launches and 128 columns level, 401408 x 32 x 128 13.7 and 14.6), with the
+// pair table one of eight or sixteen waves; the ring has what is left of the LDS, up to eight blocks, and its first CW blocks (with
+// the pair table: its place) are where the weights are exchanged before.
 template <int NB, int KS, int ADD, bool WIDE, bool ZW> struct RingGeometry {
     static constexpr int kWaves = ADD == 3 ? 16 : ADD == 2 ? 8 : 4;
     static constexpr int kCw = ADD == 3 ? (WIDE ? 8 : 4) : (WIDE ? 4 : 1), kRw = kWaves / kCw; // waves side by side, and on other rows
@@ -87,7 +89,7 @@ template <int NB, int KS, int ADD, bool WIDE, bool ZW> struct RingGeometry {
 // a function of two 8-bit codes, so the workgroup (8 waves here, to share it) first tabulates all 65536 results in LDS; combining
 // a pair of codes is then one byte gather.  3: the same with 16 waves of half the columns, whose gathers, rescale
 // and memory streams overlap better, for more reads of the ring: 200704 x 512 x 128 62 -> 60 us, but 50176 x 1024 x 256 42 -> 43 and
-// 802816 x 256 x 64 level, so for 64 < K <= 128 only.
+// 802816 x 256 x 64 level, so for 96 < K <= 128 only.  Which launches have the add here: launch_ring_add.
 // ZW: per-column weight zero-points, as in shortk.h.  STRIDED: rows are the pixels of a strided 1x1 convolution.
 // The set-up is kept short, small launches consist of it: 32-bit offsets, no division.
 template <int NB, int KS, bool INT4, int ADD, bool WIDE, bool ZW, bool STRIDED>
