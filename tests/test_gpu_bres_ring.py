@@ -1,5 +1,5 @@
-"""GPU parity of the weight-resident kernel for matrices with its rows in an LDS ring (bres_ring.h): three and six slots, one to
-four column blocks, the last block of rows whole, partial and missing, row-spaced operands, outputs that are no whole chunks."""
+"""GPU parity of the weight-resident kernel for matrices with its rows in an LDS ring (bres_ring.h): three and six slots, and weights
+that leave no room for three (200 columns with K = 768: bres.h), one to four column blocks, the last block of rows whole, partial and missing, row-spaced operands, outputs that are no whole chunks."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M", [4096, 4129, 70003])
-@pytest.mark.parametrize("N,K", [(24, 320), (64, 512), (128, 512), (200, 768), (256, 1024), (72, 384)])
+@pytest.mark.parametrize("N,K", [(24, 320), (64, 512), (128, 512), (200, 768), (256, 1024), (72, 384), (200, 448), (160, 512)])
 @pytest.mark.parametrize("bits", [8, 4])
 def test_rows_through_the_ring(tuning, M, N, K, bits):
     tuning.setenv("QNN_BRES", "1")  # shapes this small take the kernel only on request
