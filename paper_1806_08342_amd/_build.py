@@ -14,9 +14,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqnn.so")
 NATIVE = os.path.join(HERE, "_native.so")
-SOURCES = ["host_helpers.hip", "elementwise.hip", "igemm.hip", "igemm_tiles.hip", "igemm_shortk.hip", "igemm_shortk4.hip", "igemm_ring_int8_low.hip",
-           "igemm_ring_int8_high.hip", "igemm_ring_int4_low.hip", "igemm_ring_int4_high.hip", "igemm_bres.hip",
-           "igemm_stem.hip", "igemm_smallk.hip", "igemm_tail.hip", "igemm_tile64.hip", "igemm_repack.hip", "dwconv.hip", "calibrate.hip"]
+# (the ones that take longest first)
+SOURCES = ["igemm_bres.hip", "igemm_bres4.hip", "igemm_ring_int8_low.hip", "igemm_ring_int4_low.hip", "igemm.hip", "igemm_shortk.hip", "igemm_shortk4.hip",
+           "dwconv.hip", "igemm_ring_int8_high.hip", "igemm_ring_int4_high.hip", "igemm_tiles.hip", "igemm_stem.hip", "igemm_smallk.hip", "igemm_tail.hip",
+           "igemm_tile64.hip", "elementwise.hip", "igemm_repack.hip", "host_helpers.hip", "calibrate.hip"]
 FLAGS = [
     "-O3",
     "--offload-arch=gfx950",

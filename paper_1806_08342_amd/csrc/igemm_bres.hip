@@ -1,56 +1,13 @@
-// Launch routine of the weight-resident kernel.
-#include "igemm_launch.h"
+// Launch routine of the weight-resident kernels; forms for 8-bit weights.
+#include "bres_launch.h"
 #include "tuning.h"
-#include "bres_ring.h"
 
 namespace qnn {
 
+hipError_t launch_bres_int8(const BResArgs &a, int nb, bool conv, int slots, unsigned blocks, int lds, hipStream_t s) { return launch_bres<false>(a, nb, conv, slots, blocks, lds, s); }
+
 // Medium reduction, few output channels: weight-resident kernel of bres.h.  Returns false when the
 // shape or the alignment does not fit (the caller then takes the tiled route).
-template <int NB, int KC, bool INT4, bool CONV, bool PAD = false>
-static hipError_t launch_bres_one(const BResArgs &a, unsigned blocks, int lds, hipStream_t s)
-{
-    auto kernel = bres_kernel<NB, KC, INT4, CONV, PAD>;
-    static LdsOptIn opt_in; // per instantiation
-    if (hipError_t e = opt_in.ensure(reinterpret_cast<const void *>(kernel), lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(512), lds, s, a);
-    return hipGetLastError();
-}
-
-template <int NB, bool INT4, bool CONV>
-static hipError_t launch_bres_kc(const BResArgs &a, unsigned blocks, int lds, hipStream_t s)
-{
-    // A fragments travel in chunks of KC K sub-steps; a chunk size that divides K / 32 wastes no MFMA
-    const int ks = a.g.K / 32;
-    if (ks % 8 == 0) return launch_bres_one<NB, 8, INT4, CONV>(a, blocks, lds, s);
-    if (ks % 6 == 0) return launch_bres_one<NB, 6, INT4, CONV>(a, blocks, lds, s);
-    if (ks % 4 == 0) return launch_bres_one<NB, 4, INT4, CONV>(a, blocks, lds, s);
-    return launch_bres_one<NB, 6, INT4, CONV, true>(a, blocks, lds, s); // last chunk padded with zero operands
-}
-
-template <int NB> static hipError_t launch_bres_nb(const BResArgs &a, bool i4, bool conv, unsigned blocks, int lds, hipStream_t s)
-{
-    if (conv) return i4 ? launch_bres_kc<NB, true, true>(a, blocks, lds, s) : launch_bres_kc<NB, false, true>(a, blocks, lds, s);
-    return i4 ? launch_bres_kc<NB, true, false>(a, blocks, lds, s) : launch_bres_kc<NB, false, false>(a, blocks, lds, s);
-}
-
-// the form with its rows through an LDS ring of RING slots per wave
-template <int NB, int RING, bool INT4> static hipError_t launch_ring_one(const BResArgs &a, unsigned blocks, int lds, hipStream_t s)
-{
-    auto kernel = bres_ring_kernel<NB, RING, INT4>;
-    static LdsOptIn opt_in; // per instantiation
-    if (hipError_t e = opt_in.ensure(reinterpret_cast<const void *>(kernel), lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(512), lds, s, a);
-    return hipGetLastError();
-}
-
-template <int NB> static hipError_t launch_ring_nb(const BResArgs &a, bool i4, int slots, unsigned blocks, int lds, hipStream_t s)
-{
-    lds += (slots >= 6 ? 6 : 3) * 8 * 2048;
-    if (slots >= 6) return i4 ? launch_ring_one<NB, 6, true>(a, blocks, lds, s) : launch_ring_one<NB, 6, false>(a, blocks, lds, s);
-    return i4 ? launch_ring_one<NB, 3, true>(a, blocks, lds, s) : launch_ring_one<NB, 3, false>(a, blocks, lds, s);
-}
-
 bool try_bres(IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *status)
 {
     const int mode = tuning().bres; // tuning aid: 0 = never, 1 = whenever the shape fits
@@ -81,19 +38,10 @@ bool try_bres(IgemmArgs &g, int a_mode, int b_mode, hipStream_t s, qnn_status *s
     a.groups_walkers = (int)walkers;
     const unsigned blocks = (unsigned)(walkers * col_groups);
     const int lds = lds_for(nb);
-    const bool i4 = b_mode == B_INT4;
-    hipError_t e;
-    // six slots per wave where the weights leave the room, else three
-    const int slots = (160 * 1024 - lds) / (8 * 2048);
-    if (!conv && slots >= 3 && g.K % 64 == 0 && g.M < (1 << 30) && g.lda < (1 << 26)) {
-        e = nb == 4 ? launch_ring_nb<4>(a, i4, slots, blocks, lds, s) : nb == 2 ? launch_ring_nb<2>(a, i4, slots, blocks, lds, s) : launch_ring_nb<1>(a, i4, slots, blocks, lds, s);
-        *status = launch_status(e);
-        return true;
-    }
-    if (nb == 4) e = launch_bres_nb<4>(a, i4, conv, blocks, lds, s);
-    else if (nb == 2) e = launch_bres_nb<2>(a, i4, conv, blocks, lds, s);
-    else e = launch_bres_nb<1>(a, i4, conv, blocks, lds, s);
-    *status = launch_status(e);
+    // the rows through an LDS ring: six slots per wave where the weights leave the room, else three
+    const bool ring = !conv && g.K % 64 == 0 && g.M < (1 << 30) && g.lda < (1 << 26);
+    const int slots = ring ? (160 * 1024 - lds) / (8 * 2048) : 0;
+    *status = launch_status(b_mode == B_INT4 ? launch_bres_int4(a, nb, conv, slots, blocks, lds, s) : launch_bres_int8(a, nb, conv, slots, blocks, lds, s));
     return true;
 }
 
