@@ -12,7 +12,7 @@ namespace qnn {
 //  - up to 32 columns, or 64 with K <= 128: always (a form as wide as the columns; 25088 x 24 x 144 5.2 and 4.6), but for strided
 //    launches of one step with K > 128 (28800 x 32 x 176 5.7 and 6.0).
 //  - one step per walker: the launch is its set-up, and the weight exchange and its barriers lose (4-bit weights, 6272 x 576 x 96
-//    5.2 and 5.9, 1568 x 960 x 160 4.3 and 4.9; 2000 x 1000 x 208 6.3 and 6.8, 2000 x 1000 x 64 6.1 and 6.4), unless the weight
+//    5.1 and 5.9, 1568 x 960 x 160 4.3 and 4.9; 2000 x 1000 x 208 6.3 and 6.8, 2000 x 1000 x 64 6.1 and 6.4), unless the weight
 //    rows are a multiple of 128 bytes apart, where fragment loads meet in the same channels (2000 x 1000 x 256 7.1 and 6.7,
 //    55614 x 128 x 128 10.0 and 7.3), with weight zero-points 96 < K <= 128 altogether, or K <= 128 fills the chip (94226 x 128 x 32
 //    8.1 and 7.0, 39421 x 71 x 64 7.6 and 7.5).
